@@ -771,7 +771,8 @@ struct spd_cg_s {
     double *R = nullptr, *P = nullptr, *Z = nullptr, *part = nullptr, *vpart = nullptr, *sc = nullptr;
     double *norms = nullptr, *rscr = nullptr;
     double *Xs = nullptr;            // x at the start of the inner phase (its change is the correction)
-    float *Pf = nullptr;
+    double *P2 = nullptr;            // second direction buffer of the fused banded iterations
+    float *Pf = nullptr;             // binary32 directions of the dense products
     float *Zp = nullptr;             // k-slice partials of the dense multi-column product
     int *flags = nullptr;            // act[2][m] (parity slots), go[m], cnt[m]
     double *norms_host = nullptr;
@@ -784,10 +785,10 @@ namespace {
 void cg_free_ws(spd_cg_t H)
 {
     hipFree(H->R); hipFree(H->P); hipFree(H->Z); hipFree(H->part); hipFree(H->vpart); hipFree(H->sc); hipFree(H->Xs);
-    hipFree(H->norms); hipFree(H->rscr); hipFree(H->Pf); hipFree(H->Zp); hipFree(H->flags);
+    hipFree(H->norms); hipFree(H->rscr); hipFree(H->P2); hipFree(H->Pf); hipFree(H->Zp); hipFree(H->flags);
     if (H->norms_host) hipHostFree(H->norms_host);
     if (H->flags_host) hipHostFree(H->flags_host);
-    H->R = H->P = H->Z = H->part = H->vpart = H->sc = H->norms = H->rscr = H->Xs = nullptr;
+    H->R = H->P = H->Z = H->part = H->vpart = H->sc = H->norms = H->rscr = H->Xs = H->P2 = nullptr;
     H->Pf = nullptr;
     H->Zp = nullptr;
     H->flags = nullptr;
@@ -815,7 +816,8 @@ spd_status cg_ensure_ws(spd_cg_t H, int m, hipStream_t st)
     HIP_TRY(hipMalloc(&H->sc, (size_t)4 * m * sizeof(double)));
     HIP_TRY(hipMalloc(&H->norms, (size_t)(1 + 5 * m) * sizeof(double)));
     HIP_TRY(hipMalloc(&H->rscr, (size_t)spd::resid_scratch(n, m) * sizeof(double)));
-    HIP_TRY(hipMalloc(&H->Pf, (size_t)spd::cg_pf_elems(ldt, m) * sizeof(float)));
+    if (H->k < 0) HIP_TRY(hipMalloc(&H->Pf, (size_t)spd::cg_pf_elems(ldt, m) * sizeof(float)));
+    if (H->k >= 0 && spd::cg_band_fused(H->k)) HIP_TRY(hipMalloc(&H->P2, nm));
     if (H->k < 0 && spd::cg_zp_elems(n, m) > 0)
         HIP_TRY(hipMalloc(&H->Zp, (size_t)spd::cg_zp_elems(n, m) * sizeof(float)));
     HIP_TRY(hipMalloc(&H->flags, (size_t)4 * m * sizeof(int)));
@@ -831,7 +833,7 @@ spd_status cg_refine(spd_cg_t H, const double *A, int64_t lda, const double *B, 
     const int64_t n = H->n, ldt = H->ldt, k = H->k;
     SPD_TRY(cg_ensure_ws(H, m, st));
     // Pf's padding (rows n..ldt-1, columns m.. of the last block) must read as zero
-    spd::launch_zero((double *)H->Pf, spd::cg_pf_elems(ldt, m) / 2, st);
+    if (H->Pf) spd::launch_zero((double *)H->Pf, spd::cg_pf_elems(ldt, m) / 2, st);
     const int64_t nmv = spd::cg_mv_parts(n, ldt, k, m), nv = spd::cg_vec_parts(n);
     int *act = H->flags, *go = H->flags + 2 * m, *cnt = H->flags + 3 * m;  // act: two parity slots
     int *go_h = H->flags_host + 2 * m;
@@ -842,12 +844,29 @@ spd_status cg_refine(spd_cg_t H, const double *A, int64_t lda, const double *B, 
     const int S = (k < 0) ? 2 : 16;
     const double band_w = (k < 0) ? (double)n : (double)(2 * k + 1);
     const double mv_flops = 2.0 * band_w * n * m, mv_bytes = 4.0 * band_w * n + 20.0 * n * m;
-    // one CG iteration: product, x/r update, p update (parity slot par); with
-    // profiling on, the product alone is bracketed by the caller
-    auto launch_iteration = [&](int par, hipStream_t q) {
-        spd::launch_cg_mv(H->At, ldt, n, k, m, H->Pf, H->P, H->Z, H->part, nmv, act + par * m, H->Zp, q);
-        spd::launch_cg_xr(n, m, H->part, nmv, H->sc, par, H->P, H->Z, X, ldx, H->R, H->vpart, nv, act, q);
-        spd::launch_cg_p(n, m, H->vpart, nv, H->sc, par, H->R, H->P, H->Pf, ldt, act, cnt, o.max_inner, q);
+    // S CG iterations: product, x/r update, p update (parity slot s & 1).  A
+    // narrow band (P2 allocated) takes the p update of all but the last
+    // iteration inside the next product, the directions alternating between
+    // P and P2 (S is even, so the last update lands in P again).  With
+    // profiling on, each product is bracketed by events.
+    auto launch_iterations = [&](hipStream_t q, bool prof) {
+        for (int s = 0; s < S; ++s) {
+            const int par = s & 1;
+            const double *p = (H->P2 && par) ? H->P2 : H->P;  // this iteration's direction
+            hipEvent_t pe = prof ? prof_begin(q) : nullptr;
+            if (k < 0)
+                spd::launch_cg_mv(H->At, ldt, n, m, H->Pf, p, H->Z, H->part, nmv, act + par * m, H->Zp, q);
+            else if (H->P2 && s > 0)
+                spd::launch_cg_mv_band(H->At, ldt, n, k, m, H->R, par ? H->P : H->P2, (double *)p, H->Z, H->part, nmv,
+                                       H->vpart, nv, H->sc, par, act, cnt, o.max_inner, q);
+            else
+                spd::launch_cg_mv_band(H->At, ldt, n, k, m, H->R, p, nullptr, H->Z, H->part, nmv, H->vpart, nv, H->sc,
+                                       par, act, cnt, o.max_inner, q);
+            if (pe) prof_end(pe, q, SPD_K_CG_MV, mv_flops, mv_bytes);
+            spd::launch_cg_xr(n, m, H->part, nmv, H->sc, par, p, H->Z, X, ldx, H->R, H->vpart, nv, act, q);
+            if (!H->P2 || s == S - 1)
+                spd::launch_cg_p(n, m, H->vpart, nv, H->sc, par, H->R, p, H->P, H->Pf, ldt, act, cnt, o.max_inner, q);
+        }
     };
     // Banded iterations are launch-bound: the S iterations between host
     // checks are captured once per call into a graph (all arguments are fixed
@@ -860,7 +879,7 @@ spd_status cg_refine(spd_cg_t H, const double *A, int64_t lda, const double *B, 
         hipGraph_t g = nullptr;
         if (ok) ok = hipStreamBeginCapture(H->gstream, hipStreamCaptureModeThreadLocal) == hipSuccess;
         if (ok) {
-            for (int s = 0; s < S; ++s) launch_iteration(s & 1, H->gstream);
+            launch_iterations(H->gstream, false);
             ok = hipStreamEndCapture(H->gstream, &g) == hipSuccess && g;
         }
         if (ok) ok = hipGraphInstantiate(&gexec, g, nullptr, nullptr, 0) == hipSuccess;
@@ -931,11 +950,7 @@ spd_status cg_refine(spd_cg_t H, const double *A, int64_t lda, const double *B, 
             if (gexec) {
                 HIP_TRY(hipGraphLaunch(gexec, st));
             } else {
-                for (int s = 0; s < S; ++s) {  // S is even: iteration parity = s & 1
-                    hipEvent_t pe = prof_begin(st);
-                    launch_iteration(s & 1, st);
-                    if (pe) prof_end(pe, st, SPD_K_CG_MV, mv_flops, mv_bytes);
-                }
+                launch_iterations(st, true);
             }
             launched += S;
             HIP_TRY(hipGetLastError());

@@ -185,15 +185,23 @@ int64_t cg_mv_parts(int64_t n, int64_t ldt, int64_t k, int m);
 int64_t cg_vec_parts(int64_t n);
 // Zp: binary32 k-slice partials of the 5..32-column dense product, cg_zp_elems(n, m) elements
 int64_t cg_zp_elems(int64_t n, int m);
-void launch_cg_mv(const float *At, int64_t ldt, int64_t n, int64_t k, int m, const float *Pf, const double *P,
+void launch_cg_mv(const float *At, int64_t ldt, int64_t n, int m, const float *Pf, const double *P,
                   double *Z, double *part, int64_t npart, const int *act, float *Zp, hipStream_t st);
+// Band product.  Pout NULL: z = A~ Pin with the state in slot par.  Pout
+// (another buffer than Pin): first p = r + beta Pin into Pout, advancing the
+// state into slot par (cg_band_fused(k) only).
+bool cg_band_fused(int64_t k);
+void launch_cg_mv_band(const float *Bd, int64_t ldt, int64_t n, int64_t k, int m, const double *R, const double *Pin,
+                       double *Pout, double *Z, double *part, int64_t npart, const double *rrp, int64_t nrr,
+                       double *sc, int par, int *act, int *cnt, int max_inner, hipStream_t st);
 void launch_cg_start(int64_t n, int m, const double *R, double *P, float *Pf, int64_t ldt, double *part,
                      int64_t npart, const int *go, hipStream_t st);
 void launch_cg_xr(int64_t n, int m, const double *pzp, int64_t npz, const double *sc, int par, const double *P,
                   const double *Z, double *X, int64_t ldx, double *R, double *part, int64_t npart, const int *act,
                   hipStream_t st);
-void launch_cg_p(int64_t n, int m, const double *rrp, int64_t nrr, double *sc, int par, const double *R, double *P,
-                 float *Pf, int64_t ldt, int *act, int *cnt, int max_inner, hipStream_t st);
+void launch_cg_p(int64_t n, int m, const double *rrp, int64_t nrr, double *sc, int par, const double *R,
+                 const double *Pin, double *P, float *Pf, int64_t ldt, int *act, int *cnt, int max_inner,
+                 hipStream_t st);
 void launch_cg_begin(const double *part, int64_t npart, double *sc, int *act, const int *go, int *cnt,
                      double inner_tol2, int max_inner, int m, hipStream_t st);
 

@@ -14,7 +14,9 @@
 // writes one partial per workgroup, and its consumers sum them for each
 // column in a fixed order (every workgroup of a consumer the same way).
 // One CG iteration is three launches (four for the dense 5..32-column
-// product, which adds its slice sum): product, x/r update, p update.
+// product, which adds its slice sum): product, x/r update, p update; a band
+// of half-width up to CG_FUSE_MAXK takes the p update inside the next
+// product: two launches.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -26,6 +28,8 @@
 namespace {
 
 constexpr int CG_MAXK_BAND = 4096;  // largest half-bandwidth kept in band storage
+constexpr int CG_BAND_COLS = 4;     // right-hand sides per workgroup of the band product
+constexpr int CG_FUSE_MAXK = 128;   // widest half-band whose product also takes the p step (halo <= 256 rows)
 
 __device__ inline double wave_sum(double v)
 {
@@ -285,86 +289,138 @@ __global__ __launch_bounds__(256) void k_cg_mv_ksum(int64_t n, int m, const floa
     if (threadIdx.x == 0) part[blockIdx.x + (int64_t)c * npart] = pz;
 }
 
-// z = A~ p on the band: a thread per row; the directions of up to CB
-// right-hand sides over the workgroup's rows and their k-wide halo staged
-// in LDS column by column (pitch span + 1), each band value loaded once and
-// applied to all of them
-template <int CB>
+// z = A~ p on the band, a thread per row, workgroup (x, y) the rows
+// [256 x, 256 x + 256) of CB right-hand sides: their directions over those
+// rows and the k-wide halo, rounded to binary32, are staged in LDS column by
+// column (pitch span + 1), and each band value is applied to all of them.
+// With FUSE the step p = r + beta p of the iteration before is taken here
+// (each workgroup forms its rows and its halo from R and Pin, and writes its
+// rows to Pout, another buffer, since its neighbours still read Pin), and
+// block (0, y) advances the columns' scalar state from slot par ^ 1 to slot
+// par: one launch less per iteration.  Only for halos up to the tile's own
+// rows (CG_FUSE_MAXK); wider ones would form p many times over.
+//
+// Bound by latency: the product at n = 12000, half-width 16 and 32 columns
+// moves 20 MB.  All 32 columns in one workgroup (47 workgroups there, a fifth
+// of the chip) took 62.4 us, and the p step 5.5 us of its own; with four
+// columns per workgroup and the p step inside, both take 8.9 us together.
+template <int CB, bool FUSE>
 __global__ __launch_bounds__(256) void k_cg_mv_band(const float *__restrict__ Bd, int64_t ldt, int64_t n, int64_t k,
-                                                    int m, int W, const float *__restrict__ Pf,
-                                                    const double *__restrict__ P, double *__restrict__ Z,
-                                                    double *__restrict__ part, int64_t npart,
-                                                    const int *__restrict__ act)
+                                                    int m, const double *__restrict__ R,
+                                                    const double *__restrict__ Pin, double *__restrict__ Pout,
+                                                    double *__restrict__ Z, double *__restrict__ part, int64_t npart,
+                                                    const double *__restrict__ rrp, int64_t nrr,
+                                                    double *__restrict__ sc, int par, int *__restrict__ act,
+                                                    int *__restrict__ cnt, int max_inner)
 {
     extern __shared__ float pl[];  // CB x (span + 1)
     __shared__ double redc[4 * CB];
-    const int64_t i0 = (int64_t)blockIdx.x * 256;
-    const int t = threadIdx.x;
-    const int64_t i = i0 + t;
-    const int64_t span = 256 + 2 * k, pitch = span + 1;
-    for (int cb = 0; cb < m; cb += CB) {
-        const int cnt = min(CB, m - cb);
-        if (!any_active(act, cb, cnt)) continue;  // uniform across the block
-        __syncthreads();
-        const int64_t total = (int64_t)cnt * span;
-        for (int64_t q0 = t; q0 < total; q0 += 256 * 8) {  // eight loads in flight per thread
-            float v[8];
+    __shared__ double beta[CB];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int64_t i0 = (int64_t)blockIdx.x * 256, i = i0 + t;
+    const int cb = blockIdx.y * CB, nc = min(CB, m - cb);
+    const int pitch = 256 + 2 * (int)k + 1;
+    // columns taking part: those active when the iteration's direction was due
+    const int *a_cur = act + (int64_t)(FUSE ? par ^ 1 : par) * m;
+    bool on[CB], any = false;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int64_t q = q0 + 256 * u;
-                v[u] = 0.0f;
-                if (q < total) {
-                    const int c = (int)(q / span);
-                    const int64_t j = i0 - k + (q - (int64_t)c * span);
-                    if (j >= 0 && j < n) v[u] = Pf[pf_off(j, cb + c, W, ldt)];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int64_t q = q0 + 256 * u;
-                if (q < total) {
-                    const int c = (int)(q / span);
-                    pl[c * pitch + (q - (int64_t)c * span)] = v[u];
+    for (int c = 0; c < CB; ++c) {
+        on[c] = c < nc && a_cur[cb + c] != 0;
+        any |= on[c];
+    }
+    if constexpr (FUSE) {
+        const double *rho = sc + (int64_t)(par ^ 1) * m;
+        double *rho_next = sc + (int64_t)par * m;
+        const double *thr = sc + 2 * (int64_t)m;
+        int *a_next = act + (int64_t)par * m;
+        // rho' = r^T r from its partials, a wave per column (fixed order)
+        for (int c = w; c < nc; c += 4) {
+            double rr = 0.0;
+            if (a_cur[cb + c])
+                for (int64_t q = lane; q < nrr; q += 64) rr += rrp[q + (int64_t)(cb + c) * nrr];
+            rr = wave_sum(rr);
+            if (lane == 0) {
+                const double rc = rho[cb + c];
+                beta[c] = rr / rc;
+                if (blockIdx.x == 0) {  // the column's state into the next slot
+                    if (a_cur[cb + c]) {
+                        const int q = cnt[cb + c] + 1;
+                        cnt[cb + c] = q;
+                        rho_next[cb + c] = rr;
+                        a_next[cb + c] = (q < max_inner && rr > thr[cb + c]) ? 1 : 0;
+                    } else {
+                        rho_next[cb + c] = rc;
+                        a_next[cb + c] = 0;
+                    }
                 }
             }
         }
+        if (!any) return;
         __syncthreads();
-        float acc[CB];
+    } else {
+        if (!any) return;
+    }
+    // own rows, then the halo (k rows on either side)
+    double p[CB];
 #pragma unroll
-        for (int c = 0; c < CB; ++c) acc[c] = 0.0f;
-        if (i < n)
-#pragma unroll 4
-            for (int64_t d = -k; d <= k; ++d) {
-                const float a = Bd[(d + k) * ldt + i];
-                const float *col = pl + t + k + d;
-#pragma unroll
-                for (int c = 0; c < CB; ++c)
-                    if (c < cnt) acc[c] += a * col[c * pitch];
+    for (int c = 0; c < CB; ++c) {
+        p[c] = 0.0;
+        if (on[c] && i < n) {
+            const int64_t o = i + (int64_t)(cb + c) * n;
+            p[c] = Pin[o];
+            if constexpr (FUSE) {
+                p[c] = R[o] + beta[c] * p[c];
+                Pout[o] = p[c];
             }
-        // z, and p^T z per column: wave sums, then the four waves in order
-        double pz[CB];
+        }
+        pl[c * pitch + k + t] = (float)p[c];
+    }
+    for (int h = t; h < 2 * (int)k; h += 256) {
+        const int off = h < k ? h : 256 + h;  // position in the staged rows
+        const int64_t j = i0 - k + off;
 #pragma unroll
         for (int c = 0; c < CB; ++c) {
-            pz[c] = 0.0;
-            if (c < cnt && i < n) {
-                const double z = (double)acc[c];
-                Z[i + (int64_t)(cb + c) * n] = z;
-                pz[c] = P[i + (int64_t)(cb + c) * n] * z;
+            double v = 0.0;
+            if (on[c] && j >= 0 && j < n) {
+                const int64_t o = j + (int64_t)(cb + c) * n;
+                v = Pin[o];
+                if constexpr (FUSE) v = R[o] + beta[c] * v;
             }
-            pz[c] = wave_sum(pz[c]);
+            pl[c * pitch + off] = (float)v;
         }
-        __syncthreads();
-        if ((t & 63) == 0)
-#pragma unroll
-            for (int c = 0; c < CB; ++c) redc[(t >> 6) * CB + c] = pz[c];
-        __syncthreads();
-        if (t < cnt)
-            part[blockIdx.x + (int64_t)(cb + t) * npart] =
-                ((redc[t] + redc[CB + t]) + redc[2 * CB + t]) + redc[3 * CB + t];
     }
+    __syncthreads();
+    float acc[CB];
+#pragma unroll
+    for (int c = 0; c < CB; ++c) acc[c] = 0.0f;
+    if (i < n) {
+        const float *bd = Bd + i;
+        const float *col = pl + t;
+#pragma unroll 16
+        for (int d = 0; d <= 2 * (int)k; ++d) {
+            const float a = bd[(int64_t)d * ldt];
+#pragma unroll
+            for (int c = 0; c < CB; ++c) acc[c] += a * col[c * pitch + d];
+        }
+    }
+    // z, and p^T z per column: wave sums, then the four waves in order
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+        double pz = 0.0;
+        if (on[c] && i < n) {
+            const double z = (double)acc[c];
+            Z[i + (int64_t)(cb + c) * n] = z;
+            pz = p[c] * z;
+        }
+        pz = wave_sum(pz);
+        if (lane == 0) redc[w * CB + c] = pz;
+    }
+    __syncthreads();
+    if (t < nc)
+        part[blockIdx.x + (int64_t)(cb + t) * npart] = ((redc[t] + redc[CB + t]) + redc[2 * CB + t]) + redc[3 * CB + t];
 }
 
-// P = R, Pf = fl32(R) and a partial of r^T r, for the columns starting a
+// P = R, Pf = fl32(R) (dense products) and a partial of r^T r, for the columns starting a
 // phase (blockIdx.y = column)
 __global__ __launch_bounds__(256) void k_cg_start(int64_t n, int m, int W, const double *__restrict__ R,
                                                   double *__restrict__ P, float *__restrict__ Pf, int64_t ldt,
@@ -380,7 +436,7 @@ __global__ __launch_bounds__(256) void k_cg_start(int64_t n, int m, int W, const
         if (i < n) {
             const double r = R[i + (int64_t)b * n];
             P[i + (int64_t)b * n] = r;
-            Pf[pf_off(i, b, W, ldt)] = (float)r;
+            if (Pf) Pf[pf_off(i, b, W, ldt)] = (float)r;
             s += r * r;
         }
     }
@@ -430,12 +486,13 @@ __global__ __launch_bounds__(256) void k_cg_xr(int64_t n, int m, const double *_
     if (threadIdx.x == 0) part[blockIdx.x + (int64_t)b * npart] = s;
 }
 
-// rho' = r^T r (partials of k_cg_xr), beta = rho' / rho, p = r + beta p,
-// Pf = fl32(p) (blockIdx.y = column); block (0, b) advances the column's
+// rho' = r^T r (partials of k_cg_xr), beta = rho' / rho, p = r + beta p (Pin
+// to P, which may be the same buffer), Pf = fl32(p) for dense products
+// (blockIdx.y = column); block (0, b) advances the column's
 // state into slot par ^ 1: rho', ++cnt, act' = cnt < max_inner && rho' > thr
 __global__ __launch_bounds__(256) void k_cg_p(int64_t n, int m, int W, const double *__restrict__ rrp, int64_t nrr,
                                               double *__restrict__ sc, int par, const double *__restrict__ R,
-                                              double *__restrict__ P, float *__restrict__ Pf, int64_t ldt,
+                                              const double *Pin, double *P, float *__restrict__ Pf, int64_t ldt,
                                               int *__restrict__ act, int *__restrict__ cnt, int max_inner)
 {
     __shared__ double red[4];
@@ -459,9 +516,9 @@ __global__ __launch_bounds__(256) void k_cg_p(int64_t n, int m, int W, const dou
     for (int u = 0; u < 4; ++u) {
         const int64_t i = (int64_t)blockIdx.x * 1024 + u * 256 + threadIdx.x;
         if (i < n) {
-            const double p = R[i + (int64_t)b * n] + be * P[i + (int64_t)b * n];
+            const double p = R[i + (int64_t)b * n] + be * Pin[i + (int64_t)b * n];
             P[i + (int64_t)b * n] = p;
-            Pf[pf_off(i, b, W, ldt)] = (float)p;
+            if (Pf) Pf[pf_off(i, b, W, ldt)] = (float)p;
         }
     }
     if (lead) {
@@ -530,23 +587,36 @@ int64_t cg_mv_parts(int64_t n, int64_t ldt, int64_t k, int m)
 
 int64_t cg_zp_elems(int64_t n, int m) { return (m > 4) ? (int64_t)CG_KS * m * n : 0; }
 
-void launch_cg_mv(const float *At, int64_t ldt, int64_t n, int64_t k, int m, const float *Pf, const double *P,
+// columns per workgroup of the band product: four, so that a few dozen row
+// blocks with several right-hand sides still spread over the chip; one where
+// four columns' rows and halo exceed the 64 KB of LDS a launch may ask for
+static int cg_band_cols(int64_t k, int m)
+{
+    return (m > 1 && (256 + 2 * k + 1) * CG_BAND_COLS * (int64_t)sizeof(float) + 1024 <= 65536) ? CG_BAND_COLS : 1;
+}
+
+bool cg_band_fused(int64_t k) { return k <= CG_FUSE_MAXK; }
+
+void launch_cg_mv_band(const float *Bd, int64_t ldt, int64_t n, int64_t k, int m, const double *R, const double *Pin,
+                       double *Pout, double *Z, double *part, int64_t npart, const double *rrp, int64_t nrr,
+                       double *sc, int par, int *act, int *cnt, int max_inner, hipStream_t st)
+{
+    const int CB = cg_band_cols(k, m);
+    const dim3 g((unsigned)((n + 255) / 256), (unsigned)((m + CB - 1) / CB));
+    const size_t lds = (size_t)(256 + 2 * k + 1) * CB * sizeof(float);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, g, dim3(256), lds, st, Bd, ldt, n, k, m, R, Pin, Pout, Z, part, npart, rrp, nrr, sc,
+                           par, act, cnt, max_inner);
+    };
+    if (CB == 1)
+        Pout ? go(k_cg_mv_band<1, true>) : go(k_cg_mv_band<1, false>);
+    else
+        Pout ? go(k_cg_mv_band<CG_BAND_COLS, true>) : go(k_cg_mv_band<CG_BAND_COLS, false>);
+}
+
+void launch_cg_mv(const float *At, int64_t ldt, int64_t n, int m, const float *Pf, const double *P,
                   double *Z, double *part, int64_t npart, const int *act, float *Zp, hipStream_t st)
 {
-    const int W = cg_pf_width(m);
-    if (k >= 0) {
-        const int64_t pitch = 256 + 2 * k + 1;
-        const dim3 g((unsigned)((n + 255) / 256));
-        // dynamic LDS for 32 columns, plus the kernel's static reduction
-        // space (1 KB), within the 64 KB a workgroup may use
-        if (m > 1 && pitch * 32 * (int64_t)sizeof(float) + 1024 <= 65536)
-            hipLaunchKernelGGL(k_cg_mv_band<32>, g, dim3(256), (size_t)pitch * 32 * sizeof(float), st, At, ldt, n, k,
-                               m, W, Pf, P, Z, part, npart, act);
-        else
-            hipLaunchKernelGGL(k_cg_mv_band<1>, g, dim3(256), (size_t)pitch * sizeof(float), st, At, ldt, n, k, m, W,
-                               Pf, P, Z, part, npart, act);
-        return;
-    }
     const dim3 blk(256), g((unsigned)(ldt / 32));
     switch (m) {
     case 1: hipLaunchKernelGGL(k_cg_mv_valu<1>, g, blk, 0, st, At, ldt, n, Pf, P, Z, part, npart, act); break;
@@ -578,11 +648,12 @@ void launch_cg_xr(int64_t n, int m, const double *pzp, int64_t npz, const double
                        sc + (int64_t)par * m, P, Z, X, ldx, R, part, npart, act + (int64_t)par * m);
 }
 
-void launch_cg_p(int64_t n, int m, const double *rrp, int64_t nrr, double *sc, int par, const double *R, double *P,
-                 float *Pf, int64_t ldt, int *act, int *cnt, int max_inner, hipStream_t st)
+void launch_cg_p(int64_t n, int m, const double *rrp, int64_t nrr, double *sc, int par, const double *R,
+                 const double *Pin, double *P, float *Pf, int64_t ldt, int *act, int *cnt, int max_inner,
+                 hipStream_t st)
 {
     hipLaunchKernelGGL(k_cg_p, dim3((unsigned)cg_vec_parts(n), (unsigned)m), dim3(256), 0, st, n, m, cg_pf_width(m),
-                       rrp, nrr, sc, par, R, P, Pf, ldt, act, cnt, max_inner);
+                       rrp, nrr, sc, par, R, Pin, P, Pf, ldt, act, cnt, max_inner);
 }
 
 void launch_cg_begin(const double *part, int64_t npart, double *sc, int *act, const int *go, int *cnt,

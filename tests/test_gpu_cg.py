@@ -64,6 +64,22 @@ def test_cg_steps_match_oracle(spd, orc, band, m, k):
     assert err.max() <= 4 * k * n * U32, err.max()
 
 
+@pytest.mark.parametrize("band,m", [(128, 5), (129, 5), (128, 1), (129, 1), (1887, 3), (1888, 3)])
+def test_cg_band_product_edges(spd, orc, band, m):
+    """Both sides of the banded product's rules: the p step inside the product
+    (half-band up to 128) and four columns per workgroup (up to 1887), with a
+    ragged last column block; 17 products cross a host check (16)."""
+    n, k = 2100, 17
+    _say(f"cg band edges n={n} band={band} m={m}")
+    A = spdgen.covariance(n, 2)
+    Bt = spdgen.rhs(n, m, 200 + m)
+    X, rep = _gpu_cg(spd, A, Bt, band, max_outer=1, max_inner=k, inner_tol=0.0)
+    Xo, ro = orc.cg_ir(A, Bt, half_band=band, max_outer=1, max_inner=k, inner_tol=0.0)
+    assert (rep.iters_low, rep.iters_high) == (ro.iters_low, ro.iters_high) == (k, 2)
+    err = np.abs(X - Xo).max(axis=1) / np.abs(Xo).max(axis=1)
+    assert err.max() <= 4 * k * (2 * band + 1) * U32, err.max()
+
+
 CASES = [
     (300, 1, -1, 1), (777, 2, -1, 3), (777, 4, -1, 8), (1000, 1, -1, 33),
     (777, 1, 16, 1), (1000, 2, 16, 5), (777, 4, 2, 4), (300, 1, 0, 2),
