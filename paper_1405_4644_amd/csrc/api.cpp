@@ -31,9 +31,8 @@ struct spd_factor_s {
     int prec = -1;
     int elem = 0;            // bytes per factor element (4 or 8)
     int nb = 0;              // panel width
-    size_t cap_L = 0;        // allocated bytes of L / W / Winv
+    size_t cap_L = 0;        // allocated bytes of L and Winv
     void *L = nullptr;       // npad x npad, column-major, lower used
-    void *W = nullptr;       // nt blocks NB x NB: inverses of the diagonal blocks
     void *Winv = nullptr;    // npad/32 blocks 32 x 32: inverses of the 32-wide diagonal sub-blocks
     double *d = nullptr;     // n: equilibration
     int64_t cap_d = 0;
@@ -333,13 +332,12 @@ spd_status factor_blocked(spd_factor_t F, hipStream_t st)
         HIP_TRY(hipStreamWaitEvent(st, evP, 0));
     }
     HIP_TRY(hipGetLastError());
-    spd::launch_trtri_blocks<T>(H, npad, nt, Wi, (T *)F->W, st);
-    spd::launch_build_winv<T>(H, npad, npad, (const T *)F->W, (T *)F->WB, (T *)F->Tb, st);
+    spd::launch_build_winv<T>(H, npad, npad, Wi, (T *)F->WB, (T *)F->Tb, st);
     HIP_TRY(hipGetLastError());
     return SPD_OK;
 }
 
-// sizes and buffers of a factor of order n at precision prec (L, W, Winv
+// sizes and buffers of a factor of order n at precision prec (L and Winv
 // zeroed when (re)allocated), the solve structures, d; mu and the operand
 // rounding from prec
 spd_status prepare_factor(spd_factor_t F, int64_t n, int prec, double theta, hipStream_t st)
@@ -356,27 +354,25 @@ spd_status prepare_factor(spd_factor_t F, int64_t n, int prec, double theta, hip
     if (F->npad == 0) F->npad = pad;
     const int64_t npad = F->npad;
     SPD_TRY(ensure_stream_objs(F));
-    // one allocation for L, W and Winv (all zeroed when (re)allocated)
+    // one allocation for L and Winv (both zeroed when (re)allocated)
     const size_t bL = (size_t)npad * npad * F->elem;
-    const size_t bW = (size_t)npad * F->nb * F->elem;
     const size_t bWi = (size_t)npad * SPD_IB_H * F->elem;
     size_t cap = F->cap_L;
     void *base = F->L;
-    SPD_TRY(grow(&base, &cap, bL + bW + bWi, true, st));
+    SPD_TRY(grow(&base, &cap, bL + bWi, true, st));
     F->L = base;
     F->cap_L = cap;
-    F->W = (char *)base + bL;
-    F->Winv = (char *)base + bL + bW;
+    F->Winv = (char *)base + bL;
     size_t capw = F->cap_WB;
     const size_t bWB = (size_t)spd::solve_winv_elems(npad) * F->elem;
     SPD_TRY(grow(&F->WB, &capw, bWB, true, st));
     F->cap_WB = capw;
-    // The factorisation writes only the lower parts of W, Winv and WB; the
+    // The factorisation writes only the lower parts of Winv and WB; the
     // zeros above rely on these buffers being zero there.  Buffers kept from
     // a factor of another layout (npad or element size: a precision switch
     // on the handle) hold that factor's values at those places: clear them.
     if (old_npad != npad || old_elem != F->elem) {
-        spd::launch_zero((double *)F->W, (int64_t)((bW + bWi) / sizeof(double)), st);
+        spd::launch_zero((double *)F->Winv, (int64_t)(bWi / sizeof(double)), st);
         spd::launch_zero((double *)F->WB, (int64_t)(bWB / sizeof(double)), st);
     }
     size_t capt = F->cap_Tb;
@@ -453,12 +449,11 @@ spd_status do_factor(spd_factor_t F, const double *A, int64_t n, int64_t lda, in
 template <typename T>
 void import_factor(spd_factor_t F, const double *L, int64_t ldl, hipStream_t st)
 {
-    const int64_t n = F->n, npad = F->npad, nt = npad / spd::Panel<T>::NB;
+    const int64_t n = F->n, npad = F->npad;
     spd::launch_equil(L, ldl, n, F->d, 0, st);  // d = 1
     spd::launch_convert<T>(L, ldl, n, npad, F->d, 1.0, (T *)F->L, npad, st);
     spd::launch_inv32_blocks<T>((const T *)F->L, npad, npad, (T *)F->Winv, F->info_dev, st);
-    spd::launch_trtri_blocks<T>((const T *)F->L, npad, nt, (const T *)F->Winv, (T *)F->W, st);
-    spd::launch_build_winv<T>((const T *)F->L, npad, npad, (const T *)F->W, (T *)F->WB, (T *)F->Tb, st);
+    spd::launch_build_winv<T>((const T *)F->L, npad, npad, (const T *)F->Winv, (T *)F->WB, (T *)F->Tb, st);
 }
 
 spd_status do_import(spd_factor_t F, const double *L, int64_t n, int64_t ldl, int prec, hipStream_t st,

@@ -56,8 +56,6 @@ void launch_syrk_update_h256(float *H, int64_t ld, const void *Lh, int slot0, in
                              int half, int64_t r0, int t, int tj_lo, int tj_hi, const unsigned long long *info,
                              hipStream_t st, int prio = 0, int max_grid = 0);
 // max_grid > 0 caps the workgroups (multiple of 8); they then loop over tiles
-template <typename T>
-void launch_trtri_blocks(const T *H, int64_t ld, int64_t nt, const T *Winv, T *W, hipStream_t st);
 // Inverses of the 32 x 32 diagonal sub-blocks of a given factor (Winv layout
 // as left by the factorisation); a non-positive diagonal entry raises info.
 template <typename T>
@@ -76,14 +74,15 @@ void launch_rhs_scale(const double *R, int64_t ldr, int64_t n, int64_t npad, int
                       hipStream_t st);
 // Triangular solves (k_trsv.hip), blocked by big diagonal blocks of
 // solve_nbs(npad) rows whose inverses WB (solve_winv_elems(npad) elements)
-// are built once per factorisation from L and the 128-wide block inverses
-// W128, with solve_tmp_elems(npad) elements of scratch Tb.
+// are built once per factorisation from L and the inverses Winv of its 32 x 32
+// diagonal sub-blocks, with solve_tmp_elems(npad) elements of scratch Tb.  Only
+// the blocks on and below the diagonal are written: WB is zero above it.
 int solve_nbs(int64_t npad);
 int solve_nblocks(int64_t npad);
 int64_t solve_winv_elems(int64_t npad);
 int64_t solve_tmp_elems(int64_t npad);
 template <typename T>
-void launch_build_winv(const T *L, int64_t ld, int64_t npad, const T *W128, T *WB, T *Tb, hipStream_t st);
+void launch_build_winv(const T *L, int64_t ld, int64_t npad, const T *Winv, T *WB, T *Tb, hipStream_t st);
 // Forward Y -> Z then backward Z -> Y for m right-hand sides (TRSV_MC per
 // launch).  P: trsv_scratch_elems(npad) elements; ctl: 2 trsv_ctl_ints(npad)
 // ints (the first half for the forward direction, the second for the

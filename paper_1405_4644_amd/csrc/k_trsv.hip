@@ -2,9 +2,10 @@
 // backward L^T x = y), blocked by big diagonal blocks of NBS (1024) rows.
 //
 // Set-up, once per factorisation: W_k = L_kk^{-1} for every big diagonal
-// block, built from the 128-wide block inverses by repeated doubling,
+// block, built from the 32-wide block inverses by repeated doubling,
 //   [W11 0; W21 W22] with W21 = -W22 (L21 W11),
-// two batched MFMA products per doubling level.
+// two batched MFMA products per doubling level (the first two levels in
+// shared memory).
 //
 // Solve, one persistent launch per direction.  With K big blocks the forward
 // solve is z_k = W_k (b_k - sum_{j<k} L_kj z_j).  It is cut into tasks of R
@@ -35,6 +36,9 @@
 // invalidate) either.
 #include "common.h"
 #include "internal.h"
+
+#include <algorithm>
+#include <type_traits>
 
 #define TRSV_NBS 1024                    // big diagonal block
 #define TRSV_NCRIT 64                    // workgroups on the chain's tasks
@@ -76,39 +80,143 @@ SPD_DEV T load_shared(const T *p)
 // Big-block inverses.
 // WB holds K blocks of nbs x nbs (column-major, leading dimension nbs); block
 // k covers rows [k nbs, k nbs + s_k), s_k = min(nbs, npad - k nbs).
-__global__ __launch_bounds__(256) void k_inv_init_f(const float *__restrict__ W128, int64_t npad, int nbs,
-                                                    float *__restrict__ WB)
+//
+// Base: the inverse of each 128-wide diagonal block from the inverses of its
+// four 32 x 32 diagonal sub-blocks (left by the factorisation), two doubling
+// levels in shared memory; one workgroup per block.  Blocks are 32 x 32, held
+// as [row][column] with pitch 33, so both operands and the results are read
+// and written without bank conflicts; products are formed transposed, so that
+// each lane stores contiguous rows.
+template <typename T>
+struct InvBlk {
+    static constexpr int P = SPD_IB + 1, N = SPD_IB * P;
+    // acc += (A B)^T for the 32 x 32 blocks A and B
+    static SPD_DEV void mul(Acc32<T> &acc, const T *A, const T *B, int lane)
+    {
+        if constexpr (sizeof(T) == 4) {
+            const int r = lane & 31, u = lane >> 5;
+#pragma unroll
+            for (int k = 0; k < SPD_IB; k += 2) acc.mma(B[(k + u) * P + r], A[r * P + k + u]);
+        } else {
+            const int r = lane & 15, u = lane >> 4;
+#pragma unroll
+            for (int k = 0; k < SPD_IB; k += 4) {
+                const double b[2] = {B[(k + u) * P + r], B[(k + u) * P + 16 + r]};
+                const double a[2] = {A[r * P + k + u], A[(16 + r) * P + k + u]};
+                acc.mma(b, a);
+            }
+        }
+    }
+    // D = s acc^T, and to global memory (column-major) when given
+    static SPD_DEV void put(const Acc32<T> &acc, T s, T *D, T *G, int64_t ldg, int lane)
+    {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int c = Acc32<T>::row(j, lane), r = Acc32<T>::col(j, lane);
+            const T v = s * acc.get(j);
+            if (D)
+                D[r * P + c] = v;
+            if (G)
+                G[r + c * ldg] = v;
+        }
+    }
+};
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_inv_base(const T *__restrict__ L, int64_t ld, const T *__restrict__ Winv,
+                                                  int nbs, T *__restrict__ WB)
 {
-    // one workgroup per 128-block b: WB_kb[128 i + r][128 i + c] = W128_b[r][c]
-    const int64_t b = blockIdx.x, g = b * 128, kb = g / nbs, i = (g - kb * nbs) / 128;
-    float *dst = WB + kb * nbs * nbs + 128 * i + 128 * i * nbs;
-    const float *src = W128 + b * 128 * 128;
-    for (int idx = threadIdx.x; idx < 128 * 128; idx += 256)
-        dst[(idx % 128) + (int64_t)(idx / 128) * nbs] = src[idx];
-}
-__global__ __launch_bounds__(256) void k_inv_init_d(const double *__restrict__ W128, int64_t npad, int nbs,
-                                                    double *__restrict__ WB)
-{
-    const int64_t b = blockIdx.x, g = b * 128, kb = g / nbs, i = (g - kb * nbs) / 128;
-    double *dst = WB + kb * nbs * nbs + 128 * i + 128 * i * nbs;
-    const double *src = W128 + b * 128 * 128;
-    for (int idx = threadIdx.x; idx < 128 * 128; idx += 256)
-        dst[(idx % 128) + (int64_t)(idx / 128) * nbs] = src[idx];
+    using IBk = InvBlk<T>;
+    constexpr int IB = SPD_IB;
+    // blocks: W_00, W_11, W_22, W_33, then L_10, L_20, L_21, L_30, L_31, L_32
+    // (row by row of the strict lower triangle); L_10 and L_32 become W_10
+    // and W_32, the other four become T = L_21 W_11 of the second level
+    __shared__ T S[10][IBk::N];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t b = blockIdx.x, g = b * 128, kb = g / nbs, o = g - kb * nbs;
+    const T *Lb = L + g + g * ld, *Wi = Winv + b * 4 * IB * IB;
+    T *Wb = WB + kb * nbs * nbs + o + o * nbs;
+    auto rowof = [](int q) { return q < 1 ? 1 : (q < 3 ? 2 : 3); };  // block row of strict lower block q
+    constexpr int U = 20;  // loads in flight per thread
+    for (int base = 0; base < 10 * IB * IB; base += 256 * U) {
+        T v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = base + u * 256 + tid, blk = e >> 10, r = e & 31, c = (e >> 5) & 31;
+            if (blk < 4) {
+                v[u] = Wi[e];
+            } else {
+                const int i = rowof(blk - 4), j = blk - 4 - i * (i - 1) / 2;
+                v[u] = Lb[(IB * i + r) + (int64_t)(IB * j + c) * ld];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = base + u * 256 + tid, blk = e >> 10, r = e & 31, c = (e >> 5) & 31;
+            S[blk][r * IBk::P + c] = v[u];
+            if (blk < 4)
+                Wb[(IB * blk + r) + (int64_t)(IB * blk + c) * nbs] = v[u];
+        }
+    }
+    __syncthreads();
+    // first level: waves 0 and 1, W_{2p+1,2p} = -W_{2p+1} (L W_{2p})
+    if (wave < 2) {
+        T *Lq = S[wave == 0 ? 4 : 9];
+        const T *W1 = S[2 * wave], *W2 = S[2 * wave + 1];
+        Acc32<T> acc;
+        acc.zero();
+        IBk::mul(acc, Lq, W1, lane);
+        __builtin_amdgcn_wave_barrier();
+        IBk::put(acc, (T)1, Lq, nullptr, 0, lane);
+        __builtin_amdgcn_wave_barrier();
+        acc.zero();
+        IBk::mul(acc, W2, Lq, lane);
+        __builtin_amdgcn_wave_barrier();
+        IBk::put(acc, (T)-1, Lq, Wb + (IB * (2 * wave + 1)) + (int64_t)(IB * 2 * wave) * nbs, nbs, lane);
+    }
+    __syncthreads();
+    // second level, one output block (i, j) per wave, i = 2, 3 and j = 0, 1:
+    // T = L_21 W_11, then W_21 = -W_22 T
+    const int i = 2 + (wave >> 1), j = wave & 1;
+    auto Lblk = [&](int ii, int jj) { return S[4 + ii * (ii - 1) / 2 + jj]; };
+    Acc32<T> acc;
+    acc.zero();
+    if (j == 0) {
+        IBk::mul(acc, Lblk(i, 0), S[0], lane);
+        IBk::mul(acc, Lblk(i, 1), S[4], lane);
+    } else {
+        IBk::mul(acc, Lblk(i, 1), S[1], lane);
+    }
+    __syncthreads();
+    IBk::put(acc, (T)1, Lblk(i, j), nullptr, 0, lane);
+    __syncthreads();
+    acc.zero();
+    if (i == 3)
+        IBk::mul(acc, S[9], Lblk(2, j), lane);
+    IBk::mul(acc, S[i], Lblk(i, j), lane);
+    IBk::put(acc, (T)-1, nullptr, Wb + IB * i + (int64_t)(IB * j) * nbs, nbs, lane);
 }
 
 // One doubling level of width s.  Workgroup (x, y, z): output tile (x, y) of
 // pair p of big block kb (z = kb * ppb + p); the pair is [a0, a1) + [a1, b1)
-// inside the block.  PHASE 1: Tk = L21 W11 (W11 lower: k >= 128 y);
-// PHASE 2: W21 = -W22 Tk (W22 lower: k < 128 (x + 1)).  128 x 128 tiles on
-// MFMA, computed transposed so that each lane stores contiguous rows.
+// inside the block.  PHASE 1: Tk = L21 W11 (W11 lower: k >= 64 y);
+// PHASE 2: W21 = -W22 Tk (W22 lower: k < 64 (x + 1)).  64 x 64 tiles, one
+// 32 x 32 block per wave on MFMA, computed transposed so that each lane
+// stores contiguous rows.  The operands go straight from the caches to
+// registers, the next 32 values of k in flight while the current ones are
+// multiplied: the k-slots of an MFMA are a free summation order, so a lane
+// takes its right operand as one 16-byte load of consecutive k and the left
+// operand's columns are picked to match.
+// Bound by latency for one or two big blocks (n up to 2048: 8 to 64
+// workgroups of a 512-deep product).  128 x 128 tiles staged through shared
+// memory with no load ahead took 18 us per launch at n = 300 and 35 us at
+// n = 1300 and 3000 (average over the levels); these take 7 and 11 us.  At
+// n = 16384 (16 big blocks) both fill the chip: 37 us.
 template <typename T, int PHASE>
 __global__ __launch_bounds__(256) void k_inv_merge(const T *__restrict__ L, int64_t ld, int64_t npad,
                                                    T *__restrict__ WB, int nbs, int s, T *__restrict__ Tb)
 {
-    constexpr int KC = sizeof(T) == 4 ? 32 : 16;
-    constexpr int LDA = 128 + 4, LDB = KC + 1;
-    __shared__ T As[KC * LDA];   // As[k * LDA + m]
-    __shared__ T Bs[128 * LDB];  // Bs[n * LDB + k]
+    constexpr int F32 = sizeof(T) == 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ppb = (nbs + 2 * s - 1) / (2 * s);
     const int kb = blockIdx.z / ppb, p = blockIdx.z % ppb;
@@ -118,7 +226,7 @@ __global__ __launch_bounds__(256) void k_inv_merge(const T *__restrict__ L, int6
     if (a1 >= sk)
         return;
     const int M = b1 - a1;
-    const int m0 = blockIdx.x * 128, n0 = blockIdx.y * 128;
+    const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
     if (m0 >= M)
         return;
     T *Wk = WB + (int64_t)kb * nbs * nbs;
@@ -146,60 +254,64 @@ __global__ __launch_bounds__(256) void k_inv_merge(const T *__restrict__ L, int6
         Cp = Wk + a1 + (int64_t)a0 * nbs;
         ldc = nbs;
         kbeg = 0;
-        kend = (m0 + 128 < M) ? m0 + 128 : M;
+        kend = m0 + 64;  // M is a multiple of 128
         alpha = (T)-1;
     }
-    const int wn = wave >> 1, wm = wave & 1;
-    Acc32<T> acc[2][2];
+    const int mw = m0 + 32 * (wave & 1), nw = n0 + 32 * (wave >> 1);
+    // lane: row r of a 32 (binary32) / 16 (binary64) row block, k-slot u;
+    // group g of 8 values of k: slot u takes k = 8 g + V u + q at step q
+    constexpr int RB = F32 ? 32 : 16, NRB = 32 / RB, V = F32 ? 4 : 2, G = 4;
+    using VT = typename std::conditional<F32, float4, double2>::type;
+    const int r = lane & (RB - 1), u = lane / RB;
+    const T *pA = A + mw + r + (int64_t)(V * u) * lda;
+    const T *pB = B + V * u + (int64_t)(nw + r) * ldb;
+    Acc32<T> acc;
+    acc.zero();
+    T fa[2][G][NRB][V];
+    VT fb[2][G][NRB];
+    auto load = [&](int st, int k0) {
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+        for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b].zero();
-    for (int k0 = kbeg; k0 < kend; k0 += KC) {
-        __syncthreads();
-        copy_g2s<T, 128, 256, 8>(As, LDA, A + m0 + (int64_t)k0 * lda, lda, KC, tid);
-        copy_g2s<T, KC, 256, 8>(Bs, LDB, B + k0 + (int64_t)n0 * ldb, ldb, 128, tid);
-        __syncthreads();
+            for (int h = 0; h < NRB; ++h) {
+                fb[st][g][h] = *(const VT *)(pB + k0 + 8 * g + (int64_t)(RB * h) * ldb);
 #pragma unroll
-        for (int kk = 0; kk < KC; kk += Frag<T>::K) {
-            if constexpr (sizeof(T) == 4) {
-                float fa[2], fb[2];
+                for (int q = 0; q < V; ++q) fa[st][g][h][q] = pA[RB * h + (int64_t)(k0 + 8 * g + q) * lda];
+            }
+    };
+    auto mul = [&](int st) {
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    fa[q] = Bs[(64 * wn + 32 * q + (lane & 31)) * LDB + kk + (lane >> 5)];
-                    fb[q] = As[(kk + (lane >> 5)) * LDA + 64 * wm + 32 * q + (lane & 31)];
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int q = 0; q < V; ++q) {
+                if constexpr (F32) {
+                    const float4 b = fb[st][g][0];
+                    acc.mma(q == 0 ? b.x : q == 1 ? b.y : q == 2 ? b.z : b.w, fa[st][g][0][q]);
+                } else {
+                    const double b[2] = {q == 0 ? fb[st][g][0].x : fb[st][g][0].y,
+                                         q == 0 ? fb[st][g][NRB - 1].x : fb[st][g][NRB - 1].y};
+                    const double a[2] = {fa[st][g][0][q], fa[st][g][NRB - 1][q]};
+                    acc.mma(b, a);
                 }
-#pragma unroll
-                for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-                    for (int mi = 0; mi < 2; ++mi) acc[ni][mi].mma(fa[ni], fb[mi]);
-            } else {
-                double fa[2][2], fb[2][2];
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        fa[q][h] = Bs[(64 * wn + 32 * q + 16 * h + (lane & 15)) * LDB + kk + (lane >> 4)];
-                        fb[q][h] = As[(kk + (lane >> 4)) * LDA + 64 * wm + 32 * q + 16 * h + (lane & 15)];
-                    }
-#pragma unroll
-                for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-                    for (int mi = 0; mi < 2; ++mi) acc[ni][mi].mma(fa[ni], fb[mi]);
             }
-        }
+    };
+    // kend - kbeg is a multiple of 64
+    load(0, kbeg);
+    for (int k0 = kbeg; k0 < kend; k0 += 64) {
+        load(1, k0 + 32);
+        __builtin_amdgcn_sched_barrier(0);
+        mul(0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (k0 + 64 < kend)
+            load(0, k0 + 64);
+        __builtin_amdgcn_sched_barrier(0);
+        mul(1);
+        __builtin_amdgcn_sched_barrier(0);
     }
-    // register j of acc[ni][mi]: n = 64 wn + 32 ni + row(j), m = 64 wm + 32 mi + col(j)
+    // register j: n = row(j), m = col(j)
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int n = 64 * wn + 32 * ni + Acc32<T>::row(j, lane);
-                const int m = 64 * wm + 32 * mi + Acc32<T>::col(j, lane);
-                Cp[(m0 + m) + (int64_t)(n0 + n) * ldc] = alpha * acc[ni][mi].get(j);
-            }
+    for (int j = 0; j < 16; ++j)
+        Cp[(mw + Acc32<T>::col(j, lane)) + (int64_t)(nw + Acc32<T>::row(j, lane)) * ldc] = alpha * acc.get(j);
 }
 
 // ---------------------------------------------------------------------------
@@ -590,16 +702,13 @@ int64_t trsv_scratch_elems(int64_t npad)
 int trsv_ctl_ints(int64_t npad) { return (3 + 3 * solve_nblocks(npad) + 63) & ~63; }
 
 template <typename T>
-void launch_build_winv(const T *L, int64_t ld, int64_t npad, const T *W128, T *WB, T *Tb, hipStream_t st)
+void launch_build_winv(const T *L, int64_t ld, int64_t npad, const T *Winv, T *WB, T *Tb, hipStream_t st)
 {
     const int nbs = solve_nbs(npad), K = solve_nblocks(npad);
-    if constexpr (sizeof(T) == 4)
-        hipLaunchKernelGGL(k_inv_init_f, dim3((unsigned)(npad / 128)), dim3(256), 0, st, W128, npad, nbs, WB);
-    else
-        hipLaunchKernelGGL(k_inv_init_d, dim3((unsigned)(npad / 128)), dim3(256), 0, st, W128, npad, nbs, WB);
+    hipLaunchKernelGGL(k_inv_base<T>, dim3((unsigned)(npad / 128)), dim3(256), 0, st, L, ld, Winv, nbs, WB);
     for (int s = 128; s < nbs; s *= 2) {
         const int ppb = (nbs + 2 * s - 1) / (2 * s);
-        const dim3 grid((unsigned)(s / 128), (unsigned)(s / 128), (unsigned)(K * ppb));
+        const dim3 grid((unsigned)(s / 64), (unsigned)(s / 64), (unsigned)(K * ppb));
         hipLaunchKernelGGL((k_inv_merge<T, 1>), grid, dim3(256), 0, st, L, ld, npad, WB, nbs, s, Tb);
         hipLaunchKernelGGL((k_inv_merge<T, 2>), grid, dim3(256), 0, st, L, ld, npad, WB, nbs, s, Tb);
     }

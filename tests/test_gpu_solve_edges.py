@@ -1,0 +1,44 @@
+"""The triangular solves at the edges of their blocking: a given factor L
+(unit diagonal, N(0, 1/(16 n)) entries below it) is imported and
+X = L^{-T} L^{-1} B is compared with numpy's binary64 solution.
+
+Bound: each substitution with rounded factor and explicit block inverses has
+a forward error of at most about 2 n u kappa(L), kappa(L) = || |L^{-1}| |L| ||_inf,
+and the first one's error is carried through the second:
+4 n u kappa(L) kappa(L^T) relative to max|x|, u the factor's unit roundoff.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+U = {"fp32": 2.0 ** -24, "fp64": 2.0 ** -53}
+
+
+def check(spd, n, m, prec):
+    import torch
+    print(f"solve edges n={n} m={m} {prec}", flush=True)
+    sys.stdout.flush()
+    rng = np.random.Generator(np.random.PCG64(n * 100 + m))
+    L = np.tril(rng.standard_normal((n, n)) / (4 * np.sqrt(n)), -1) + np.eye(n)
+    B = rng.standard_normal((m, n))
+    Li = np.linalg.inv(L)
+    ref = (Li.T @ (Li @ B.T)).T
+    kap = (np.abs(Li) @ np.abs(L)).sum(axis=1).max() * (np.abs(Li.T) @ np.abs(L.T)).sum(axis=1).max()
+    F, info, st = spd.factor_import(torch.from_numpy(L).cuda(), prec=prec)
+    assert info == 0 and st == 0
+    X = spd.solve(F, torch.from_numpy(B).cuda()).cpu().numpy()
+    F.close()
+    err = np.abs(X - ref).max(axis=1) / np.abs(ref).max(axis=1)
+    assert err.max() <= 4 * n * U[prec] * kap, (err.max(), 4 * n * U[prec] * kap)
+    # a wrong or missing block shows as an error of the size of an entry of L
+    assert err.max() <= (1e-3 if prec == "fp32" else 1e-11), err.max()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", [1, 33, 128, 129, 256, 300, 512, 640, 897, 1024, 1025, 1536, 1700])
+def test_block_inverses(spd, n, prec):
+    """Orders around the doubling levels of the block inverses (128, 256, 512,
+    1024), with whole, ragged and single-block pairs at each level."""
+    check(spd, n, 1, prec)
