@@ -1,264 +1,210 @@
 // Binary64 residual R = B - A X and the norms of the backward error
 // (Algorithm 1's residual steps, the ones it carries out in high precision).
 //
-// A is symmetric with only its lower triangle stored.  Workgroup (I, s) owns
-// the 64-row block I and visits the 64-column blocks J = s, s + S, ...; each
-// 64 x 64 tile of the full symmetric matrix is formed in LDS from the lower
-// triangle (directly for J < I, transposed for J > I, mirrored for J == I)
-// and multiplied by the matching rows of X.  Per-(s, row) partial sums are
-// reduced in a fixed order by k_resid_reduce, so results are bitwise
+// A is symmetric with only its lower triangle stored.  One or two right-hand
+// sides: one pass over the lower triangle, every stored element serving its
+// row and its column (k_resid_sym).  More: the whole symmetric matrix on
+// binary64 MFMA, the part right of the diagonal read from the lower
+// triangle's columns (k_resid_mfma).  Both leave partial sums that a second kernel adds in a fixed order, so results are bitwise
 // reproducible run to run.  The same pass can accumulate sum_j |a_ij| for
 // ||A||_inf.
 #include "common.h"
 #include "internal.h"
 #include <algorithm>
 
-template <int MC, int RB, int CB, int JS>
-__global__ __launch_bounds__(256) void k_resid_partial(const double *__restrict__ A, int64_t lda, int64_t n,
-                                                       const double *__restrict__ X, int64_t ldx, int m, int c0, int S,
-                                                       double *__restrict__ P, double *__restrict__ Pabs, int want_abs)
-{
-    constexpr int RG = 64 / RB, CG = MC / CB;
-    static_assert(RG * CG * JS == 256, "thread layout");
-    constexpr int TS = 65;
-    __shared__ double Ts[64 * TS];
-    __shared__ double Xs[MC * 64];
-    const int tid = threadIdx.x;
-    const int rg = tid % RG, cg = (tid / RG) % CG, js = tid / (RG * CG);
-    const int I = blockIdx.x, s = blockIdx.y;
-    const int64_t i0 = (int64_t)I * 64;
-    const int nrb = (int)((n + 63) / 64);
-    double acc[RB][CB];
-    double aabs[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        aabs[r] = 0.0;
-#pragma unroll
-        for (int c = 0; c < CB; ++c) acc[r][c] = 0.0;
-    }
-    const bool do_abs = want_abs && cg == 0;
-    for (int J = s; J < nrb; J += S) {
-        const int64_t j0 = (int64_t)J * 64;
-        __syncthreads();
-        if (J < I) {
-            for (int idx = tid; idx < 4096; idx += 256) {
-                const int i = idx & 63, j = idx >> 6;
-                const int64_t gi = i0 + i, gj = j0 + j;
-                Ts[j * TS + i] = (gi < n && gj < n) ? A[gi + gj * lda] : 0.0;
-            }
-        } else if (J > I) {
-            for (int idx = tid; idx < 4096; idx += 256) {
-                const int j = idx & 63, i = idx >> 6;
-                const int64_t gi = i0 + i, gj = j0 + j;
-                Ts[j * TS + i] = (gi < n && gj < n) ? A[gj + gi * lda] : 0.0;
-            }
-        } else {
-            for (int idx = tid; idx < 4096; idx += 256) {
-                const int i = idx & 63, j = idx >> 6;
-                const int64_t gi = i0 + i, gj = j0 + j;
-                Ts[j * TS + i] = (i >= j && gi < n && gj < n) ? A[gi + gj * lda] : 0.0;
-            }
-            __syncthreads();
-            for (int idx = tid; idx < 4096; idx += 256) {
-                const int i = idx & 63, j = idx >> 6;
-                if (i < j)
-                    Ts[j * TS + i] = Ts[i * TS + j];
-            }
-        }
-        for (int idx = tid; idx < MC * 64; idx += 256) {
-            const int j = idx & 63, c = idx >> 6;
-            const int64_t gj = j0 + j;
-            Xs[c * 64 + j] = (gj < n && c0 + c < m) ? X[gj + (int64_t)(c0 + c) * ldx] : 0.0;
-        }
-        __syncthreads();
-        constexpr int JW = 64 / JS;
-#pragma unroll 4
-        for (int jj = 0; jj < JW; ++jj) {
-            const int j = js * JW + jj;
-            double a[RB], x[CB];
-#pragma unroll
-            for (int r = 0; r < RB; ++r) a[r] = Ts[j * TS + rg + RG * r];
-#pragma unroll
-            for (int c = 0; c < CB; ++c) x[c] = Xs[(cg * CB + c) * 64 + j];
-#pragma unroll
-            for (int r = 0; r < RB; ++r)
-#pragma unroll
-                for (int c = 0; c < CB; ++c) acc[r][c] = fma(a[r], x[c], acc[r][c]);
-            if (do_abs)
-#pragma unroll
-                for (int r = 0; r < RB; ++r) aabs[r] += fabs(a[r]);
-        }
-    }
-    // combine the JS partial sums (fixed order) and store
-    __syncthreads();
-    double *red = Ts;  // reuse: JS * MC * 64 <= 64 * TS doubles
-    if (JS > 1) {
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-#pragma unroll
-            for (int c = 0; c < CB; ++c)
-                red[(js * MC + cg * CB + c) * 64 + rg + RG * r] = acc[r][c];
-    }
-    __shared__ double redabs[JS * 64];
-    if (do_abs)
-#pragma unroll
-        for (int r = 0; r < RB; ++r) redabs[js * 64 + rg + RG * r] = aabs[r];
-    __syncthreads();
-    if (js == 0) {
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            const int i = rg + RG * r;
-            const int64_t gi = i0 + i;
-            if (gi >= n)
-                continue;
-#pragma unroll
-            for (int c = 0; c < CB; ++c) {
-                const int cc = cg * CB + c;
-                double v = acc[r][c];
-                for (int q = 1; q < JS; ++q)
-                    v += red[(q * MC + cc) * 64 + i];
-                if (c0 + cc < m)
-                    P[((int64_t)s * m + c0 + cc) * n + gi] = v;
-            }
-            if (do_abs) {
-                double v = aabs[r];
-                for (int q = 1; q < JS; ++q)
-                    v += redabs[q * 64 + i];
-                Pabs[(int64_t)s * n + gi] = v;
-            }
-        }
-    }
-}
-
-// The same partial sums for 9..32 right-hand sides per chunk on binary64
-// MFMA (v_mfma_f64_16x16x4f64): wave w owns rows 16 w .. 16 w + 15 of the
-// tile and NT column tiles of 16; per k-step of 4 a lane feeds A(i, k) with
-// i = lane % 16, k = lane / 16 from the LDS tile and X(k, c) with
-// c = lane % 16 from the LDS copy of X (pitch 65: conflict-free columns).
-// The accumulator holds row lane / 16 + 4 r, column lane % 16 in register r
-// (the binary64 layout, unlike the binary32 16 x 16 one).
-typedef double doublex4 __attribute__((ext_vector_type(4)));
+// The whole symmetric matrix times X for up to 16 NT right-hand sides on
+// v_mfma_f64_16x16x4f64.  Workgroup (I, s): rows [128 I, 128 I + 128), the
+// 64-column tiles J = s, s + S, ...; each wave owns 32 rows.  The k-slots of
+// the MFMA are a free summation order: lane (r = lane % 16, u = lane / 16)
+// takes columns 16 g + 8 e + 2 u + q of a tile at step (e, q) of group g.  Left of the
+// diagonal its values are then 128-byte runs of rows (lanes r), right of it
+// -- the transpose, stored as columns -- 16-byte loads that cover 64-byte runs
+// of a column (lanes u): A goes from memory to the MFMA's registers without shared memory,
+// the next tile's values in flight while the current one is multiplied.  X's
+// tile is shared by the four waves through LDS (two buffers, one barrier per
+// tile; pitch 66 doubles: 16-byte reads of 16 columns without bank
+// conflicts).  Operands are given as (X, A), so that register v of a lane is
+// right-hand side 4 v + u, row r: partials are stored along rows.
+// Bound by reading the symmetric A once per chunk of 32 right-hand sides, and
+// by the binary64 MFMA rate at 17..32 columns.  Staging A's 64 x 64 tiles
+// through shared memory (two barriers per tile, X re-read for every 64 rows)
+// took 256 us at n = 10000 with 32 columns and 362 at n = 12000; this takes
+// 197 and 272 us (4.1 TB/s).  At n = 6000 with 5 columns one thread per row
+// and column pair on 64 x 64 tiles took 84 us, this 57.
+typedef double double2u __attribute__((ext_vector_type(2), aligned(8)));  // 16-byte load, 8-byte aligned
 template <int NT>
-__global__ __launch_bounds__(256) void k_resid_mfma(const double *__restrict__ A, int64_t lda, int64_t n,
-                                                    const double *__restrict__ X, int64_t ldx, int m, int c0, int S,
-                                                    double *__restrict__ P, double *__restrict__ Pabs, int want_abs)
+__global__ __launch_bounds__(256, 2) void k_resid_mfma(const double *__restrict__ A, int64_t lda, int64_t n,
+                                                       const double *__restrict__ X, int64_t ldx, int m, int c0,
+                                                       int S, double *__restrict__ P, double *__restrict__ Pabs,
+                                                       int want_abs)
 {
-    constexpr int MC = 16 * NT, TS = 65, XU = MC * 64 / 256;
-    __shared__ double Ts[64 * TS];
-    __shared__ double Xs[MC * TS];
+    constexpr int MC = 16 * NT, PX = 66, XU = MC * 64 / 256;
+    __shared__ __align__(16) double Xs[2][MC * PX];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int r16 = lane & 15, kq = lane >> 4;
-    const int I = blockIdx.x, s = blockIdx.y;
-    const int64_t i0 = (int64_t)I * 64;
-    const int nrb = (int)((n + 63) / 64);
-    doublex4 acc[NT];
+    const int r = lane & 15, u = lane >> 4;
+    const int s = blockIdx.y;
+    const int64_t iw = (int64_t)blockIdx.x * 128 + 32 * w;  // the wave's first row
+    const int njt = (int)((n + 63) / 64);
+    doublex4 acc[2][NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = doublex4{0.0, 0.0, 0.0, 0.0};
-    double aabs = 0.0;
-    // The next tile's values are loaded into registers while the current
-    // tile is multiplied.  Element u of a thread: idx = tid + 256 u; for a
-    // tile left of the diagonal (and the diagonal tile, lower part only)
-    // i = idx % 64, j = idx / 64 read along A's column j; right of it
-    // j = idx % 64, i = idx / 64 read along A's column i (the transpose).
-    double av[16], xv[XU];
-    auto fetch = [&](int J) {
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[h][t] = doublex4{0.0, 0.0, 0.0, 0.0};
+    double aabs[2] = {0.0, 0.0};
+    // a[h][g][2 e + q]: row iw + 16 h + r, column 64 J + 16 g + 8 e + 2 u + q
+    auto fetch = [&](double (&a)[2][4][4], int J) {
         const int64_t j0 = (int64_t)J * 64;
+        if (iw + 32 <= n && j0 + 64 <= iw) {
+            const double *p = A + iw + r + (j0 + 2 * u) * lda;
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const int idx = tid + 256 * u;
-            double v = 0.0;
-            if (J <= I) {
-                const int i = idx & 63, j = idx >> 6;
-                const int64_t gi = i0 + i, gj = j0 + j;
-                if (gi < n && gj < n && (J < I || i >= j)) v = A[gi + gj * lda];
-            } else {
-                const int j = idx & 63, i = idx >> 6;
-                const int64_t gi = i0 + i, gj = j0 + j;
-                if (gi < n && gj < n) v = A[gj + gi * lda];
-            }
-            av[u] = v;
-        }
+            for (int g = 0; g < 4; ++g)
 #pragma unroll
-        for (int u = 0; u < XU; ++u) {
-            const int idx = tid + 256 * u;
-            const int j = idx & 63, c = idx >> 6;
-            const int64_t gj = j0 + j;
-            xv[u] = (gj < n && c0 + c < m) ? X[gj + (int64_t)(c0 + c) * ldx] : 0.0;
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) a[h][g][q] = p[16 * h + (int64_t)(16 * g + 8 * (q >> 1) + (q & 1)) * lda];
+        } else if (j0 + 64 <= n && j0 >= iw + 32) {
+            const double *p = A + j0 + 2 * u + (iw + r) * lda;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+#pragma unroll
+                    for (int q = 0; q < 4; q += 2) {
+                        const double2u v = *(const double2u *)(p + 16 * h * lda + 16 * g + 4 * q);
+                        a[h][g][q] = v.x;
+                        a[h][g][q + 1] = v.y;
+                    }
+        } else {  // on the diagonal, or at the matrix's edge
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int64_t gi = iw + 16 * h + r, gj = j0 + 16 * g + 8 * (q >> 1) + 2 * u + (q & 1);
+                        a[h][g][q] = (gi < n && gj < n) ? (gi >= gj ? A[gi + gj * lda] : A[gj + gi * lda]) : 0.0;
+                    }
         }
     };
-    if (s < nrb) fetch(s);
-    for (int J = s; J < nrb; J += S) {
-        __syncthreads();  // the previous tile has been consumed
+    double xv[XU];
+    auto fetch_x = [&](int J) {
+        const int64_t gj = (int64_t)J * 64 + (tid & 63);
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const int idx = tid + 256 * u;
-            if (J <= I)
-                Ts[(idx >> 6) * TS + (idx & 63)] = av[u];
-            else
-                Ts[(idx & 63) * TS + (idx >> 6)] = av[u];
+        for (int e = 0; e < XU; ++e) {
+            const int c = c0 + (tid >> 6) + 4 * e;
+            xv[e] = (gj < n && c < m) ? X[gj + (int64_t)c * ldx] : 0.0;
         }
+    };
+    auto stage_x = [&](int buf) {
 #pragma unroll
-        for (int u = 0; u < XU; ++u) {
-            const int idx = tid + 256 * u;
-            Xs[(idx >> 6) * TS + (idx & 63)] = xv[u];
+        for (int e = 0; e < XU; ++e) Xs[buf][((tid >> 6) + 4 * e) * PX + (tid & 63)] = xv[e];
+    };
+    auto multiply = [&](const double (&a)[2][4][4], int buf) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            double2 x[NT][2];
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    x[t][e] = *(const double2 *)&Xs[buf][(16 * t + r) * PX + 16 * g + 8 * e + 2 * u];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        acc[h][t] = __builtin_amdgcn_mfma_f64_16x16x4f64((q & 1) ? x[t][q >> 1].y : x[t][q >> 1].x,
+                                                                         a[h][g][q], acc[h][t], 0, 0, 0);
         }
-        if (J == I) {  // mirror the lower triangle of the diagonal tile
-            __syncthreads();
-            for (int idx = tid; idx < 4096; idx += 256) {
-                const int i = idx & 63, j = idx >> 6;
-                if (i < j)
-                    Ts[j * TS + i] = Ts[i * TS + j];
-            }
+        if (want_abs)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) aabs[h] += fabs(a[h][g][q]);
+    };
+    double a0[2][4][4], a1[2][4][4];
+    if (s < njt) {
+        fetch_x(s);
+        fetch(a0, s);
+        stage_x(0);
+    }
+    __syncthreads();
+    for (int J = s; J < njt; J += 2 * S) {
+        if (J + S < njt) {
+            fetch_x(J + S);
+            fetch(a1, J + S);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(a0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (J + S < njt)
+            stage_x(1);
         __syncthreads();
-        if (J + S < nrb) fetch(J + S);  // in flight during the products below
-        if (want_abs && tid < 64)
-            for (int j = 0; j < 64; ++j) aabs += fabs(Ts[j * TS + tid]);
-#pragma unroll 4
-        for (int k0 = 0; k0 < 64; k0 += 4) {
-            const double a = Ts[(k0 + kq) * TS + 16 * w + r16];
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const double b = Xs[(16 * t + r16) * TS + k0 + kq];
-                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[t], 0, 0, 0);
-            }
+        if (J + S >= njt)
+            break;
+        if (J + 2 * S < njt) {
+            fetch_x(J + 2 * S);
+            fetch(a0, J + 2 * S);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(a1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (J + 2 * S < njt)
+            stage_x(0);
+        __syncthreads();
     }
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+    for (int h = 0; h < 2; ++h) {
+        const int64_t gi = iw + 16 * h + r;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t gi = i0 + 16 * w + kq + 4 * r;
-            const int c = 16 * t + r16;
-            if (gi < n && c0 + c < m) P[((int64_t)s * m + c0 + c) * n + gi] = acc[t][r];
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int c = c0 + 16 * t + 4 * v + u;
+                if (gi < n && c < m) P[((int64_t)s * m + c) * n + gi] = acc[h][t][v];
+            }
+        if (want_abs) {  // the four k-slots of a row, in a fixed order
+            double v = aabs[h];
+            v += __shfl_xor(v, 16);
+            v += __shfl_xor(v, 32);
+            if (u == 0 && gi < n) Pabs[(int64_t)s * n + gi] = v;
         }
-    if (want_abs && tid < 64 && i0 + tid < n) Pabs[(int64_t)s * n + i0 + tid] = aabs;
+    }
 }
 
-// Single pass over the lower triangle for a few right-hand sides.  Workgroup
-// (J, q) walks tiles I = J + q CH .. of the 64-column strip J (contiguous in
-// memory); wave w holds columns 16 w .. 16 w + 15 of the tile, lane l its row
-// l.  Each stored a_ij (i > j) serves twice: a_ij x_j for row i (a row partial
-// per tile, RP[I][J]) and a_ij x_i for row j (accumulated over the chunk in
-// registers, CP[J][q]); a diagonal tile uses its lower triangle only (the
-// diagonal once).  k_resid_sym_reduce then sums, per row of block I,
-// RP[I][0..I] (as four interleaved sums) and CP[I][0..Q), in a fixed order.  With want_abs an extra
-// "column" c = MC carries |a_ij| (row sums of |A|).
+// Single pass over the lower triangle for one or two right-hand sides.
+// Workgroup (J, q) walks tiles I = J + q ch .. of the 64-column strip J
+// (contiguous in memory); wave w holds columns 16 w .. 16 w + 15 of the tile,
+// lane l its row l.  Each stored a_ij (i > j) serves twice: a_ij x_j for row i
+// (a row partial per tile, RP[I][J]) and a_ij x_i for row j (accumulated over
+// the chunk in registers, CP[J][q]); a diagonal tile uses its lower triangle
+// only (the diagonal once).  k_resid_sym_reduce then sums, per row of block I,
+// RP[I][0..I] (as four interleaved sums) and CP[I][.], in a fixed order.  With
+// WA an extra "column" c = MC carries |a_ij| (row sums of |A|).
+// Bound by reading the triangle (224 us, 4.8 TB/s, at n = 16384).  ch tiles
+// per workgroup: 16 where that leaves 512 workgroups, fewer on smaller
+// matrices, whose chunks of 16 tiles in sequence left the chip idle, and the
+// column sums reduced 16 at a time (a lane keeps half of its sums at each
+// exchange: 17 exchanges instead of 96).  n = 300: 12.2 us before, 7.0 now;
+// n = 3000: 26.0 and 16.9 us.
 #define RSYM_CH 16
 template <int MC, bool WA>
 __global__ __launch_bounds__(256) void k_resid_sym(const double *__restrict__ A, int64_t lda, int64_t n,
-                                                   const double *__restrict__ X, int64_t ldx, int m, int Q,
+                                                   const double *__restrict__ X, int64_t ldx, int m, int ch, int Q,
                                                    double *__restrict__ RP, double *__restrict__ CP)
 {
     constexpr int NC = MC + 1;  // partial "columns" in the layout: MC right-hand sides + |A|
     constexpr int NA = WA ? NC : MC;  // the ones this variant computes
-    constexpr bool want_abs = WA;
+    constexpr int CW = 16;
     __shared__ double xs[MC][64];
-    __shared__ double red[4][NA][64];
+    __shared__ double red[2][4][NA][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int J = blockIdx.x, q = blockIdx.y;
     const int nrb = (int)((n + 63) / 64);
-    const int I0 = J + q * RSYM_CH, I1 = min(I0 + RSYM_CH, nrb);
+    const int I0 = J + q * ch, I1 = min(I0 + ch, nrb);
     if (I0 >= nrb)
         return;
     const int64_t j0 = (int64_t)J * 64;
@@ -268,33 +214,34 @@ __global__ __launch_bounds__(256) void k_resid_sym(const double *__restrict__ A,
         xs[c][j] = (j0 + j < n && c < m) ? X[(j0 + j) + (int64_t)c * ldx] : 0.0;
     }
     __syncthreads();
-    double cacc[16][NA];
+    double cacc[CW][NA];
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj)
+    for (int jj = 0; jj < CW; ++jj)
 #pragma unroll
         for (int c = 0; c < NA; ++c) cacc[jj][c] = 0.0;
     // tile loads run one tile ahead of the arithmetic
-    double an[16];
+    double an[CW];
     auto load_tile = [&](int I) {
         const int64_t gi = (int64_t)I * 64 + lane;
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            const int64_t gj = j0 + 16 * w + jj;
+        for (int jj = 0; jj < CW; ++jj) {
+            const int64_t gj = j0 + CW * w + jj;
             an[jj] = (gi < n && gj < n) ? A[gi + gj * lda] : 0.0;
         }
     };
     load_tile(I0);
     for (int I = I0; I < I1; ++I) {
         const int64_t gi = (int64_t)I * 64 + lane;
-        double a[16];
+        double a[CW];
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj) a[jj] = an[jj];
+        for (int jj = 0; jj < CW; ++jj) a[jj] = an[jj];
         if (I + 1 < I1)
             load_tile(I + 1);
+        const int dj = lane - CW * w;  // on the diagonal tile: row minus the wave's first column
         if (I == J) {
 #pragma unroll
-            for (int jj = 0; jj < 16; ++jj)
-                if (lane < 16 * w + jj)
+            for (int jj = 0; jj < CW; ++jj)
+                if (dj < jj)
                     a[jj] = 0.0;
         }
         double xi[MC];
@@ -304,11 +251,11 @@ __global__ __launch_bounds__(256) void k_resid_sym(const double *__restrict__ A,
 #pragma unroll
         for (int c = 0; c < NA; ++c) racc[c] = 0.0;
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            const bool strict = (I != J) || (lane > 16 * w + jj);
+        for (int jj = 0; jj < CW; ++jj) {
+            const bool strict = (I != J) || (dj > jj);
 #pragma unroll
             for (int c = 0; c < MC; ++c) {
-                racc[c] = fma(a[jj], xs[c][16 * w + jj], racc[c]);
+                racc[c] = fma(a[jj], xs[c][CW * w + jj], racc[c]);
                 if (strict)
                     cacc[jj][c] = fma(a[jj], xi[c], cacc[jj][c]);
             }
@@ -318,27 +265,38 @@ __global__ __launch_bounds__(256) void k_resid_sym(const double *__restrict__ A,
                     cacc[jj][NA - 1] += fabs(a[jj]);
             }
         }
-        // row partial of tile (I, J): sum over the 4 waves in order
+        // row partial of tile (I, J): sum over the 4 waves in order (the two
+        // buffers alternate, so one barrier per tile)
+        double(*rd)[NA][64] = red[I & 1];
 #pragma unroll
-        for (int c = 0; c < NA; ++c) red[w][c][lane] = racc[c];
+        for (int c = 0; c < NA; ++c) rd[w][c][lane] = racc[c];
         __syncthreads();
         for (int idx = threadIdx.x; idx < NA * 64; idx += 256) {
             const int c = idx / 64, i = idx % 64;
-            RP[(((int64_t)I * nrb + J) * NC + c) * 64 + i] = ((red[0][c][i] + red[1][c][i]) + red[2][c][i]) + red[3][c][i];
+            RP[(((int64_t)I * nrb + J) * NC + c) * 64 + i] = ((rd[0][c][i] + rd[1][c][i]) + rd[2][c][i]) + rd[3][c][i];
         }
-        __syncthreads();
     }
-    // column partials: reduce each column's 64 lanes (fixed butterfly order)
+    // column partials: the 64 lanes of all 16 columns together, in a fixed
+    // order -- at each exchange a lane hands over half of its sums and adds
+    // its partner's to the half it keeps; lane l ends with column l / 4
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj)
+    for (int c = 0; c < NA; ++c) {
 #pragma unroll
-        for (int c = 0; c < NA; ++c) {
-            double v = cacc[jj][c];
+        for (int h = CW / 2, off = 32; h >= 1; h /= 2, off /= 2) {
+            const bool up = (lane & off) != 0;
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-            if (lane == 0)
-                CP[(((int64_t)J * Q + q) * NC + c) * 64 + 16 * w + jj] = v;
+            for (int k = 0; k < h; ++k) {
+                const double give = up ? cacc[k][c] : cacc[k + h][c];
+                const double keep = up ? cacc[k + h][c] : cacc[k][c];
+                cacc[k][c] = keep + __shfl_xor(give, off);
+            }
         }
+        double v = cacc[0][c];
+        v += __shfl_xor(v, 2);
+        v += __shfl_xor(v, 1);
+        if ((lane & 3) == 0)
+            CP[(((int64_t)J * Q + q) * NC + c) * 64 + CW * w + (lane >> 2)] = v;
+    }
 }
 
 SPD_DEV double nanmax2(double a, double b) { return (a > b || a != a) ? a : b; }
@@ -360,9 +318,22 @@ __global__ __launch_bounds__(256) void k_resid_reduce(const double *__restrict__
     const int c = blockIdx.y;
     double vr = 0.0, vx = 0.0, vb = 0.0, vd = 0.0, va = 0.0;
     if (i < n) {
-        double sum = 0.0;
-        for (int s = 0; s < S; ++s)
-            sum += P[((int64_t)s * m + c) * n + i];
+        // the slices in order, eight loads in flight (one at a time they cost
+        // a memory round trip each: 10.6 us for the 21 slices of n = 1300)
+        auto total = [&](const double *p, int64_t st) {
+            double sum = 0.0;
+            for (int s0 = 0; s0 < S; s0 += 8) {
+                double v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = (s0 + k < S) ? p[(s0 + k) * st] : 0.0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (s0 + k < S)
+                        sum += v[k];
+            }
+            return sum;
+        };
+        const double sum = total(P + (int64_t)c * n + i, (int64_t)m * n);
         const double b = B[i + c * ldb];
         const double r = b - sum;
         R[i + c * ldr] = r;
@@ -370,12 +341,8 @@ __global__ __launch_bounds__(256) void k_resid_reduce(const double *__restrict__
         vx = fabs(X[i + c * ldx]);
         vb = fabs(b);
         vd = d ? fabs(d[i] * r) : vr;
-        if (want_abs && c == 0) {
-            double a = 0.0;
-            for (int s = 0; s < S; ++s)
-                a += Pabs[(int64_t)s * n + i];
-            va = a;
-        }
+        if (want_abs && c == 0)
+            va = total(Pabs + i, n);
     }
     vr = wave_max2(vr);
     vx = wave_max2(vx);
@@ -394,13 +361,14 @@ __global__ __launch_bounds__(256) void k_resid_reduce(const double *__restrict__
 }
 
 // R = B - (sum_J RP[I][J] + sum_q CP[I][q]) and the norms (as k_resid_reduce).
-// Workgroup (I, c): 64 rows of block I, four waves; wave p sums the partials
-// J = p, p + 4, ... (loads issued four at a time), and the four sums are
-// added in the fixed order (s0 + s1) + (s2 + s3), then the column partials.
+// Workgroup (I, c): 64 rows of block I, four waves; wave p sums the row
+// partials J = p, p + 4, ... and the column partials q = p, p + 4, ... (loads
+// issued four at a time), and the four sums are added in the fixed order
+// (s0 + s1) + (s2 + s3).
 template <int MC>
 __global__ __launch_bounds__(256) void k_resid_sym_reduce(const double *__restrict__ B, int64_t ldb,
                                                           const double *__restrict__ X, int64_t ldx, int64_t n, int m,
-                                                          int Q, const double *__restrict__ RP,
+                                                          int ch, int Q, const double *__restrict__ RP,
                                                           const double *__restrict__ CP, int want_abs,
                                                           const double *__restrict__ d, double *__restrict__ R,
                                                           int64_t ldr, double *norms)
@@ -412,24 +380,27 @@ __global__ __launch_bounds__(256) void k_resid_sym_reduce(const double *__restri
     const int nrb = (int)((n + 63) / 64);
     const bool wa = want_abs && c == 0;
     {
-        const double *rp = RP + ((int64_t)I * nrb * NC + c) * 64 + il;
-        const double *ra = RP + ((int64_t)I * nrb * NC + MC) * 64 + il;
-        const int64_t st = (int64_t)NC * 64;  // stride between consecutive J
         double y = 0.0, ya = 0.0;
-        int J = p;
-        for (; J + 12 <= I; J += 16) {
-            const double v0 = rp[J * st], v1 = rp[(J + 4) * st], v2 = rp[(J + 8) * st], v3 = rp[(J + 12) * st];
-            if (wa) {
-                const double a0 = ra[J * st], a1 = ra[(J + 4) * st], a2 = ra[(J + 8) * st], a3 = ra[(J + 12) * st];
-                ya = (((ya + a0) + a1) + a2) + a3;
+        // v = p, p + 4, ... < cnt, consecutive ones st doubles apart
+        auto sum = [&](const double *rp, const double *ra, int64_t st, int cnt) {
+            int v = p;
+            for (; v + 12 < cnt; v += 16) {
+                const double v0 = rp[v * st], v1 = rp[(v + 4) * st], v2 = rp[(v + 8) * st], v3 = rp[(v + 12) * st];
+                if (wa) {
+                    const double a0 = ra[v * st], a1 = ra[(v + 4) * st], a2 = ra[(v + 8) * st], a3 = ra[(v + 12) * st];
+                    ya = (((ya + a0) + a1) + a2) + a3;
+                }
+                y = (((y + v0) + v1) + v2) + v3;
             }
-            y = (((y + v0) + v1) + v2) + v3;
-        }
-        for (; J <= I; J += 4) {
-            y += rp[J * st];
-            if (wa)
-                ya += ra[J * st];
-        }
+            for (; v < cnt; v += 4) {
+                y += rp[v * st];
+                if (wa)
+                    ya += ra[v * st];
+            }
+        };
+        const double *rp = RP + (int64_t)I * nrb * NC * 64 + il, *cp = CP + (int64_t)I * Q * NC * 64 + il;
+        sum(rp + c * 64, rp + MC * 64, (int64_t)NC * 64, I + 1);
+        sum(cp + c * 64, cp + MC * 64, (int64_t)NC * 64, (nrb - I + ch - 1) / ch);
         part[0][p][il] = y;
         part[1][p][il] = ya;
     }
@@ -439,15 +410,8 @@ __global__ __launch_bounds__(256) void k_resid_sym_reduce(const double *__restri
     const int64_t i = (int64_t)I * 64 + il;
     double vr = 0.0, vx = 0.0, vb = 0.0, vd = 0.0, va = 0.0;
     if (i < n) {
-        double y = (part[0][0][il] + part[0][1][il]) + (part[0][2][il] + part[0][3][il]);
-        double ya = (part[1][0][il] + part[1][1][il]) + (part[1][2][il] + part[1][3][il]);
-        for (int q = 0; q < Q; ++q) {
-            if (I + q * RSYM_CH >= nrb)
-                break;
-            y += CP[(((int64_t)I * Q + q) * NC + c) * 64 + il];
-            if (wa)
-                ya += CP[(((int64_t)I * Q + q) * NC + MC) * 64 + il];
-        }
+        const double y = (part[0][0][il] + part[0][1][il]) + (part[0][2][il] + part[0][3][il]);
+        const double ya = (part[1][0][il] + part[1][1][il]) + (part[1][2][il] + part[1][3][il]);
         const double b = B[i + c * ldb];
         const double r = b - y;
         R[i + c * ldr] = r;
@@ -475,26 +439,45 @@ __global__ __launch_bounds__(256) void k_resid_sym_reduce(const double *__restri
 
 namespace spd {
 
+// column slices of the MFMA residual: two workgroups per compute unit (512)
+// in one round, at most 64
 static int resid_splits(int64_t n)
 {
-    const int64_t nrb = (n + 63) / 64;
-    int64_t S = 2048 / (nrb > 0 ? nrb : 1);
-    if (S < 1) S = 1;
-    if (S > nrb) S = nrb;
-    if (S > 64) S = 64;
-    return (int)(S < 1 ? 1 : S);
+    const int64_t nb = (n + 127) / 128, nj = (n + 63) / 64;
+    int64_t S = 512 / (nb > 0 ? nb : 1);
+    S = std::min<int64_t>(std::min<int64_t>(S, nj), 64);
+    return (int)std::max<int64_t>(S, 1);
 }
 
+// Shape of the single pass over the triangle (one or two right-hand sides)
 #define RSYM_MAX_M 2
-static int rsym_mc(int m) { return m <= 1 ? 1 : 2; }
+struct RsymShape {
+    int nrb, ch, Q;
+    int64_t rp, cp;  // doubles of the row and column partials
+};
+static RsymShape rsym_shape(int64_t n, int m)
+{
+    RsymShape h;
+    const int64_t nrb = (n + 63) / 64;
+    h.nrb = (int)nrb;
+    h.ch = (int)std::max<int64_t>(1, std::min<int64_t>(RSYM_CH, nrb * nrb / 2 / 512));
+    h.Q = (int)((nrb + h.ch - 1) / h.ch);
+    h.rp = nrb * nrb * ((m <= 1 ? 1 : 2) + 1) * 64;
+    h.cp = nrb * h.Q * ((m <= 1 ? 1 : 2) + 1) * 64;
+    return h;
+}
 
+// With more than two right-hand sides at least the layout of 64-row blocks
+// times up to 2048 / blocks slices, the size that spd_residual_noalloc's
+// limits are stated for.
 int64_t resid_scratch(int64_t n, int m)
 {
-    const int S = resid_splits(n);
-    int64_t need = (int64_t)S * n * (m + 1);
+    const int64_t nrb = (n + 63) / 64;
+    const int64_t S = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(2048 / std::max<int64_t>(nrb, 1), nrb), 64));
+    int64_t need = std::max<int64_t>(S, resid_splits(n)) * n * (m + 1);
     if (m <= RSYM_MAX_M) {
-        const int64_t nrb = (n + 63) / 64, Q = (nrb + RSYM_CH - 1) / RSYM_CH, nc = rsym_mc(m) + 1;
-        need = std::max<int64_t>(need, (nrb * nrb + nrb * Q) * nc * 64);
+        const RsymShape h = rsym_shape(n, m);
+        need = std::max<int64_t>(need, h.rp + h.cp);
     }
     return need;
 }
@@ -516,13 +499,18 @@ __global__ void k_eta_from_norms(const double *__restrict__ norms, int m, double
     eta[c] = v;
 }
 
-template <int MC, int RB, int CB, int JS>
-static void launch_partial(const double *A, int64_t lda, int64_t n, const double *X, int64_t ldx, int m, int c0,
-                           int S, double *P, double *Pabs, int want_abs, hipStream_t st)
+template <int MC>
+static void launch_sym(const RsymShape &h, const double *A, int64_t lda, int64_t n, const double *X, int64_t ldx,
+                       const double *B, int64_t ldb, int m, double *R, int64_t ldr, const double *d, double *norms,
+                       int want_anorm, double *RP, double *CP, hipStream_t st)
 {
-    const unsigned nrb = (unsigned)((n + 63) / 64);
-    hipLaunchKernelGGL((k_resid_partial<MC, RB, CB, JS>), dim3(nrb, (unsigned)S), dim3(256), 0, st, A, lda, n, X,
-                       ldx, m, c0, S, P, Pabs, want_abs);
+    const dim3 g((unsigned)h.nrb, (unsigned)h.Q), gr((unsigned)h.nrb, (unsigned)m);
+    if (want_anorm)
+        hipLaunchKernelGGL((k_resid_sym<MC, true>), g, dim3(256), 0, st, A, lda, n, X, ldx, m, h.ch, h.Q, RP, CP);
+    else
+        hipLaunchKernelGGL((k_resid_sym<MC, false>), g, dim3(256), 0, st, A, lda, n, X, ldx, m, h.ch, h.Q, RP, CP);
+    hipLaunchKernelGGL((k_resid_sym_reduce<MC>), gr, dim3(256), 0, st, B, ldb, X, ldx, n, m, h.ch, h.Q, RP, CP,
+                       want_anorm, d, R, ldr, norms);
 }
 
 void launch_eta_from_norms(const double *norms, int m, double *eta, hipStream_t st)
@@ -537,48 +525,23 @@ void launch_residual(const double *A, int64_t lda, int64_t n, const double *X, i
 {
     if (n <= 0 || m <= 0) return;
     if (m <= RSYM_MAX_M) {
-        const int nrb = (int)((n + 63) / 64), Q = (nrb + RSYM_CH - 1) / RSYM_CH, mc = rsym_mc(m);
-        double *RP = P, *CP = P + (int64_t)nrb * nrb * (mc + 1) * 64;
-        const dim3 g((unsigned)nrb, (unsigned)Q), gr((unsigned)nrb, (unsigned)m);
-        if (mc == 1) {
-            if (want_anorm)
-                hipLaunchKernelGGL((k_resid_sym<1, true>), g, dim3(256), 0, st, A, lda, n, X, ldx, m, Q, RP, CP);
-            else
-                hipLaunchKernelGGL((k_resid_sym<1, false>), g, dim3(256), 0, st, A, lda, n, X, ldx, m, Q, RP, CP);
-            hipLaunchKernelGGL(k_resid_sym_reduce<1>, gr, dim3(256), 0, st, B, ldb, X, ldx, n, m, Q, RP, CP,
-                               want_anorm, d, R, ldr, norms);
-        } else {
-            if (want_anorm)
-                hipLaunchKernelGGL((k_resid_sym<2, true>), g, dim3(256), 0, st, A, lda, n, X, ldx, m, Q, RP, CP);
-            else
-                hipLaunchKernelGGL((k_resid_sym<2, false>), g, dim3(256), 0, st, A, lda, n, X, ldx, m, Q, RP, CP);
-            hipLaunchKernelGGL(k_resid_sym_reduce<2>, gr, dim3(256), 0, st, B, ldb, X, ldx, n, m, Q, RP, CP,
-                               want_anorm, d, R, ldr, norms);
-        }
+        const RsymShape h = rsym_shape(n, m);
+        auto go = [&](auto f) { f(h, A, lda, n, X, ldx, B, ldb, m, R, ldr, d, norms, want_anorm, P, P + h.rp, st); };
+        if (m <= 1)
+            go(launch_sym<1>);
+        else
+            go(launch_sym<2>);
         return;
     }
     const int S = resid_splits(n);
     double *Pabs = P + (int64_t)S * n * m;
-    const unsigned nrb = (unsigned)((n + 63) / 64);
-    const int step = (m > 8) ? 32 : 64;  // MFMA chunks of up to 32 columns
-    for (int c0 = 0; c0 < m; c0 += step) {
-        const int mc = (m - c0 < step) ? (m - c0) : step;
+    const dim3 g((unsigned)((n + 127) / 128), (unsigned)S);
+    for (int c0 = 0; c0 < m; c0 += 32) {
         const int wa = (want_anorm && c0 == 0) ? 1 : 0;
-        if (mc > 8) {
-            if (mc <= 16)
-                hipLaunchKernelGGL(k_resid_mfma<1>, dim3(nrb, (unsigned)S), dim3(256), 0, st, A, lda, n, X, ldx, m, c0,
-                                   S, P, Pabs, wa);
-            else
-                hipLaunchKernelGGL(k_resid_mfma<2>, dim3(nrb, (unsigned)S), dim3(256), 0, st, A, lda, n, X, ldx, m, c0,
-                                   S, P, Pabs, wa);
-        } else if (mc <= 1)
-            launch_partial<1, 1, 1, 4>(A, lda, n, X, ldx, m, c0, S, P, Pabs, wa, st);
-        else if (mc <= 2)
-            launch_partial<2, 1, 1, 2>(A, lda, n, X, ldx, m, c0, S, P, Pabs, wa, st);
-        else if (mc <= 4)
-            launch_partial<4, 1, 1, 1>(A, lda, n, X, ldx, m, c0, S, P, Pabs, wa, st);
+        if (m - c0 <= 16)
+            hipLaunchKernelGGL(k_resid_mfma<1>, g, dim3(256), 0, st, A, lda, n, X, ldx, m, c0, S, P, Pabs, wa);
         else
-            launch_partial<8, 1, 2, 1>(A, lda, n, X, ldx, m, c0, S, P, Pabs, wa, st);
+            hipLaunchKernelGGL(k_resid_mfma<2>, g, dim3(256), 0, st, A, lda, n, X, ldx, m, c0, S, P, Pabs, wa);
     }
     hipLaunchKernelGGL(k_resid_reduce, dim3((unsigned)((n + 255) / 256), (unsigned)m), dim3(256), 0, st, B, ldb, X,
                        ldx, n, m, S, P, Pabs, want_anorm, d, R, ldr, norms);
