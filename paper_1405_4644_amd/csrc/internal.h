@@ -83,12 +83,12 @@ int64_t solve_winv_elems(int64_t npad);
 int64_t solve_tmp_elems(int64_t npad);
 template <typename T>
 void launch_build_winv(const T *L, int64_t ld, int64_t npad, const T *Winv, T *WB, T *Tb, hipStream_t st);
-// Forward Y -> Z then backward Z -> Y for m right-hand sides (TRSV_MC per
-// launch).  P: trsv_scratch_elems(npad) elements; ctl: 2 trsv_ctl_ints(npad)
+// Forward Y -> Z then backward Z -> Y for m right-hand sides (up to TRSV_MC on
+// the VALU, more on MFMA).  P: trsv_scratch_elems(npad) elements; ctl: 2 trsv_ctl_ints(npad)
 // ints (the first half for the forward direction, the second for the
 // backward), zeroed by the launches themselves unless ctl_zeroed says the
 // caller cleared both halves; err: sticky int raised on a timed-out wait.
-#define TRSV_MC 8
+#define TRSV_MC 2
 int64_t trsv_scratch_elems(int64_t npad);
 int trsv_ctl_ints(int64_t npad);
 template <typename T>

@@ -662,6 +662,271 @@ __global__ __launch_bounds__(256) void k_trsv_blk(const T *__restrict__ L, int64
     }
 }
 
+// ---------------------------------------------------------------------------
+// Three or more right-hand sides: the same block recurrence on MFMA, 16 NT of
+// them per launch.  Tasks of R rows (32 binary32 / 16 binary64) of a big block
+// in processing order p, handed out by a counter in the order U(p, 0..), Z(p,
+// 0..), p = 0, 1, ... (no U at p = 0):
+//   U(p, c): v_p[c] = y_p[c] - sum_{q < p} L_pq[rows c] z_q    (q in order)
+//   Z(p, c): z_p[c] = W_p[rows c] v_p                          (v_0 = y_0)
+// (transposed blocks for the backward solve).  A task waits only for tasks
+// handed out before it.  The sum over q stays in the MFMA accumulators of one
+// workgroup, so there are no partial products in memory: with 32 columns
+// they would be as large as the blocks themselves.
+//
+// Eight waves split a block's columns (the k of the product) evenly; the
+// k-slots of an MFMA are a free summation order, so lane (r = lane % 16,
+// u = lane / 16) takes k = 16 g + 4 u + i at step i of group g: its vector
+// values are 16 consecutive bytes, and so are its matrix values in the
+// backward solve.  Each vector value is needed by one wave only, so neither
+// operand goes through shared memory.  The matrix block is loaded before the
+// wait, the next one before the product.  The waves' sums are added in order
+// through shared memory.
+//
+// Bound by the chain of 2 K tasks, each a poll, the loads of the vector and a
+// 1024-deep product.  In passes of 8 columns on the VALU (BlockVec) a solve
+// with 32 right-hand sides took 4 x (305 + 236) us at n = 10000, one with 5
+// 163 + 123 us at n = 6000; here 192 + 231 and 71 + 73 us.  One right-hand
+// side stays on BlockVec, whose 256 workgroups stream more (n = 16384: 231 +
+// 192 us against 268 + 279 here; n = 3000: 27 + 27 against 30 + 34).
+#define TRSM_WAVES 8
+// raw buffer loads coherent at agent scope (the SC1 cache policy bit)
+#define SPD_BUFFER_AGENT 16
+typedef double double2v __attribute__((ext_vector_type(2)));
+// buffer resource over memory from a workgroup-uniform address on
+template <typename T>
+SPD_DEV __amdgpu_buffer_rsrc_t uniform_rsrc(const T *p)
+{
+    const unsigned long long b = (unsigned long long)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffull));
+    const unsigned hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(((unsigned long long)hi << 32) | lo), (short)0, 0x7fffffff,
+                                             SPD_BUFFER_RSRC_WORD3);
+}
+template <typename T, int NT, bool FWD>
+__global__ __launch_bounds__(64 * TRSM_WAVES) void k_trsv_mfma(const T *__restrict__ L, int64_t ld,
+                                                               const T *__restrict__ WB, int64_t npad, int nbs, int K,
+                                                               const T *__restrict__ Yin, T *__restrict__ Zout,
+                                                               int64_t ldy, int c0, int m, T *__restrict__ V,
+                                                               int *ctl, int *err, unsigned long long tmo)
+{
+    constexpr bool F32 = sizeof(T) == 4;
+    constexpr int MT = F32 ? 2 : 1, R = 16 * MT, MC = 16 * NT, NW = TRSM_WAVES, NBS = TRSV_NBS,
+                  GM = NBS / (16 * NW);
+    using acc_t = typename std::conditional<F32, floatx4, doublex4>::type;
+    __shared__ T red[NW][MC][R + 1];
+    __shared__ int s_task, s_ok[2];
+    // the wave's number as a scalar: addresses are then a scalar base plus one
+    // 32-bit lane offset per operand
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, u = lane >> 4;
+    int *ticket = ctl, *cntV = ctl + 3, *cntZ = ctl + 3 + K;
+    const int mc = min(MC, m - c0);
+    const int slast = (int)(npad - (int64_t)(K - 1) * nbs);
+    auto proc_size = [&](int p) -> int { return (FWD ? p == K - 1 : p == 0) ? slast : nbs; };
+
+    // All loads are buffer loads: a scalar base and offset plus one 32-bit
+    // lane offset per operand (flat addresses would not fit the registers
+    // beside the blocks).  Wave w takes k in [128 w, 128 w + 128); past a short
+    // block's end (len) it takes k = 0 again with a zero vector, so that every
+    // block runs the same straight-line code.  a[g][i][t]: row tile t.
+    constexpr int EB = sizeof(T);
+    auto group = [&](int g, int len) -> int {
+        const int k = 16 * GM * w + 16 * g;
+        return k < len ? k : 0;
+    };
+    auto load_block = [&](T (&a)[GM][4][MT], const T *base, int mld, int len) {
+        // FWD, base the strip's first row: rows MT r + t of column k + i;
+        // BWD, base its first column: rows k .. k + 3 of column 16 t + r
+        const __amdgpu_buffer_rsrc_t rc = uniform_rsrc(base);
+        const int o0 = (FWD ? MT * r + 4 * u * mld : r * mld + 4 * u) * EB, o1 = o0 + 16 * mld * EB;
+#pragma unroll
+        for (int g = 0; g < GM; ++g) {
+            const int k = group(g, len);
+            if constexpr (FWD) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b64(rc, o0, (k + i) * mld * EB, 0);
+                    if constexpr (F32) {
+                        a[g][i][0] = __builtin_bit_cast(float, (unsigned)v[0]);
+                        a[g][i][MT - 1] = __builtin_bit_cast(float, (unsigned)v[1]);
+                    } else {
+                        a[g][i][0] = __builtin_bit_cast(double, v);
+                    }
+                }
+            } else if constexpr (F32) {
+#pragma unroll
+                for (int t = 0; t < MT; ++t) {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rc, t ? o1 : o0, k * EB, 0);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) a[g][i][t] = __builtin_bit_cast(float, (unsigned)v[i]);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; i += 2) {
+                    const auto v =
+                        __builtin_bit_cast(double2v, __builtin_amdgcn_raw_buffer_load_b128(rc, o0, (k + i) * EB, 0));
+                    a[g][i][0] = v[0];
+                    a[g][i + 1][0] = v[1];
+                }
+            }
+        }
+    };
+    // acc += block times the vector (columns past the last right-hand side
+    // repeat column c0: their products are dropped).  The vector is read with
+    // agent-scope loads (SPD_BUFFER_AGENT), like load_shared.
+    acc_t acc[MT][NT];
+    int oz[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) oz[t] = (4 * u + (16 * t + r < mc ? 16 * t + r : 0) * (int)ldy) * EB;
+    auto multiply = [&](const T (&a)[GM][4][MT], const T *vec, int len) {
+        const __amdgpu_buffer_rsrc_t rc = uniform_rsrc(vec);
+        T z[GM][NT][4];
+#pragma unroll
+        for (int g = 0; g < GM; ++g) {
+            const int k = group(g, len);
+            const bool in = 16 * GM * w + 16 * g < len;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                if constexpr (F32) {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rc, oz[t], k * EB, SPD_BUFFER_AGENT);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) z[g][t][i] = in ? __builtin_bit_cast(float, (unsigned)v[i]) : 0.0f;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; i += 2) {
+                        const auto v = __builtin_bit_cast(
+                            double2v, __builtin_amdgcn_raw_buffer_load_b128(rc, oz[t], (k + i) * EB, SPD_BUFFER_AGENT));
+                        z[g][t][i] = in ? v[0] : 0.0;
+                        z[g][t][i + 1] = in ? v[1] : 0.0;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < GM; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int h = 0; h < MT; ++h) {
+                        if constexpr (F32)
+                            acc[h][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(z[g][t][i], a[g][i][h], acc[h][t], 0, 0, 0);
+                        else
+                            acc[h][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(z[g][t][i], a[g][i][h], acc[h][t], 0, 0, 0);
+                    }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int slot = 0;  // s_ok alternates: a slot is rewritten only after the barrier that follows its reading
+    auto wait = [&](int *ctr, int want) -> bool {
+        slot ^= 1;
+        if (tid == 0)
+            s_ok[slot] = wait_ge(ctr, want, err, tmo) ? 1 : 0;
+        __syncthreads();
+        return s_ok[slot] != 0;
+    };
+
+    for (;;) {
+        if (tid == 0)
+            s_task = atomicAdd(ticket, 1);
+        __syncthreads();
+        int rem = __builtin_amdgcn_readfirstlane(s_task), p = -1, c = 0;
+        bool ztask = false;
+        for (int q = 0; q < K; ++q) {
+            const int nt = proc_size(q) / R;
+            if (q > 0) {
+                if (rem < nt) {
+                    p = q;
+                    c = rem;
+                    break;
+                }
+                rem -= nt;
+            }
+            if (rem < nt) {
+                p = q;
+                c = rem;
+                ztask = true;
+                break;
+            }
+            rem -= nt;
+        }
+        if (p < 0)
+            return;
+        const int ki = FWD ? p : K - 1 - p;
+        int64_t oi;
+        int si;
+        big_block(npad, nbs, ki, oi, si);
+        const int nc = si / R;
+#pragma unroll
+        for (int h = 0; h < MT; ++h)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[h][t] = acc_t{0, 0, 0, 0};
+        if (ztask) {
+            // the strip's rows (FWD) or columns (BWD) of W_ki, with its zeros
+            const T *Wk = WB + (int64_t)ki * nbs * nbs;
+            T a0[GM][4][MT];
+            load_block(a0, FWD ? Wk + c * R : Wk + (int64_t)(c * R) * nbs, nbs, si);
+            if (p > 0 && !wait(&cntV[p], nc))
+                return;
+            multiply(a0, p > 0 ? V + oi : Yin + oi + (int64_t)c0 * ldy, si);
+        } else {
+            T a0[GM][4][MT], a1[GM][4][MT];
+            auto fetch = [&](T (&a)[GM][4][MT], int q) {  // past the last block: that one again, unused
+                q = q < p ? q : p - 1;
+                const int64_t oj = (int64_t)(FWD ? q : K - 1 - q) * nbs;
+                load_block(a, FWD ? L + oi + c * R + oj * ld : L + oj + (oi + c * R) * ld, (int)ld, proc_size(q));
+            };
+            auto step = [&](const T (&a)[GM][4][MT], int q) -> bool {
+                if (!wait(&cntZ[q], proc_size(q) / R))
+                    return false;
+                multiply(a, Zout + (int64_t)(FWD ? q : K - 1 - q) * nbs + (int64_t)c0 * ldy, proc_size(q));
+                return true;
+            };
+            fetch(a0, 0);
+            for (int q = 0;;) {
+                fetch(a1, q + 1);
+                if (!step(a0, q))
+                    return;
+                if (++q >= p)
+                    break;
+                fetch(a0, q + 1);
+                if (!step(a1, q))
+                    return;
+                if (++q >= p)
+                    break;
+            }
+        }
+        // accumulator register v: right-hand side 4 u + v (binary32) or
+        // 4 v + u (binary64) of its tile, strip row MT r + h (FWD) or 16 h + r
+#pragma unroll
+        for (int h = 0; h < MT; ++h)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    red[w][16 * t + (F32 ? 4 * u + v : 4 * v + u)][FWD ? MT * r + h : 16 * h + r] = acc[h][t][v];
+        __syncthreads();
+        for (int e = tid; e < R * mc; e += 64 * NW) {
+            const int row = e % R, cc = e / R;
+            T s = red[0][cc][row];
+#pragma unroll
+            for (int q = 1; q < NW; ++q) s += red[q][cc][row];
+            const int64_t i = oi + c * R + row;
+            if (ztask)
+                store_shared(&Zout[i + (int64_t)(c0 + cc) * ldy], s);
+            else
+                store_shared(&V[i + (int64_t)cc * ldy], Yin[i + (int64_t)(c0 + cc) * ldy] - s);
+        }
+        // every thread's result stores complete, then one relaxed increment
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (tid == 0)
+            __hip_atomic_fetch_add(ztask ? &cntZ[p] : &cntV[p], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 __global__ void k_zero_int(int *p, int count)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
@@ -694,7 +959,9 @@ int64_t solve_tmp_elems(int64_t npad)
 int64_t trsv_scratch_elems(int64_t npad)
 {
     const int64_t K = solve_nblocks(npad);
-    return std::max<int64_t>(K * (K - 1) / 2, 1) * TRSV_NBS * TRSV_MC;
+    // the partial products of up to TRSV_MC columns, or the updated right-hand
+    // sides v of up to 32
+    return std::max<int64_t>(std::max<int64_t>(K * (K - 1) / 2, 1) * TRSV_NBS * TRSV_MC, npad * 32);
 }
 
 // counters of one direction, padded to 256 bytes (a caller keeping one set
@@ -737,23 +1004,38 @@ static void launch_dir(const T *L, int64_t ld, const T *WB, int64_t npad, int m,
     const int ncrit = (int)std::min<int64_t>(ncrit_tasks, TRSV_NCRIT);
     const int grid = ncrit + (int)std::min<int64_t>(nbulk_tasks, TRSV_NBULK);
     const int nctl = trsv_ctl_ints(npad);
-    for (int c0 = 0; c0 < m; c0 += TRSV_MC) {
-        if (c0 > 0 || !ctl_zeroed)
-            hipLaunchKernelGGL(k_zero_int, dim3((nctl + 255) / 256), dim3(256), 0, st, ctl, nctl);
-        const int mc = m - c0;
-        if (mc == 1)
-            hipLaunchKernelGGL((k_trsv_blk<T, 1, FWD>), dim3(grid), dim3(256), 0, st, L, ld, WB, npad, nbs, K, Yin,
-                               Zout, ldy, c0, m, P, ctl, err, ncrit, cdepth, tmo);
-        else if (mc == 2)
-            hipLaunchKernelGGL((k_trsv_blk<T, 2, FWD>), dim3(grid), dim3(256), 0, st, L, ld, WB, npad, nbs, K, Yin,
-                               Zout, ldy, c0, m, P, ctl, err, ncrit, cdepth, tmo);
-        else if (mc <= 4)
-            hipLaunchKernelGGL((k_trsv_blk<T, 4, FWD>), dim3(grid), dim3(256), 0, st, L, ld, WB, npad, nbs, K, Yin,
-                               Zout, ldy, c0, m, P, ctl, err, ncrit, cdepth, tmo);
-        else
-            hipLaunchKernelGGL((k_trsv_blk<T, TRSV_MC, FWD>), dim3(grid), dim3(256), 0, st, L, ld, WB, npad, nbs, K,
-                               Yin, Zout, ldy, c0, m, P, ctl, err, ncrit, cdepth, tmo);
+    if (m > TRSV_MC) {
+        // MFMA: 32 columns per launch (16 in binary64, whose registers hold half as many)
+        constexpr int RM = sizeof(T) == 4 ? 32 : 16, STEP = sizeof(T) == 4 ? 32 : 16;
+        const int64_t ntask = 2 * (npad / RM) - (FWD ? std::min<int64_t>(nbs, npad) : npad - (int64_t)(K - 1) * nbs) / RM;
+        const dim3 grid_m((unsigned)std::min<int64_t>(ntask, TRSV_NCRIT + TRSV_NBULK));
+        for (int c0 = 0; c0 < m; c0 += STEP) {
+            if (c0 > 0 || !ctl_zeroed)
+                hipLaunchKernelGGL(k_zero_int, dim3((nctl + 255) / 256), dim3(256), 0, st, ctl, nctl);
+            auto go = [&](auto kern) {
+                hipLaunchKernelGGL(kern, grid_m, dim3(64 * TRSM_WAVES), 0, st, L, ld, WB, npad, nbs, K, Yin, Zout, ldy,
+                                   c0, m, P, ctl, err, tmo);
+            };
+            if constexpr (sizeof(T) == 4) {
+                if (m - c0 > 16) {
+                    go(k_trsv_mfma<T, 2, FWD>);
+                    continue;
+                }
+            }
+            go(k_trsv_mfma<T, 1, FWD>);
+        }
+        return;
     }
+    if (!ctl_zeroed)
+        hipLaunchKernelGGL(k_zero_int, dim3((nctl + 255) / 256), dim3(256), 0, st, ctl, nctl);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, L, ld, WB, npad, nbs, K, Yin, Zout, ldy, 0, m, P, ctl,
+                           err, ncrit, cdepth, tmo);
+    };
+    if (m == 1)
+        go(k_trsv_blk<T, 1, FWD>);
+    else
+        go(k_trsv_blk<T, 2, FWD>);
 }
 
 template <typename T>

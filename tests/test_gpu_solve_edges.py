@@ -42,3 +42,12 @@ def test_block_inverses(spd, n, prec):
     """Orders around the doubling levels of the block inverses (128, 256, 512,
     1024), with whole, ragged and single-block pairs at each level."""
     check(spd, n, 1, prec)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", [1, 128, 129, 1024, 1025, 2048, 2200, 3300])
+@pytest.mark.parametrize("m", [2, 3, 16, 17, 32, 35])
+def test_many_right_hand_sides(spd, n, m, prec):
+    """The VALU (up to 2) and MFMA solves: column tiles and launches (16, 32)
+    with ragged ends, one to four big blocks with a whole or short last one."""
+    check(spd, n, m, prec)
