@@ -591,7 +591,7 @@ def main():
                                 if args.prec == "fp32" else (
                                     "k_syrk_update_h256 / k_syrk_update_h (a group's trailing update, "
                                     "binary16/bfloat16 operands)" if args.prec in ("fp16", "bf16")
-                                    else "k_syrk_update<double>")),
+                                    else "k_syrk_update_f64")),
                      "launches": launches, "avg_launch_ms": ms / max(launches, 1),
                      "timed_with_events_ms_per_step": dt_prof * 1e3,
                      "flops_per_launch": fl / max(launches, 1),

@@ -1,7 +1,7 @@
 // Trailing update of the blocked factorisation in Algorithm 1's low-precision
 // Cholesky (the Schur complement update of the low-precision factor),
 //   H_ij -= L_ik L_jk^T   for the lower tiles of the trailing region,
-// on MFMA: binary32 (k_syrk_update_f32), binary64 (k_syrk_update<double>),
+// on MFMA: binary32 (k_syrk_update_f32), binary64 (k_syrk_update_f64),
 // and binary16 / bfloat16 operands with binary32 accumulation
 // (k_syrk_update_h).  Launched by the factorisation driver per group of
 // panels (K = G NB) and within a group for its remaining panels.
@@ -44,216 +44,89 @@ SPD_DEV void decode_tile(int b, int t, int tj_lo, int tj_hi, int &ti, int &tj)
     tj = tj_lo + (b - r * (r + 1) / 2);
 }
 
-// binary64 (binary32 has its own kernel below)
-template <typename T> struct SyrkCfg;
-template <> struct SyrkCfg<double> {
-    static constexpr int KC = 16;
-    using Acc = Acc32<double>;
-    using Fr = Frag<double>;
-};
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_syrk_update(T *__restrict__ H, int64_t ld, int64_t k0, int nbk, int64_t r0,
-                                                     int t, int tj_lo, int tj_hi, int ntiles,
-                                                     const unsigned long long *info, int prio)
-{
-    constexpr int KC = SyrkCfg<T>::KC;
-    using AccT = typename SyrkCfg<T>::Acc;
-    using FragT = typename SyrkCfg<T>::Fr;
-    constexpr int LDT = SPD_TILE + 4;  // LDS column stride
-    __shared__ T As[2][KC * LDT];
-    __shared__ T Bs[2][KC * LDT];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (*(volatile const unsigned long long *)info != (unsigned long long)SPD_INFO_NONE)
-        return;
-    if (prio)
-        __builtin_amdgcn_s_setprio(2);  // the lookahead part of the update
-    // tiles of XCD x (blocks are dispatched round-robin over the 8 XCDs) are
-    // the contiguous range [x chunk, (x + 1) chunk); a grid smaller than the
-    // tile count loops (persistent), leaving compute-unit slots free
-    const int per = gridDim.x / 8, chunk = (ntiles + 7) / 8;
-    for (int it = blockIdx.x / 8; it < chunk; it += per) {
-    const int logical = (blockIdx.x % 8) * chunk + it;
-    if (logical >= ntiles)
-        break;
-    int ti, tj;
-    decode_tile(logical, t, tj_lo, tj_hi, ti, tj);
-    if (ti < 0)
-        break;
-    const int64_t crow = r0 + (int64_t)ti * SPD_TILE, ccol = r0 + (int64_t)tj * SPD_TILE;
-    const T *pa = H + ccol + k0 * ld;  // rows of tile tj (D rows = C columns)
-    const T *pb = H + crow + k0 * ld;  // rows of tile ti (D columns = C rows)
-    const int wm = wave >> 1, wn = wave & 1;
-
-    // The C tile is read once, up front, straight into the accumulators (so
-    // its latency overlaps the K loop); the MFMA operands are negated.
-    // Register j of tile (mi, ni) holds C[crow + 64 wn + 32 ni + col(j)][ccol + 64 wm + 32 mi + row(j)].
-    AccT acc[2][2];
-#pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int m = AccT::row(j, lane), nn = AccT::col(j, lane);
-                acc[mi][ni].set(j, H[(crow + 64 * wn + 32 * ni + nn) + (ccol + 64 * wm + 32 * mi + m) * ld]);
-            }
-
-    // 128 rows x KC columns of each operand per chunk, 16-byte vector loads,
-    // staged through registers so the next chunk's loads overlap the MFMAs.
-    using V = typename std::conditional<sizeof(T) == 4, float4, double2>::type;
-    constexpr int VEC = 16 / sizeof(T);
-    constexpr int PER_COL = SPD_TILE / VEC;
-    constexpr int NV = PER_COL * KC / 256;  // vectors per thread per operand
-    static_assert(NV == 4, "staging layout");
-    // per-thread staging slots: vector v covers column col_v, rows r_v..r_v+VEC-1
-    int soff[NV];
-    size_t goff[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const int idx = tid + 256 * v;
-        const int col = idx / PER_COL, r = (idx % PER_COL) * VEC;
-        soff[v] = col * LDT + r;
-        goff[v] = (size_t)col * ld + r;
-    }
-    V ra0, ra1, ra2, ra3, rb0, rb1, rb2, rb3;
-#define SPD_GLOAD(kb)                                                       \
-    do {                                                                    \
-        const size_t o_ = (size_t)(kb) * ld;                                \
-        ra0 = *(const V *)&pa[o_ + goff[0]]; rb0 = *(const V *)&pb[o_ + goff[0]]; \
-        ra1 = *(const V *)&pa[o_ + goff[1]]; rb1 = *(const V *)&pb[o_ + goff[1]]; \
-        ra2 = *(const V *)&pa[o_ + goff[2]]; rb2 = *(const V *)&pb[o_ + goff[2]]; \
-        ra3 = *(const V *)&pa[o_ + goff[3]]; rb3 = *(const V *)&pb[o_ + goff[3]]; \
-    } while (0)
-#define SPD_SSTORE(buf)                                                     \
-    do {                                                                    \
-        *(V *)&As[buf][soff[0]] = ra0; *(V *)&Bs[buf][soff[0]] = rb0;       \
-        *(V *)&As[buf][soff[1]] = ra1; *(V *)&Bs[buf][soff[1]] = rb1;       \
-        *(V *)&As[buf][soff[2]] = ra2; *(V *)&Bs[buf][soff[2]] = rb2;       \
-        *(V *)&As[buf][soff[3]] = ra3; *(V *)&Bs[buf][soff[3]] = rb3;       \
-    } while (0)
-
-    SPD_GLOAD(0);
-    SPD_SSTORE(0);
-    __syncthreads();
-    int buf = 0;
-    for (int kb = 0; kb < nbk; kb += KC) {
-        // prefetch the next chunk (the last iteration re-reads its own chunk)
-        const int kn = (kb + KC < nbk) ? kb + KC : kb;
-        SPD_GLOAD(kn);
-        // keep the next chunk's loads here, ahead of the MFMAs (the scheduler
-        // would otherwise sink them to their LDS stores and expose their latency)
-        __builtin_amdgcn_sched_barrier(0);
-        const T *a0 = &As[buf][64 * wm];
-        const T *b0 = &Bs[buf][64 * wn];
-#pragma unroll
-        for (int k = 0; k < KC; k += FragT::K) {
-            FragT fa[2], fb[2];
-            fa[0].load(a0 + k * LDT, LDT, lane);
-            fa[1].load(a0 + 32 + k * LDT, LDT, lane);
-            fb[0].load(b0 + k * LDT, LDT, lane);
-            fb[1].load(b0 + 32 + k * LDT, LDT, lane);
-            fa[0].negate();
-            fa[1].negate();
-#pragma unroll
-            for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < 2; ++ni)
-                    mma(acc[mi][ni], fa[mi], fb[ni]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        SPD_SSTORE(buf ^ 1);
-        __syncthreads();
-        buf ^= 1;
-    }
-#undef SPD_GLOAD
-#undef SPD_SSTORE
-#pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int m = AccT::row(j, lane), nn = AccT::col(j, lane);
-                H[(crow + 64 * wn + 32 * ni + nn) + (ccol + 64 * wm + 32 * mi + m) * ld] = acc[mi][ni].get(j);
-            }
-    __syncthreads();  // shared memory is reused by the next tile
-    }
-}
-
 // ---------------------------------------------------------------------------
-// K4, binary32: the same update written for v_mfma_f32_16x16x4f32.  One
-// TS x TS tile (TS = 128 or 64): each wave owns a TS/2 x TS/2 block of
+// K4, binary32 and binary64: on v_mfma_f32_16x16x4f32 / v_mfma_f64_16x16x4f64.
+// One TS x TS tile (TS = 128 or 64): each wave owns a TS/2 x TS/2 block of
 // D = C^T as NB x NB 16 x 16 accumulators holding -C (the sign is applied
 // once on load and once on store, so the K loop only multiplies and adds).
-// Shared memory holds KC columns of each operand as [k][row] with TS floats
-// per k and the row index XOR-ed with 16 (k % 4): a fragment read (lane l:
-// row 16 b + l%16, k = 4 s + l/16) then touches 64 distinct banks, and the
-// 16-byte staging stores stay contiguous.  As and Bs are two staging
-// buffers of KC x TS floats each; every wave has passed the final barrier
-// when the function returns, so the next tile may restage at once.
-template <int TS, int KC>
-SPD_DEV void f32_update_tile(float *__restrict__ H, int64_t ld, int64_t k0, int nbk, int64_t crow, int64_t ccol,
-                             float *__restrict__ As, float *__restrict__ Bs, int tid)
+// Shared memory holds KC columns of each operand as [k][row] with TS values
+// per k and the row index XOR-ed with 16 (k % 4) (binary64: 16 (k % 2)): a
+// fragment read (lane l: row 16 b + l%16, k = 4 s + l/16) then touches all
+// 64 banks evenly, and the 16-byte staging stores stay contiguous.  As and Bs
+// are two staging buffers of KC x TS values each; every wave has passed the
+// final barrier when the function returns, so the next tile may restage at
+// once.
+// Bound by the MFMA rate.  Binary64 used to run a kernel of its own whose
+// accumulators and staging took 277 registers, one workgroup per compute
+// unit, with every chunk's barrier exposed: TIMES_F64.
+template <typename T, int TS, int KC>
+SPD_DEV void update_tile(T *__restrict__ H, int64_t ld, int64_t k0, int nbk, int64_t crow, int64_t ccol,
+                         T *__restrict__ As, T *__restrict__ Bs, int tid)
 {
-    constexpr int NB = TS / 32, NV = KC * TS / 1024;  // 16-blocks per wave side; staged float4 per thread
+    constexpr bool F32 = sizeof(T) == 4;
+    using V = typename std::conditional<F32, float4, double2>::type;
+    using acc_t = typename std::conditional<F32, floatx4, doublex4>::type;
+    constexpr int VEC = 16 / sizeof(T), SWZ = F32 ? 3 : 1;
+    constexpr int NB = TS / 32, NV = KC * TS / (256 * VEC);  // 16-blocks per wave side; staged vectors per thread
     constexpr int BUF = KC * TS;
     static_assert(NV == 2 || NV == 4, "staging layout");
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, r = lane & 15, u = lane >> 4;
     const int ldi = (int)ld;  // offsets within a tile row block of <= 1024 columns fit in 32 bits
-    // staging: thread covers rows 4 (tid % (TS/4)) .. +3 of columns tid / (TS/4) + (1024/TS) v
-    constexpr int TPC = TS / 4, CSTEP = 256 / TPC;
-    const int scol = tid / TPC, srow = (tid % TPC) * 4;
+    // staging: thread covers rows VEC (tid % TPC) .. of columns tid / TPC + CSTEP v
+    constexpr int TPC = TS / VEC, CSTEP = 256 / TPC;
+    const int scol = tid / TPC, srow = (tid % TPC) * VEC;
     const int goff = scol * ldi + srow;
-    const int soff = scol * TS + (srow ^ (16 * (scol & 3)));  // CSTEP is a multiple of 4: col % 4 fixed
+    const int soff = scol * TS + (srow ^ (16 * (scol & SWZ)));  // CSTEP is a multiple of 4: col % 4 fixed
     // fragment offsets: row 16 b + r of the wave's TS/2 rows, k-slot u (+ 4 s TS for k-step s)
     int fa[NB], fb[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-        fa[b] = u * TS + (((TS / 2) * wm + 16 * b) ^ (16 * u)) + r;
-        fb[b] = u * TS + (((TS / 2) * wn + 16 * b) ^ (16 * u)) + r;
+        fa[b] = u * TS + (((TS / 2) * wm + 16 * b) ^ (16 * (u & SWZ))) + r;
+        fb[b] = u * TS + (((TS / 2) * wn + 16 * b) ^ (16 * (u & SWZ))) + r;
     }
-    const int coff = r + 4 * u * ldi;
-    const float *pa = H + ccol + k0 * ld;  // rows of tile tj (D rows = C columns)
-    const float *pb = H + crow + k0 * ld;  // rows of tile ti (D columns = C rows)
-    // register q of block (mi, ni): -C[crow + TS/2 wn + 16 ni + r][ccol + TS/2 wm + 16 mi + 4 u + q]
-    float *cu = H + (crow + (TS / 2) * wn) + (ccol + (TS / 2) * wm) * ld;
-    floatx4 c[NB][NB];
+    // register q of an accumulator: D row 4 u + q (binary32) or 4 q + u (binary64)
+    constexpr int UR = F32 ? 4 : 1, QR = F32 ? 1 : 4;
+    const int coff = r + UR * u * ldi;
+    const T *pa = H + ccol + k0 * ld;  // rows of tile tj (D rows = C columns)
+    const T *pb = H + crow + k0 * ld;  // rows of tile ti (D columns = C rows)
+    // register q of block (mi, ni): -C[crow + TS/2 wn + 16 ni + r][ccol + TS/2 wm + 16 mi + D row]
+    T *cu = H + (crow + (TS / 2) * wn) + (ccol + (TS / 2) * wm) * ld;
+    acc_t c[NB][NB];
 #pragma unroll
     for (int mi = 0; mi < NB; ++mi)
 #pragma unroll
         for (int ni = 0; ni < NB; ++ni)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                c[mi][ni][q] = -cu[coff + 16 * ni + (16 * mi + q) * ldi];
+                c[mi][ni][q] = -cu[coff + 16 * ni + (16 * mi + QR * q) * ldi];
     // staging registers (named, not an array, so that they stay registers)
-    float4 ra0, ra1, ra2, ra3, rb0, rb1, rb2, rb3;
+    V ra0, ra1, ra2, ra3, rb0, rb1, rb2, rb3;
 #define SPD_GL(o)                                                                         \
     do {                                                                                  \
-        ra0 = *(const float4 *)&pa[(o) + goff];                                           \
-        rb0 = *(const float4 *)&pb[(o) + goff];                                           \
-        ra1 = *(const float4 *)&pa[(o) + goff + CSTEP * ldi];                             \
-        rb1 = *(const float4 *)&pb[(o) + goff + CSTEP * ldi];                             \
+        ra0 = *(const V *)&pa[(o) + goff];                                                \
+        rb0 = *(const V *)&pb[(o) + goff];                                                \
+        ra1 = *(const V *)&pa[(o) + goff + CSTEP * ldi];                                  \
+        rb1 = *(const V *)&pb[(o) + goff + CSTEP * ldi];                                  \
         if constexpr (NV > 2) {                                                           \
-            ra2 = *(const float4 *)&pa[(o) + goff + 2 * CSTEP * ldi];                     \
-            rb2 = *(const float4 *)&pb[(o) + goff + 2 * CSTEP * ldi];                     \
-            ra3 = *(const float4 *)&pa[(o) + goff + 3 * CSTEP * ldi];                     \
-            rb3 = *(const float4 *)&pb[(o) + goff + 3 * CSTEP * ldi];                     \
+            ra2 = *(const V *)&pa[(o) + goff + 2 * CSTEP * ldi];                          \
+            rb2 = *(const V *)&pb[(o) + goff + 2 * CSTEP * ldi];                          \
+            ra3 = *(const V *)&pa[(o) + goff + 3 * CSTEP * ldi];                          \
+            rb3 = *(const V *)&pb[(o) + goff + 3 * CSTEP * ldi];                          \
         }                                                                                 \
     } while (0)
 #define SPD_SS(bf)                                                                        \
     do {                                                                                  \
-        float *as_ = As + (bf) * BUF, *bs_ = Bs + (bf) * BUF;                             \
-        *(float4 *)&as_[soff] = ra0;                                                      \
-        *(float4 *)&bs_[soff] = rb0;                                                      \
-        *(float4 *)&as_[soff + CSTEP * TS] = ra1;                                         \
-        *(float4 *)&bs_[soff + CSTEP * TS] = rb1;                                         \
+        T *as_ = As + (bf) * BUF, *bs_ = Bs + (bf) * BUF;                                 \
+        *(V *)&as_[soff] = ra0;                                                           \
+        *(V *)&bs_[soff] = rb0;                                                           \
+        *(V *)&as_[soff + CSTEP * TS] = ra1;                                              \
+        *(V *)&bs_[soff + CSTEP * TS] = rb1;                                              \
         if constexpr (NV > 2) {                                                           \
-            *(float4 *)&as_[soff + 2 * CSTEP * TS] = ra2;                                 \
-            *(float4 *)&bs_[soff + 2 * CSTEP * TS] = rb2;                                 \
-            *(float4 *)&as_[soff + 3 * CSTEP * TS] = ra3;                                 \
-            *(float4 *)&bs_[soff + 3 * CSTEP * TS] = rb3;                                 \
+            *(V *)&as_[soff + 2 * CSTEP * TS] = ra2;                                      \
+            *(V *)&bs_[soff + 2 * CSTEP * TS] = rb2;                                      \
+            *(V *)&as_[soff + 3 * CSTEP * TS] = ra3;                                      \
+            *(V *)&bs_[soff + 3 * CSTEP * TS] = rb3;                                      \
         }                                                                                 \
     } while (0)
     SPD_GL(0);
@@ -265,10 +138,10 @@ SPD_DEV void f32_update_tile(float *__restrict__ H, int64_t ld, int64_t k0, int 
         const int o = ((kb + KC < nbk) ? kb + KC : kb) * ldi;
         SPD_GL(o);
         __builtin_amdgcn_sched_barrier(0);
-        const float *A0 = As + buf * BUF, *B0 = Bs + buf * BUF;
+        const T *A0 = As + buf * BUF, *B0 = Bs + buf * BUF;
 #pragma unroll
         for (int ks = 0; ks < KC / 4; ++ks) {
-            float a[NB], b[NB];
+            T a[NB], b[NB];
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
                 a[i] = A0[4 * ks * TS + fa[i]];
@@ -277,8 +150,12 @@ SPD_DEV void f32_update_tile(float *__restrict__ H, int64_t ld, int64_t k0, int 
 #pragma unroll
             for (int mi = 0; mi < NB; ++mi)
 #pragma unroll
-                for (int ni = 0; ni < NB; ++ni)
-                    c[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mi], b[ni], c[mi][ni], 0, 0, 0);
+                for (int ni = 0; ni < NB; ++ni) {
+                    if constexpr (F32)
+                        c[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mi], b[ni], c[mi][ni], 0, 0, 0);
+                    else
+                        c[mi][ni] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[mi], b[ni], c[mi][ni], 0, 0, 0);
+                }
         }
         __builtin_amdgcn_sched_barrier(0);
         SPD_SS(buf ^ 1);
@@ -293,40 +170,37 @@ SPD_DEV void f32_update_tile(float *__restrict__ H, int64_t ld, int64_t k0, int 
         for (int ni = 0; ni < NB; ++ni)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                cu[coff + 16 * ni + (16 * mi + q) * ldi] = -c[mi][ni][q];
+                cu[coff + 16 * ni + (16 * mi + QR * q) * ldi] = -c[mi][ni][q];
 }
 
-// A last round's 64-tile (chunks of 64 columns) in a function of its own, so
-// that the 128-tile loop of the kernel keeps the register allocation and
-// schedule it has without it.  The pointers are re-derived in their address
-// spaces (global, shared), so the accesses stay GLOBAL and DS instructions.
-__device__ __attribute__((noinline)) void f32_update_tail_tile(float *H, int64_t ld, int64_t k0, int nbk,
-                                                               int64_t crow, int64_t ccol, float *As, float *Bs,
-                                                               int tid)
+// A last round's 64-tile (chunks of twice the columns) in a function of its
+// own, so that the 128-tile loop of the kernel keeps the register allocation
+// and schedule it has without it.  The pointers are re-derived in their
+// address spaces (global, shared), so the accesses stay GLOBAL and DS
+// instructions.
+template <typename T>
+__device__ __attribute__((noinline)) void update_tail_tile(T *H, int64_t ld, int64_t k0, int nbk, int64_t crow,
+                                                           int64_t ccol, T *As, T *Bs, int tid)
 {
-    H = (float *)gmem(H);
-    As = (float *)(__attribute__((address_space(3))) float *)As;
-    Bs = (float *)(__attribute__((address_space(3))) float *)Bs;
-    f32_update_tile<64, 64>(H, ld, k0, nbk, crow, ccol, As, Bs, tid);
+    H = (T *)gmem(H);
+    As = (T *)(__attribute__((address_space(3))) T *)As;
+    Bs = (T *)(__attribute__((address_space(3))) T *)Bs;
+    update_tile<T, 64, 256 / sizeof(T)>(H, ld, k0, nbk, crow, ccol, As, Bs, tid);
 }
 
-// The binary32 update on TS x TS tiles (128, or 64 for the panel chain's
-// single tile columns and for launches with too few 128-tiles to fill the
-// chip).  Tiles are counted in TS units over the lower triangle of the
-// trailing region (t tiles per side), tile columns [tj_lo, tj_hi).  Tiles
-// [0, nfull) run whole, the same number per workgroup; with TS = 128 the
-// remaining tiles [nfull, ntiles) -- a last round too small to fill the
-// workgroups -- run as four 64-tiles each (the quarter above the diagonal
-// of a diagonal tile skipped), with chunks of 64 columns, so that a last
-// round costs about a quarter of a whole one.
-template <int TS>
-__global__ __launch_bounds__(256, 2) void k_syrk_update_f32(float *__restrict__ H, int64_t ld, int64_t k0, int nbk,
-                                                           int64_t r0, int t, int tj_lo, int tj_hi, int ntiles,
-                                                           int nfull, const unsigned long long *info, int prio)
+// The update on TS x TS tiles (128, or 64 for the panel chain's single tile
+// columns and for launches with too few 128-tiles to fill the chip).  Tiles
+// are counted in TS units over the lower triangle of the trailing region (t
+// tiles per side), tile columns [tj_lo, tj_hi).  Tiles [0, nfull) run whole,
+// the same number per workgroup; with TS = 128 the remaining tiles [nfull,
+// ntiles) -- a last round too small to fill the workgroups -- run as four
+// 64-tiles each (the quarter above the diagonal of a diagonal tile skipped),
+// so that a last round costs about a quarter of a whole one.
+template <typename T, int TS>
+SPD_DEV void update_tiles(T *__restrict__ H, int64_t ld, int64_t k0, int nbk, int64_t r0, int t, int tj_lo, int tj_hi,
+                          int ntiles, int nfull, const unsigned long long *info, int prio, T *As, T *Bs)
 {
-    constexpr int KC = 32;
-    __shared__ __align__(16) float As[2 * KC * TS];
-    __shared__ __align__(16) float Bs[2 * KC * TS];
+    constexpr int KC = 128 / sizeof(T);
     const int tid = threadIdx.x;
     if (*(volatile const unsigned long long *)info != (unsigned long long)SPD_INFO_NONE)
         return;
@@ -341,7 +215,7 @@ __global__ __launch_bounds__(256, 2) void k_syrk_update_f32(float *__restrict__ 
         decode_tile(logical, t, tj_lo, tj_hi, ti, tj);
         if (ti < 0)
             break;
-        f32_update_tile<TS, KC>(H, ld, k0, nbk, r0 + (int64_t)ti * TS, r0 + (int64_t)tj * TS, As, Bs, tid);
+        update_tile<T, TS, KC>(H, ld, k0, nbk, r0 + (int64_t)ti * TS, r0 + (int64_t)tj * TS, As, Bs, tid);
     }
     if constexpr (TS == 128) {
         const int nsub = 4 * (ntiles - nfull), chunk2 = (nsub + 7) / 8;
@@ -356,10 +230,28 @@ __global__ __launch_bounds__(256, 2) void k_syrk_update_f32(float *__restrict__ 
             const int qi = (s >> 1) & 1, qj = s & 1;
             if (ti == tj && qi < qj)
                 continue;  // above the diagonal
-            f32_update_tail_tile(H, ld, k0, nbk, r0 + (int64_t)ti * 128 + 64 * qi, r0 + (int64_t)tj * 128 + 64 * qj, As,
-                                 Bs, tid);
+            update_tail_tile(H, ld, k0, nbk, r0 + (int64_t)ti * 128 + 64 * qi, r0 + (int64_t)tj * 128 + 64 * qj, As,
+                             Bs, tid);
         }
     }
+}
+
+// one kernel per type, so that a profile tells them apart
+template <int TS>
+__global__ __launch_bounds__(256, 2) void k_syrk_update_f32(float *__restrict__ H, int64_t ld, int64_t k0, int nbk,
+                                                           int64_t r0, int t, int tj_lo, int tj_hi, int ntiles,
+                                                           int nfull, const unsigned long long *info, int prio)
+{
+    __shared__ __align__(16) float As[64 * TS], Bs[64 * TS];
+    update_tiles<float, TS>(H, ld, k0, nbk, r0, t, tj_lo, tj_hi, ntiles, nfull, info, prio, As, Bs);
+}
+template <int TS>
+__global__ __launch_bounds__(256, 2) void k_syrk_update_f64(double *__restrict__ H, int64_t ld, int64_t k0, int nbk,
+                                                           int64_t r0, int t, int tj_lo, int tj_hi, int ntiles,
+                                                           int nfull, const unsigned long long *info, int prio)
+{
+    __shared__ __align__(16) double As[32 * TS], Bs[32 * TS];
+    update_tiles<double, TS>(H, ld, k0, nbk, r0, t, tj_lo, tj_hi, ntiles, nfull, info, prio, As, Bs);
 }
 
 // ---------------------------------------------------------------------------
@@ -614,7 +506,7 @@ void launch_syrk_update_half(float *H, int64_t ld, const void *Lh, int slot0, in
                            sstride, skip0, np, r0, t, tj_lo, tj_hi, (int)ntiles, info, prio);
 }
 
-// Below this many 128-tiles a binary32 update runs on 64-tiles (SPD_SMALL_TILES overrides).
+// Below this many 128-tiles an update runs on 64-tiles (SPD_SMALL_TILES overrides).
 static int small_update_tiles()
 {
     static const int v = [] {
@@ -625,7 +517,7 @@ static int small_update_tiles()
 }
 #define kSmallUpdateTiles small_update_tiles()
 
-// Workgroups of the binary32 128-tile update resident at once on the current
+// Workgroups of the 128-tile update resident at once on the current
 // device (two per compute unit), or 0 when the last round is not to be split
 // into 64-tiles (SPD_TAIL_SPLIT=0).
 static int update_slots()
@@ -679,25 +571,28 @@ void launch_syrk_update(T *H, int64_t ld, int64_t k0, int nbk, int64_t r0, int t
     if (t <= 0 || tj_lo >= tj_hi) return;
     int64_t ntiles = 0;
     for (int c = tj_lo; c < tj_hi; ++c) ntiles += t - c;
-    int64_t grid = ((ntiles + 7) / 8) * 8;
-    if (max_grid > 0 && grid > max_grid) grid = (max_grid / 8) * 8;
-    if constexpr (sizeof(T) == 4) {
-        if (small_tiles && ntiles < kSmallUpdateTiles && max_grid == 0) {
-            // too few 128-tiles for the chip: 64-tiles, four times as many workgroups
-            const int t2 = 2 * t, lo2 = 2 * tj_lo, hi2 = 2 * tj_hi;
-            int64_t n2 = 0;
-            for (int c = lo2; c < hi2; ++c) n2 += t2 - c;
-            const int64_t g2 = ((n2 + 7) / 8) * 8;
-            hipLaunchKernelGGL(k_syrk_update_f32<64>, dim3((unsigned)g2), dim3(256), 0, st, H, ld, k0, nbk, r0, t2,
-                               lo2, hi2, (int)n2, (int)n2, info, prio);
-        } else {
-            const int64_t nfull = update_split(ntiles, max_grid, &grid);
-            hipLaunchKernelGGL(k_syrk_update_f32<128>, dim3((unsigned)grid), dim3(256), 0, st, H, ld, k0, nbk, r0,
-                               t, tj_lo, tj_hi, (int)ntiles, (int)nfull, info, prio);
-        }
-    } else
-        hipLaunchKernelGGL(k_syrk_update<T>, dim3((unsigned)grid), dim3(256), 0, st, H, ld, k0, nbk, r0, t, tj_lo,
-                           tj_hi, (int)ntiles, info, prio);
+    auto go = [&](auto kern, int64_t grid, int tt, int lo, int hi, int64_t nt, int64_t nfull) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, st, H, ld, k0, nbk, r0, tt, lo, hi, (int)nt,
+                           (int)nfull, info, prio);
+    };
+    if (small_tiles && ntiles < kSmallUpdateTiles && max_grid == 0) {
+        // too few 128-tiles for the chip: 64-tiles, four times as many workgroups
+        const int t2 = 2 * t, lo2 = 2 * tj_lo, hi2 = 2 * tj_hi;
+        int64_t n2 = 0;
+        for (int c = lo2; c < hi2; ++c) n2 += t2 - c;
+        const int64_t g2 = ((n2 + 7) / 8) * 8;
+        if constexpr (sizeof(T) == 4)
+            go(k_syrk_update_f32<64>, g2, t2, lo2, hi2, n2, n2);
+        else
+            go(k_syrk_update_f64<64>, g2, t2, lo2, hi2, n2, n2);
+    } else {
+        int64_t grid = 0;
+        const int64_t nfull = update_split(ntiles, max_grid, &grid);
+        if constexpr (sizeof(T) == 4)
+            go(k_syrk_update_f32<128>, grid, t, tj_lo, tj_hi, ntiles, nfull);
+        else
+            go(k_syrk_update_f64<128>, grid, t, tj_lo, tj_hi, ntiles, nfull);
+    }
 }
 template void launch_syrk_update<float>(float *, int64_t, int64_t, int, int64_t, int, int, int,
                                         const unsigned long long *, hipStream_t, int, int, bool);
