@@ -1,9 +1,9 @@
 // Batched solver: many independent SPD systems A_s X_s = B_s (Eq. (2) per
 // system) in one persistent launch, each system taken through all of
 // Algorithm 1 by one workgroup:
-//   equilibrate and round (mu D A D), blocked Cholesky in the factor's
-//   precision (32-wide panels; trailing update on MFMA, with binary16 /
-//   bfloat16 rounded operands for the half formats), triangular solves with
+//   equilibrate and round (mu D A D), left-looking blocked Cholesky in the
+//   factor's precision (32-wide panels on MFMA, with binary16 / bfloat16
+//   rounded operands for the half formats), triangular solves on MFMA with
 //   the 32 x 32 diagonal-block inverses, binary64 residual and backward error,
 //   correction loop with the same stopping, divergence and fallback rules as
 //   the single-system path (BF16/FP16 -> FP32 -> FP64).
@@ -21,6 +21,7 @@
 #include "internal.h"
 
 #define BNB 32  // panel and tile width
+#define BDIAG_S 36  // row stride of a diagonal block in shared memory
 // precision picker: 16 features -> 64 -> 64 -> 4 classes (BF16, FP16, FP32, FP64)
 #define PICK_NFEAT 16
 #define PICK_NH 64
@@ -47,8 +48,8 @@ struct BatchArgs {
 
 // workspace slice of one workgroup
 struct BatchWs {
-    void *L;      // np x np factor (binary32 or binary64), column-major
-    void *Winv;   // np/32 blocks of 32 x 32 inverses of the diagonal blocks
+    void *L;      // the factor's 32 x 32 tiles below the diagonal (binary32 or binary64), see BTile
+    void *Winv;   // the inverses of its diagonal tiles, in the same layout
     double *d;    // equilibration
     double *R;    // n x m residual
     double *Am;   // np x np: A's strict lower triangle mirrored into the strict upper (Am[i + j np] = a_ji, i < j)
@@ -74,9 +75,8 @@ SPD_DEV double b_nanmax(double a, double b) { return (a > b || a != a) ? a : b; 
 
 // shared state of the workgroup
 struct SolveSmem {
-    double ys[SPD_BATCH_MAXRHS * SPD_BATCH_NMAX];  // solve vectors (factor type)
-    double Lk[BNB * (BNB + 1)];                    // inverse of the diagonal block
-    double ts[SPD_BATCH_MAXRHS * BNB];
+    double ys[SPD_BATCH_MAXRHS * (SPD_BATCH_NMAX + 2)];  // solve vectors (factor type); tile buffers
+    double Lk[BNB * (BNB + 1)];                          // inverse of the diagonal block
     double red[16][4 * SPD_BATCH_MAXRHS + 1];
     double norms[1 + 4 * SPD_BATCH_MAXRHS];
     double smax[SPD_BATCH_MAXRHS];
@@ -125,100 +125,120 @@ SPD_DEV double rl(double v, int src)
 }
 
 // ---------------------------------------------------------------------------
-// H = round(mu D A D) (lower), identity padding up to np; d (binary64); and
-// Am, A's strict lower triangle mirrored into the strict upper triangle of an
-// np x np array, so that the residual can stream whole rows of A with
-// coalesced loads while A itself is read only in its lower triangle.  32 x 32
-// tiles of the lower triangle, one per wave at a time: the tile is loaded
-// once (lane = row, 16 columns per lane), converted into L, and transposed
-// through the wave's buffer in shared memory (element (c, r) at
-// c * 32 + (r ^ c)) for the mirror's coalesced stores.
-template <typename T, int WAVES>
-__device__ __attribute__((noinline)) void b_convert(const double *A, int n, int np, double *d, double mu, int equil,
-                                                    T *L, double *Am, SolveSmem &sm)
-{
-    // global memory (see gmem): the parameters re-derived as global pointers
-    A = (const double *)gmem(A);
-    d = (double *)gmem(d);
-    L = (T *)gmem(L);
-    Am = (double *)gmem(Am);
-    constexpr int NT = WAVES * 64;
-    static_assert(WAVES * BNB * BNB * 8 <= (int)sizeof(sm.ys), "tile buffers");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    double *dsh = sm.arow;
-    for (int i = tid; i < n; i += NT) {
-        const double a = A[i + (int64_t)i * n];
-        const double di = (equil && a > 0.0) ? 1.0 / sqrt(a) : 1.0;
-        d[i] = di;
-        dsh[i] = di;
-    }
-    __syncthreads();
-    const int r = lane & 31, h = lane >> 5;
-    const int nb = np / BNB, ntiles = nb * (nb + 1) / 2;
-    double *tb = sm.ys + wave * BNB * BNB;
-    for (int q = wave; q < ntiles; q += WAVES) {
-        int I = (int)((sqrt(8.0 * q + 1.0) - 1.0) * 0.5);  // q = I (I + 1) / 2 + J, J <= I
-        while (I * (I + 1) / 2 > q) --I;
-        while ((I + 1) * (I + 2) / 2 <= q) ++I;
-        const int J = q - I * (I + 1) / 2;
-        const int i = I * BNB + r;
-        double a[BNB / 2];
+// The factor is stored as 32 x 32 tiles, tile (I, J) at 1024 (I (I + 1)/2 + J),
+// each in the order in which an MFMA accumulator holds it (transposed:
+// Acc32 register j of a lane is column row(j), row col(j) of the tile), four
+// registers next to each other: a solved tile is stored straight from its
+// accumulator, and loaded with 16-byte loads, contiguous across the wave, as
+// the operand of a later product -- the MFMA's k-slots are a free summation
+// order, and an accumulator's columns fall on them.
+//   binary32: column c, row r at ((c / 4) 32 + r) 4 + c % 4
+//   binary64: at ((4 (c / 16) + c % 4) 32 + r) 4 + (c / 4) % 4
+template <typename T> struct BTile;
+template <> struct BTile<float> {
+    using V = floatx4;
+    float v[16];  // lane (r = l % 32, h = l / 32): column 8 (j / 4) + 4 h + j % 4 in v[j]
+    static SPD_DEV int pos(int r, int c) { return ((c >> 2) * 32 + r) * 4 + (c & 3); }
+    static SPD_DEV void coords(int e, int &r, int &c) { r = (e >> 2) & 31; c = 4 * (e >> 7) + (e & 3); }
+    SPD_DEV void load(const float *t, int lane)
+    {
 #pragma unroll
-        for (int u = 0; u < BNB / 2; ++u) {
-            const int j = J * BNB + 2 * u + h;
-            a[u] = (i < n && j < n && j <= i) ? A[i + (int64_t)j * n] : 0.0;
+        for (int g = 0; g < 4; ++g) {
+            const V x = *(const V *)(gmem(t) + (2 * g * 32 + lane) * 4);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[4 * g + i] = x[i];
         }
-        const double di = (i < n) ? dsh[i] : 0.0;
+    }
+    static SPD_DEV void store(float *t, const Acc32<float> &a, int lane)
+    {
 #pragma unroll
-        for (int u = 0; u < BNB / 2; ++u) {
-            const int c = 2 * u + h, j = J * BNB + c;
-            if (j <= i) {
-                T v;
-                if (i < n && j < n)
-                    v = (T)(((mu * di) * a[u]) * dsh[j]);
-                else
-                    v = (i == j) ? (T)1 : (T)0;
-                L[i + (int64_t)j * np] = v;
+        for (int g = 0; g < 4; ++g)
+            *(__attribute__((address_space(1))) V *)(gmem(t) + (2 * g * 32 + lane) * 4) =
+                V{a.v[4 * g], a.v[4 * g + 1], a.v[4 * g + 2], a.v[4 * g + 3]};
+    }
+    // acc += (this as rows of D) (b as columns of D)^T, this negated
+    static SPD_DEV void submul(Acc32<float> &acc, const BTile &a, const BTile &b)
+    {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc.mma(-a.v[j], b.v[j]);
+    }
+};
+template <> struct BTile<double> {
+    typedef double V __attribute__((ext_vector_type(2)));
+    double v[2][2][4];  // lane (r = l % 16, u = l / 16): row 16 b + r, column 16 a + 4 q + u in v[b][a][q]
+    static SPD_DEV int pos(int r, int c) { return ((4 * (c >> 4) + (c & 3)) * 32 + r) * 4 + ((c >> 2) & 3); }
+    static SPD_DEV void coords(int e, int &r, int &c)
+    {
+        const int g = e >> 7;
+        r = (e >> 2) & 31;
+        c = 16 * (g >> 2) + 4 * (e & 3) + (g & 3);
+    }
+    SPD_DEV void load(const double *t, int lane)
+    {
+        const int r = lane & 15, u = lane >> 4;
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; q += 2) {
+                    const V x = *(const V *)(gmem(t) + ((4 * a + u) * 32 + 16 * b + r) * 4 + q);
+                    v[b][a][q] = x[0];
+                    v[b][a][q + 1] = x[1];
+                }
+    }
+    static SPD_DEV void store(double *t, const Acc32<double> &acc, int lane)
+    {
+        const int r = lane & 15, u = lane >> 4;
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; q += 2)
+                    *(__attribute__((address_space(1))) V *)(gmem(t) + ((4 * a + u) * 32 + 16 * b + r) * 4 + q) =
+                        V{acc.v[a][b][q], acc.v[a][b][q + 1]};
+    }
+    static SPD_DEV void submul(Acc32<double> &acc, const BTile &x, const BTile &y)
+    {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double fx[2] = {-x.v[0][a][q], -x.v[1][a][q]}, fy[2] = {y.v[0][a][q], y.v[1][a][q]};
+                acc.mma(fx, fy);
             }
-            tb[c * BNB + (r ^ c)] = a[u];
-        }
-        __builtin_amdgcn_wave_barrier();
-        // Am (row J*32 + c, column I*32 + rr) = a (I*32 + rr, J*32 + c), c = lane % 32, strictly above the diagonal
-        double *dst = Am + (int64_t)J * BNB + (int64_t)I * BNB * np;
-#pragma unroll
-        for (int u = 0; u < BNB / 2; ++u) {
-            const int rr = 2 * u + h;
-            if (I > J || r < rr)
-                dst[r + (int64_t)rr * np] = tb[r * BNB + (rr ^ r)];
-        }
-        __builtin_amdgcn_wave_barrier();
     }
-    __syncthreads();
+};
+template <typename T>
+SPD_DEV T *b_tile(T *L, int I, int J)
+{
+    return L + (int64_t)(I * (I + 1) / 2 + J) * (BNB * BNB);
 }
 
-// Factor the 32 x 32 diagonal block at (k0, k0) in one wavefront and form
-// its inverse W, left-looking: lane r holds row r; at column j every lane
+// Factor a 32 x 32 diagonal block, given row-major in Lr (its lower triangle),
+// in one wavefront and form its inverse W, left-looking: lane r holds row r; at column j every lane
 // forms a_rj - sum_{q<j} L[r][q] L[j][q] with row j of L read from shared
 // memory (Lr, row-major, every lane the same address: a broadcast, four
 // values per read), lane j's value is the pivot (one readlane), and each lane
 // publishes its new L[r][j] to Lr.  W follows by forward substitution
 // L W = I, lane c building column c (W[r][c] = (delta_rc -
 // sum_{q<r} L[r][q] W[q][c]) / L[r][r]) from the same rows.  Lanes 32..63
-// mirror lanes 0..31 and store nothing.  Outputs: the block in L, W in Ws
-// (Ws[c * 33 + r]) and Wg (column-major).  Returns the 1-based failing
-// column of the block, 0 on success.
+// mirror lanes 0..31 and store nothing.  Outputs: W in Ws (Ws[c * 33 + r])
+// and Wg (tile layout; nothing reads the block of L itself again).  Returns
+// the 1-based failing column of the block, 0 on success.
 template <typename T>
-__device__ __attribute__((noinline)) int b_diag(T *L, int np, int k0, T *Ws, T *Wg, T *Lr)
+__device__ __attribute__((noinline)) int b_diag(T *Ws, T *Wg, T *Lr)
 {
-    L = (T *)gmem(L);  // global memory (see gmem)
-    Wg = (T *)gmem(Wg);
-    constexpr int S = 36;  // Lr row stride (16-byte aligned rows)
+    Wg = (T *)gmem(Wg);  // global memory (see gmem)
+    constexpr int S = BDIAG_S;  // Lr row stride (16-byte aligned rows)
     const int lane = threadIdx.x & 63, r = lane & 31;
     const bool store = lane < BNB;
     T row[BNB];
 #pragma unroll
     for (int c = 0; c < BNB; ++c)
-        row[c] = (c <= r) ? L[(k0 + r) + (int64_t)(k0 + c) * np] : (T)0;
+        row[c] = (c <= r) ? Lr[r * S + c] : (T)0;
+    __builtin_amdgcn_wave_barrier();
     int bad = 0;
 #pragma unroll
     for (int j = 0; j < BNB; ++j) {
@@ -254,125 +274,170 @@ __device__ __attribute__((noinline)) int b_diag(T *L, int np, int k0, T *Ws, T *
         __builtin_amdgcn_sched_barrier(0);
     }
     __builtin_amdgcn_wave_barrier();
-    // the block of L and W (column-major) to global memory, column by column
     for (int e = lane; e < BNB * BNB; e += 64) {
-        const int rr = e % BNB, cc = e / BNB;
-        if (cc <= rr)
-            L[(k0 + rr) + (int64_t)(k0 + cc) * np] = Lr[rr * S + cc];
+        int rr, cc;
+        BTile<T>::coords(e, rr, cc);
         Wg[e] = Ws[cc * (BNB + 1) + rr];
     }
     return 0;
 }
 
 // ---------------------------------------------------------------------------
-// Blocked right-looking Cholesky of the np x np lower matrix in L.  Returns
-// the 1-based failing column (0 on success); Winv receives the inverses of
-// the 32 x 32 diagonal blocks.  With half != HALF_NONE the trailing-update
-// operands are rounded to that format (binary32 accumulation).
+// Left-looking blocked Cholesky of H = round(mu D A D) (identity padding up
+// to np = 32 nb): panel kb's tiles (I, kb), I = kb + wave + 4 s, are formed
+// from A in the waves' accumulators (d_i = a_ii^{-1/2} also goes to d), take
+// the products of the earlier panels, the diagonal one is factored by wave 0,
+// and the others become L_Ik = H_Ik W^T, W the diagonal tile's inverse, and
+// are stored once.  With half != HALF_NONE the products' operands are rounded
+// to that format (binary32 accumulation).  Returns the 1-based failing column
+// (0 on success).
+//
+// Also writes Am, A's strict lower triangle mirrored into the strict upper
+// triangle of an np x np array, so that the residual can stream whole rows of
+// A with coalesced loads while A itself is read only in its lower triangle:
+// each tile of A, in registers anyway, is transposed through the wave's
+// buffer in shared memory (element (c, r) at c * 32 + (r ^ c)).
+//
+// Bound by memory traffic, with 512 systems in flight.  Right-looking, with H
+// written out by a conversion and every trailing tile read and written once
+// per panel, 4096 systems of the batched distribution moved 40 GB in binary32
+// (9.4 ms) and 31 GB in binary64 (7.1 ms), 4.3 TB/s; TIMES_BFAC.
 template <typename T, int WAVES>
-__device__ __attribute__((noinline)) int b_factor(T *L, int np, T *Winv, int half, SolveSmem &sm)
+__device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np, double *d, double mu, int equil,
+                                                  T *L, T *Winv, double *Am, int half, SolveSmem &sm)
 {
-    L = (T *)gmem(L);  // global memory (see gmem)
+    A = (const double *)gmem(A);  // global memory (see gmem)
+    d = (double *)gmem(d);
+    L = (T *)gmem(L);
     Winv = (T *)gmem(Winv);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    Am = (double *)gmem(Am);
+    constexpr int NT = WAVES * 64, SLOTS = SPD_BATCH_NMAX / BNB / WAVES;
+    static_assert(WAVES * BNB * BNB * 8 <= (int)sizeof(sm.ys), "tile buffers");
+    static_assert(BNB * BDIAG_S * 8 <= (int)sizeof(sm.part), "diagonal block");
+    using A32 = Acc32<T>;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nb = np / BNB;
-    T *Ws = (T *)sm.Lk;  // inverse of the diagonal block: Ws[c * 33 + r] = W[r][c]
+    T *Ws = (T *)sm.Lk;   // inverse of the diagonal block: Ws[c * 33 + r] = W[r][c]
+    T *Lr = (T *)sm.part;  // the diagonal block, row-major
+    double *dsh = sm.arow;
+    for (int i = tid; i < n; i += NT) {
+        const double a = A[i + (int64_t)i * n];
+        const double di = (equil && a > 0.0) ? 1.0 / sqrt(a) : 1.0;
+        d[i] = di;
+        dsh[i] = di;
+    }
+    __syncthreads();
+    double *tb = sm.ys + wave * BNB * BNB;
     for (int kb = 0; kb < nb; ++kb) {
-        const int k0 = kb * BNB;
+        A32 acc[SLOTS];
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            const int I = kb + wave + WAVES * s;
+            if (I >= nb)
+                continue;
+            // A's tile: register j of the accumulator is column row(j), row col(j)
+            double a[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const int i = I * BNB + A32::col(j, lane), c = kb * BNB + A32::row(j, lane);
+                a[j] = (i < n && c < n && c <= i) ? A[i + (int64_t)c * n] : 0.0;
+            }
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const int r = A32::col(j, lane), c = A32::row(j, lane), i = I * BNB + r, k = kb * BNB + c;
+                T v = (i == k) ? (T)1 : (T)0;
+                if (i < n && k < n)
+                    v = (T)(((mu * dsh[i]) * a[j]) * dsh[k]);
+                acc[s].set(j, v);
+                tb[c * BNB + (r ^ c)] = a[j];
+            }
+            __builtin_amdgcn_wave_barrier();
+            // Am (row kb*32 + c, column I*32 + rr) = a (I*32 + rr, kb*32 + c), c = lane % 32, strictly above the diagonal
+            double *dst = Am + (int64_t)kb * BNB + (int64_t)I * BNB * np;
+            const int cc = lane & 31, h = lane >> 5;
+#pragma unroll
+            for (int u = 0; u < BNB / 2; ++u) {
+                const int rr = 2 * u + h;
+                if (I > kb || cc < rr)
+                    dst[cc + (int64_t)rr * np] = tb[cc * BNB + (rr ^ cc)];
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        // the earlier panels' products
+        if (kb + wave < nb) {
+            for (int q = 0; q < kb; ++q) {
+                BTile<T> fk, fi;
+                fk.load(b_tile(L, kb, q), lane);
+                fi.load(b_tile(L, kb + wave, q), lane);
+                if constexpr (sizeof(T) == 4) {
+                    if (half)
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) fk.v[j] = round_half(fk.v[j], half);
+                }
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s) {
+                    const int I = kb + wave + WAVES * s;
+                    if (I >= nb)
+                        break;
+                    BTile<T> nx;
+                    if (s + 1 < SLOTS && I + WAVES < nb)
+                        nx.load(b_tile(L, I + WAVES, q), lane);
+                    if constexpr (sizeof(T) == 4) {
+                        if (half)
+#pragma unroll
+                            for (int j = 0; j < 16; ++j) fi.v[j] = round_half(fi.v[j], half);
+                    }
+                    BTile<T>::submul(acc[s], fk, fi);
+                    fi = nx;
+                }
+            }
+        }
         if (wave == 0) {
-            const int bad = b_diag<T>(L, np, k0, Ws, Winv + (int64_t)kb * BNB * BNB, (T *)sm.ys);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) Lr[A32::col(j, lane) * BDIAG_S + A32::row(j, lane)] = acc[0].get(j);
+            __builtin_amdgcn_wave_barrier();
+            const int bad = b_diag<T>(Ws, Winv + (int64_t)kb * BNB * BNB, Lr);
             if (lane == 0)
-                sm.info = bad ? k0 + bad : 0;
+                sm.info = bad ? kb * BNB + bad : 0;
         }
         __syncthreads();
         if (sm.info)
             return sm.info;
-        // panel: L_ik = H_ik W^T for the row blocks below, one 32 x 32 block per
-        // wave.  A binary32 factor's blocks also go, transposed, to U = L^T in
-        // the strict upper triangle of the same array (for its backward
-        // substitutions), through the wave's 32 x 32 buffer in shared memory
-        // (element (c, r) at c * 32 + (r ^ c): both sides conflict-free) so
-        // that both global stores are coalesced.  The buffers overlap b_diag's
-        // rows, which are no longer needed.
-        T *tb = (T *)sm.ys + wave * BNB * BNB;
-        for (int I = kb + 1 + wave; I < nb; I += WAVES) {
-            Acc32<T> acc;
-            acc.zero();
-            // D[c][r] = sum_q W[c][q] H[r][q]
-            mma_tile<T>(acc, Ws, BNB + 1, L + (int64_t)I * BNB + (int64_t)k0 * np, np, BNB, lane);
+        // L_Ik = H_Ik W^T: D[c][r] = sum_q W[c][q] H[r][q], H the accumulator itself
+        BTile<T> w;
+        if constexpr (sizeof(T) == 4) {
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int c = Acc32<T>::row(j, lane), r = Acc32<T>::col(j, lane);
-                L[((int64_t)I * BNB + r) + (int64_t)(k0 + c) * np] = acc.get(j);
-                if constexpr (sizeof(T) == 4)
-                    tb[c * BNB + (r ^ c)] = acc.get(j);
-            }
+            for (int j = 0; j < 16; ++j) w.v[j] = Ws[A32::row(j, lane) * (BNB + 1) + (lane & 31)];
+        } else {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        w.v[b][a][q] = Ws[(16 * a + 4 * q + (lane >> 4)) * (BNB + 1) + 16 * b + (lane & 15)];
+        }
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            const int I = kb + wave + WAVES * s;
+            if (I >= nb || I == kb)
+                continue;
+            A32 y;
+            y.zero();
             if constexpr (sizeof(T) == 4) {
-                __builtin_amdgcn_wave_barrier();
-                // U (row k0 + c, column I*32 + rr) = L (I*32 + rr, k0 + c), c = lane % 32
-                const int cc = lane & 31, h = lane >> 5;
-                T *dst = L + k0 + (int64_t)I * BNB * np;
 #pragma unroll
-                for (int u = 0; u < BNB / 2; ++u) {
-                    const int rr = 2 * u + h;
-                    dst[cc + (int64_t)rr * np] = tb[cc * BNB + (rr ^ cc)];
-                }
-                __builtin_amdgcn_wave_barrier();
-            }
-        }
-        __syncthreads();
-        // trailing update of the lower tiles (I, J), kb < J <= I; a wave's
-        // next tile's C values and this tile's operands are loaded before
-        // this tile's MFMAs
-        const int t = nb - kb - 1, ntile = t * (t + 1) / 2;
-        auto tile_of = [&](int q, int &gI, int &gJ) {
-            int I = (int)((sqrt(8.0 * q + 1.0) - 1.0) * 0.5);
-            while (I * (I + 1) / 2 > q) --I;
-            while ((I + 1) * (I + 2) / 2 <= q) ++I;
-            gI = kb + 1 + I;
-            gJ = kb + 1 + q - I * (I + 1) / 2;
-        };
-        auto load_c = [&](Acc32<T> &acc, const T *C) {
-            // register j: column Acc32::row(j) of the tile, row Acc32::col(j)
+                for (int j = 0; j < 16; ++j) y.mma(w.v[j], acc[s].v[j]);
+            } else {
 #pragma unroll
-            for (int j = 0; j < 16; ++j)
-                acc.set(j, C[Acc32<T>::col(j, lane) + (int64_t)Acc32<T>::row(j, lane) * np]);
-        };
-        int gI = 0, gJ = 0;
-        Acc32<T> nxt;
-        if (wave < ntile) {
-            tile_of(wave, gI, gJ);
-            load_c(nxt, L + (int64_t)gI * BNB + (int64_t)gJ * BNB * np);
-        }
-        for (int q = wave; q < ntile; q += WAVES) {
-            T *C = L + (int64_t)gI * BNB + (int64_t)gJ * BNB * np;
-            const T *pJ = L + (int64_t)gJ * BNB + (int64_t)k0 * np;
-            const T *pI = L + (int64_t)gI * BNB + (int64_t)k0 * np;
-            Acc32<T> acc = nxt;
-            Frag<T> fa[BNB / Frag<T>::K], fb[BNB / Frag<T>::K];
+                for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int s2 = 0; s2 < BNB / Frag<T>::K; ++s2) {
-                fa[s2].load(pJ + (int64_t)s2 * Frag<T>::K * np, np, lane);
-                fb[s2].load(pI + (int64_t)s2 * Frag<T>::K * np, np, lane);
-            }
-            if (q + WAVES < ntile) {
-                tile_of(q + WAVES, gI, gJ);
-                load_c(nxt, L + (int64_t)gI * BNB + (int64_t)gJ * BNB * np);
-            }
-#pragma unroll
-            for (int s2 = 0; s2 < BNB / Frag<T>::K; ++s2) {
-                if constexpr (sizeof(T) == 4) {
-                    if (half) {
-                        fa[s2].v = round_half(fa[s2].v, half);
-                        fb[s2].v = round_half(fb[s2].v, half);
+                    for (int q = 0; q < 4; ++q) {
+                        const double fw[2] = {w.v[0][a][q], w.v[1][a][q]};
+                        const double fh[2] = {acc[s].v[a][0][q], acc[s].v[a][1][q]};
+                        y.mma(fw, fh);
                     }
-                }
-                fa[s2].negate();
-                mma(acc, fa[s2], fb[s2]);
             }
-#pragma unroll
-            for (int j = 0; j < 16; ++j)
-                C[Acc32<T>::col(j, lane) + (int64_t)Acc32<T>::row(j, lane) * np] = acc.get(j);
+            BTile<T>::store(b_tile(L, I, kb), y, lane);
         }
         __syncthreads();
     }
@@ -381,234 +446,160 @@ __device__ __attribute__((noinline)) int b_factor(T *L, int np, T *Winv, int hal
 
 // ---------------------------------------------------------------------------
 // X (+)= s mu D L^{-T} L^{-1} round(D R / s) for m right-hand sides; the
-// scales s_c = pow2_ceil(smax[c]) (smax in shared memory).  Every global
-// read is coalesced across lanes and issued in batches (no loop carries a
-// load-to-use dependency).
+// scales s_c = pow2_ceil(smax[c]) (smax in shared memory).
+//
+// Both sweeps are right-looking over the factor's tiles on MFMA (16 x 16 x 4,
+// the right-hand sides as the 16 columns): z_k = W_k y_k, then y_I -= L_Ik z_k
+// for the tiles below, wave w taking I = k + 1 + w, ... -- wave 0, which has
+// the next diagonal tile's rows first, goes on to z_{k+1} at once, so a step
+// costs one barrier.  The backward sweep is the mirror on the transposed
+// tiles.  ys[c * YS + i] holds right-hand side c (YS: pitch without bank
+// conflicts between the 16 columns).  On the VALU, with the vectors read from
+// shared memory for every product, a binary32 solve took 62 us (mean n = 270),
+// a binary64 one 218 us; TIMES_BSOLVE.
+template <typename T> struct BVec;
+template <> struct BVec<float> {
+    using acc = floatx4;
+    static constexpr int YS = SPD_BATCH_NMAX + 4;
+    static SPD_DEV floatx4 mma(float a, float b, floatx4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+    // k index of slot u at step s (0..7): the columns of a tile as 16-byte runs
+    static SPD_DEV int k(int s, int u) { return 16 * (s >> 2) + 4 * u + (s & 3); }
+    static SPD_DEV int row(int q, int u) { return 4 * u + q; }  // accumulator register q
+};
+template <> struct BVec<double> {
+    using acc = doublex4;
+    static constexpr int YS = SPD_BATCH_NMAX + 2;
+    static SPD_DEV doublex4 mma(double a, double b, doublex4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+    static SPD_DEV int k(int s, int u) { return 4 * s + u; }
+    static SPD_DEV int row(int q, int u) { return 4 * q + u; }
+};
+// a tile as the left operand of tile times vectors (t[h][s]: row 16 h + r,
+// column k(s, u)), or of its transpose (column 16 h + r, row 4 s + u)
+template <typename T, bool TR>
+struct BOp {
+    T v[2][8];
+    SPD_DEV void load(const T *t, int lane)
+    {
+        const int r = lane & 15, u = lane >> 4;
+        const auto g = gmem(t);
+        using V = typename BTile<T>::V;
+        constexpr int VN = 16 / sizeof(T);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if constexpr (TR) {
+#pragma unroll
+                for (int s = 0; s < 8; ++s) v[h][s] = g[BTile<T>::pos(4 * s + u, 16 * h + r)];
+            } else {
+                // k(s, u), s = 4 j .. 4 j + 3, are next to each other
+#pragma unroll
+                for (int s = 0; s < 8; s += VN) {
+                    const V x = *(const __attribute__((address_space(1))) V *)(g + BTile<T>::pos(16 * h + r, BVec<T>::k(s, u)));
+#pragma unroll
+                    for (int i = 0; i < VN; ++i) v[h][s + i] = x[i];
+                }
+            }
+        }
+    }
+};
+
 template <typename T, int WAVES>
 __device__ __attribute__((noinline)) void b_solve(const T *L, const T *Winv, int n, int np, int m, const double *R, const double *d, double mu,
                      double *X, int accumulate, SolveSmem &sm)
 {
-    constexpr int NT = WAVES * 64, MR = SPD_BATCH_MAXRHS;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int NT = WAVES * 64, YS = BVec<T>::YS;
+    using acc_t = typename BVec<T>::acc;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, u = lane >> 4;
     const int nb = np / BNB;
-    const auto gL = gmem(L), gW = gmem(Winv);
     const auto gR = gmem(R), gd = gmem(d);
     const auto gX = gmem(X);
-    T *ys = (T *)sm.ys;  // ys[c * NMAX + i]
-    constexpr int NM = SPD_BATCH_NMAX;
+    T *ys = (T *)sm.ys;
+    static_assert(SPD_BATCH_MAXRHS * YS * sizeof(T) <= sizeof(sm.ys), "solve vectors");
     for (int idx = tid; idx < m * np; idx += NT) {
         const int c = idx / np, i = idx % np;
         const double s = pow2_ceil(sm.smax[c]);
-        ys[c * NM + i] = (i < n) ? (T)(gd[i] * gR[i + (int64_t)c * n] / s) : (T)0;
+        ys[c * YS + i] = (i < n) ? (T)(gd[i] * gR[i + (int64_t)c * n] / s) : (T)0;
     }
     __syncthreads();
-    // Each step first issues the loads it needs -- the W block (staged in
-    // shared memory, Wl[q * 33 + r] = W[r][q]) and the matrix values of the
-    // step -- so that their latencies overlap; sums keep the same order.
-    constexpr int WPT = BNB * BNB / NT;  // W values staged per thread
-    static_assert(WPT * NT == BNB * BNB, "W staging");
-    T *Wl = (T *)sm.Lk;
-    T *zs = (T *)sm.ts;  // the block just solved, zs[c * BNB + r]
-    // forward: z_k = W_k y_k, then y_below -= L_below,k z_k
-    for (int kb = 0; kb < nb; ++kb) {
-        const int k0 = kb * BNB;
-        const auto W = gW + (int64_t)kb * BNB * BNB;
-        T wt[WPT];
+    // the lane's right-hand side (lanes past the last one repeat the first;
+    // their products are dropped)
+    const bool live = r < m;
+    T *yc = ys + (live ? r : 0) * YS;
+    // block k's vectors as the right operand, and D's rows back
+    auto take = [&](T (&z)[8], int k, bool tr) {
 #pragma unroll
-        for (int u = 0; u < WPT; ++u) wt[u] = W[tid + u * NT];
-        const int i1 = k0 + BNB + tid;
-        T lv[BNB];
-        if (i1 < np) {
+        for (int s = 0; s < 8; ++s) z[s] = yc[k * BNB + (tr ? 4 * s + u : BVec<T>::k(s, u))];
+    };
+    auto sweep = [&](auto trc) {
+        constexpr bool TR = decltype(trc)::value;
+        using Op = BOp<T, TR>;
+        auto product = [&](const Op &a, const T (&z)[8], acc_t (&o)[2]) {
 #pragma unroll
-            for (int q = 0; q < BNB; ++q) lv[q] = gL[i1 + (int64_t)(k0 + q) * np];
-        }
+            for (int h = 0; h < 2; ++h) o[h] = acc_t{0, 0, 0, 0};
 #pragma unroll
-        for (int u = 0; u < WPT; ++u) {
-            const int e = tid + u * NT;
-            Wl[(e / BNB) * (BNB + 1) + e % BNB] = wt[u];
-        }
+            for (int s = 0; s < 8; ++s)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) o[h] = BVec<T>::mma(a.v[h][s], z[s], o[h]);
+        };
+        // steps t = 0 .. nb - 1 on block blk(t); wave w's tiles at step t are
+        // blocks blk(t + 1 + w), blk(t + 1 + w + WAVES), ...
+        auto blk = [&](int t) { return TR ? nb - 1 - t : t; };
+        auto tile = [&](int t, int o) { return TR ? b_tile(L, blk(t), blk(o)) : b_tile(L, blk(o), blk(t)); };
+        auto diag = [&](int t) {  // wave 0: z_k = W_k y_k in place
+            Op w;
+            w.load(Winv + (int64_t)blk(t) * BNB * BNB, lane);
+            T z[8];
+            take(z, blk(t), TR);
+            acc_t o[2];
+            product(w, z, o);
+            if (live)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) yc[blk(t) * BNB + 16 * h + BVec<T>::row(q, u)] = o[h][q];
+        };
+        if (wave == 0)
+            diag(0);
+        Op cur;
+        if (1 + wave < nb)
+            cur.load(tile(0, 1 + wave), lane);
         __syncthreads();
-        if (tid < BNB * m) {
-            const int r = tid % BNB, c = tid / BNB;
-            T z = (T)0;
+        for (int t = 0; t + 1 < nb; ++t) {
+            T z[8];
+            take(z, blk(t), TR);
+            for (int o = t + 1 + wave; o < nb; o += WAVES) {
+                Op nx;
+                const bool more = o + WAVES < nb;
+                if (more)
+                    nx.load(tile(t, o + WAVES), lane);
+                acc_t p[2];
+                product(cur, z, p);
+                if (live)
 #pragma unroll
-            for (int q = 0; q < BNB; ++q) z += Wl[q * (BNB + 1) + r] * ys[c * NM + k0 + q];  // W is zero above its diagonal
-            zs[tid] = z;
-        }
-        __syncthreads();
-        if (tid < BNB * m)
-            ys[(tid / BNB) * NM + k0 + tid % BNB] = zs[tid];
-        if (i1 < np) {
+                    for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int c = 0; c < MR; ++c) {
-                if (c < m) {
-                    T sacc = (T)0;
-#pragma unroll
-                    for (int q = 0; q < BNB; ++q) sacc += lv[q] * zs[c * BNB + q];
-                    ys[c * NM + i1] -= sacc;
+                        for (int q = 0; q < 4; ++q) yc[blk(o) * BNB + 16 * h + BVec<T>::row(q, u)] -= p[h][q];
+                if (wave == 0 && o == t + 1) {
+                    __builtin_amdgcn_wave_barrier();
+                    diag(t + 1);
                 }
+                if (more)
+                    cur = nx;
             }
-        }
-        for (int i = i1 + NT; i < np; i += NT) {
-            T lw[BNB];
-#pragma unroll
-            for (int q = 0; q < BNB; ++q) lw[q] = gL[i + (int64_t)(k0 + q) * np];
-#pragma unroll
-            for (int c = 0; c < MR; ++c) {
-                if (c < m) {
-                    T sacc = (T)0;
-#pragma unroll
-                    for (int q = 0; q < BNB; ++q) sacc += lw[q] * zs[c * BNB + q];
-                    ys[c * NM + i] -= sacc;
-                }
-            }
-        }
-        __syncthreads();
-    }
-    // backward.  A binary32 factor serves three or more solves on average and
-    // carries U = L^T (written by its panel steps): a sweep that mirrors the
-    // forward one.  A binary64 factor serves one solve, where the copy did not
-    // pay (measured): column sums by wave over L itself.
-    if constexpr (sizeof(T) == 4) {
-        // backward, right-looking on U = L^T (held in the strict upper triangle
-        // of the same array, written by the factorisation's panel steps):
-        // x_k = W_k^T y_k, then
-        // y_above -= U_above,k x_k -- the forward sweep's mirror, each row's
-        // values of a step one coalesced load per column of the block
-        for (int kb = nb - 1; kb >= 0; --kb) {
-            const int k0 = kb * BNB;
-            const auto W = gW + (int64_t)kb * BNB * BNB;
-            T wt[WPT];
-#pragma unroll
-            for (int u = 0; u < WPT; ++u) wt[u] = W[tid + u * NT];
-            const int i1 = tid;  // rows above the block: 0 .. k0 - 1
-            T lv[BNB];
-            if (i1 < k0) {
-#pragma unroll
-                for (int q = 0; q < BNB; ++q) lv[q] = gL[i1 + (int64_t)(k0 + q) * np];
-            }
-#pragma unroll
-            for (int u = 0; u < WPT; ++u) {
-                const int e = tid + u * NT;
-                Wl[(e / BNB) * (BNB + 1) + e % BNB] = wt[u];
-            }
-            __syncthreads();
-            if (tid < BNB * m) {
-                const int r = tid % BNB, c = tid / BNB;
-                T x = (T)0;
-#pragma unroll
-                for (int q = 0; q < BNB; ++q) x += Wl[r * (BNB + 1) + q] * ys[c * NM + k0 + q];  // W^T: zero below
-                zs[tid] = x;
-            }
-            __syncthreads();
-            if (tid < BNB * m)
-                ys[(tid / BNB) * NM + k0 + tid % BNB] = zs[tid];
-            if (i1 < k0) {
-#pragma unroll
-                for (int c = 0; c < MR; ++c) {
-                    if (c < m) {
-                        T sacc = (T)0;
-#pragma unroll
-                        for (int q = 0; q < BNB; ++q) sacc += lv[q] * zs[c * BNB + q];
-                        ys[c * NM + i1] -= sacc;
-                    }
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            for (int i = i1 + NT; i < k0; i += NT) {
-                T lw[BNB];
-#pragma unroll
-                for (int q = 0; q < BNB; ++q) lw[q] = gL[i + (int64_t)(k0 + q) * np];
-#pragma unroll
-                for (int c = 0; c < MR; ++c) {
-                    if (c < m) {
-                        T sacc = (T)0;
-#pragma unroll
-                        for (int q = 0; q < BNB; ++q) sacc += lw[q] * zs[c * BNB + q];
-                        ys[c * NM + i] -= sacc;
-                    }
-                }
-            }
+            if (t + 2 + wave < nb)
+                cur.load(tile(t + 1, t + 2 + wave), lane);
             __syncthreads();
         }
-    } else {
-        // backward: x_k = W_k^T (y_k - L_below,k^T x_below); the column sums by
-        // wave (lanes over rows), column q + WAVES's values loaded while column
-        // q's are used
-        constexpr int RCH = NM / 64;
-        T *ts = (T *)sm.ts;
-        for (int kb = nb - 1; kb >= 0; --kb) {
-            const int k0 = kb * BNB, r0 = k0 + BNB;
-            const auto W = gW + (int64_t)kb * BNB * BNB;
-            T wt[WPT];
-#pragma unroll
-            for (int u = 0; u < WPT; ++u) wt[u] = W[tid + u * NT];
-            const int nch = (np - r0 + 63) / 64;
-            T cur[RCH], nxt[RCH];
-            auto load_col = [&](T *dst, int q) {
-                const auto col = gL + (int64_t)(k0 + q) * np;
-#pragma unroll
-                for (int u = 0; u < RCH; ++u) {
-                    const int i = r0 + 64 * u + lane;
-                    dst[u] = (u < nch && i < np) ? col[i] : (T)0;
-                }
-            };
-            load_col(cur, wave);
-#pragma unroll 1
-            for (int q = wave; q < BNB; q += WAVES) {
-                if (q + WAVES < BNB)
-                    load_col(nxt, q + WAVES);
-                T acc[MR];
-#pragma unroll
-                for (int c = 0; c < MR; ++c) acc[c] = (T)0;
-#pragma unroll
-                for (int u = 0; u < RCH; ++u) {
-                    const int i = r0 + 64 * u + lane;
-                    if (u < nch && i < np) {
-#pragma unroll
-                        for (int c = 0; c < MR; ++c)
-                            if (c < m)
-                                acc[c] += cur[u] * ys[c * NM + i];
-                    }
-                }
-#pragma unroll
-                for (int c = 0; c < MR; ++c) {
-                    if (c < m) {
-                        T v = acc[c];
-#pragma unroll
-                        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-                        if (lane == 0)
-                            ts[c * BNB + q] = v;
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < RCH; ++u) cur[u] = nxt[u];
-            }
-#pragma unroll
-            for (int u = 0; u < WPT; ++u) {
-                const int e = tid + u * NT;
-                Wl[(e / BNB) * (BNB + 1) + e % BNB] = wt[u];
-            }
-            __syncthreads();
-            T x = (T)0;
-            if (tid < BNB * m) {
-                const int r = tid % BNB, c = tid / BNB;
-#pragma unroll
-                for (int q = 0; q < BNB; ++q) x += Wl[r * (BNB + 1) + q] * (ys[c * NM + k0 + q] - ts[c * BNB + q]);
-            }
-            __syncthreads();
-            if (tid < BNB * m)
-                ys[(tid / BNB) * NM + k0 + tid % BNB] = x;
-            __syncthreads();
-        }
-    }
+    };
+    sweep(std::false_type());
+    sweep(std::true_type());
     if (tid < m)
         sm.zmax[tid] = 0ull;
     __syncthreads();
     for (int idx = tid; idx < m * n; idx += NT) {
         const int c = idx / n, i = idx % n;
         const double s = pow2_ceil(sm.smax[c]);
-        const double z = ((s * mu) * gd[i]) * (double)ys[c * NM + i];
+        const double z = ((s * mu) * gd[i]) * (double)ys[c * YS + i];
         const auto px = gX + i + (int64_t)c * n;
         *px = accumulate ? *px + z : z;
         atomicMax(&sm.zmax[c], (unsigned long long)__double_as_longlong(fabs(z)));
@@ -1222,13 +1213,11 @@ SPD_DEV int b_factor_p(const BatchArgs &a, const double *A, int n, int np, const
 {
     if constexpr (sizeof(T) == 8) {
         mu = 1.0;
-        b_convert<double, WAVES>(A, n, np, w.d, 1.0, 0, (double *)w.L, w.Am, sm);
-        return b_factor<double, WAVES>((double *)w.L, np, (double *)w.Winv, HALF_NONE, sm);
+        return b_factor<double, WAVES>(A, n, np, w.d, 1.0, 0, (double *)w.L, (double *)w.Winv, w.Am, HALF_NONE, sm);
     } else {
         mu = (p == SPD_FP16) ? a.mu16 : 1.0;
-        b_convert<float, WAVES>(A, n, np, w.d, mu, a.equilibrate, (float *)w.L, w.Am, sm);
         const int half = (p == SPD_FP16) ? HALF_F16 : (p == SPD_BF16) ? HALF_BF16 : HALF_NONE;
-        return b_factor<float, WAVES>((float *)w.L, np, (float *)w.Winv, half, sm);
+        return b_factor<float, WAVES>(A, n, np, w.d, mu, a.equilibrate, (float *)w.L, (float *)w.Winv, w.Am, half, sm);
     }
 }
 
