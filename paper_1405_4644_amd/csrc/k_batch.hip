@@ -52,7 +52,6 @@ struct BatchWs {
     void *Winv;   // the inverses of its diagonal tiles, in the same layout
     double *d;    // equilibration
     double *R;    // n x m residual
-    double *Am;   // np x np: A's strict lower triangle mirrored into the strict upper (Am[i + j np] = a_ji, i < j)
 };
 
 SPD_DEV BatchWs batch_ws(const BatchArgs &a)
@@ -66,35 +65,54 @@ SPD_DEV BatchWs batch_ws(const BatchArgs &a)
     w.d = (double *)p;
     p += (int64_t)SPD_BATCH_NMAX * 8;
     w.R = (double *)p;
-    p += (int64_t)SPD_BATCH_NMAX * SPD_BATCH_MAXRHS * 8;
-    w.Am = (double *)p;
     return w;
+}
+
+// Arguments of a function that is not inlined arrive in vector registers; the
+// workgroup's own n, pointers and so on as scalars again (addresses are then a
+// scalar base plus a 32-bit lane offset)
+SPD_DEV int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+template <typename P>
+SPD_DEV P *uni(P *p)
+{
+    const unsigned long long b = (unsigned long long)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffull));
+    const unsigned hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return (P *)gmem((P *)(((unsigned long long)hi << 32) | lo));
 }
 
 SPD_DEV double b_nanmax(double a, double b) { return (a > b || a != a) ? a : b; }
 
-// shared state of the workgroup
+// pitch of a binary64 vector array in shared memory (16 of them read side by
+// side without bank conflicts)
+#define BPITCH (SPD_BATCH_NMAX + 2)
+
+// a wave's buffer in the symmetric product: a 16 x 16 quarter tile, then its
+// sums over a strip's 32 columns for 8 vectors and |A|
+#define BSYM_TB ((SPD_BATCH_MAXRHS + 1) * BNB)
+
+// shared state of the workgroup (two workgroups per compute unit: at most 80 KB)
 struct SolveSmem {
-    double ys[SPD_BATCH_MAXRHS * (SPD_BATCH_NMAX + 2)];  // solve vectors (factor type); tile buffers
-    double Lk[BNB * (BNB + 1)];                          // inverse of the diagonal block
-    double red[16][4 * SPD_BATCH_MAXRHS + 1];
+    double ys[SPD_BATCH_MAXRHS * BPITCH];  // solve vectors (factor type); x of the residual
+    double yo[SPD_BATCH_MAXRHS * BPITCH];  // A x of the residual
+    double tb[4 * BSYM_TB];                // the symmetric product's buffers; inverse of the diagonal block
+    double arow[SPD_BATCH_NMAX];           // row sums of |A|; d of the factorisation
+    double red[4][4 * SPD_BATCH_MAXRHS];
     double norms[1 + 4 * SPD_BATCH_MAXRHS];
     double smax[SPD_BATCH_MAXRHS];
     unsigned long long zmax[SPD_BATCH_MAXRHS];  // max |z| per column of the last solve (binary64 bits)
-    double arow[SPD_BATCH_NMAX];  // row sums of |A|
-    double part[4][SPD_BATCH_MAXRHS + 1][64];  // the residual's per-wave partial row sums (+ |A|)
     int info;
 };
-// the picker's features and perceptron (about 30 KB: several workgroups per CU)
+// the picker's features and perceptron (about 35 KB: several workgroups per CU)
 struct PickSmem {
-    double d[SPD_BATCH_NMAX];   // d_i = a_ii^{-1/2}
+    double d[BPITCH];   // d_i = a_ii^{-1/2}
     double v[SPD_BATCH_NMAX];   // Lanczos vectors v_j, v_{j-1}, w
     double vp[SPD_BATCH_NMAX];
-    double w[SPD_BATCH_NMAX];
+    double w[BPITCH];
+    double x[BPITCH];   // D v
     double rs[SPD_BATCH_NMAX];  // Gershgorin radii of H
-    double ycol[SPD_BATCH_NMAX];
-    double rcol[SPD_BATCH_NMAX];
-    double red[16][8];
+    double tb[4 * BSYM_TB];
+    double red[4][8];
     double ab[2][PICK_LANCZOS];  // Lanczos alpha, beta
     double th[PICK_LANCZOS];     // Ritz values
     float feat[PICK_NFEAT];
@@ -144,7 +162,7 @@ template <> struct BTile<float> {
     {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            const V x = *(const V *)(gmem(t) + (2 * g * 32 + lane) * 4);
+            const V x = *(const V *)(gmem(t) + (unsigned)((2 * g * 32 + lane) * 4));
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[4 * g + i] = x[i];
         }
@@ -153,7 +171,7 @@ template <> struct BTile<float> {
     {
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-            *(__attribute__((address_space(1))) V *)(gmem(t) + (2 * g * 32 + lane) * 4) =
+            *(__attribute__((address_space(1))) V *)(gmem(t) + (unsigned)((2 * g * 32 + lane) * 4)) =
                 V{a.v[4 * g], a.v[4 * g + 1], a.v[4 * g + 2], a.v[4 * g + 3]};
     }
     // acc += (this as rows of D) (b as columns of D)^T, this negated
@@ -173,19 +191,30 @@ template <> struct BTile<double> {
         r = (e >> 2) & 31;
         c = 16 * (g >> 2) + 4 * (e & 3) + (g & 3);
     }
-    SPD_DEV void load(const double *t, int lane)
+    // columns 16 a .. 16 a + 15
+    static SPD_DEV void load_half(double (&x)[2][4], const double *t, int a, int lane)
     {
         const int r = lane & 15, u = lane >> 4;
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; q += 2) {
+                const V p = *(const V *)(gmem(t) + (unsigned)(((4 * a + u) * 32 + 16 * b + r) * 4 + q));
+                x[b][q] = p[0];
+                x[b][q + 1] = p[1];
+            }
+    }
+    SPD_DEV void load(const double *t, int lane)
+    {
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            double x[2][4];
+            load_half(x, t, a, lane);
 #pragma unroll
             for (int b = 0; b < 2; ++b)
 #pragma unroll
-                for (int q = 0; q < 4; q += 2) {
-                    const V x = *(const V *)(gmem(t) + ((4 * a + u) * 32 + 16 * b + r) * 4 + q);
-                    v[b][a][q] = x[0];
-                    v[b][a][q + 1] = x[1];
-                }
+                for (int q = 0; q < 4; ++q) v[b][a][q] = x[b][q];
+        }
     }
     static SPD_DEV void store(double *t, const Acc32<double> &acc, int lane)
     {
@@ -196,18 +225,17 @@ template <> struct BTile<double> {
             for (int b = 0; b < 2; ++b)
 #pragma unroll
                 for (int q = 0; q < 4; q += 2)
-                    *(__attribute__((address_space(1))) V *)(gmem(t) + ((4 * a + u) * 32 + 16 * b + r) * 4 + q) =
+                    *(__attribute__((address_space(1))) V *)(gmem(t) + (unsigned)(((4 * a + u) * 32 + 16 * b + r) * 4 + q)) =
                         V{acc.v[a][b][q], acc.v[a][b][q + 1]};
     }
-    static SPD_DEV void submul(Acc32<double> &acc, const BTile &x, const BTile &y)
+    // acc += (columns 16 a .. of this as rows of D) (the half tile y as columns of D)^T, this negated
+    SPD_DEV void submul_half(Acc32<double> &acc, int a, const double (&y)[2][4]) const
     {
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const double fx[2] = {-x.v[0][a][q], -x.v[1][a][q]}, fy[2] = {y.v[0][a][q], y.v[1][a][q]};
-                acc.mma(fx, fy);
-            }
+        for (int q = 0; q < 4; ++q) {
+            const double fx[2] = {-v[0][a][q], -v[1][a][q]}, fy[2] = {y[0][q], y[1][q]};
+            acc.mma(fx, fy);
+        }
     }
 };
 template <typename T>
@@ -292,42 +320,38 @@ __device__ __attribute__((noinline)) int b_diag(T *Ws, T *Wg, T *Lr)
 // to that format (binary32 accumulation).  Returns the 1-based failing column
 // (0 on success).
 //
-// Also writes Am, A's strict lower triangle mirrored into the strict upper
-// triangle of an np x np array, so that the residual can stream whole rows of
-// A with coalesced loads while A itself is read only in its lower triangle:
-// each tile of A, in registers anyway, is transposed through the wave's
-// buffer in shared memory (element (c, r) at c * 32 + (r ^ c)).
-//
 // Bound by memory traffic, with 512 systems in flight.  Right-looking, with H
 // written out by a conversion and every trailing tile read and written once
 // per panel, 4096 systems of the batched distribution moved 40 GB in binary32
 // (9.4 ms) and 31 GB in binary64 (7.1 ms), 4.3 TB/s; TIMES_BFAC.
 template <typename T, int WAVES>
 __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np, double *d, double mu, int equil,
-                                                  T *L, T *Winv, double *Am, int half, SolveSmem &sm)
+                                                  T *L, T *Winv, int half, SolveSmem &sm)
 {
-    A = (const double *)gmem(A);  // global memory (see gmem)
-    d = (double *)gmem(d);
-    L = (T *)gmem(L);
-    Winv = (T *)gmem(Winv);
-    Am = (double *)gmem(Am);
+    const auto gA = gmem(uni(A));
+    const auto gd = gmem(uni(d));
+    L = uni(L);
+    Winv = uni(Winv);
+    n = uni(n);
+    np = uni(np);
+    half = uni(half);
+    equil = uni(equil);
     constexpr int NT = WAVES * 64, SLOTS = SPD_BATCH_NMAX / BNB / WAVES;
-    static_assert(WAVES * BNB * BNB * 8 <= (int)sizeof(sm.ys), "tile buffers");
-    static_assert(BNB * BDIAG_S * 8 <= (int)sizeof(sm.part), "diagonal block");
+    static_assert(BNB * (BNB + 1) * 8 <= (int)sizeof(sm.tb), "inverse of the diagonal block");
+    static_assert(BNB * BDIAG_S * 8 <= (int)sizeof(sm.yo), "diagonal block");
     using A32 = Acc32<T>;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nb = np / BNB;
-    T *Ws = (T *)sm.Lk;   // inverse of the diagonal block: Ws[c * 33 + r] = W[r][c]
-    T *Lr = (T *)sm.part;  // the diagonal block, row-major
+    T *Ws = (T *)sm.tb;  // inverse of the diagonal block: Ws[c * 33 + r] = W[r][c]
+    T *Lr = (T *)sm.yo;  // the diagonal block, row-major
     double *dsh = sm.arow;
     for (int i = tid; i < n; i += NT) {
-        const double a = A[i + (int64_t)i * n];
+        const double a = gA[i + (int64_t)i * n];
         const double di = (equil && a > 0.0) ? 1.0 / sqrt(a) : 1.0;
-        d[i] = di;
+        gd[i] = di;
         dsh[i] = di;
     }
     __syncthreads();
-    double *tb = sm.ys + wave * BNB * BNB;
     for (int kb = 0; kb < nb; ++kb) {
         A32 acc[SLOTS];
 #pragma unroll
@@ -335,60 +359,72 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
             const int I = kb + wave + WAVES * s;
             if (I >= nb)
                 continue;
-            // A's tile: register j of the accumulator is column row(j), row col(j)
+            // A's tile: register j of the accumulator is column row(j), row
+            // col(j); past the matrix and above the diagonal the nearest
+            // element below it, dropped
+            // (the lane number anew for each tile: what follows from it would
+            // otherwise be kept in registers across the whole loop)
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
             double a[16];
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
-                const int i = I * BNB + A32::col(j, lane), c = kb * BNB + A32::row(j, lane);
-                a[j] = (i < n && c < n && c <= i) ? A[i + (int64_t)c * n] : 0.0;
+                const int i = min(I * BNB + A32::col(j, ln), n - 1), c = min(kb * BNB + A32::row(j, ln), i);
+                a[j] = gA[(unsigned)(i + c * n)];
             }
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
-                const int r = A32::col(j, lane), c = A32::row(j, lane), i = I * BNB + r, k = kb * BNB + c;
-                T v = (i == k) ? (T)1 : (T)0;
-                if (i < n && k < n)
-                    v = (T)(((mu * dsh[i]) * a[j]) * dsh[k]);
+                const int i = I * BNB + A32::col(j, ln), k = kb * BNB + A32::row(j, ln);
+                T v = (T)(((mu * dsh[min(i, n - 1)]) * a[j]) * dsh[min(k, n - 1)]);
+                if (i >= n || k >= n)
+                    v = (i == k) ? (T)1 : (T)0;
                 acc[s].set(j, v);
-                tb[c * BNB + (r ^ c)] = a[j];
             }
-            __builtin_amdgcn_wave_barrier();
-            // Am (row kb*32 + c, column I*32 + rr) = a (I*32 + rr, kb*32 + c), c = lane % 32, strictly above the diagonal
-            double *dst = Am + (int64_t)kb * BNB + (int64_t)I * BNB * np;
-            const int cc = lane & 31, h = lane >> 5;
-#pragma unroll
-            for (int u = 0; u < BNB / 2; ++u) {
-                const int rr = 2 * u + h;
-                if (I > kb || cc < rr)
-                    dst[cc + (int64_t)rr * np] = tb[cc * BNB + (rr ^ cc)];
-            }
-            __builtin_amdgcn_wave_barrier();
         }
         // the earlier panels' products
         if (kb + wave < nb) {
             for (int q = 0; q < kb; ++q) {
-                BTile<T> fk, fi;
+                BTile<T> fk;
                 fk.load(b_tile(L, kb, q), lane);
-                fi.load(b_tile(L, kb + wave, q), lane);
                 if constexpr (sizeof(T) == 4) {
+                    BTile<T> fi;
+                    fi.load(b_tile(L, kb + wave, q), lane);
                     if (half)
 #pragma unroll
                         for (int j = 0; j < 16; ++j) fk.v[j] = round_half(fk.v[j], half);
-                }
 #pragma unroll
-                for (int s = 0; s < SLOTS; ++s) {
-                    const int I = kb + wave + WAVES * s;
-                    if (I >= nb)
-                        break;
-                    BTile<T> nx;
-                    if (s + 1 < SLOTS && I + WAVES < nb)
-                        nx.load(b_tile(L, I + WAVES, q), lane);
-                    if constexpr (sizeof(T) == 4) {
+                    for (int s = 0; s < SLOTS; ++s) {
+                        const int I = kb + wave + WAVES * s;
+                        if (I >= nb)
+                            break;
+                        BTile<T> nx;
+                        if (s + 1 < SLOTS && I + WAVES < nb)
+                            nx.load(b_tile(L, I + WAVES, q), lane);
                         if (half)
 #pragma unroll
                             for (int j = 0; j < 16; ++j) fi.v[j] = round_half(fi.v[j], half);
+                        BTile<T>::submul(acc[s], fk, fi);
+                        fi = nx;
                     }
-                    BTile<T>::submul(acc[s], fk, fi);
-                    fi = nx;
+                } else {
+                    // half a tile ahead: the accumulators take half of the registers
+                    double x0[2][4], x1[2][4];
+                    BTile<T>::load_half(x0, b_tile(L, kb + wave, q), 0, lane);
+#pragma unroll
+                    for (int s = 0; s < SLOTS; ++s) {
+                        const int I = kb + wave + WAVES * s;
+                        if (I >= nb)
+                            break;
+                        BTile<T>::load_half(x1, b_tile(L, I, q), 1, lane);
+                        __builtin_amdgcn_sched_barrier(0);
+                        fk.submul_half(acc[s], 0, x0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (s + 1 < SLOTS)
+                            BTile<T>::load_half(x0, b_tile(L, min(I + WAVES, nb - 1), q), 0, lane);
+                        __builtin_amdgcn_sched_barrier(0);
+                        fk.submul_half(acc[s], 1, x1);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
             }
         }
@@ -488,12 +524,12 @@ struct BOp {
         for (int h = 0; h < 2; ++h) {
             if constexpr (TR) {
 #pragma unroll
-                for (int s = 0; s < 8; ++s) v[h][s] = g[BTile<T>::pos(4 * s + u, 16 * h + r)];
+                for (int s = 0; s < 8; ++s) v[h][s] = g[(unsigned)BTile<T>::pos(4 * s + u, 16 * h + r)];
             } else {
                 // k(s, u), s = 4 j .. 4 j + 3, are next to each other
 #pragma unroll
                 for (int s = 0; s < 8; s += VN) {
-                    const V x = *(const __attribute__((address_space(1))) V *)(g + BTile<T>::pos(16 * h + r, BVec<T>::k(s, u)));
+                    const V x = *(const __attribute__((address_space(1))) V *)(g + (unsigned)BTile<T>::pos(16 * h + r, BVec<T>::k(s, u)));
 #pragma unroll
                     for (int i = 0; i < VN; ++i) v[h][s + i] = x[i];
                 }
@@ -510,9 +546,15 @@ __device__ __attribute__((noinline)) void b_solve(const T *L, const T *Winv, int
     using acc_t = typename BVec<T>::acc;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, u = lane >> 4;
+    L = uni(L);
+    Winv = uni(Winv);
+    n = uni(n);
+    np = uni(np);
+    m = uni(m);
+    accumulate = uni(accumulate);
     const int nb = np / BNB;
-    const auto gR = gmem(R), gd = gmem(d);
-    const auto gX = gmem(X);
+    const auto gR = gmem(uni(R)), gd = gmem(uni(d));
+    const auto gX = gmem(uni(X));
     T *ys = (T *)sm.ys;
     static_assert(SPD_BATCH_MAXRHS * YS * sizeof(T) <= sizeof(sm.ys), "solve vectors");
     for (int idx = tid; idx < m * np; idx += NT) {
@@ -608,138 +650,265 @@ __device__ __attribute__((noinline)) void b_solve(const T *L, const T *Winv, int
 }
 
 // ---------------------------------------------------------------------------
-// R = B - A X (binary64) and the norms: norms[1 + k m + c], k = 0..3:
-// max|r|, max|x|, max|b|, max|d r|; with want_anorm also norms[0] =
-// ||A||_inf.  X is staged in shared memory.  Rows in passes of 64 (lane =
-// row), the columns split among the waves in whole batches of CH: a_ij from
-// A for j <= i and from the mirror Am (written by b_convert) for j > i, so
-// each load is coalesced (reading the lower triangle alone would need a
-// second, column-wise pass whose loads touch a cache line per lane), with the
-// next batch in flight.  Each row's four wave partials are added in a fixed
-// order, so the result does not depend on timing.  Splitting the columns
-// rather than the rows keeps the waves level for every n (rows per wave
-// left one wave a second full pass whenever n was just above 256).
-template <int WAVES>
-__device__ __attribute__((noinline)) void b_residual(const double *A, const double *Am, int n, int np, int m,
-                                                     const double *X, const double *B, const double *d, double *R,
-                                                     int want_anorm, SolveSmem &sm)
+// y = A x (binary64) for m <= 8 vectors in shared memory (pitch BPITCH) and the
+// symmetric A given by its lower triangle, in one pass over that triangle on
+// v_mfma_f64_16x16x4f64 (the vectors as the 16 rows of the result).  32-column
+// strips J, wave w takes the 32 x 32 blocks I = J + w, J + w + 4, ...: a lane
+// (j = l % 16, u = l / 16) holds columns 16 h + j, rows 8 s + 2 u + e, loaded
+// 16 bytes at a time with the next block in flight.  As they are, these are
+// the operands of the columns' sums (sum_i a_ij x_i, kept in the accumulators
+// over the strip); transposed by 16 x 16 quarters through the wave's buffer
+// they are those of the rows' (added to y in shared memory: a row block has
+// one wave at a time).  After the strip the waves' column sums are added in
+// order, so nothing depends on timing.  A diagonal block is read as a full
+// symmetric one and serves its rows only.
+// With WA also ya_i = sum_j |a_ij| xa_j (xa NULL: ones; excl: j = i left out),
+// with HS the largest |h_ij| off the diagonal and the sum of h_ij^2 of
+// H = D A D, per thread.
+//
+// Bound by reading the triangle with 512 (the picker: 768) systems in flight.
+// The residual used to read whole rows, the upper half from a mirror that the
+// factorisation wrote (557 us for a binary32 system's 3.5 passes); the
+// picker's products read the triangle once by rows and once by columns, a
+// cache line per lane (3.7 ms for 4096 systems); TIMES_BSYM.
+SPD_DEV int bsym_pos(int r, int c)  // element (r, c) of a quarter tile: written and read without bank conflicts
 {
-    constexpr int NT = WAVES * 64, NM = SPD_BATCH_NMAX;
-    static_assert(WAVES == 4, "partial sums are laid out for four waves");
-    const auto gA = gmem(A), gAm = gmem(Am), gX = gmem(X), gB = gmem(B);
-    const auto gR = gmem(R);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    constexpr int MR = SPD_BATCH_MAXRHS;
-    double *xs = sm.ys;  // xs[c * NMAX + j]
-    double *abs_rows = sm.arow;
-    for (int idx = tid; idx < m * n; idx += NT) {
-        const int c = idx / n, j = idx % n;
-        xs[c * NM + j] = gX[j + (int64_t)c * n];
-    }
-    __syncthreads();
-    constexpr int CH = 16;
-    const int nch = (n + CH - 1) / CH, cpw = (nch + WAVES - 1) / WAVES;
-    const int jlo = wave * cpw * CH, jhi = min(n, (wave + 1) * cpw * CH);
-    for (int i0 = 0; i0 < n; i0 += 64) {
-        const int i = i0 + lane;
-        double acc[MR], aa = 0.0;
+    const int rr = (r & ~3) | ((r & 1) << 1) | ((r >> 1) & 1);
+    return rr * 16 + (c ^ (((r & 1) << 2) | ((r & 4) << 1)));
+}
+template <int WAVES, bool WA, bool HS>
+SPD_DEV void b_sym(const double *A, int n, int m, const double *x, double *y, double *tbs, const double *xa,
+                   double *ya, bool excl, const double *d, double &hmax, double &fro)
+{
+    typedef double double2u __attribute__((ext_vector_type(2), aligned(8)));  // 16-byte load, 8-byte aligned
+    constexpr int NT = WAVES * 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int j16 = lane & 15, u = lane >> 4;
+    const int nb = (n + BNB - 1) / BNB;
+    const auto gA = gmem(A);
+    double *tb = tbs + wave * BSYM_TB;
+    const double *xc = x + (j16 < m ? j16 : 0) * BPITCH;  // lanes past the last vector repeat the first, dropped
+    for (int idx = tid; idx < m * BPITCH; idx += NT) y[idx] = 0.0;
+    if constexpr (WA)
+        for (int i = tid; i < n; i += NT) ya[i] = 0.0;
+    // a[h][t]: row 32 I + 8 (t / 2) + 2 u + t % 2, column 32 J + 16 h + j16
+    auto load = [&](double (&a)[2][8], int I, int J) {
+        if (I > J && I * BNB + BNB <= n) {
+            const unsigned o = (unsigned)(I * BNB + 2 * u + (J * BNB + j16) * n);
 #pragma unroll
-        for (int c = 0; c < MR; ++c) acc[c] = 0.0;
-        double a[CH], an[CH];
-        auto load = [&](double *dst, int j0) {
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int u = 0; u < CH; ++u) {
-                const int j = j0 + u;
-                dst[u] = (i < n && j < jhi) ? ((j <= i) ? gA[i + (int64_t)j * n] : gAm[i + (int64_t)j * np]) : 0.0;
-            }
-        };
-        if (jlo < jhi)
-            load(a, jlo);
-        for (int j0 = jlo; j0 < jhi; j0 += CH) {
-            if (j0 + CH < jhi)
-                load(an, j0 + CH);
+                for (int t = 0; t < 8; t += 2) {
+                    const double2u v = *(const __attribute__((address_space(1))) double2u *)(gA + (o + (unsigned)(16 * h * n + 4 * t)));
+                    a[h][t] = v.x;
+                    a[h][t + 1] = v.y;
+                }
+        } else {
 #pragma unroll
-            for (int u = 0; u < CH; ++u) {
-                const int j = min(j0 + u, n - 1);
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int c = 0; c < MR; ++c)
-                    if (c < m)
-                        acc[c] = fma(a[u], xs[c * NM + j], acc[c]);
-                if (want_anorm)
-                    aa += fabs(a[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < CH; ++u) a[u] = an[u];
-        }
-#pragma unroll
-        for (int c = 0; c < MR; ++c)
-            if (c < m)
-                sm.part[wave][c][lane] = acc[c];
-        sm.part[wave][MR][lane] = aa;
-        __syncthreads();
-        for (int idx = tid; idx < (m + 1) * 64; idx += NT) {
-            const int c = idx / 64, l = idx % 64, r = i0 + l;
-            const int slot = (c < m) ? c : MR;
-            if (r < n && (c < m || want_anorm)) {
-                const double s = ((sm.part[0][slot][l] + sm.part[1][slot][l]) + sm.part[2][slot][l]) + sm.part[3][slot][l];
-                if (c < m)
-                    gR[r + (int64_t)c * n] = gB[r + (int64_t)c * n] - s;
-                else
-                    abs_rows[r] = s;
-            }
-        }
-        __syncthreads();
-    }
-    // maxima (NaN propagates), per column, one kind at a time (kind 0..3:
-    // |r|, |x|, |b|, |d r|), then ||A||_inf
-#pragma unroll 1
-    for (int kind = 0; kind < 4; ++kind) {
-        double v[MR];
-#pragma unroll
-        for (int c = 0; c < MR; ++c) v[c] = 0.0;
-        for (int i = tid; i < n; i += NT) {
-#pragma unroll
-            for (int c = 0; c < MR; ++c)
-                if (c < m) {
-                    const double x = (kind == 0) ? gR[i + (int64_t)c * n]
-                                     : (kind == 1) ? xs[c * NM + i]
-                                     : (kind == 2) ? gB[i + (int64_t)c * n]
-                                                   : gmem(d)[i] * gR[i + (int64_t)c * n];
-                    v[c] = b_nanmax(v[c], fabs(x));
+                for (int t = 0; t < 8; ++t) {
+                    const int i = I * BNB + 8 * (t >> 1) + 2 * u + (t & 1), j = J * BNB + 16 * h + j16;
+                    const int lo = min(max(i, j), n - 1), hi = min(min(i, j), n - 1);
+                    const double v = gA[(unsigned)(lo + hi * n)];
+                    a[h][t] = (i < n && j < n) ? v : 0.0;
                 }
         }
+    };
+    double a[2][8], an[2][8];
+    if (wave < nb)
+        load(a, wave, 0);
+    __syncthreads();
+    for (int J = 0; J < nb; ++J) {
+        doublex4 accc[2] = {doublex4{0.0, 0.0, 0.0, 0.0}, doublex4{0.0, 0.0, 0.0, 0.0}};
+        double cs[2] = {0.0, 0.0};
+        double xj[2][4], xaj[2][4];
 #pragma unroll
-        for (int c = 0; c < MR; ++c) {
-            if (c >= m)
-                break;
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v[c] = b_nanmax(v[c], __shfl_xor(v[c], off));
-            if (lane == 0)
-                sm.red[wave][c] = v[c];
+            for (int s = 0; s < 4; ++s) {
+                const int j = J * BNB + 16 * h + 4 * s + u;
+                xj[h][s] = xc[j];
+                if constexpr (WA)
+                    xaj[h][s] = xa ? xa[j] : 1.0;
+            }
+        for (int I = J + wave; I < nb; I += WAVES) {
+            // the wave's next block: in this strip, or its first of the next
+            const bool same = I + WAVES < nb;
+            const int In = same ? I + WAVES : J + 1 + wave, Jn = same ? J : J + 1;
+            if (In < nb)
+                load(an, In, Jn);
+            __builtin_amdgcn_sched_barrier(0);
+            double xi[8];
+#pragma unroll
+            for (int t = 0; t < 8; t += 2) {
+                const double2 v = *(const double2 *)(xc + I * BNB + 4 * t + 2 * u);
+                xi[t] = v.x;
+                xi[t + 1] = v.y;
+            }
+            doublex4 accr[2] = {doublex4{0.0, 0.0, 0.0, 0.0}, doublex4{0.0, 0.0, 0.0, 0.0}};
+            double rs[2] = {0.0, 0.0};
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) tb[bsym_pos(8 * (t >> 1) + 2 * u + (t & 1), j16)] = a[h][4 * b + t];
+                    __builtin_amdgcn_wave_barrier();
+                    double at[4];
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) at[s] = tb[bsym_pos(j16, 4 * s + u)];
+                    if (I > J)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            accc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(xi[4 * b + t], a[h][4 * b + t], accc[h], 0, 0, 0);
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+                        accr[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xj[h][s], at[s], accr[b], 0, 0, 0);
+                    if constexpr (WA) {
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) {
+                            const bool drop = excl && I == J && b == h && j16 == 4 * s + u;
+                            rs[b] += drop ? 0.0 : fabs(at[s]) * xaj[h][s];
+                        }
+                        if (I > J)
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) {
+                                const int i = I * BNB + 16 * b + 8 * (t >> 1) + 2 * u + (t & 1);
+                                cs[h] += fabs(a[h][4 * b + t]) * (xa ? xa[i] : 1.0);
+                            }
+                    }
+                    if constexpr (HS) {
+                        const double dj = d[J * BNB + 16 * h + j16];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const int il = 16 * b + 8 * (t >> 1) + 2 * u + (t & 1);
+                            const double hv = (d[I * BNB + il] * a[h][4 * b + t]) * dj;
+                            const bool dg = I == J && il == 16 * h + j16;
+                            hmax = dg ? hmax : fmax(hmax, fabs(hv));
+                            fro += (I == J ? 1.0 : 2.0) * hv * hv;
+                        }
+                    }
+                }
+            // accumulator register q: vector 4 q + u, row 16 b + j16
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (4 * q + u < m)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) y[(4 * q + u) * BPITCH + I * BNB + 16 * b + j16] += accr[b][q];
+            if constexpr (WA)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    double v = rs[b];
+                    v += __shfl_xor(v, 16);
+                    v += __shfl_xor(v, 32);
+                    if (u == 0 && I * BNB + 16 * b + j16 < n)
+                        ya[I * BNB + 16 * b + j16] += v;
+                }
+            if (In < nb)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) a[h][t] = an[h][t];
+        }
+        // the strip's column sums: the waves' in order
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (4 * q + u < m)
+                    tb[(4 * q + u) * BNB + 16 * h + j16] = accc[h][q];
+            if constexpr (WA) {
+                double v = cs[h];
+                v += __shfl_xor(v, 16);
+                v += __shfl_xor(v, 32);
+                if (u == 0)
+                    tb[m * BNB + 16 * h + j16] = v;
+            }
         }
         __syncthreads();
-        if (tid < m) {
-            double x = 0.0;
-            for (int w = 0; w < WAVES; ++w) x = b_nanmax(x, sm.red[w][tid]);
-            sm.norms[1 + kind * m + tid] = x;
+        for (int idx = tid; idx < (WA ? m + 1 : m) * BNB; idx += NT) {
+            const int c = idx / BNB, j = J * BNB + idx % BNB;
+            static_assert(WAVES == 4, "partial sums are laid out for four waves");
+            const double v = ((tbs[idx] + tbs[BSYM_TB + idx]) + tbs[2 * BSYM_TB + idx]) + tbs[3 * BSYM_TB + idx];
+            if (!WA || c < m)
+                y[c * BPITCH + j] += v;
+            else if (j < n)
+                ya[j] += v;
         }
         __syncthreads();
     }
-    if (want_anorm) {
+}
+
+// R = B - A X (binary64) and the norms: norms[1 + k m + c], k = 0..3:
+// max|r|, max|x|, max|b|, max|d r|; with want_anorm also norms[0] =
+// ||A||_inf.
+template <int WAVES>
+__device__ __attribute__((noinline)) void b_residual(const double *A, int n, int m, const double *X, const double *B,
+                                                     const double *d, double *R, int want_anorm, SolveSmem &sm)
+{
+    constexpr int NT = WAVES * 64;
+    n = uni(n);
+    m = uni(m);
+    want_anorm = uni(want_anorm);
+    A = uni(A);
+    const auto gX = gmem(uni(X)), gB = gmem(uni(B)), gd = gmem(uni(d));
+    const auto gR = gmem(uni(R));
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double *xs = sm.ys;
+    const int np = (n + BNB - 1) / BNB * BNB;
+    for (int idx = tid; idx < m * np; idx += NT) {
+        const int c = idx / np, j = idx % np;
+        xs[c * BPITCH + j] = (j < n) ? gX[j + (int64_t)c * n] : 0.0;
+    }
+    double h0 = 0.0, h1 = 0.0;
+    if (want_anorm)
+        b_sym<WAVES, true, false>(A, n, m, xs, sm.yo, sm.tb, nullptr, sm.arow, false, nullptr, h0, h1);
+    else
+        b_sym<WAVES, false, false>(A, n, m, xs, sm.yo, sm.tb, nullptr, nullptr, false, nullptr, h0, h1);
+    // r and the maxima (NaN propagates), per column
+    for (int c = 0; c < m; ++c) {
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int i = tid; i < n; i += NT) {
+            const double b = gB[i + (int64_t)c * n], r = b - sm.yo[c * BPITCH + i];
+            gR[i + (int64_t)c * n] = r;
+            v[0] = b_nanmax(v[0], fabs(r));
+            v[1] = b_nanmax(v[1], fabs(xs[c * BPITCH + i]));
+            v[2] = b_nanmax(v[2], fabs(b));
+            v[3] = b_nanmax(v[3], fabs(gd[i] * r));
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) v[k] = b_nanmax(v[k], __shfl_xor(v[k], off));
+            if (lane == 0)
+                sm.red[wave][k * m + c] = v[k];
+        }
+    }
+    __syncthreads();
+    if (tid < 4 * m) {
         double x = 0.0;
-        for (int i = tid; i < n; i += NT) x = b_nanmax(x, abs_rows[i]);
+        for (int w = 0; w < WAVES; ++w) x = b_nanmax(x, sm.red[w][tid]);
+        sm.norms[1 + tid] = x;
+    }
+    if (want_anorm) {
+        __syncthreads();
+        double x = 0.0;
+        for (int i = tid; i < n; i += NT) x = b_nanmax(x, sm.arow[i]);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) x = b_nanmax(x, __shfl_xor(x, off));
         if (lane == 0)
             sm.red[wave][0] = x;
         __syncthreads();
         if (tid == 0) {
-            double y = 0.0;
-            for (int w = 0; w < WAVES; ++w) y = b_nanmax(y, sm.red[w][0]);
-            sm.norms[0] = y;
+            double z = 0.0;
+            for (int w = 0; w < WAVES; ++w) z = b_nanmax(z, sm.red[w][0]);
+            sm.norms[0] = z;
         }
-        __syncthreads();
     }
+    __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
@@ -788,94 +957,23 @@ SPD_DEV void b_reduce(double v[NV], const int op[NV], PickSmem &sm)
 
 // y = H v (v, y in shared memory), H = D A D from the lower triangle of A.
 // With first: rs[i] = r_i, and per thread the partial max off-diagonal |h|
-// and sum of h^2 (each stored element once, off-diagonal ones counted twice).
+// and sum of h^2.
 template <int WAVES>
 SPD_DEV void b_hv(const double *A, int n, const double *v, double *y, bool first, double &hmax, double &fro,
                   PickSmem &sm)
 {
-    constexpr int NT = WAVES * 64, CH = 8;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const double *d = sm.d;
-    // rows: sum_{j <= i} h_ij v_j; 8 columns per batch of loads, the next
-    // batch in flight while the current one is used
-    for (int i0 = wave * 64; i0 < n; i0 += NT) {
-        const int i = i0 + lane;
-        const int jmax = min(i0 + 63, n - 1);
-        const double di = (i < n) ? d[i] : 0.0;
-        double acc = 0.0, ra = 0.0;
-        double a[CH], an[CH];
-        auto load = [&](double *dst, int j0) {
-#pragma unroll
-            for (int u = 0; u < CH; ++u) {
-                const int j = j0 + u;
-                dst[u] = (i < n && j <= i) ? A[i + (int64_t)j * n] : 0.0;
-            }
-        };
-        load(a, 0);
-        for (int j0 = 0; j0 <= jmax; j0 += CH) {
-            if (j0 + CH <= jmax)
-                load(an, j0 + CH);
-#pragma unroll
-            for (int u = 0; u < CH; ++u) {
-                const int j = min(j0 + u, n - 1);
-                const double h = (di * a[u]) * d[j];
-                acc = fma(h, v[j], acc);
-                if (first && i < n && j0 + u < i) {
-                    ra += fabs(h);
-                    hmax = fmax(hmax, fabs(h));
-                    fro += 2.0 * h * h;
-                } else if (first && i < n && j0 + u == i) {
-                    fro += h * h;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < CH; ++u) a[u] = an[u];
-        }
-        if (i < n) {
-            y[i] = acc;
-            if (first)
-                sm.rs[i] = ra;
-        }
-    }
-    // columns: lane = column, sum_{i > j} h_ij v_i, the same double buffering
-    for (int j0 = wave * 64; j0 < n; j0 += NT) {
-        const int j = j0 + lane;
-        const double dj = (j < n) ? d[j] : 0.0;
-        double acc = 0.0, ca = 0.0;
-        double a[CH], an[CH];
-        auto load = [&](double *dst, int i0) {
-#pragma unroll
-            for (int u = 0; u < CH; ++u) {
-                const int i = i0 + u;
-                dst[u] = (j < n && i > j && i < n) ? A[i + (int64_t)j * n] : 0.0;
-            }
-        };
-        load(a, j0 + 1);
-        for (int i0 = j0 + 1; i0 < n; i0 += CH) {
-            if (i0 + CH < n)
-                load(an, i0 + CH);
-#pragma unroll
-            for (int u = 0; u < CH; ++u) {
-                const int i = min(i0 + u, n - 1);
-                const double h = (d[i] * a[u]) * dj;
-                acc = fma(h, v[i], acc);
-                if (first)
-                    ca += fabs(h);
-            }
-#pragma unroll
-            for (int u = 0; u < CH; ++u) a[u] = an[u];
-        }
-        if (j < n) {
-            sm.ycol[j] = acc;
-            if (first)
-                sm.rcol[j] = ca;
-        }
-    }
-    __syncthreads();
+    constexpr int NT = WAVES * 64;
+    const int tid = threadIdx.x;
+    const int np = (n + BNB - 1) / BNB * BNB;
+    for (int i = tid; i < np; i += NT) sm.x[i] = (i < n) ? sm.d[i] * v[i] : 0.0;
+    if (first)
+        b_sym<WAVES, true, true>(A, n, 1, sm.x, y, sm.tb, sm.d, sm.rs, true, sm.d, hmax, fro);
+    else
+        b_sym<WAVES, false, false>(A, n, 1, sm.x, y, sm.tb, nullptr, nullptr, false, nullptr, hmax, fro);
     for (int i = tid; i < n; i += NT) {
-        y[i] += sm.ycol[i];
+        y[i] *= sm.d[i];
         if (first)
-            sm.rs[i] += sm.rcol[i];
+            sm.rs[i] *= sm.d[i];
     }
     __syncthreads();
 }
@@ -944,6 +1042,7 @@ SPD_DEV void b_features(const double *A, int n, int m, PickSmem &sm)
         v[i] = 1.0 / sqrt((double)n);
         vp[i] = 0.0;
     }
+    for (int i = n + tid; i < (n + BNB - 1) / BNB * BNB; i += NT) d[i] = 0.0;
     b_reduce<WAVES, 3>(st, ops3, sm);
     const double mean_la = st[0] / n;
     double sq[1] = {0.0};
@@ -1107,7 +1206,7 @@ SPD_DEV int b_refine(const BatchArgs &a, const double *A, const double *B, doubl
     for (;;) {
         const int first = (rep.iters_high == 0);
         const int k = rep.iters_high;  // corrections applied so far
-        b_residual<WAVES>(A, w.Am, n, np, m, X, B, w.d, w.R, first, sm);
+        b_residual<WAVES>(A, n, m, X, B, w.d, w.R, first, sm);
         rep.iters_high++;
         if (first)
             anorm = sm.norms[0];
@@ -1213,11 +1312,11 @@ SPD_DEV int b_factor_p(const BatchArgs &a, const double *A, int n, int np, const
 {
     if constexpr (sizeof(T) == 8) {
         mu = 1.0;
-        return b_factor<double, WAVES>(A, n, np, w.d, 1.0, 0, (double *)w.L, (double *)w.Winv, w.Am, HALF_NONE, sm);
+        return b_factor<double, WAVES>(A, n, np, w.d, 1.0, 0, (double *)w.L, (double *)w.Winv, HALF_NONE, sm);
     } else {
         mu = (p == SPD_FP16) ? a.mu16 : 1.0;
         const int half = (p == SPD_FP16) ? HALF_F16 : (p == SPD_BF16) ? HALF_BF16 : HALF_NONE;
-        return b_factor<float, WAVES>(A, n, np, w.d, mu, a.equilibrate, (float *)w.L, (float *)w.Winv, w.Am, half, sm);
+        return b_factor<float, WAVES>(A, n, np, w.d, mu, a.equilibrate, (float *)w.L, (float *)w.Winv, half, sm);
     }
 }
 
@@ -1309,7 +1408,7 @@ SPD_DEV void b_system(const BatchArgs &a, int64_t s, SolveSmem &sm)
 
 // The precision picker for SPD_AUTO systems: features and perceptron by one
 // workgroup per system; prec[s] becomes the chosen class.
-__global__ __launch_bounds__(256, 3) void k_batch_pick(BatchArgs a)
+__global__ __launch_bounds__(256, 2) void k_batch_pick(BatchArgs a)
 {
     __shared__ PickSmem sm;
     __shared__ int s_q;
@@ -1354,7 +1453,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_batch(BatchArgs a)
 }
 
 // Features of every system (one workgroup each), for training the picker.
-__global__ __launch_bounds__(256) void k_features(int64_t batch, const int32_t *__restrict__ n,
+__global__ __launch_bounds__(256, 2) void k_features(int64_t batch, const int32_t *__restrict__ n,
                                                   const int32_t *__restrict__ nrhs, const int64_t *__restrict__ a_off,
                                                   const double *__restrict__ A, float *__restrict__ feat)
 {
@@ -1412,8 +1511,7 @@ namespace spd {
 int64_t batch_ws_stride()
 {
     int64_t b = (int64_t)SPD_BATCH_NMAX * SPD_BATCH_NMAX * 8 + (int64_t)SPD_BATCH_NMAX * BNB * 8 +
-                (int64_t)SPD_BATCH_NMAX * 8 + (int64_t)SPD_BATCH_NMAX * SPD_BATCH_MAXRHS * 8 +
-                (int64_t)SPD_BATCH_NMAX * SPD_BATCH_NMAX * 8;
+                (int64_t)SPD_BATCH_NMAX * 8 + (int64_t)SPD_BATCH_NMAX * SPD_BATCH_MAXRHS * 8;
     return (b + 255) / 256 * 256;
 }
 
