@@ -228,12 +228,12 @@ template <> struct BTile<double> {
                     *(__attribute__((address_space(1))) V *)(gmem(t) + (unsigned)(((4 * a + u) * 32 + 16 * b + r) * 4 + q)) =
                         V{acc.v[a][b][q], acc.v[a][b][q + 1]};
     }
-    // acc += (columns 16 a .. of this as rows of D) (the half tile y as columns of D)^T, this negated
-    SPD_DEV void submul_half(Acc32<double> &acc, int a, const double (&y)[2][4]) const
+    // acc += (the half tile x as rows of D) (the half tile y as columns of D)^T, x negated
+    static SPD_DEV void submul_half(Acc32<double> &acc, const double (&x)[2][4], const double (&y)[2][4])
     {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const double fx[2] = {-v[0][a][q], -v[1][a][q]}, fy[2] = {y[0][q], y[1][q]};
+            const double fx[2] = {-x[0][q], -x[1][q]}, fy[2] = {y[0][q], y[1][q]};
             acc.mma(fx, fy);
         }
     }
@@ -312,7 +312,7 @@ __device__ __attribute__((noinline)) int b_diag(T *Ws, T *Wg, T *Lr)
 
 // ---------------------------------------------------------------------------
 // Left-looking blocked Cholesky of H = round(mu D A D) (identity padding up
-// to np = 32 nb): panel kb's tiles (I, kb), I = kb + wave + 4 s, are formed
+// to np = 32 nb): panel kb's tiles (I, kb) are formed
 // from A in the waves' accumulators (d_i = a_ii^{-1/2} also goes to d), take
 // the products of the earlier panels, the diagonal one is factored by wave 0,
 // and the others become L_Ik = H_Ik W^T, W the diagonal tile's inverse, and
@@ -336,7 +336,7 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
     np = uni(np);
     half = uni(half);
     equil = uni(equil);
-    constexpr int NT = WAVES * 64, SLOTS = SPD_BATCH_NMAX / BNB / WAVES;
+    constexpr int NT = WAVES * 64;
     static_assert(BNB * (BNB + 1) * 8 <= (int)sizeof(sm.tb), "inverse of the diagonal block");
     static_assert(BNB * BDIAG_S * 8 <= (int)sizeof(sm.yo), "diagonal block");
     using A32 = Acc32<T>;
@@ -352,94 +352,162 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
         dsh[i] = di;
     }
     __syncthreads();
-    for (int kb = 0; kb < nb; ++kb) {
-        A32 acc[SLOTS];
+    // H's tile (I, kb) in the accumulator's layout (register j: column
+    // row(j), row col(j)): A's values, past the matrix and above the diagonal
+    // the nearest element below it, dropped
+    auto init = [&](A32 &acc, int I, int kb) {
+        // (the lane number anew for each tile: what follows from it would
+        // otherwise be kept in registers across the whole loop)
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        double a[16];
 #pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-            const int I = kb + wave + WAVES * s;
-            if (I >= nb)
-                continue;
-            // A's tile: register j of the accumulator is column row(j), row
-            // col(j); past the matrix and above the diagonal the nearest
-            // element below it, dropped
-            // (the lane number anew for each tile: what follows from it would
-            // otherwise be kept in registers across the whole loop)
-            int ln = lane;
-            asm volatile("" : "+v"(ln));
-            double a[16];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int i = min(I * BNB + A32::col(j, ln), n - 1), c = min(kb * BNB + A32::row(j, ln), i);
-                a[j] = gA[(unsigned)(i + c * n)];
-            }
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int i = I * BNB + A32::col(j, ln), k = kb * BNB + A32::row(j, ln);
-                T v = (T)(((mu * dsh[min(i, n - 1)]) * a[j]) * dsh[min(k, n - 1)]);
-                if (i >= n || k >= n)
-                    v = (i == k) ? (T)1 : (T)0;
-                acc[s].set(j, v);
-            }
+        for (int j = 0; j < 16; ++j) {
+            const int i = min(I * BNB + A32::col(j, ln), n - 1), c = min(kb * BNB + A32::row(j, ln), i);
+            a[j] = gA[(unsigned)(i + c * n)];
         }
-        // the earlier panels' products
-        if (kb + wave < nb) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int i = I * BNB + A32::col(j, ln), k = kb * BNB + A32::row(j, ln);
+            T v = (T)(((mu * dsh[min(i, n - 1)]) * a[j]) * dsh[min(k, n - 1)]);
+            if (i >= n || k >= n)
+                v = (i == k) ? (T)1 : (T)0;
+            acc.set(j, v);
+        }
+    };
+    // acc[s] -= L_Iq L_kb,q^T for q < kb and I = I0 + step s < nb, s < NS; the
+    // next tile (binary64: half a tile, the accumulators take half of the
+    // registers) is in flight
+    auto products = [&](auto ns, A32 *acc, int I0, int step, int kb) {
+        constexpr int NS = decltype(ns)::value;
+        if (kb == 0)
+            return;
+        if constexpr (sizeof(T) == 4) {
+            auto rounded = [&](BTile<T> &f) {
+                if (half)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) f.v[j] = round_half(f.v[j], half);
+            };
+            BTile<T> fk, fi, fkn, nx;
+            fk.load(b_tile(L, kb, 0), lane);
+            fi.load(b_tile(L, I0, 0), lane);
             for (int q = 0; q < kb; ++q) {
-                BTile<T> fk;
-                fk.load(b_tile(L, kb, q), lane);
-                if constexpr (sizeof(T) == 4) {
-                    BTile<T> fi;
-                    fi.load(b_tile(L, kb + wave, q), lane);
-                    if (half)
+                const int qn = min(q + 1, kb - 1);
+                rounded(fk);
+                fkn.load(b_tile(L, kb, qn), lane);
 #pragma unroll
-                        for (int j = 0; j < 16; ++j) fk.v[j] = round_half(fk.v[j], half);
+                for (int s = 0; s < NS; ++s) {
+                    const int I = I0 + step * s;
+                    if (I >= nb)
+                        break;
+                    const bool last = s + 1 == NS || I + step >= nb;
+                    nx.load(last ? b_tile(L, I0, qn) : b_tile(L, I + step, q), lane);
+                    rounded(fi);
+                    BTile<T>::submul(acc[s], fk, fi);
+                    fi = nx;
+                }
+                fk = fkn;
+            }
+        } else {
+            double k0[2][4], k1[2][4], x0[2][4], x1[2][4];
+            BTile<T>::load_half(k0, b_tile(L, kb, 0), 0, lane);
+            BTile<T>::load_half(x0, b_tile(L, I0, 0), 0, lane);
+            BTile<T>::load_half(k1, b_tile(L, kb, 0), 1, lane);
+            for (int q = 0; q < kb; ++q) {
+                const int qn = min(q + 1, kb - 1);
 #pragma unroll
-                    for (int s = 0; s < SLOTS; ++s) {
-                        const int I = kb + wave + WAVES * s;
-                        if (I >= nb)
-                            break;
-                        BTile<T> nx;
-                        if (s + 1 < SLOTS && I + WAVES < nb)
-                            nx.load(b_tile(L, I + WAVES, q), lane);
-                        if (half)
-#pragma unroll
-                            for (int j = 0; j < 16; ++j) fi.v[j] = round_half(fi.v[j], half);
-                        BTile<T>::submul(acc[s], fk, fi);
-                        fi = nx;
-                    }
-                } else {
-                    // half a tile ahead: the accumulators take half of the registers
-                    double x0[2][4], x1[2][4];
-                    BTile<T>::load_half(x0, b_tile(L, kb + wave, q), 0, lane);
-#pragma unroll
-                    for (int s = 0; s < SLOTS; ++s) {
-                        const int I = kb + wave + WAVES * s;
-                        if (I >= nb)
-                            break;
-                        BTile<T>::load_half(x1, b_tile(L, I, q), 1, lane);
-                        __builtin_amdgcn_sched_barrier(0);
-                        fk.submul_half(acc[s], 0, x0);
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (s + 1 < SLOTS)
-                            BTile<T>::load_half(x0, b_tile(L, min(I + WAVES, nb - 1), q), 0, lane);
-                        __builtin_amdgcn_sched_barrier(0);
-                        fk.submul_half(acc[s], 1, x1);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
+                for (int s = 0; s < NS; ++s) {
+                    const int I = I0 + step * s;
+                    if (I >= nb)
+                        break;
+                    const bool last = s + 1 == NS || I + step >= nb;
+                    BTile<T>::load_half(x1, b_tile(L, I, q), 1, lane);
+                    __builtin_amdgcn_sched_barrier(0);
+                    BTile<T>::submul_half(acc[s], k0, x0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (last)
+                        BTile<T>::load_half(k0, b_tile(L, kb, qn), 0, lane);
+                    BTile<T>::load_half(x0, last ? b_tile(L, I0, qn) : b_tile(L, I + step, q), 0, lane);
+                    __builtin_amdgcn_sched_barrier(0);
+                    BTile<T>::submul_half(acc[s], k1, x1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (last)
+                        BTile<T>::load_half(k1, b_tile(L, kb, qn), 1, lane);
                 }
             }
         }
+    };
+    // the same for the diagonal tile, both operands the same tile
+    auto products_diag = [&](A32 &acc, int kb) {
+        if (kb == 0)
+            return;
+        BTile<T> f, nx;
+        f.load(b_tile(L, kb, 0), lane);
+        for (int q = 0; q < kb; ++q) {
+            nx.load(b_tile(L, kb, min(q + 1, kb - 1)), lane);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (sizeof(T) == 4) {
+                if (half)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) f.v[j] = round_half(f.v[j], half);
+                BTile<T>::submul(acc, f, f);
+            } else {
+#pragma unroll
+                for (int a = 0; a < 2; ++a) {
+                    double x[2][4];
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+#pragma unroll
+                        for (int p = 0; p < 4; ++p) x[b][p] = f.v[b][a][p];
+                    BTile<T>::submul_half(acc, x, x);
+                }
+            }
+            f = nx;
+        }
+    };
+    // L_Ik = H_Ik W^T: D[c][r] = sum_q W[c][q] H[r][q], H the accumulator itself
+    auto solve = [&](const BTile<T> &w, const A32 &h, int I, int kb) {
+        A32 y;
+        y.zero();
+        if constexpr (sizeof(T) == 4) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) y.mma(w.v[j], h.v[j]);
+        } else {
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const double fw[2] = {w.v[0][a][q], w.v[1][a][q]}, fh[2] = {h.v[a][0][q], h.v[a][1][q]};
+                    y.mma(fw, fh);
+                }
+        }
+        BTile<T>::store(b_tile(L, I, kb), y, lane);
+    };
+    constexpr int OW = WAVES - 1, SLOTS = 4;
+    for (int kb = 0; kb < nb; ++kb) {
+        // wave 0 has the diagonal tile alone, whose factor takes as long as
+        // the other waves' tiles I = kb + wave + OW s
+        const int I0 = kb + wave;
+        A32 acc[SLOTS];
         if (wave == 0) {
+            init(acc[0], kb, kb);
+            products_diag(acc[0], kb);
 #pragma unroll
             for (int j = 0; j < 16; ++j) Lr[A32::col(j, lane) * BDIAG_S + A32::row(j, lane)] = acc[0].get(j);
             __builtin_amdgcn_wave_barrier();
             const int bad = b_diag<T>(Ws, Winv + (int64_t)kb * BNB * BNB, Lr);
             if (lane == 0)
                 sm.info = bad ? kb * BNB + bad : 0;
+        } else if (I0 < nb) {
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s)
+                if (I0 + OW * s < nb)
+                    init(acc[s], I0 + OW * s, kb);
+            products(std::integral_constant<int, SLOTS>(), acc, I0, OW, kb);
         }
         __syncthreads();
         if (sm.info)
             return sm.info;
-        // L_Ik = H_Ik W^T: D[c][r] = sum_q W[c][q] H[r][q], H the accumulator itself
         BTile<T> w;
         if constexpr (sizeof(T) == 4) {
 #pragma unroll
@@ -453,27 +521,17 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
                     for (int q = 0; q < 4; ++q)
                         w.v[b][a][q] = Ws[(16 * a + 4 * q + (lane >> 4)) * (BNB + 1) + 16 * b + (lane & 15)];
         }
+        if (wave > 0)
 #pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-            const int I = kb + wave + WAVES * s;
-            if (I >= nb || I == kb)
-                continue;
-            A32 y;
-            y.zero();
-            if constexpr (sizeof(T) == 4) {
-#pragma unroll
-                for (int j = 0; j < 16; ++j) y.mma(w.v[j], acc[s].v[j]);
-            } else {
-#pragma unroll
-                for (int a = 0; a < 2; ++a)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const double fw[2] = {w.v[0][a][q], w.v[1][a][q]};
-                        const double fh[2] = {acc[s].v[a][0][q], acc[s].v[a][1][q]};
-                        y.mma(fw, fh);
-                    }
-            }
-            BTile<T>::store(b_tile(L, I, kb), y, lane);
+            for (int s = 0; s < SLOTS; ++s)
+                if (I0 + OW * s < nb)
+                    solve(w, acc[s], I0 + OW * s, kb);
+        // the tiles past the slots (n > 416)
+        static_assert(SPD_BATCH_NMAX / BNB <= 1 + OW * SLOTS + WAVES, "a tile per wave is left at most");
+        if (const int I = kb + 1 + OW * SLOTS + wave; I < nb) {
+            init(acc[0], I, kb);
+            products(std::integral_constant<int, 1>(), acc, I, 1, kb);
+            solve(w, acc[0], I, kb);
         }
         __syncthreads();
     }
@@ -587,9 +645,7 @@ __device__ __attribute__((noinline)) void b_solve(const T *L, const T *Winv, int
         // blocks blk(t + 1 + w), blk(t + 1 + w + WAVES), ...
         auto blk = [&](int t) { return TR ? nb - 1 - t : t; };
         auto tile = [&](int t, int o) { return TR ? b_tile(L, blk(t), blk(o)) : b_tile(L, blk(o), blk(t)); };
-        auto diag = [&](int t) {  // wave 0: z_k = W_k y_k in place
-            Op w;
-            w.load(Winv + (int64_t)blk(t) * BNB * BNB, lane);
+        auto diag = [&](const Op &w, int t) {  // wave 0: z_k = W_k y_k in place
             T z[8];
             take(z, blk(t), TR);
             acc_t o[2];
@@ -600,11 +656,18 @@ __device__ __attribute__((noinline)) void b_solve(const T *L, const T *Winv, int
 #pragma unroll
                     for (int q = 0; q < 4; ++q) yc[blk(t) * BNB + 16 * h + BVec<T>::row(q, u)] = o[h][q];
         };
+        // wave 0: the next step's W, loaded a step ahead
+        auto winv = [&](int t) { return Winv + (int64_t)blk(t) * BNB * BNB; };
+        Op cur, w;
         if (wave == 0)
-            diag(0);
-        Op cur;
+            w.load(winv(0), lane);
         if (1 + wave < nb)
             cur.load(tile(0, 1 + wave), lane);
+        if (wave == 0) {
+            diag(w, 0);
+            if (nb > 1)
+                w.load(winv(1), lane);
+        }
         __syncthreads();
         for (int t = 0; t + 1 < nb; ++t) {
             T z[8];
@@ -623,7 +686,9 @@ __device__ __attribute__((noinline)) void b_solve(const T *L, const T *Winv, int
                         for (int q = 0; q < 4; ++q) yc[blk(o) * BNB + 16 * h + BVec<T>::row(q, u)] -= p[h][q];
                 if (wave == 0 && o == t + 1) {
                     __builtin_amdgcn_wave_barrier();
-                    diag(t + 1);
+                    diag(w, t + 1);
+                    if (t + 2 < nb)
+                        w.load(winv(t + 2), lane);
                 }
                 if (more)
                     cur = nx;
