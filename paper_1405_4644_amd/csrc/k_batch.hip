@@ -245,67 +245,113 @@ SPD_DEV T *b_tile(T *L, int I, int J)
 }
 
 // Factor a 32 x 32 diagonal block, given row-major in Lr (its lower triangle),
-// in one wavefront and form its inverse W, left-looking: lane r holds row r; at column j every lane
-// forms a_rj - sum_{q<j} L[r][q] L[j][q] with row j of L read from shared
-// memory (Lr, row-major, every lane the same address: a broadcast, four
-// values per read), lane j's value is the pivot (one readlane), and each lane
-// publishes its new L[r][j] to Lr.  W follows by forward substitution
-// L W = I, lane c building column c (W[r][c] = (delta_rc -
-// sum_{q<r} L[r][q] W[q][c]) / L[r][r]) from the same rows.  Lanes 32..63
-// mirror lanes 0..31 and store nothing.  Outputs: W in Ws (Ws[c * 33 + r])
-// and Wg (tile layout; nothing reads the block of L itself again).  Returns
-// the 1-based failing column of the block, 0 on success.
+// in one wavefront and form its inverse W, by 16 x 16 blocks
+//   [L11; L21 L22],  W = [W11; -W22 L21 W11, W22].
+// Lane r holds row r (lanes 32..63 mirror 0..31): 16 column steps on all 32
+// rows give L11 and L21 (pivot and multipliers by readlane), L22 takes
+// L21 L21^T on MFMA and another 16 steps; W11 and W22 follow side by side by
+// forward substitution, lane c building column c % 16 of block c / 16 from
+// the rows of L in shared memory (every lane of a block the same address);
+// W21 on MFMA.  Outputs: W in Ws (Ws[c * 33 + r]) and Wg (tile layout; nothing
+// reads the block of L itself again).  Returns the 1-based failing column of
+// the block, 0 on success.
+// On the path of the whole factorisation: 8.4 blocks per system.  32 column
+// steps with row j read back from shared memory, and a 32-deep substitution,
+// took 16 us (binary32) and 20 us (binary64) a block; TIMES_BDIAG.
 template <typename T>
 __device__ __attribute__((noinline)) int b_diag(T *Ws, T *Wg, T *Lr)
 {
-    Wg = (T *)gmem(Wg);  // global memory (see gmem)
+    const auto gW = gmem(uni(Wg));
     constexpr int S = BDIAG_S;  // Lr row stride (16-byte aligned rows)
-    const int lane = threadIdx.x & 63, r = lane & 31;
+    constexpr int H = BNB / 2;
+    const int lane = threadIdx.x & 63, r = lane & 31, r16 = lane & 15, u = lane >> 4;
     const bool store = lane < BNB;
-    T row[BNB];
+    auto mma = [](T a, T b, auto c) {
+        if constexpr (sizeof(T) == 4)
+            return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+        else
+            return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    };
+    using acc_t = typename std::conditional<sizeof(T) == 4, floatx4, doublex4>::type;
+    // row of accumulator register q
+    auto arow = [&](int q) { return sizeof(T) == 4 ? 4 * u + q : 4 * q + u; };
+    T v[H];
+    // columns c0 .. c0 + 15 of rows c0 .. 31, the steps' multipliers from lane c0 + k
+    auto steps = [&](auto c0c) -> int {
+        constexpr int c0 = decltype(c0c)::value;
 #pragma unroll
-    for (int c = 0; c < BNB; ++c)
-        row[c] = (c <= r) ? Lr[r * S + c] : (T)0;
-    __builtin_amdgcn_wave_barrier();
-    int bad = 0;
+        for (int c = 0; c < H; ++c) v[c] = Lr[r * S + c0 + c];
 #pragma unroll
-    for (int j = 0; j < BNB; ++j) {
-        T p[4] = {(T)0, (T)0, (T)0, (T)0};
+        for (int j = 0; j < H; ++j) {
+            const T piv = rl(v[j], c0 + j);
+            if (!(piv > (T)0))
+                return c0 + j + 1;
+            const T ljj = sqrt(piv);
+            const T l = (r == c0 + j) ? ljj : ((r > c0 + j) ? v[j] / ljj : (T)0);
+            v[j] = l;
 #pragma unroll
-        for (int q = 0; q < j; ++q) p[q & 3] = fma(row[q], Lr[j * S + q], p[q & 3]);
-        const T sv = row[j] - ((p[0] + p[1]) + (p[2] + p[3]));
-        const T piv = rl(sv, j);
-        if (!(piv > (T)0)) {
-            bad = j + 1;
-            break;
+            for (int k = j + 1; k < H; ++k) v[k] = fma(-l, rl(l, c0 + k), v[k]);
         }
-        const T ljj = sqrt(piv);
-        row[j] = (r == j) ? ljj : ((r > j) ? sv / ljj : (T)0);
-        if (store)
-            Lr[r * S + j] = row[j];
+        if (store && r >= c0)
+#pragma unroll
+            for (int c = 0; c < H; ++c) Lr[r * S + c0 + c] = v[c];
         __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    if (bad)
+        return 0;
+    };
+    if (const int bad = steps(std::integral_constant<int, 0>()))
         return bad;
-    // W: each new row of W goes to Ws as it is formed
-    T w[BNB];
+    {
+        acc_t d = acc_t{0, 0, 0, 0};
 #pragma unroll
-    for (int i = 0; i < BNB; ++i) {
-        T p[4] = {(T)0, (T)0, (T)0, (T)0};
+        for (int s = 0; s < 4; ++s) {
+            const T x = Lr[(H + r16) * S + 4 * s + u];
+            d = mma(x, x, d);
+        }
+        // symmetric: row r16, columns arow(q)
 #pragma unroll
-        for (int q = 0; q < i; ++q) p[q & 3] = fma(Lr[i * S + q], w[q], p[q & 3]);
-        const T rhs = ((r == i) ? (T)1 : (T)0) - ((p[0] + p[1]) + (p[2] + p[3]));
-        w[i] = (i < r) ? (T)0 : rhs / Lr[i * S + i];
-        if (store)
-            Ws[r * (BNB + 1) + i] = w[i];  // lane r = column r of W
-        __builtin_amdgcn_sched_barrier(0);
+        for (int q = 0; q < 4; ++q) Lr[(H + r16) * S + H + arow(q)] -= d[q];
+        __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_wave_barrier();
+    if (const int bad = steps(std::integral_constant<int, H>()))
+        return bad;
+    // W11 and W22
+    {
+        const int b0 = r & H;  // 0 or 16
+        const T *Lb = Lr + b0 * S + b0;
+        T w[H];
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            T p[4] = {(T)0, (T)0, (T)0, (T)0};
+#pragma unroll
+            for (int q = 0; q < i; ++q) p[q & 3] = fma(Lb[i * S + q], w[q], p[q & 3]);
+            const T rhs = ((r16 == i) ? (T)1 : (T)0) - ((p[0] + p[1]) + (p[2] + p[3]));
+            w[i] = (i < r16) ? (T)0 : rhs / Lb[i * S + i];
+        }
+        if (store)
+#pragma unroll
+            for (int i = 0; i < H; ++i) {
+                Ws[r * (BNB + 1) + b0 + i] = w[i];  // lane r = column r of W
+                if (b0)
+                    Ws[r * (BNB + 1) + i] = (T)0;
+            }
+        __builtin_amdgcn_wave_barrier();
+    }
+    // W21 = -W22 (L21 W11): the inner product's rows fall on the k-slots of the outer one
+    {
+        acc_t p = acc_t{0, 0, 0, 0}, d = acc_t{0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            p = mma(Lr[(H + r16) * S + 4 * s + u], Ws[r16 * (BNB + 1) + 4 * s + u], p);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) d = mma(Ws[(H + arow(q)) * (BNB + 1) + H + r16], p[q], d);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) Ws[r16 * (BNB + 1) + H + arow(q)] = -d[q];
+        __builtin_amdgcn_wave_barrier();
+    }
     for (int e = lane; e < BNB * BNB; e += 64) {
         int rr, cc;
         BTile<T>::coords(e, rr, cc);
-        Wg[e] = Ws[cc * (BNB + 1) + rr];
+        gW[e] = Ws[cc * (BNB + 1) + rr];
     }
     return 0;
 }
