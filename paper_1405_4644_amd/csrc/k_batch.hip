@@ -257,9 +257,13 @@ SPD_DEV T *b_tile(T *L, int I, int J)
 // the block, 0 on success.
 // On the path of the whole factorisation: 8.4 blocks per system.  32 column
 // steps with row j read back from shared memory, and a 32-deep substitution,
-// took 16 us (binary32) and 20 us (binary64) a block; TIMES_BDIAG.
+// took 16 us (binary32) and 20 us (binary64) a block; this takes 11 and 17.
+// Binary32 runs both halves of the columns as a loop, inlined into the
+// factorisation (unrolled for each half, 31 KB of code, the call took as long
+// to fetch as to run); binary64 keeps a function of its own, unrolled: either
+// of the two spills there.
 template <typename T>
-__device__ __attribute__((noinline)) int b_diag(T *Ws, T *Wg, T *Lr)
+SPD_DEV int b_diag_body(T *Ws, T *Wg, T *Lr)
 {
     const auto gW = gmem(uni(Wg));
     constexpr int S = BDIAG_S;  // Lr row stride (16-byte aligned rows)
@@ -275,32 +279,36 @@ __device__ __attribute__((noinline)) int b_diag(T *Ws, T *Wg, T *Lr)
     using acc_t = typename std::conditional<sizeof(T) == 4, floatx4, doublex4>::type;
     // row of accumulator register q
     auto arow = [&](int q) { return sizeof(T) == 4 ? 4 * u + q : 4 * q + u; };
-    T v[H];
     // columns c0 .. c0 + 15 of rows c0 .. 31, the steps' multipliers from lane c0 + k
-    auto steps = [&](auto c0c) -> int {
-        constexpr int c0 = decltype(c0c)::value;
+    auto half = [&](auto c0) -> int {
+        T v[H];
+        int bad = 0;
 #pragma unroll
         for (int c = 0; c < H; ++c) v[c] = Lr[r * S + c0 + c];
 #pragma unroll
         for (int j = 0; j < H; ++j) {
             const T piv = rl(v[j], c0 + j);
-            if (!(piv > (T)0))
-                return c0 + j + 1;
+            if constexpr (sizeof(T) == 4) {
+                bad = (bad == 0 && !(piv > (T)0)) ? c0 + j + 1 : bad;
+            } else {
+                if (!(piv > (T)0))
+                    return c0 + j + 1;
+            }
             const T ljj = sqrt(piv);
             const T l = (r == c0 + j) ? ljj : ((r > c0 + j) ? v[j] / ljj : (T)0);
             v[j] = l;
 #pragma unroll
             for (int k = j + 1; k < H; ++k) v[k] = fma(-l, rl(l, c0 + k), v[k]);
         }
+        if (bad)
+            return bad;
         if (store && r >= c0)
 #pragma unroll
             for (int c = 0; c < H; ++c) Lr[r * S + c0 + c] = v[c];
         __builtin_amdgcn_wave_barrier();
         return 0;
     };
-    if (const int bad = steps(std::integral_constant<int, 0>()))
-        return bad;
-    {
+    auto update = [&]() {  // L22's block takes L21 L21^T
         acc_t d = acc_t{0, 0, 0, 0};
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -311,9 +319,22 @@ __device__ __attribute__((noinline)) int b_diag(T *Ws, T *Wg, T *Lr)
 #pragma unroll
         for (int q = 0; q < 4; ++q) Lr[(H + r16) * S + H + arow(q)] -= d[q];
         __builtin_amdgcn_wave_barrier();
+    };
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll 1
+        for (int c0 = 0; c0 < BNB; c0 += H) {
+            if (const int bad = half(c0))
+                return bad;
+            if (c0 == 0)
+                update();
+        }
+    } else {
+        if (const int bad = half(std::integral_constant<int, 0>()))
+            return bad;
+        update();
+        if (const int bad = half(std::integral_constant<int, H>()))
+            return bad;
     }
-    if (const int bad = steps(std::integral_constant<int, H>()))
-        return bad;
     // W11 and W22
     {
         const int b0 = r & H;  // 0 or 16
@@ -356,6 +377,12 @@ __device__ __attribute__((noinline)) int b_diag(T *Ws, T *Wg, T *Lr)
     return 0;
 }
 
+__device__ __attribute__((noinline)) int b_diag(double *Ws, double *Wg, double *Lr)
+{
+    return b_diag_body<double>(Ws, Wg, Lr);
+}
+SPD_DEV int b_diag(float *Ws, float *Wg, float *Lr) { return b_diag_body<float>(Ws, Wg, Lr); }
+
 // ---------------------------------------------------------------------------
 // Left-looking blocked Cholesky of H = round(mu D A D) (identity padding up
 // to np = 32 nb): panel kb's tiles (I, kb) are formed
@@ -369,7 +396,9 @@ __device__ __attribute__((noinline)) int b_diag(T *Ws, T *Wg, T *Lr)
 // Bound by memory traffic, with 512 systems in flight.  Right-looking, with H
 // written out by a conversion and every trailing tile read and written once
 // per panel, 4096 systems of the batched distribution moved 40 GB in binary32
-// (9.4 ms) and 31 GB in binary64 (7.1 ms), 4.3 TB/s; TIMES_BFAC.
+// and 31 GB in binary64, at 4.3 TB/s, a factorisation of 394 and 600 us (mean
+// over the systems).  With the residual's mirror of A gone as well (b_sym),
+// 20 and 17 GB, 194 and 330 us.
 template <typename T, int WAVES>
 __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np, double *d, double mu, int equil,
                                                   T *L, T *Winv, int half, SolveSmem &sm)
@@ -541,7 +570,7 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
 #pragma unroll
             for (int j = 0; j < 16; ++j) Lr[A32::col(j, lane) * BDIAG_S + A32::row(j, lane)] = acc[0].get(j);
             __builtin_amdgcn_wave_barrier();
-            const int bad = b_diag<T>(Ws, Winv + (int64_t)kb * BNB * BNB, Lr);
+            const int bad = b_diag(Ws, Winv + (int64_t)kb * BNB * BNB, Lr);
             if (lane == 0)
                 sm.info = bad ? kb * BNB + bad : 0;
         } else if (I0 < nb) {
@@ -596,7 +625,7 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
 // tiles.  ys[c * YS + i] holds right-hand side c (YS: pitch without bank
 // conflicts between the 16 columns).  On the VALU, with the vectors read from
 // shared memory for every product, a binary32 solve took 62 us (mean n = 270),
-// a binary64 one 218 us; TIMES_BSOLVE.
+// a binary64 one 218 us; here 42 and 75 us.
 template <typename T> struct BVec;
 template <> struct BVec<float> {
     using acc = floatx4;
@@ -781,7 +810,7 @@ __device__ __attribute__((noinline)) void b_solve(const T *L, const T *Winv, int
 // The residual used to read whole rows, the upper half from a mirror that the
 // factorisation wrote (557 us for a binary32 system's 3.5 passes); the
 // picker's products read the triangle once by rows and once by columns, a
-// cache line per lane (3.7 ms for 4096 systems); TIMES_BSYM.
+// cache line per lane (3.7 ms for 4096 systems).  Now 370 us, and 2.0 ms.
 SPD_DEV int bsym_pos(int r, int c)  // element (r, c) of a quarter tile: written and read without bank conflicts
 {
     const int rr = (r & ~3) | ((r & 1) << 1) | ((r >> 1) & 1);
