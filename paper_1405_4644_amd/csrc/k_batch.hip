@@ -22,6 +22,7 @@
 
 #define BNB 32  // panel and tile width
 #define BDIAG_S 36  // row stride of a diagonal block in shared memory
+#define BDIAG_P 4   // row stride of its panels' buffer
 // precision picker: 16 features -> 64 -> 64 -> 4 classes (BF16, FP16, FP32, FP64)
 #define PICK_NFEAT 16
 #define PICK_NH 64
@@ -174,6 +175,13 @@ template <> struct BTile<float> {
             *(__attribute__((address_space(1))) V *)(gmem(t) + (unsigned)((2 * g * 32 + lane) * 4)) =
                 V{a.v[4 * g], a.v[4 * g + 1], a.v[4 * g + 2], a.v[4 * g + 3]};
     }
+    SPD_DEV void store(float *t, int lane) const
+    {
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *(__attribute__((address_space(1))) V *)(gmem(t) + (unsigned)((2 * g * 32 + lane) * 4)) =
+                V{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+    }
     // acc += (this as rows of D) (b as columns of D)^T, this negated
     static SPD_DEV void submul(Acc32<float> &acc, const BTile &a, const BTile &b)
     {
@@ -228,6 +236,18 @@ template <> struct BTile<double> {
                     *(__attribute__((address_space(1))) V *)(gmem(t) + (unsigned)(((4 * a + u) * 32 + 16 * b + r) * 4 + q)) =
                         V{acc.v[a][b][q], acc.v[a][b][q + 1]};
     }
+    SPD_DEV void store(double *t, int lane) const
+    {
+        const int r = lane & 15, u = lane >> 4;
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; q += 2)
+                    *(__attribute__((address_space(1))) V *)(gmem(t) + (unsigned)(((4 * a + u) * 32 + 16 * b + r) * 4 + q)) =
+                        V{v[b][a][q], v[b][a][q + 1]};
+    }
     // acc += (the half tile x as rows of D) (the half tile y as columns of D)^T, x negated
     static SPD_DEV void submul_half(Acc32<double> &acc, const double (&x)[2][4], const double (&y)[2][4])
     {
@@ -245,31 +265,28 @@ SPD_DEV T *b_tile(T *L, int I, int J)
 }
 
 // Factor a 32 x 32 diagonal block, given row-major in Lr (its lower triangle),
-// in one wavefront and form its inverse W, by 16 x 16 blocks
-//   [L11; L21 L22],  W = [W11; -W22 L21 W11, W22].
-// Lane r holds row r (lanes 32..63 mirror 0..31): 16 column steps on all 32
-// rows give L11 and L21 (pivot and multipliers by readlane), L22 takes
-// L21 L21^T on MFMA and another 16 steps; W11 and W22 follow side by side by
-// forward substitution, lane c building column c % 16 of block c / 16 from
-// the rows of L in shared memory (every lane of a block the same address);
-// W21 on MFMA.  Outputs: W in Ws (Ws[c * 33 + r]) and Wg (tile layout; nothing
-// reads the block of L itself again).  Returns the 1-based failing column of
+// in one wavefront and form its inverse W: column operations that take A to L
+// take the identity below it to L^{-T}, so lane l < 32 works on row l of
+// [A; I] and lane 32 + c on the identity's row c, column c of W, with the same
+// instructions.  Panels of 4 columns: a lane has its 4 elements in registers
+// (pivot and multipliers by readlane); the columns to the right take the
+// panel's product on MFMA, kept in 16 x 16 accumulators (transposed: a
+// register's row is a column of [A; I]) from where the next panel's columns
+// go to the lanes through buf.  Output: W in Ws (Ws[c * 33 + r]); nothing
+// reads the block of L itself again.  Returns the 1-based failing column of
 // the block, 0 on success.
-// On the path of the whole factorisation: 8.4 blocks per system.  32 column
-// steps with row j read back from shared memory, and a 32-deep substitution,
-// took 16 us (binary32) and 20 us (binary64) a block; this takes 11 and 17.
-// Binary32 runs both halves of the columns as a loop, inlined into the
-// factorisation (unrolled for each half, 31 KB of code, the call took as long
-// to fetch as to run); binary64 keeps a function of its own, unrolled: either
-// of the two spills there.
+// A serial chain, on the path of the whole factorisation: 8.4 blocks per
+// system.  32 column steps with row j read back from shared memory, and a
+// 32-deep substitution, took 16 us (binary32) and 20 us (binary64) a block;
+// 16 columns in registers at a time, unrolled (29 KB of code, which took
+// longer to fetch than to run), 11 and 16; this takes 8.6 and 11.4.
 template <typename T>
-SPD_DEV int b_diag_body(T *Ws, T *Wg, T *Lr)
+SPD_DEV int b_diag_body(T *Ws, T *Lr, T *buf)
 {
-    const auto gW = gmem(uni(Wg));
     constexpr int S = BDIAG_S;  // Lr row stride (16-byte aligned rows)
     constexpr int H = BNB / 2;
-    const int lane = threadIdx.x & 63, r = lane & 31, r16 = lane & 15, u = lane >> 4;
-    const bool store = lane < BNB;
+    constexpr int P = BDIAG_P;  // row stride of the panel's buffer
+    const int lane = threadIdx.x & 63, r16 = lane & 15, u = lane >> 4;
     auto mma = [](T a, T b, auto c) {
         if constexpr (sizeof(T) == 4)
             return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -279,109 +296,87 @@ SPD_DEV int b_diag_body(T *Ws, T *Wg, T *Lr)
     using acc_t = typename std::conditional<sizeof(T) == 4, floatx4, doublex4>::type;
     // row of accumulator register q
     auto arow = [&](int q) { return sizeof(T) == 4 ? 4 * u + q : 4 * q + u; };
-    // columns c0 .. c0 + 15 of rows c0 .. 31, the steps' multipliers from lane c0 + k
-    auto half = [&](auto c0) -> int {
-        T v[H];
-        int bad = 0;
+    // columns 16 c .. 16 c + 15: of A's rows (ta: block rows 0 and 1 of column
+    // 0, block row 1 of column 1) and of the identity's (ti: block row 0 of
+    // columns 0 and 1, block row 1 of column 1)
+    acc_t ta[3], ti[3];
 #pragma unroll
-        for (int c = 0; c < H; ++c) v[c] = Lr[r * S + c0 + c];
+    for (int q = 0; q < 4; ++q) {
+        ta[0][q] = Lr[r16 * S + arow(q)];
+        ta[1][q] = Lr[(H + r16) * S + arow(q)];
+        ta[2][q] = Lr[(H + r16) * S + H + arow(q)];
+        ti[0][q] = ti[2][q] = (r16 == arow(q)) ? (T)1 : (T)0;
+        ti[1][q] = (T)0;
+    }
+    // the 4 columns of accumulator t from 4 pc into rows r0 .. r0 + 15 of the buffer
+    auto put = [&](const acc_t &t, int pc, int r0) {
+        if constexpr (sizeof(T) == 4) {
+            if (u == pc)
+                *(floatx4 *)&buf[(r0 + r16) * P] = t;
+        } else {
+            buf[(r0 + r16) * P + u] = pc < 2 ? (pc == 0 ? t[0] : t[1]) : (pc == 2 ? t[2] : t[3]);
+        }
+    };
+    int bad = 0;
+#pragma unroll 1
+    for (int p = 0; p < BNB / 4; ++p) {
+        const int c0 = 4 * p, pc = p & 3;
+        if (p < 4) {
+            put(ta[0], pc, 0);
+            put(ta[1], pc, H);
+            put(ti[0], pc, 2 * H);
+        } else {
+            put(ta[2], pc, H);
+            put(ti[1], pc, 2 * H);
+            put(ti[2], pc, 3 * H);
+        }
+        __builtin_amdgcn_wave_barrier();
+        T v[4];
 #pragma unroll
-        for (int j = 0; j < H; ++j) {
+        for (int j = 0; j < 4; ++j) v[j] = (p < 4 && lane >= 3 * H) ? (T)0 : buf[lane * P + j];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
             const T piv = rl(v[j], c0 + j);
-            if constexpr (sizeof(T) == 4) {
-                bad = (bad == 0 && !(piv > (T)0)) ? c0 + j + 1 : bad;
-            } else {
-                if (!(piv > (T)0))
-                    return c0 + j + 1;
-            }
+            bad = (bad == 0 && !(piv > (T)0)) ? c0 + j + 1 : bad;
             const T ljj = sqrt(piv);
-            const T l = (r == c0 + j) ? ljj : ((r > c0 + j) ? v[j] / ljj : (T)0);
+            const T q = v[j] / ljj;  // by every lane: no branch around the division
+            const T l = (lane == c0 + j) ? ljj : ((lane > c0 + j) ? q : (T)0);
             v[j] = l;
 #pragma unroll
-            for (int k = j + 1; k < H; ++k) v[k] = fma(-l, rl(l, c0 + k), v[k]);
+            for (int k = j + 1; k < 4; ++k) v[k] = fma(-l, rl(l, c0 + k), v[k]);
         }
         if (bad)
             return bad;
-        if (store && r >= c0)
-#pragma unroll
-            for (int c = 0; c < H; ++c) Lr[r * S + c0 + c] = v[c];
         __builtin_amdgcn_wave_barrier();
-        return 0;
-    };
-    auto update = [&]() {  // L22's block takes L21 L21^T
-        acc_t d = acc_t{0, 0, 0, 0};
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const T x = Lr[(H + r16) * S + 4 * s + u];
-            d = mma(x, x, d);
+        for (int j = 0; j < 4; ++j) buf[lane * P + j] = v[j];
+        if (lane >= BNB)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) Ws[(lane - BNB) * (BNB + 1) + c0 + j] = v[j];
+        __builtin_amdgcn_wave_barrier();
+        T o[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) o[t] = buf[(H * t + r16) * P + u];
+        if (p < 4) {
+            ta[0] = mma(-o[0], o[0], ta[0]);
+            ta[1] = mma(-o[0], o[1], ta[1]);
+            ti[0] = mma(-o[0], o[2], ti[0]);
+        } else {
+            ti[2] = mma(-o[1], o[3], ti[2]);
         }
-        // symmetric: row r16, columns arow(q)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) Lr[(H + r16) * S + H + arow(q)] -= d[q];
+        ta[2] = mma(-o[1], o[1], ta[2]);
+        ti[1] = mma(-o[1], o[2], ti[1]);
         __builtin_amdgcn_wave_barrier();
-    };
-    if constexpr (sizeof(T) == 4) {
-#pragma unroll 1
-        for (int c0 = 0; c0 < BNB; c0 += H) {
-            if (const int bad = half(c0))
-                return bad;
-            if (c0 == 0)
-                update();
-        }
-    } else {
-        if (const int bad = half(std::integral_constant<int, 0>()))
-            return bad;
-        update();
-        if (const int bad = half(std::integral_constant<int, H>()))
-            return bad;
-    }
-    // W11 and W22
-    {
-        const int b0 = r & H;  // 0 or 16
-        const T *Lb = Lr + b0 * S + b0;
-        T w[H];
-#pragma unroll
-        for (int i = 0; i < H; ++i) {
-            T p[4] = {(T)0, (T)0, (T)0, (T)0};
-#pragma unroll
-            for (int q = 0; q < i; ++q) p[q & 3] = fma(Lb[i * S + q], w[q], p[q & 3]);
-            const T rhs = ((r16 == i) ? (T)1 : (T)0) - ((p[0] + p[1]) + (p[2] + p[3]));
-            w[i] = (i < r16) ? (T)0 : rhs / Lb[i * S + i];
-        }
-        if (store)
-#pragma unroll
-            for (int i = 0; i < H; ++i) {
-                Ws[r * (BNB + 1) + b0 + i] = w[i];  // lane r = column r of W
-                if (b0)
-                    Ws[r * (BNB + 1) + i] = (T)0;
-            }
-        __builtin_amdgcn_wave_barrier();
-    }
-    // W21 = -W22 (L21 W11): the inner product's rows fall on the k-slots of the outer one
-    {
-        acc_t p = acc_t{0, 0, 0, 0}, d = acc_t{0, 0, 0, 0};
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-            p = mma(Lr[(H + r16) * S + 4 * s + u], Ws[r16 * (BNB + 1) + 4 * s + u], p);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) d = mma(Ws[(H + arow(q)) * (BNB + 1) + H + r16], p[q], d);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) Ws[r16 * (BNB + 1) + H + arow(q)] = -d[q];
-        __builtin_amdgcn_wave_barrier();
-    }
-    for (int e = lane; e < BNB * BNB; e += 64) {
-        int rr, cc;
-        BTile<T>::coords(e, rr, cc);
-        gW[e] = Ws[cc * (BNB + 1) + rr];
     }
     return 0;
 }
 
-__device__ __attribute__((noinline)) int b_diag(double *Ws, double *Wg, double *Lr)
+// (inlined, binary64's registers would spill in the products)
+__device__ __attribute__((noinline)) int b_diag(double *Ws, double *Lr, double *buf)
 {
-    return b_diag_body<double>(Ws, Wg, Lr);
+    return b_diag_body<double>(Ws, Lr, buf);
 }
-SPD_DEV int b_diag(float *Ws, float *Wg, float *Lr) { return b_diag_body<float>(Ws, Wg, Lr); }
+SPD_DEV int b_diag(float *Ws, float *Lr, float *buf) { return b_diag_body<float>(Ws, Lr, buf); }
 
 // ---------------------------------------------------------------------------
 // Left-looking blocked Cholesky of H = round(mu D A D) (identity padding up
@@ -413,7 +408,7 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
     equil = uni(equil);
     constexpr int NT = WAVES * 64;
     static_assert(BNB * (BNB + 1) * 8 <= (int)sizeof(sm.tb), "inverse of the diagonal block");
-    static_assert(BNB * BDIAG_S * 8 <= (int)sizeof(sm.yo), "diagonal block");
+    static_assert((BNB * BDIAG_S + 2 * BNB * BDIAG_P) * 8 <= (int)sizeof(sm.yo), "diagonal block");
     using A32 = Acc32<T>;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nb = np / BNB;
@@ -570,7 +565,7 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
 #pragma unroll
             for (int j = 0; j < 16; ++j) Lr[A32::col(j, lane) * BDIAG_S + A32::row(j, lane)] = acc[0].get(j);
             __builtin_amdgcn_wave_barrier();
-            const int bad = b_diag(Ws, Winv + (int64_t)kb * BNB * BNB, Lr);
+            const int bad = b_diag(Ws, Lr, Lr + BNB * BDIAG_S);
             if (lane == 0)
                 sm.info = bad ? kb * BNB + bad : 0;
         } else if (I0 < nb) {
@@ -596,7 +591,9 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
                     for (int q = 0; q < 4; ++q)
                         w.v[b][a][q] = Ws[(16 * a + 4 * q + (lane >> 4)) * (BNB + 1) + 16 * b + (lane & 15)];
         }
-        if (wave > 0)
+        if (wave == 0)
+            w.store(Winv + (int64_t)kb * BNB * BNB, lane);
+        else
 #pragma unroll
             for (int s = 0; s < SLOTS; ++s)
                 if (I0 + OW * s < nb)
@@ -690,10 +687,24 @@ __device__ __attribute__((noinline)) void b_solve(const T *L, const T *Winv, int
     const auto gX = gmem(uni(X));
     T *ys = (T *)sm.ys;
     static_assert(SPD_BATCH_MAXRHS * YS * sizeof(T) <= sizeof(sm.ys), "solve vectors");
-    for (int idx = tid; idx < m * np; idx += NT) {
-        const int c = idx / np, i = idx % np;
+    // a wave takes whole columns here and at the end, four rows a lane at a
+    // time (256): their loads are in flight together, and a column's maximum
+    // needs no other wave
+    for (int c = wave; c < m; c += WAVES) {
         const double s = pow2_ceil(sm.smax[c]);
-        ys[c * YS + i] = (i < n) ? (T)(gd[i] * gR[i + (int64_t)c * n] / s) : (T)0;
+        for (int i0 = lane; i0 < np; i0 += 4 * 64) {
+            double dv[4], rv[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = min(i0 + 64 * k, n - 1);
+                dv[k] = gd[i];
+                rv[k] = gR[i + c * n];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (i0 + 64 * k < np)
+                    ys[c * YS + i0 + 64 * k] = (i0 + 64 * k < n) ? (T)(dv[k] * rv[k] / s) : (T)0;
+        }
     }
     __syncthreads();
     // the lane's right-hand side (lanes past the last one repeat the first;
@@ -775,33 +786,49 @@ __device__ __attribute__((noinline)) void b_solve(const T *L, const T *Winv, int
     };
     sweep(std::false_type());
     sweep(std::true_type());
-    if (tid < m)
-        sm.zmax[tid] = 0ull;
-    __syncthreads();
-    for (int idx = tid; idx < m * n; idx += NT) {
-        const int c = idx / n, i = idx % n;
-        const double s = pow2_ceil(sm.smax[c]);
-        const double z = ((s * mu) * gd[i]) * (double)ys[c * YS + i];
-        const auto px = gX + i + (int64_t)c * n;
-        *px = accumulate ? *px + z : z;
-        atomicMax(&sm.zmax[c], (unsigned long long)__double_as_longlong(fabs(z)));
+    for (int c = wave; c < m; c += WAVES) {
+        const double sc = pow2_ceil(sm.smax[c]) * mu;
+        unsigned long long zm = 0ull;  // of |z|'s bits: NaN above all
+        for (int i0 = lane; i0 < n; i0 += 4 * 64) {
+            double dv[4], xv[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = min(i0 + 64 * k, n - 1);
+                dv[k] = gd[i];
+                xv[k] = accumulate ? gX[i + c * n] : 0.0;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = i0 + 64 * k;
+                if (i < n) {
+                    const double z = (sc * dv[k]) * (double)ys[c * YS + i];
+                    gX[i + c * n] = accumulate ? xv[k] + z : z;
+                    zm = max(zm, (unsigned long long)__double_as_longlong(fabs(z)));
+                }
+            }
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) zm = max(zm, __shfl_xor(zm, off));
+        if (lane == 0)
+            sm.zmax[c] = zm;
     }
     __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
-// y = A x (binary64) for m <= 8 vectors in shared memory (pitch BPITCH) and the
-// symmetric A given by its lower triangle, in one pass over that triangle on
-// v_mfma_f64_16x16x4f64 (the vectors as the 16 rows of the result).  32-column
-// strips J, wave w takes the 32 x 32 blocks I = J + w, J + w + 4, ...: a lane
-// (j = l % 16, u = l / 16) holds columns 16 h + j, rows 8 s + 2 u + e, loaded
-// 16 bytes at a time with the next block in flight.  As they are, these are
-// the operands of the columns' sums (sum_i a_ij x_i, kept in the accumulators
-// over the strip); transposed by 16 x 16 quarters through the wave's buffer
-// they are those of the rows' (added to y in shared memory: a row block has
-// one wave at a time).  After the strip the waves' column sums are added in
-// order, so nothing depends on timing.  A diagonal block is read as a full
-// symmetric one and serves its rows only.
+// y = A x (binary64) for m <= 4 G vectors in shared memory (pitch BPITCH) and
+// the symmetric A given by its lower triangle, in one pass over that triangle
+// on v_mfma_f64_4x4x4f64 (four products side by side: 4 vectors times 16
+// columns; 16x16x4 would spend a quarter or half of its rows on them).
+// 32-column strips J, wave w takes the 32 x 32 blocks I = J + w, J + w + 4,
+// ...: a lane (j = l % 16, u = l / 16) holds columns 16 h + j, rows
+// 8 s + 2 u + e, loaded 16 bytes at a time with the next block in flight.  As
+// they are, these are the operands of the columns' sums (sum_i a_ij x_i, kept
+// in the accumulators over the strip); transposed by 16 x 16 quarters through
+// the wave's buffer they are those of the rows' (added to y in shared memory:
+// a row block has one wave at a time).  After the strip the waves' column sums
+// are added in order, so nothing depends on timing.  A diagonal block is its
+// lower half with the diagonal halved: the same code as any other.
 // With WA also ya_i = sum_j |a_ij| xa_j (xa NULL: ones; excl: j = i left out),
 // with HS the largest |h_ij| off the diagonal and the sum of h_ij^2 of
 // H = D A D, per thread.
@@ -810,13 +837,15 @@ __device__ __attribute__((noinline)) void b_solve(const T *L, const T *Winv, int
 // The residual used to read whole rows, the upper half from a mirror that the
 // factorisation wrote (557 us for a binary32 system's 3.5 passes); the
 // picker's products read the triangle once by rows and once by columns, a
-// cache line per lane (3.7 ms for 4096 systems).  Now 370 us, and 2.0 ms.
+// cache line per lane (3.7 ms for 4096 systems).  One pass with 16x16x4 and
+// diagonal blocks loaded as full symmetric ones, each of whose 16 loads fell
+// on 64 cache lines, took 377 us; now 195 us.
 SPD_DEV int bsym_pos(int r, int c)  // element (r, c) of a quarter tile: written and read without bank conflicts
 {
     const int rr = (r & ~3) | ((r & 1) << 1) | ((r >> 1) & 1);
     return rr * 16 + (c ^ (((r & 1) << 2) | ((r & 4) << 1)));
 }
-template <int WAVES, bool WA, bool HS>
+template <int WAVES, int G, bool WA, bool HS>
 SPD_DEV void b_sym(const double *A, int n, int m, const double *x, double *y, double *tbs, const double *xa,
                    double *ya, bool excl, const double *d, double &hmax, double &fro)
 {
@@ -827,48 +856,64 @@ SPD_DEV void b_sym(const double *A, int n, int m, const double *x, double *y, do
     const int nb = (n + BNB - 1) / BNB;
     const auto gA = gmem(A);
     double *tb = tbs + wave * BSYM_TB;
-    const double *xc = x + (j16 < m ? j16 : 0) * BPITCH;  // lanes past the last vector repeat the first, dropped
+    const double *xc[G];  // group g: vectors 4 g .. 4 g + 3; past the last one the first again, dropped
+#pragma unroll
+    for (int g = 0; g < G; ++g) xc[g] = x + (4 * g + (j16 & 3) < m ? 4 * g + (j16 & 3) : 0) * BPITCH;
     for (int idx = tid; idx < m * BPITCH; idx += NT) y[idx] = 0.0;
     if constexpr (WA)
         for (int i = tid; i < n; i += NT) ya[i] = 0.0;
-    // a[h][t]: row 32 I + 8 (t / 2) + 2 u + t % 2, column 32 J + 16 h + j16
+    // a[h][t]: row 32 I + 8 (t / 2) + 2 u + t % 2, column 32 J + 16 h + j16.
+    // 16 bytes at a time; a pair of rows that would pass the last one comes
+    // from the last two, a column past the last one from that one (trim drops
+    // or moves what does not belong)
     auto load = [&](double (&a)[2][8], int I, int J) {
-        if (I > J && I * BNB + BNB <= n) {
-            const unsigned o = (unsigned)(I * BNB + 2 * u + (J * BNB + j16) * n);
+        unsigned cj[2];
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < 2; ++h) cj[h] = (unsigned)(min(J * BNB + 16 * h + j16, n - 1) * n);
 #pragma unroll
-                for (int t = 0; t < 8; t += 2) {
-                    const double2u v = *(const __attribute__((address_space(1))) double2u *)(gA + (o + (unsigned)(16 * h * n + 4 * t)));
+        for (int t = 0; t < 8; t += 2) {
+            const unsigned i = (unsigned)max(min(I * BNB + 4 * t + 2 * u, n - 2), 0);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (n > 1) {
+                    const double2u v = *(const __attribute__((address_space(1))) double2u *)(gA + (cj[h] + i));
                     a[h][t] = v.x;
                     a[h][t + 1] = v.y;
+                } else {
+                    a[h][t] = a[h][t + 1] = gA[0];
                 }
-        } else {
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const int i = I * BNB + 8 * (t >> 1) + 2 * u + (t & 1), j = J * BNB + 16 * h + j16;
-                    const int lo = min(max(i, j), n - 1), hi = min(min(i, j), n - 1);
-                    const double v = gA[(unsigned)(lo + hi * n)];
-                    a[h][t] = (i < n && j < n) ? v : 0.0;
-                }
+            }
         }
+    };
+    // a block at the end of the matrix or on the diagonal: rows past the last
+    // one and what is above the diagonal to zero, the diagonal halved (it is
+    // in the rows' sums and in the columns')
+    auto trim = [&](double (&a)[2][8], int I, int J) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int t = 0; t < 8; t += 2) {
+                const int i = I * BNB + 4 * t + 2 * u, j = J * BNB + 16 * h + j16;
+                const double x = (i + 1 < n) ? a[h][t] : a[h][t + 1], y = a[h][t + 1];
+                a[h][t] = (i < n && i >= j) ? (i == j ? 0.5 * x : x) : 0.0;
+                a[h][t + 1] = (i + 1 < n && i + 1 >= j) ? (i + 1 == j ? 0.5 * y : y) : 0.0;
+            }
     };
     double a[2][8], an[2][8];
     if (wave < nb)
         load(a, wave, 0);
     __syncthreads();
     for (int J = 0; J < nb; ++J) {
-        doublex4 accc[2] = {doublex4{0.0, 0.0, 0.0, 0.0}, doublex4{0.0, 0.0, 0.0, 0.0}};
+        double accc[2][G] = {};
         double cs[2] = {0.0, 0.0};
-        double xj[2][4], xaj[2][4];
+        double xj[G][2][4], xaj[2][4];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 const int j = J * BNB + 16 * h + 4 * s + u;
-                xj[h][s] = xc[j];
+#pragma unroll
+                for (int g = 0; g < G; ++g) xj[g][h][s] = xc[g][j];
                 if constexpr (WA)
                     xaj[h][s] = xa ? xa[j] : 1.0;
             }
@@ -879,14 +924,18 @@ SPD_DEV void b_sym(const double *A, int n, int m, const double *x, double *y, do
             if (In < nb)
                 load(an, In, Jn);
             __builtin_amdgcn_sched_barrier(0);
-            double xi[8];
+            if (I == J || I * BNB + BNB > n)
+                trim(a, I, J);
+            double xi[G][8];
 #pragma unroll
-            for (int t = 0; t < 8; t += 2) {
-                const double2 v = *(const double2 *)(xc + I * BNB + 4 * t + 2 * u);
-                xi[t] = v.x;
-                xi[t + 1] = v.y;
-            }
-            doublex4 accr[2] = {doublex4{0.0, 0.0, 0.0, 0.0}, doublex4{0.0, 0.0, 0.0, 0.0}};
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int t = 0; t < 8; t += 2) {
+                    const double2 v = *(const double2 *)(xc[g] + I * BNB + 4 * t + 2 * u);
+                    xi[g][t] = v.x;
+                    xi[g][t + 1] = v.y;
+                }
+            double accr[2][G] = {};
             double rs[2] = {0.0, 0.0};
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -899,25 +948,28 @@ SPD_DEV void b_sym(const double *A, int n, int m, const double *x, double *y, do
                     double at[4];
 #pragma unroll
                     for (int s = 0; s < 4; ++s) at[s] = tb[bsym_pos(j16, 4 * s + u)];
-                    if (I > J)
 #pragma unroll
-                        for (int t = 0; t < 4; ++t)
-                            accc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(xi[4 * b + t], a[h][4 * b + t], accc[h], 0, 0, 0);
+                    for (int t = 0; t < 4; ++t)
+#pragma unroll
+                        for (int g = 0; g < G; ++g)
+                            accc[h][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(xi[g][4 * b + t], a[h][4 * b + t], accc[h][g], 0, 0, 0);
 #pragma unroll
                     for (int s = 0; s < 4; ++s)
-                        accr[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xj[h][s], at[s], accr[b], 0, 0, 0);
+#pragma unroll
+                        for (int g = 0; g < G; ++g)
+                            accr[b][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(xj[g][h][s], at[s], accr[b][g], 0, 0, 0);
                     if constexpr (WA) {
 #pragma unroll
                         for (int s = 0; s < 4; ++s) {
                             const bool drop = excl && I == J && b == h && j16 == 4 * s + u;
                             rs[b] += drop ? 0.0 : fabs(at[s]) * xaj[h][s];
                         }
-                        if (I > J)
 #pragma unroll
-                            for (int t = 0; t < 4; ++t) {
-                                const int i = I * BNB + 16 * b + 8 * (t >> 1) + 2 * u + (t & 1);
-                                cs[h] += fabs(a[h][4 * b + t]) * (xa ? xa[i] : 1.0);
-                            }
+                        for (int t = 0; t < 4; ++t) {
+                            const int il = 16 * b + 8 * (t >> 1) + 2 * u + (t & 1);
+                            const bool drop = excl && I == J && il == 16 * h + j16;
+                            cs[h] += drop ? 0.0 : fabs(a[h][4 * b + t]) * (xa ? xa[I * BNB + il] : 1.0);
+                        }
                     }
                     if constexpr (HS) {
                         const double dj = d[J * BNB + 16 * h + j16];
@@ -925,18 +977,18 @@ SPD_DEV void b_sym(const double *A, int n, int m, const double *x, double *y, do
                         for (int t = 0; t < 4; ++t) {
                             const int il = 16 * b + 8 * (t >> 1) + 2 * u + (t & 1);
                             const double hv = (d[I * BNB + il] * a[h][4 * b + t]) * dj;
-                            const bool dg = I == J && il == 16 * h + j16;
+                            const bool dg = I == J && il == 16 * h + j16;  // halved
                             hmax = dg ? hmax : fmax(hmax, fabs(hv));
-                            fro += (I == J ? 1.0 : 2.0) * hv * hv;
+                            fro += (dg ? 4.0 : 2.0) * hv * hv;
                         }
                     }
                 }
-            // accumulator register q: vector 4 q + u, row 16 b + j16
+            // accumulator of group g: vector 4 g + u, row 16 b + j16
 #pragma unroll
-            for (int q = 0; q < 2; ++q)
-                if (4 * q + u < m)
+            for (int g = 0; g < G; ++g)
+                if (4 * g + u < m)
 #pragma unroll
-                    for (int b = 0; b < 2; ++b) y[(4 * q + u) * BPITCH + I * BNB + 16 * b + j16] += accr[b][q];
+                    for (int b = 0; b < 2; ++b) y[(4 * g + u) * BPITCH + I * BNB + 16 * b + j16] += accr[b][g];
             if constexpr (WA)
 #pragma unroll
                 for (int b = 0; b < 2; ++b) {
@@ -957,9 +1009,9 @@ SPD_DEV void b_sym(const double *A, int n, int m, const double *x, double *y, do
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
 #pragma unroll
-            for (int q = 0; q < 2; ++q)
-                if (4 * q + u < m)
-                    tb[(4 * q + u) * BNB + 16 * h + j16] = accc[h][q];
+            for (int g = 0; g < G; ++g)
+                if (4 * g + u < m)
+                    tb[(4 * g + u) * BNB + 16 * h + j16] = accc[h][g];
             if constexpr (WA) {
                 double v = cs[h];
                 v += __shfl_xor(v, 16);
@@ -996,42 +1048,63 @@ __device__ __attribute__((noinline)) void b_residual(const double *A, int n, int
     A = uni(A);
     const auto gX = gmem(uni(X)), gB = gmem(uni(B)), gd = gmem(uni(d));
     const auto gR = gmem(uni(R));
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     double *xs = sm.ys;
     const int np = (n + BNB - 1) / BNB * BNB;
-    for (int idx = tid; idx < m * np; idx += NT) {
-        const int c = idx / np, j = idx % np;
-        xs[c * BPITCH + j] = (j < n) ? gX[j + (int64_t)c * n] : 0.0;
-    }
+    // a wave takes whole columns (as in b_solve), four rows a lane at a time
+    for (int c = wave; c < m; c += WAVES)
+        for (int i0 = lane; i0 < np; i0 += 4 * 64) {
+            double xv[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) xv[k] = gX[min(i0 + 64 * k, n - 1) + c * n];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (i0 + 64 * k < np)
+                    xs[c * BPITCH + i0 + 64 * k] = (i0 + 64 * k < n) ? xv[k] : 0.0;
+        }
     double h0 = 0.0, h1 = 0.0;
-    if (want_anorm)
-        b_sym<WAVES, true, false>(A, n, m, xs, sm.yo, sm.tb, nullptr, sm.arow, false, nullptr, h0, h1);
+    const auto ax = [&](auto groups) {
+        constexpr int G = decltype(groups)::value;
+        if (want_anorm)
+            b_sym<WAVES, G, true, false>(A, n, m, xs, sm.yo, sm.tb, nullptr, sm.arow, false, nullptr, h0, h1);
+        else
+            b_sym<WAVES, G, false, false>(A, n, m, xs, sm.yo, sm.tb, nullptr, nullptr, false, nullptr, h0, h1);
+    };
+    if (m <= 4)
+        ax(std::integral_constant<int, 1>());
     else
-        b_sym<WAVES, false, false>(A, n, m, xs, sm.yo, sm.tb, nullptr, nullptr, false, nullptr, h0, h1);
+        ax(std::integral_constant<int, 2>());
     // r and the maxima (NaN propagates), per column
-    for (int c = 0; c < m; ++c) {
+    for (int c = wave; c < m; c += WAVES) {
         double v[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int i = tid; i < n; i += NT) {
-            const double b = gB[i + (int64_t)c * n], r = b - sm.yo[c * BPITCH + i];
-            gR[i + (int64_t)c * n] = r;
-            v[0] = b_nanmax(v[0], fabs(r));
-            v[1] = b_nanmax(v[1], fabs(xs[c * BPITCH + i]));
-            v[2] = b_nanmax(v[2], fabs(b));
-            v[3] = b_nanmax(v[3], fabs(gd[i] * r));
+        for (int i0 = lane; i0 < n; i0 += 4 * 64) {
+            double bv[4], dv[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = min(i0 + 64 * k, n - 1);
+                bv[k] = gB[i + c * n];
+                dv[k] = gd[i];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = i0 + 64 * k;
+                if (i < n) {
+                    const double r = bv[k] - sm.yo[c * BPITCH + i];
+                    gR[i + c * n] = r;
+                    v[0] = b_nanmax(v[0], fabs(r));
+                    v[1] = b_nanmax(v[1], fabs(xs[c * BPITCH + i]));
+                    v[2] = b_nanmax(v[2], fabs(bv[k]));
+                    v[3] = b_nanmax(v[3], fabs(dv[k] * r));
+                }
+            }
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) v[k] = b_nanmax(v[k], __shfl_xor(v[k], off));
             if (lane == 0)
-                sm.red[wave][k * m + c] = v[k];
+                sm.norms[1 + k * m + c] = v[k];
         }
-    }
-    __syncthreads();
-    if (tid < 4 * m) {
-        double x = 0.0;
-        for (int w = 0; w < WAVES; ++w) x = b_nanmax(x, sm.red[w][tid]);
-        sm.norms[1 + tid] = x;
     }
     if (want_anorm) {
         __syncthreads();
@@ -1107,9 +1180,9 @@ SPD_DEV void b_hv(const double *A, int n, const double *v, double *y, bool first
     const int np = (n + BNB - 1) / BNB * BNB;
     for (int i = tid; i < np; i += NT) sm.x[i] = (i < n) ? sm.d[i] * v[i] : 0.0;
     if (first)
-        b_sym<WAVES, true, true>(A, n, 1, sm.x, y, sm.tb, sm.d, sm.rs, true, sm.d, hmax, fro);
+        b_sym<WAVES, 1, true, true>(A, n, 1, sm.x, y, sm.tb, sm.d, sm.rs, true, sm.d, hmax, fro);
     else
-        b_sym<WAVES, false, false>(A, n, 1, sm.x, y, sm.tb, nullptr, nullptr, false, nullptr, hmax, fro);
+        b_sym<WAVES, 1, false, false>(A, n, 1, sm.x, y, sm.tb, nullptr, nullptr, false, nullptr, hmax, fro);
     for (int i = tid; i < n; i += NT) {
         y[i] *= sm.d[i];
         if (first)
