@@ -1,0 +1,43 @@
+"""The factorisation at the edges of its tiles: orders around the 16-column
+halves and 32-column strips of a diagonal block, around whole panels and (in
+binary64) around the 64- and 128-row tiles of the trailing update, each
+against its own backward error bound |H - L L^T| <= 4 (n + 1) u |L||L^T|
+elementwise, as in the parity tests; and the breakdown column at the first and
+last columns of halves, strips and panels, which has to be the oracle's."""
+import numpy as np
+import pytest
+
+import spdgen
+from test_gpu_parity import _say, dev, host
+
+pytestmark = pytest.mark.gpu
+U = {"fp32": 2.0 ** -24, "fp64": 2.0 ** -53}
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 31, 32, 33, 48, 65, 97, 127, 128, 129, 161, 256, 385, 640, 1153])
+def test_backward_error(spd, n, prec):
+    _say(f"factor edges {prec} n={n}")
+    A = spdgen.logspaced(n, 1e2, 700 + n)
+    F, info, st = spd.factor(dev(A), prec)
+    assert info == 0 and st == 0
+    L, d, mu = spd.export(F)
+    L, d = host(L), host(d)
+    F.close()
+    H = (((d[:, None] * A) * d[None, :]).astype(np.float32).astype(np.float64)) if prec == "fp32" else A
+    assert np.count_nonzero(np.triu(L, 1)) == 0
+    E = np.abs(H - L @ L.T)
+    assert np.all(E <= 4 * (n + 1) * U[prec] * (np.abs(L) @ np.abs(L.T))), np.max(E)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_breakdown_columns(spd, orc, prec):
+    n = 300
+    for j0 in (1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 64, 65, 80, 96, 97, 112, 113, 127, 128, 129, 144, 145, 256,
+               272, 273, 300):
+        _say(f"breakdown edges {prec} j0={j0}")
+        A = spdgen.indefinite(n, j0, seed=90 + j0)
+        F, info, st = spd.factor(dev(A), prec)
+        if F is not None:
+            F.close()
+        assert st == spd.ERR_NOT_SPD and info == j0, (j0, info, st)
