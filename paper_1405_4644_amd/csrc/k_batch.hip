@@ -2,8 +2,8 @@
 // system) in one persistent launch, each system taken through all of
 // Algorithm 1 by one workgroup:
 //   equilibrate and round (mu D A D), left-looking blocked Cholesky in the
-//   factor's precision (32-wide panels on MFMA, with binary16 / bfloat16
-//   rounded operands for the half formats), triangular solves on MFMA with
+//   factor's precision (32-wide panels on MFMA; half-precision requests:
+//   k_batch_half.h), triangular solves on MFMA with
 //   the 32 x 32 diagonal-block inverses, binary64 residual and backward error,
 //   correction loop with the same stopping, divergence and fallback rules as
 //   the single-system path (BF16/FP16 -> FP32 -> FP64).
@@ -53,6 +53,7 @@ struct BatchWs {
     void *Winv;   // the inverses of its diagonal tiles, in the same layout
     double *d;    // equilibration
     double *R;    // n x m residual
+    double *Am;   // half-precision requests: A's strict lower triangle mirrored into the strict upper of an np x np array
 };
 
 SPD_DEV BatchWs batch_ws(const BatchArgs &a)
@@ -66,6 +67,8 @@ SPD_DEV BatchWs batch_ws(const BatchArgs &a)
     w.d = (double *)p;
     p += (int64_t)SPD_BATCH_NMAX * 8;
     w.R = (double *)p;
+    p += (int64_t)SPD_BATCH_NMAX * SPD_BATCH_MAXRHS * 8;
+    w.Am = (double *)p;
     return w;
 }
 
@@ -142,6 +145,8 @@ SPD_DEV double rl(double v, int src)
     const int hi = __builtin_amdgcn_readlane((int)(b >> 32), src);
     return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
 }
+
+#include "k_batch_half.h"
 
 // ---------------------------------------------------------------------------
 // The factor is stored as 32 x 32 tiles, tile (I, J) at 1024 (I (I + 1)/2 + J),
@@ -384,9 +389,7 @@ SPD_DEV int b_diag(float *Ws, float *Lr, float *buf) { return b_diag_body<float>
 // from A in the waves' accumulators (d_i = a_ii^{-1/2} also goes to d), take
 // the products of the earlier panels, the diagonal one is factored by wave 0,
 // and the others become L_Ik = H_Ik W^T, W the diagonal tile's inverse, and
-// are stored once.  With half != HALF_NONE the products' operands are rounded
-// to that format (binary32 accumulation).  Returns the 1-based failing column
-// (0 on success).
+// are stored once.  Returns the 1-based failing column (0 on success).
 //
 // Bound by memory traffic, with 512 systems in flight.  Right-looking, with H
 // written out by a conversion and every trailing tile read and written once
@@ -396,7 +399,7 @@ SPD_DEV int b_diag(float *Ws, float *Lr, float *buf) { return b_diag_body<float>
 // 20 and 17 GB, 194 and 330 us.
 template <typename T, int WAVES>
 __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np, double *d, double mu, int equil,
-                                                  T *L, T *Winv, int half, SolveSmem &sm)
+                                                  T *L, T *Winv, SolveSmem &sm)
 {
     const auto gA = gmem(uni(A));
     const auto gd = gmem(uni(d));
@@ -404,7 +407,6 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
     Winv = uni(Winv);
     n = uni(n);
     np = uni(np);
-    half = uni(half);
     equil = uni(equil);
     constexpr int NT = WAVES * 64;
     static_assert(BNB * (BNB + 1) * 8 <= (int)sizeof(sm.tb), "inverse of the diagonal block");
@@ -453,17 +455,11 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
         if (kb == 0)
             return;
         if constexpr (sizeof(T) == 4) {
-            auto rounded = [&](BTile<T> &f) {
-                if (half)
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) f.v[j] = round_half(f.v[j], half);
-            };
             BTile<T> fk, fi, fkn, nx;
             fk.load(b_tile(L, kb, 0), lane);
             fi.load(b_tile(L, I0, 0), lane);
             for (int q = 0; q < kb; ++q) {
                 const int qn = min(q + 1, kb - 1);
-                rounded(fk);
                 fkn.load(b_tile(L, kb, qn), lane);
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
@@ -472,7 +468,6 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
                         break;
                     const bool last = s + 1 == NS || I + step >= nb;
                     nx.load(last ? b_tile(L, I0, qn) : b_tile(L, I + step, q), lane);
-                    rounded(fi);
                     BTile<T>::submul(acc[s], fk, fi);
                     fi = nx;
                 }
@@ -517,9 +512,6 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
             nx.load(b_tile(L, kb, min(q + 1, kb - 1)), lane);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (sizeof(T) == 4) {
-                if (half)
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) f.v[j] = round_half(f.v[j], half);
                 BTile<T>::submul(acc, f, f);
             } else {
 #pragma unroll
@@ -1396,9 +1388,9 @@ SPD_DEV int b_pick(const float *P, PickSmem &sm)
 // accepted at eta <= tol.  Divergence as before; max_iter corrections
 // without success: no convergence.  Returns SPD_OK or SPD_ERR_NO_CONVERGENCE
 // and fills the iteration counts and eta.
-template <typename T, int WAVES>
-SPD_DEV int b_refine(const BatchArgs &a, const double *A, const double *B, double *X, int n, int np, int m,
-                     const BatchWs &w, double mu, spd_report &rep, SolveSmem &sm)
+// residual(first) and solve() as in b_residual and b_solve, by the caller.
+template <typename T, typename Smem, typename Res, typename Sol>
+SPD_DEV int b_refine(double tol, int max_iter, int m, spd_report &rep, Smem &sm, Res residual, Sol solve)
 {
     constexpr double U = 0x1p-53, FLOOR = 0x1p-51;
     constexpr bool STABLE = sizeof(T) == 8;
@@ -1419,7 +1411,7 @@ SPD_DEV int b_refine(const BatchArgs &a, const double *A, const double *B, doubl
     for (;;) {
         const int first = (rep.iters_high == 0);
         const int k = rep.iters_high;  // corrections applied so far
-        b_residual<WAVES>(A, n, m, X, B, w.d, w.R, first, sm);
+        residual(first);
         rep.iters_high++;
         if (first)
             anorm = sm.norms[0];
@@ -1443,7 +1435,7 @@ SPD_DEV int b_refine(const BatchArgs &a, const double *A, const double *B, doubl
                 const double zn = __longlong_as_double((long long)sm.zmax[c]);
                 zeta[c] = (zn == 0.0) ? 0.0 : zn / xn;
             }
-            if (!done[c] && v <= a.tol) {
+            if (!done[c] && v <= tol) {
                 if (v == 0.0 || zeta[c] <= U) {
                     done[c] = true;
                 } else if (k == 0) {
@@ -1458,7 +1450,7 @@ SPD_DEV int b_refine(const BatchArgs &a, const double *A, const double *B, doubl
         rep.eta = finite ? worst : __builtin_nan("");
         if (!finite)
             return SPD_ERR_NO_CONVERGENCE;
-        if (all && worst <= a.tol)
+        if (all && worst <= tol)
             return SPD_OK;
         if (k == 0) {
             eta0 = worst;
@@ -1469,10 +1461,10 @@ SPD_DEV int b_refine(const BatchArgs &a, const double *A, const double *B, doubl
                 if (c < m && !(eta[c] > 0.9 * eprev[c]))
                     all_slow = false;
             stalls = all_slow ? stalls + 1 : 0;
-            if (worst > a.tol && (worst > eta0 || stalls >= 2))
+            if (worst > tol && (worst > eta0 || stalls >= 2))
                 return SPD_ERR_NO_CONVERGENCE;
         }
-        if (rep.iters_low > a.max_iter)
+        if (rep.iters_low > max_iter)
             return SPD_ERR_NO_CONVERGENCE;
 #pragma unroll
         for (int c = 0; c < MR; ++c) {
@@ -1483,14 +1475,14 @@ SPD_DEV int b_refine(const BatchArgs &a, const double *A, const double *B, doubl
         if (threadIdx.x < m)
             sm.smax[threadIdx.x] = sm.norms[1 + 3 * m + threadIdx.x];
         __syncthreads();
-        b_solve<T, WAVES>((const T *)w.L, (const T *)w.Winv, n, np, m, w.R, w.d, mu, X, 1, sm);
+        solve();
         rep.iters_low++;
     }
 }
 
 // smax[c] = max_i |d_i B[i][c]| (the first solve's scaling)
-template <int WAVES>
-SPD_DEV void b_rhs_max(const double *B, const double *d, int n, int m, SolveSmem &sm)
+template <int WAVES, typename Smem>
+SPD_DEV void b_rhs_max(const double *B, const double *d, int n, int m, Smem &sm)
 {
     double v[SPD_BATCH_MAXRHS];
 #pragma unroll
@@ -1515,22 +1507,40 @@ SPD_DEV void b_rhs_max(const double *B, const double *d, int n, int m, SolveSmem
     __syncthreads();
 }
 
-// Factor in the factor type T at precision p (binary32 factor for BF16, FP16,
-// FP32: equilibrated, mu for FP16, rounded update operands for the half
-// formats; binary64 factor of A itself for FP64).  Returns the 1-based
-// failing column (0 on success).
-template <typename T, int WAVES>
-SPD_DEV int b_factor_p(const BatchArgs &a, const double *A, int n, int np, const BatchWs &w, int p, double &mu,
-                       SolveSmem &sm)
+// One attempt at a half precision (k_batch_half.h); its counts, eta and failing
+// column in sm.rep.  Returns SPD_OK, SPD_ERR_NOT_SPD or SPD_ERR_NO_CONVERGENCE.
+template <int WAVES>
+__device__ __attribute__((noinline)) int b_half(const double *A, const double *B, double *X, int n, int np, int m,
+                                                void *Lp, void *Wp, double *d, double *R, double *Am, double mu,
+                                                int equil, int half, double tol, int max_iter,
+                                                half_path::SolveSmem &sm)
 {
-    if constexpr (sizeof(T) == 8) {
-        mu = 1.0;
-        return b_factor<double, WAVES>(A, n, np, w.d, 1.0, 0, (double *)w.L, (double *)w.Winv, HALF_NONE, sm);
-    } else {
-        mu = (p == SPD_FP16) ? a.mu16 : 1.0;
-        const int half = (p == SPD_FP16) ? HALF_F16 : (p == SPD_BF16) ? HALF_BF16 : HALF_NONE;
-        return b_factor<float, WAVES>(A, n, np, w.d, mu, a.equilibrate, (float *)w.L, (float *)w.Winv, half, sm);
+    n = uni(n);
+    np = uni(np);
+    m = uni(m);
+    float *L = (float *)Lp, *Winv = (float *)Wp;
+    spd_report rep;
+    rep.iters_low = rep.iters_high = 0;
+    rep.eta = 0.0;
+    int r = SPD_ERR_NOT_SPD;
+    half_path::b_convert<WAVES>(A, n, np, d, mu, equil, L, Am, sm);
+    const int info = half_path::b_factor<WAVES>(L, np, Winv, half, sm);
+    if (!info) {
+        b_rhs_max<WAVES>(B, d, n, m, sm);
+        half_path::b_solve<WAVES>(L, Winv, n, np, m, B, d, mu, X, 0, sm);
+        r = b_refine<float>(
+            tol, max_iter, m, rep, sm,
+            [&](int first) { half_path::b_residual<WAVES>(A, Am, n, np, m, X, B, d, R, first, sm); },
+            [&]() { half_path::b_solve<WAVES>(L, Winv, n, np, m, R, d, mu, X, 1, sm); });
     }
+    if (threadIdx.x == 0) {
+        sm.rep.info = info;
+        sm.rep.iters_low = rep.iters_low;
+        sm.rep.iters_high = rep.iters_high;
+        sm.rep.eta = rep.eta;
+    }
+    __syncthreads();
+    return r;
 }
 
 // One system through Algorithm 1 by one workgroup, at the precisions of the
@@ -1574,21 +1584,35 @@ SPD_DEV void b_system(const BatchArgs &a, int64_t s, SolveSmem &sm)
         double *X = a.X + a.b_off[s];
         const int np = ((n + BNB - 1) / BNB) * BNB;
         const BatchWs w = batch_ws(a);
-        double mu = 1.0;
         int status = SPD_OK;
         for (;;) {
-            const int info = b_factor_p<T, WAVES>(a, A, n, np, w, p, mu, sm);
-            rep.info = info;
+            // a binary32 factor is equilibrated (for FP16 with mu), a binary64
+            // one that of A itself
+            int info, r = SPD_ERR_NOT_SPD;
             rep.prec_used = p;
-            int r;
-            if (info) {
-                r = SPD_ERR_NOT_SPD;
+            // factor; the first solve from B, then refinement
+            if (!HI && p != SPD_FP32) {
+                static_assert(sizeof(half_path::SolveSmem) <= sizeof(SolveSmem), "one workgroup's shared memory");
+                half_path::SolveSmem &hs = reinterpret_cast<half_path::SolveSmem &>(sm);
+                r = b_half<WAVES>(A, B, X, n, np, m, w.L, w.Winv, w.d, w.R, w.Am, p == SPD_FP16 ? a.mu16 : 1.0,
+                                  a.equilibrate, p == SPD_FP16 ? HALF_F16 : HALF_BF16, a.tol, a.max_iter, hs);
+                info = (int)hs.rep.info;
+                rep.iters_low = hs.rep.iters_low;
+                rep.iters_high = hs.rep.iters_high;
+                rep.eta = hs.rep.eta;
+                __syncthreads();
             } else {
-                // first solve from B, then refinement
-                b_rhs_max<WAVES>(B, w.d, n, m, sm);
-                b_solve<T, WAVES>((const T *)w.L, (const T *)w.Winv, n, np, m, B, w.d, mu, X, 0, sm);
-                r = b_refine<T, WAVES>(a, A, B, X, n, np, m, w, mu, rep, sm);
+                T *L = (T *)w.L, *Winv = (T *)w.Winv;
+                info = b_factor<T, WAVES>(A, n, np, w.d, 1.0, HI ? 0 : a.equilibrate, L, Winv, sm);
+                if (!info) {
+                    b_rhs_max<WAVES>(B, w.d, n, m, sm);
+                    b_solve<T, WAVES>(L, Winv, n, np, m, B, w.d, 1.0, X, 0, sm);
+                    r = b_refine<T>(
+                        a.tol, a.max_iter, m, rep, sm, [&](int first) { b_residual<WAVES>(A, n, m, X, B, w.d, w.R, first, sm); },
+                        [&]() { b_solve<T, WAVES>(L, Winv, n, np, m, w.R, w.d, 1.0, X, 1, sm); });
+                }
             }
+            rep.info = info;
             if (r == SPD_OK || !a.fallback || HI) {
                 status = r;
                 break;
@@ -1724,7 +1748,8 @@ namespace spd {
 int64_t batch_ws_stride()
 {
     int64_t b = (int64_t)SPD_BATCH_NMAX * SPD_BATCH_NMAX * 8 + (int64_t)SPD_BATCH_NMAX * BNB * 8 +
-                (int64_t)SPD_BATCH_NMAX * 8 + (int64_t)SPD_BATCH_NMAX * SPD_BATCH_MAXRHS * 8;
+                (int64_t)SPD_BATCH_NMAX * 8 + (int64_t)SPD_BATCH_NMAX * SPD_BATCH_MAXRHS * 8 +
+                (int64_t)SPD_BATCH_NMAX * SPD_BATCH_NMAX * 8;
     return (b + 255) / 256 * 256;
 }
 

@@ -37,3 +37,21 @@ def test_breakdown_column_in_the_block(spd, orc, prec):
     for s, j0 in enumerate(cols):
         assert reps[s]["status"] == spd.ERR_NOT_SPD, (j0, reps[s])
         assert int(reps[s]["info"]) == j0, (j0, reps[s])
+
+
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+def test_half_requests_by_themselves_and_falling_back(spd, prec):
+    """Half requests have a path of their own in the launch that also holds the
+    binary32 ones: the same systems beside binary32 requests give the same
+    bits, and what falls back ends as a binary32 request does."""
+    shapes = [(n, cond, m) for n, cond, m in ((33, 1e1, 1), (64, 1e6, 3), (130, 1e1, 8), (257, 1e6, 2), (300, 1e1, 4))]
+    _say("batched half beside binary32", prec)
+    pb = spdgen.packed_batch(shapes, config=3, first_index=6000)
+    _, X1, r1, p1 = _run(spd, pb, prec)
+    _, X2, r2, p2 = _run(spd, pb, [prec, "fp32", prec, "fp32", prec])
+    _, X3, r3, p3 = _run(spd, pb, "fp32")
+    assert np.all(r1["status"] == 0) and list(r1["fallbacks"]) == [0, 1, 0, 1, 0], r1
+    assert list(p1) == list(p2) and np.array_equal(X1, X2) and np.array_equal(r1["eta"], r2["eta"])
+    for s in (1, 3):
+        lo, hi = pb.b_off[s], pb.b_off[s] + shapes[s][0] * shapes[s][2]
+        assert p1[s] == p3[s] == spd.PREC["fp32"] and np.array_equal(X1[lo:hi], X3[lo:hi])
