@@ -38,8 +38,9 @@ struct spd_factor_s {
     int64_t cap_d = 0;
     double mu = 1.0;
     int half = HALF_NONE;    // operand rounding of the trailing update (BF16 / FP16 factors)
-    int group = 4;           // panels per trailing-update group, binary32/64 (SPD_GROUP overrides)
-    int group_half = 8;      // the same for binary16/bfloat16 operands, even, <= 8 (SPD_GROUP_HALF overrides)
+    // the schedule (default_schedule, the tuner's, or the environment's)
+    int group = 4;           // panels per trailing-update group, binary32/64 (SPD_GROUP)
+    int group_half = 8;      // the same for binary16/bfloat16 operands, even, <= 8 (SPD_GROUP_HALF)
     bool small_main = false; // a group's thin trailing updates on 64-tiles too (SPD_SMALL_MAIN=1)
     bool pinned = false;     // schedule fixed by the environment or the tuner: no cache lookup
     int upd_slots = 0;       // cap on the main-stream update's workgroups (SPD_UPD_SLOTS; 0: one per tile)
@@ -392,6 +393,32 @@ spd_status prepare_factor(spd_factor_t F, int64_t n, int prec, double theta, hip
     return SPD_OK;
 }
 
+// The factorisation's schedule where neither the environment nor the tuner has
+// set one (it changes no result).  The main stream's update leaves an eighth
+// of its slots (a quarter at one 256 x 256 tile per compute unit) to the panel
+// chain, whose kernels otherwise wait beside it for a workgroup to end: at
+// n = 16384, capped and not, binary64 30.3 and 31.0 ms, binary32 15.9 and 16.4,
+// binary16 7.10 and 7.75; n = 4096 2.07 and 2.13, 1.40 and 1.44, 1.28 and 1.29.
+// Wider groups move the trailing columns less often, but the chain takes the
+// group's own updates: binary32 with 2, 4 and 6 panels 1.40, 1.44 and 1.50 ms
+// at n = 4096, 5.75, 5.43 and 5.56 at 10000, -, 16.4 and 15.9 at 16384 (and
+// binary64's lines cross at the same orders); binary16 with 2, 4 and 8 panels
+// 0.69, 0.71 and 0.74 at 2000, -, 2.66 and 2.80 at 8192, -, 8.2 and 7.1 at
+// 16384 (12000: 4.47 and 4.48).  A few panels are one group: no second stream
+// (n = 300, a solve with 2 and 4 panels: 301 and 274-290 us; n = 1300: 802 and
+// 797).
+void default_schedule(spd_factor_t F, bool half)
+{
+    if (half) {
+        F->group_half = F->npad <= 1024 ? 8 : (F->npad < 2560 ? 2 : (F->npad < 13312 ? 4 : 8));
+        F->upd_slots = 192;
+    } else {
+        F->group = F->npad < 1536 ? 4 : (F->npad < 5120 ? 2 : (F->npad < 13312 ? 4 : 6));
+        F->upd_slots = 448;
+        F->small_main = false;
+    }
+}
+
 spd_status do_factor(spd_factor_t F, const double *A, int64_t n, int64_t lda, int prec, const spd_opts &o,
                      hipStream_t st, int64_t *info, bool sync = true)
 {
@@ -400,6 +427,7 @@ spd_status do_factor(spd_factor_t F, const double *A, int64_t n, int64_t lda, in
     F->imported = false;
     if (!F->pinned) {
         // the autotuner's schedule for this precision and size, when there is one
+        default_schedule(F, prec == SPD_FP16 || prec == SPD_BF16);
         spd::TuneVal tv;
         if (spd::tune_lookup(spd::tune_key(prec_tag(prec), spd::tune_bucket(n)), &tv)) {
             if (prec == SPD_FP16 || prec == SPD_BF16) {
@@ -1229,7 +1257,8 @@ spd_status spd_autotune(int64_t n, spd_prec prec, void *hip_stream, spd_tune_res
             cand.push_back({g, 448, 0});
         }
     } else {
-        for (int g : {2, 4, 6, 8}) cand.push_back({g, 0, 0});
+        for (int g : {2, 4, 6, 8})
+            for (int c : {0, 448}) cand.push_back({g, c, 0});
     }
     hipStream_t st = (hipStream_t)hip_stream;
     double *A = nullptr;
