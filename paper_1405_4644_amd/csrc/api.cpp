@@ -862,9 +862,13 @@ spd_status cg_refine(spd_cg_t H, const double *A, int64_t lda, const double *B, 
     int *go_h = H->flags_host + 2 * m;
     const double it2 = o.inner_tol * o.inner_tol;
     const int nn = 1 + 5 * m;  // as refine_once: the last m hold each column's change over its phase
-    // iterations launched between host checks: a dense product is long
-    // enough that one check per iteration costs nothing
-    const int S = (k < 0) ? 2 : 16;
+    // iterations launched between host checks (even).  At a check the device
+    // idles until the host has seen it; an iteration launched after the last
+    // column's end costs its empty kernels.  Dense with 2 (a check then cost
+    // as much as a short product), 8, 16 and 32: n = 1529 2611, 2110, 1971 and
+    // 2194 us, n = 4000 with 20 right-hand sides 5664, 5009, 4961 and 5154,
+    // n = 10000 16.8, 16.1, 16.0 and 16.0 ms.
+    const int S = 16;
     const double band_w = (k < 0) ? (double)n : (double)(2 * k + 1);
     const double mv_flops = 2.0 * band_w * n * m, mv_bytes = 4.0 * band_w * n + 20.0 * n * m;
     // S CG iterations: product, x/r update, p update (parity slot s & 1).  A
@@ -893,7 +897,8 @@ spd_status cg_refine(spd_cg_t H, const double *A, int64_t lda, const double *B, 
     };
     // Banded iterations are launch-bound: the S iterations between host
     // checks are captured once per call into a graph (all arguments are fixed
-    // for the call) and replayed.  Not while kernel profiling is on (its
+    // for the call) and replayed (dense ones are not: n = 1529 2044 us with a
+    // graph, 1971 without).  Not while kernel profiling is on (its
     // events bracket single launches), and any capture failure falls back to
     // direct launches.
     hipGraphExec_t gexec = nullptr;
