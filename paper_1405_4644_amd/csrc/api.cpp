@@ -841,8 +841,8 @@ spd_status cg_ensure_ws(spd_cg_t H, int m, hipStream_t st)
     HIP_TRY(hipMalloc(&H->rscr, (size_t)spd::resid_scratch(n, m) * sizeof(double)));
     if (H->k < 0) HIP_TRY(hipMalloc(&H->Pf, (size_t)spd::cg_pf_elems(ldt, m) * sizeof(float)));
     if (H->k >= 0 && spd::cg_band_fused(H->k)) HIP_TRY(hipMalloc(&H->P2, nm));
-    if (H->k < 0 && spd::cg_zp_elems(n, m) > 0)
-        HIP_TRY(hipMalloc(&H->Zp, (size_t)spd::cg_zp_elems(n, m) * sizeof(float)));
+    if (H->k < 0 && spd::cg_zp_elems(n, ldt, m) > 0)
+        HIP_TRY(hipMalloc(&H->Zp, (size_t)spd::cg_zp_elems(n, ldt, m) * sizeof(float)));
     HIP_TRY(hipMalloc(&H->flags, (size_t)4 * m * sizeof(int)));
     HIP_TRY(hipHostMalloc(&H->norms_host, (size_t)(1 + 5 * m) * sizeof(double), hipHostMallocDefault));
     HIP_TRY(hipHostMalloc(&H->flags_host, (size_t)4 * m * sizeof(int), hipHostMallocDefault));
@@ -890,7 +890,8 @@ spd_status cg_refine(spd_cg_t H, const double *A, int64_t lda, const double *B, 
                 spd::launch_cg_mv_band(H->At, ldt, n, k, m, H->R, p, nullptr, H->Z, H->part, nmv, H->vpart, nv, H->sc,
                                        par, act, cnt, o.max_inner, q);
             if (pe) prof_end(pe, q, SPD_K_CG_MV, mv_flops, mv_bytes);
-            spd::launch_cg_xr(n, m, H->part, nmv, H->sc, par, p, H->Z, X, ldx, H->R, H->vpart, nv, act, q);
+            spd::launch_cg_xr(n, m, H->part, nmv, H->sc, par, p, H->Z, H->Zp, ldt, X, ldx, H->R, H->vpart, nv,
+                               act, q);
             if (!H->P2 || s == S - 1)
                 spd::launch_cg_p(n, m, H->vpart, nv, H->sc, par, H->R, p, H->P, H->Pf, ldt, act, cnt, o.max_inner, q);
         }

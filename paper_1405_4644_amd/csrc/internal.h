@@ -182,8 +182,9 @@ int cg_pf_width(int m);
 int64_t cg_pf_elems(int64_t ldt, int m);  // binary32 direction storage (elements)
 int64_t cg_mv_parts(int64_t n, int64_t ldt, int64_t k, int m);
 int64_t cg_vec_parts(int64_t n);
-// Zp: binary32 k-slice partials of the 5..32-column dense product, cg_zp_elems(n, m) elements
-int64_t cg_zp_elems(int64_t n, int m);
+// Zp: binary32 partials of dense products (of the 5..32-column one by k-slices, of one column's by
+// 256-wide tiles, then added by launch_cg_xr), cg_zp_elems(n, ldt, m) elements for m or fewer columns
+int64_t cg_zp_elems(int64_t n, int64_t ldt, int m);
 void launch_cg_mv(const float *At, int64_t ldt, int64_t n, int m, const float *Pf, const double *P,
                   double *Z, double *part, int64_t npart, const int *act, float *Zp, hipStream_t st);
 // Band product.  Pout NULL: z = A~ Pin with the state in slot par.  Pout
@@ -196,8 +197,8 @@ void launch_cg_mv_band(const float *Bd, int64_t ldt, int64_t n, int64_t k, int m
 void launch_cg_start(int64_t n, int m, const double *R, double *P, float *Pf, int64_t ldt, double *part,
                      int64_t npart, const int *go, hipStream_t st);
 void launch_cg_xr(int64_t n, int m, const double *pzp, int64_t npz, const double *sc, int par, const double *P,
-                  const double *Z, double *X, int64_t ldx, double *R, double *part, int64_t npart, const int *act,
-                  hipStream_t st);
+                  const double *Z, const float *Zp, int64_t ldt, double *X, int64_t ldx, double *R, double *part,
+                  int64_t npart, const int *act, hipStream_t st);
 void launch_cg_p(int64_t n, int m, const double *rrp, int64_t nrr, double *sc, int par, const double *R,
                  const double *Pin, double *P, float *Pf, int64_t ldt, int *act, int *cnt, int max_inner,
                  hipStream_t st);

@@ -205,6 +205,96 @@ __global__ __launch_bounds__(256) void k_cg_mv_valu(const float *__restrict__ Af
     }
 }
 
+// z = A~ p for one right-hand side from A~'s lower triangle: a workgroup takes
+// a 256 x 256 tile (IB, JB), JB <= IB, as it is stored, its waves 64 of the
+// columns j each.  With a_ij a lane has both terms: z_i += a_ij p_j, in eight
+// accumulators (row i % 32 of the tile's eight column blocks) over the wave's
+// columns, and z_j += a_ij p_i, in eight (its columns of one row block) over
+// the eight column blocks, then over the 32 lanes by halving exchanges.  A
+// diagonal tile is read whole, for z_i only.  The tile's sums go to Zp[JB][i]
+// and Zp[IB][j] (k_cg_xr adds a row's nb of them in order); one binary64
+// partial of p^T z per tile.
+// Bound by reading the triangle.  Reading all of A~ (k_cg_mv_valu), a solve at
+// n = 10000 took 16.0 ms (80 us a product, 5.0 TB/s), now 8.8; n = 7000 6.7 and
+// 5.2 ms, n = 4000 3.89 and 3.23.  From CG_SYM_MIN on: 3072 3.07 and 2.91 ms;
+// below it the tiles are too few (2816 2.92 and 2.95, 1529 1.97 and 2.48).
+constexpr int64_t CG_SYM_MIN = 3072;
+inline bool cg_sym(int64_t ldt, int m) { return m == 1 && ldt >= CG_SYM_MIN; }
+__global__ __launch_bounds__(256) void k_cg_mv_sym(const float *__restrict__ Af, int64_t ldt, int64_t n,
+                                                   const float *__restrict__ Pf, const double *__restrict__ P,
+                                                   float *__restrict__ Zp, double *__restrict__ part,
+                                                   const int *__restrict__ act)
+{
+    __shared__ float si[4][256], sj[256];
+    __shared__ double red[4];
+    if (!act[0]) return;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = lane >> 5, l32 = lane & 31;
+    const int64_t q = blockIdx.x;  // q = IB (IB + 1) / 2 + JB
+    int64_t IB = (int64_t)((sqrt(8.0 * (double)q + 1.0) - 1.0) * 0.5);
+    while (IB * (IB + 1) / 2 > q) --IB;
+    while ((IB + 1) * (IB + 2) / 2 <= q) ++IB;
+    const int64_t JB = q - IB * (IB + 1) / 2;
+    const int64_t nJ = ldt / 16;
+    const bool off = IB != JB;
+    const float *ab = Af + (IB * 8 * nJ + JB * 16 + 4 * w) * 512 + lane * 4;
+    const float *pj = Pf + JB * 256 + 64 * w + 8 * h;
+    float pi[8], zi[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        pi[c] = Pf[IB * 256 + 32 * c + l32];
+        zi[c] = 0.0f;
+    }
+#pragma unroll 1
+    for (int J = 0; J < 4; ++J) {
+        floatx4 a[8][2];
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) a[c][e] = *reinterpret_cast<const floatx4 *>(ab + (c * nJ + J) * 512 + 256 * e);
+        const floatx4 p[2] = {*reinterpret_cast<const floatx4 *>(pj + 16 * J),
+                              *reinterpret_cast<const floatx4 *>(pj + 16 * J + 4)};
+        float zj[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) zj[e] = 0.0f;
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                zi[c] = fmaf(a[c][e >> 2][e & 3], p[e >> 2][e & 3], zi[c]);
+                zj[e] = fmaf(a[c][e >> 2][e & 3], pi[c], zj[e]);
+            }
+        // over the 32 lanes: bit 4 of the lane takes columns 4 .. 7 or 0 .. 3,
+        // bits 3 and 2 halve again
+#pragma unroll
+        for (int d = 16, k = 4; d >= 4; d >>= 1, k >>= 1)
+#pragma unroll
+            for (int e = 0; e < k; ++e) {
+                const bool up = (l32 & d) != 0;
+                const float keep = up ? zj[e + k] : zj[e], send = up ? zj[e] : zj[e + k];
+                zj[e] = keep + __shfl_xor(send, d, 64);
+            }
+        float z = zj[0];
+        z += __shfl_xor(z, 2, 64);
+        z += __shfl_xor(z, 1, 64);
+        if ((l32 & 3) == 0) sj[64 * w + 16 * J + 8 * h + (l32 >> 2)] = z;
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        zi[c] += __shfl_xor(zi[c], 32, 64);
+        if (h == 0) si[w][32 * c + l32] = zi[c];
+    }
+    __syncthreads();
+    const int64_t i = IB * 256 + tid, j = JB * 256 + tid;
+    const float vi = ((si[0][tid] + si[1][tid]) + si[2][tid]) + si[3][tid], vj = sj[tid];
+    Zp[JB * ldt + i] = vi;
+    if (off) Zp[IB * ldt + j] = vj;
+    double pz = (i < n) ? P[i] * (double)vi : 0.0;
+    if (off) pz += P[j] * (double)vj;  // (j < n: the tile is not a last column's)
+    pz = block_sum256(pz, red);
+    if (tid == 0) part[q] = pz;
+}
+
 // z = A~ p for 5..32 right-hand sides per launch row (blockIdx.y picks the
 // block of 32) on v_mfma_f32_32x32x2f32, split along k over CG_KS slices.
 // Workgroup b owns the 32 rows of z of column block b / CG_KS and the
@@ -461,15 +551,30 @@ __device__ inline double sum_parts(const double *part, int64_t npart, int b, dou
 // alpha = rho / p^T z (from the product's partials, summed identically in
 // every block), x += alpha p, r -= alpha z, and a partial of the new r^T r
 // (blockIdx.y = column)
+template <bool SYM>
 __global__ __launch_bounds__(256) void k_cg_xr(int64_t n, int m, const double *__restrict__ pzp, int64_t npz,
                                                const double *__restrict__ rho, const double *__restrict__ P,
-                                               const double *__restrict__ Z, double *__restrict__ X, int64_t ldx,
+                                               const double *__restrict__ Z, const float *__restrict__ Zp, int64_t ldt,
+                                               double *__restrict__ X, int64_t ldx,
                                                double *__restrict__ R, double *__restrict__ part, int64_t npart,
                                                const int *__restrict__ act)
 {
     __shared__ double red[4];
     const int b = blockIdx.y;
     if (!act[b]) return;
+    float zs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (SYM) {
+        // (ldt is a multiple of 256: a thread's last row may be past it, and
+        // then takes the last one's)
+        const float *zp[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) zp[u] = Zp + min((int64_t)blockIdx.x * 1024 + u * 256 + threadIdx.x, ldt - 1);
+        const int64_t nb = ldt / 256;
+#pragma unroll 8
+        for (int64_t k = 0; k < nb; ++k)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) zs[u] += zp[u][k * ldt];
+    }
     const double al = rho[b] / sum_parts(pzp, npz, b, red);
     double s = 0.0;
 #pragma unroll
@@ -477,7 +582,8 @@ __global__ __launch_bounds__(256) void k_cg_xr(int64_t n, int m, const double *_
         const int64_t i = (int64_t)blockIdx.x * 1024 + u * 256 + threadIdx.x;
         if (i < n) {
             X[i + (int64_t)b * ldx] += al * P[i + (int64_t)b * n];
-            const double r = R[i + (int64_t)b * n] - al * Z[i + (int64_t)b * n];
+            const double z = SYM ? (double)zs[u] : Z[i + (int64_t)b * n];
+            const double r = R[i + (int64_t)b * n] - al * z;
             R[i + (int64_t)b * n] = r;
             s += r * r;
         }
@@ -582,10 +688,14 @@ int64_t cg_pf_elems(int64_t ldt, int m)
 int64_t cg_mv_parts(int64_t n, int64_t ldt, int64_t k, int m)
 {
     if (k >= 0) return (n + 255) / 256;
+    if (cg_sym(ldt, m)) return (ldt / 256) * (ldt / 256 + 1) / 2;
     return (m <= 4) ? ldt / 32 : (n + 255) / 256;
 }
 
-int64_t cg_zp_elems(int64_t n, int m) { return (m > 4) ? (int64_t)CG_KS * m * n : 0; }
+int64_t cg_zp_elems(int64_t n, int64_t ldt, int m)
+{
+    return std::max((m > 4) ? (int64_t)CG_KS * m * n : 0, cg_sym(ldt, 1) ? ldt / 256 * ldt : 0);
+}
 
 // columns per workgroup of the band product: four, so that a few dozen row
 // blocks with several right-hand sides still spread over the chip; one where
@@ -618,6 +728,10 @@ void launch_cg_mv(const float *At, int64_t ldt, int64_t n, int m, const float *P
                   double *Z, double *part, int64_t npart, const int *act, float *Zp, hipStream_t st)
 {
     const dim3 blk(256), g((unsigned)(ldt / 32));
+    if (cg_sym(ldt, m)) {
+        hipLaunchKernelGGL(k_cg_mv_sym, dim3((unsigned)npart), blk, 0, st, At, ldt, n, Pf, P, Zp, part, act);
+        return;
+    }
     switch (m) {
     case 1: hipLaunchKernelGGL(k_cg_mv_valu<1>, g, blk, 0, st, At, ldt, n, Pf, P, Z, part, npart, act); break;
     case 2: hipLaunchKernelGGL(k_cg_mv_valu<2>, g, blk, 0, st, At, ldt, n, Pf, P, Z, part, npart, act); break;
@@ -641,11 +755,14 @@ void launch_cg_start(int64_t n, int m, const double *R, double *P, float *Pf, in
 }
 
 void launch_cg_xr(int64_t n, int m, const double *pzp, int64_t npz, const double *sc, int par, const double *P,
-                  const double *Z, double *X, int64_t ldx, double *R, double *part, int64_t npart, const int *act,
-                  hipStream_t st)
+                  const double *Z, const float *Zp, int64_t ldt, double *X, int64_t ldx, double *R, double *part,
+                  int64_t npart, const int *act, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_cg_xr, dim3((unsigned)npart, (unsigned)m), dim3(256), 0, st, n, m, pzp, npz,
-                       sc + (int64_t)par * m, P, Z, X, ldx, R, part, npart, act + (int64_t)par * m);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)npart, (unsigned)m), dim3(256), 0, st, n, m, pzp, npz,
+                           sc + (int64_t)par * m, P, Z, Zp, ldt, X, ldx, R, part, npart, act + (int64_t)par * m);
+    };
+    Zp && cg_sym(ldt, m) ? go(k_cg_xr<true>) : go(k_cg_xr<false>);
 }
 
 void launch_cg_p(int64_t n, int m, const double *rrp, int64_t nrr, double *sc, int par, const double *R,

@@ -224,3 +224,27 @@ def test_cg_tiny_systems_match_oracle(spd, orc, n, band, m):
     assert abs(rep.iters_low - ro.iters_low) <= max(3, 0.1 * ro.iters_low)
     if ro.status == 0:
         assert orc.backward_error(A, X, Bt).max() <= 1e-14
+
+
+@pytest.mark.parametrize("n", [2816, 2817, 3072, 3073, 3330])
+def test_cg_dense_product_edges(spd, orc, n):
+    """Both sides of the single column's rule (the lower triangle by 256-wide
+    tiles from 2817 rows on), whole and ragged last tiles, and a handle whose
+    workspace was made for more right-hand sides."""
+    import torch
+    k = 5
+    _say(f"cg dense edges n={n}")
+    A = spdgen.covariance(n, 2)
+    Bt = spdgen.rhs(n, 1, 300 + n)
+    Xo, ro = orc.cg_ir(A, Bt, half_band=-1, max_outer=1, max_inner=k, inner_tol=0.0)
+    X, rep = _gpu_cg(spd, A, Bt, -1, max_outer=1, max_inner=k, inner_tol=0.0)
+    assert (rep.iters_low, rep.iters_high) == (ro.iters_low, ro.iters_high) == (k, 2)
+    err = np.abs(X - Xo).max(axis=1) / np.abs(Xo).max(axis=1)
+    assert err.max() <= 4 * k * n * U32, err.max()
+    At, B6 = torch.from_numpy(A).cuda(), torch.from_numpy(spdgen.rhs(n, 6, 5)).cuda()
+    H = spd.cg_prepare(At)
+    o = spd.cg_default_opts(max_outer=1, max_inner=k, inner_tol=0.0)
+    spd.cg_refine(H, At, B6, opts=o)
+    X2, _ = spd.cg_refine(H, At, torch.from_numpy(Bt).cuda(), opts=o)
+    assert np.array_equal(X2.cpu().numpy(), X)
+    H.close()
