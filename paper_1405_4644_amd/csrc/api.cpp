@@ -394,27 +394,31 @@ spd_status prepare_factor(spd_factor_t F, int64_t n, int prec, double theta, hip
 }
 
 // The factorisation's schedule where neither the environment nor the tuner has
-// set one (it changes no result).  The main stream's update leaves an eighth
-// of its slots (a quarter at one 256 x 256 tile per compute unit) to the panel
-// chain, whose kernels otherwise wait beside it for a workgroup to end: at
-// n = 16384, capped and not, binary64 30.3 and 31.0 ms, binary32 15.9 and 16.4,
-// binary16 7.10 and 7.75; n = 4096 2.07 and 2.13, 1.40 and 1.44, 1.28 and 1.29.
+// set one (it changes no result).
+// The main stream's update leaves an eighth of its slots (a quarter at one
+// 256 x 256 tile per compute unit) to the panel chain, whose kernels otherwise
+// wait beside it for a workgroup to end: capped and not, at n = 16384 binary64
+// 30.3 and 31.0 ms, binary32 15.9 and 16.4, binary16 7.10 and 7.75; at n = 4096
+// 2.07 and 2.13, 1.40 and 1.44, 1.28 and 1.29.  A large update hides the chain
+// anyhow: binary32 at 20480 and 32768 28.4 and 28.4, 106 and 100 ms, binary16
+// at 24576 and 32768 15.9 and 16.2, 33.2 and 31.4.
 // Wider groups move the trailing columns less often, but the chain takes the
-// group's own updates: binary32 with 2, 4 and 6 panels 1.40, 1.44 and 1.50 ms
-// at n = 4096, 5.75, 5.43 and 5.56 at 10000, -, 16.4 and 15.9 at 16384 (and
-// binary64's lines cross at the same orders); binary16 with 2, 4 and 8 panels
-// 0.69, 0.71 and 0.74 at 2000, -, 2.66 and 2.80 at 8192, -, 8.2 and 7.1 at
-// 16384 (12000: 4.47 and 4.48).  A few panels are one group: no second stream
-// (n = 300, a solve with 2 and 4 panels: 301 and 274-290 us; n = 1300: 802 and
-// 797).
+// group's own updates: binary32 with 2, 4, 6 and 8 panels 1.40, 1.44, 1.50 and
+// - ms at n = 4096; 5.75, 5.43, 5.56, - at 10000; -, 16.4, 15.9, 16.0 at 16384;
+// -, -, 28.9, 28.4 at 20480 (binary64's lines cross at the same orders);
+// binary16 with 2, 4 and 8 panels 0.69, 0.71, 0.74 at 2000; -, 2.66, 2.80 at
+// 8192; -, 4.47, 4.48 at 12000; -, 8.2, 7.1 at 16384.  A few panels are one
+// group: no second stream (n = 300, a solve with 2 and 4 panels: 301 and
+// 274-290 us; n = 1300: 802 and 797).
 void default_schedule(spd_factor_t F, bool half)
 {
+    const int64_t N = F->npad;
     if (half) {
-        F->group_half = F->npad <= 1024 ? 8 : (F->npad < 2560 ? 2 : (F->npad < 13312 ? 4 : 8));
-        F->upd_slots = 192;
+        F->group_half = N <= 1024 ? 8 : (N < 2560 ? 2 : (N < 13312 ? 4 : 8));
+        F->upd_slots = N < 28672 ? 192 : 0;
     } else {
-        F->group = F->npad < 1536 ? 4 : (F->npad < 5120 ? 2 : (F->npad < 13312 ? 4 : 6));
-        F->upd_slots = 448;
+        F->group = N < 1536 ? 4 : (N < 5120 ? 2 : (N < 13312 ? 4 : (N < 17408 ? 6 : 8)));
+        F->upd_slots = N < 20480 ? 448 : 0;
         F->small_main = false;
     }
 }
@@ -870,7 +874,8 @@ spd_status cg_refine(spd_cg_t H, const double *A, int64_t lda, const double *B, 
     // n = 10000 16.8, 16.1, 16.0 and 16.0 ms.
     const int S = 16;
     const double band_w = (k < 0) ? (double)n : (double)(2 * k + 1);
-    const double mv_flops = 2.0 * band_w * n * m, mv_bytes = 4.0 * band_w * n + 20.0 * n * m;
+    const double mv_flops = 2.0 * band_w * n * m;
+    const double mv_bytes = (k < 0 && spd::cg_sym(ldt, m) ? 2.0 : 4.0) * band_w * n + 20.0 * n * m;
     // S CG iterations: product, x/r update, p update (parity slot s & 1).  A
     // narrow band (P2 allocated) takes the p update of all but the last
     // iteration inside the next product, the directions alternating between

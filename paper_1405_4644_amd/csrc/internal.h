@@ -35,7 +35,7 @@ void launch_potrf_diag(T *Hkk, int64_t ld, int64_t col0, T *Winv, unsigned long 
 template <typename T>
 void launch_trsm_panel(T *H, int64_t ld, int64_t k0, int64_t row0, int64_t nrows, const T *Winv,
                        const unsigned long long *info, hipStream_t st, void *Lh = nullptr, int half = HALF_NONE);
-// small_tiles: a binary32 launch with fewer than 512 128-tiles may run on
+// small_tiles: a launch with fewer than 512 128-tiles may run on
 // 64-tiles (more workgroups for a thin region)
 template <typename T>
 void launch_syrk_update(T *H, int64_t ld, int64_t k0, int nbk, int64_t r0, int t, int tj_lo, int tj_hi,
@@ -182,6 +182,8 @@ int cg_pf_width(int m);
 int64_t cg_pf_elems(int64_t ldt, int m);  // binary32 direction storage (elements)
 int64_t cg_mv_parts(int64_t n, int64_t ldt, int64_t k, int m);
 int64_t cg_vec_parts(int64_t n);
+// the dense product of m columns reads A~'s lower triangle only
+bool cg_sym(int64_t ldt, int m);
 // Zp: binary32 partials of dense products (of the 5..32-column one by k-slices, of one column's by
 // 256-wide tiles, then added by launch_cg_xr), cg_zp_elems(n, ldt, m) elements for m or fewer columns
 int64_t cg_zp_elems(int64_t n, int64_t ldt, int m);

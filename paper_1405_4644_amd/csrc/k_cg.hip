@@ -219,7 +219,6 @@ __global__ __launch_bounds__(256) void k_cg_mv_valu(const float *__restrict__ Af
 // 5.2 ms, n = 4000 3.89 and 3.23.  From CG_SYM_MIN on: 3072 3.07 and 2.91 ms;
 // below it the tiles are too few (2816 2.92 and 2.95, 1529 1.97 and 2.48).
 constexpr int64_t CG_SYM_MIN = 3072;
-inline bool cg_sym(int64_t ldt, int m) { return m == 1 && ldt >= CG_SYM_MIN; }
 __global__ __launch_bounds__(256) void k_cg_mv_sym(const float *__restrict__ Af, int64_t ldt, int64_t n,
                                                    const float *__restrict__ Pf, const double *__restrict__ P,
                                                    float *__restrict__ Zp, double *__restrict__ part,
@@ -664,6 +663,7 @@ __global__ __launch_bounds__(256) void k_cg_begin(const double *__restrict__ par
 namespace spd {
 
 int64_t cg_ldt(int64_t n) { return ((std::max<int64_t>(n, 1) + 255) / 256) * 256; }
+bool cg_sym(int64_t ldt, int m) { return m == 1 && ldt >= CG_SYM_MIN; }
 int cg_band_ok(int64_t k) { return k >= 0 && k <= CG_MAXK_BAND; }
 
 void launch_cg_dense(const double *A, int64_t lda, int64_t n, float *At, int64_t ldt, hipStream_t st)

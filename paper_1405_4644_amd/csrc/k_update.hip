@@ -58,7 +58,10 @@ SPD_DEV void decode_tile(int b, int t, int tj_lo, int tj_hi, int &ti, int &tj)
 // once.
 // Bound by the MFMA rate.  Binary64 used to run a kernel of its own whose
 // accumulators and staging took 277 registers, one workgroup per compute
-// unit, with every chunk's barrier exposed: TIMES_F64.
+// unit, with every chunk's barrier exposed: 41 TFLOP/s beside the panel chain,
+// where this reaches 48-53; the chain's update of a tile column 84 us, now
+// 20-40 alone (n = 16384, with the panel solve of k_trsm_f64: 42.1 -> 36.3 ms
+// per solve).
 template <typename T, int TS, int KC>
 SPD_DEV void update_tile(T *__restrict__ H, int64_t ld, int64_t k0, int nbk, int64_t crow, int64_t ccol,
                          T *__restrict__ As, T *__restrict__ Bs, int tid)
