@@ -394,7 +394,7 @@ spd_status prepare_factor(spd_factor_t F, int64_t n, int prec, double theta, hip
 }
 
 // The factorisation's schedule where neither the environment nor the tuner has
-// set one (it changes no result).
+// set one.
 // The main stream's update leaves an eighth of its slots (a quarter at one
 // 256 x 256 tile per compute unit) to the panel chain, whose kernels otherwise
 // wait beside it for a workgroup to end: capped and not, at n = 16384 binary64
