@@ -41,3 +41,16 @@ def test_breakdown_columns(spd, orc, prec):
         if F is not None:
             F.close()
         assert st == spd.ERR_NOT_SPD and info == j0, (j0, info, st)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("j0", [1, 2, 15, 16, 17, 32, 33, 128, 129, 200])
+def test_zero_pivot(spd, prec, j0):
+    """A pivot that is exactly zero (its row and column zero as well)."""
+    n = 200
+    A = np.array(spdgen.logspaced(n, 1e1, 40 + j0))
+    A[j0 - 1, :] = A[:, j0 - 1] = 0.0
+    _say(f"zero pivot {prec} j0={j0}")
+    F, info, st = spd.factor(dev(A), prec)
+    F.close()
+    assert st == spd.ERR_NOT_SPD and info == j0, (info, st)
