@@ -136,7 +136,7 @@ struct BatchLaunch {
     double tol, mu16;
     int max_iter, fallback, equilibrate;
     int32_t *order;  // batch entries of scratch
-    int *queue;      // one int of scratch
+    int *queue;      // five ints of scratch
     void *ws;        // grid * batch_ws_stride() bytes
     int grid, waves;
     const float *picker = nullptr;  // perceptron parameters for SPD_AUTO, or NULL

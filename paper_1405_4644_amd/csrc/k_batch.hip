@@ -1388,7 +1388,9 @@ SPD_DEV int b_pick(const float *P, PickSmem &sm)
 // accepted at eta <= tol.  Divergence as before; max_iter corrections
 // without success: no convergence.  Returns SPD_OK or SPD_ERR_NO_CONVERGENCE
 // and fills the iteration counts and eta.
-// residual(first) and solve() as in b_residual and b_solve, by the caller.
+// residual(first, sm) and solve(sm) as in b_residual and b_solve, by the caller
+// (the shared memory as an argument: captured, its address would no longer be
+// known in the functions that they call).
 template <typename T, typename Smem, typename Res, typename Sol>
 SPD_DEV int b_refine(double tol, int max_iter, int m, spd_report &rep, Smem &sm, Res residual, Sol solve)
 {
@@ -1411,7 +1413,7 @@ SPD_DEV int b_refine(double tol, int max_iter, int m, spd_report &rep, Smem &sm,
     for (;;) {
         const int first = (rep.iters_high == 0);
         const int k = rep.iters_high;  // corrections applied so far
-        residual(first);
+        residual(first, sm);
         rep.iters_high++;
         if (first)
             anorm = sm.norms[0];
@@ -1475,7 +1477,7 @@ SPD_DEV int b_refine(double tol, int max_iter, int m, spd_report &rep, Smem &sm,
         if (threadIdx.x < m)
             sm.smax[threadIdx.x] = sm.norms[1 + 3 * m + threadIdx.x];
         __syncthreads();
-        solve();
+        solve(sm);
         rep.iters_low++;
     }
 }
@@ -1507,50 +1509,64 @@ SPD_DEV void b_rhs_max(const double *B, const double *d, int n, int m, Smem &sm)
     __syncthreads();
 }
 
-// One attempt at a half precision (k_batch_half.h); its counts, eta and failing
-// column in sm.rep.  Returns SPD_OK, SPD_ERR_NOT_SPD or SPD_ERR_NO_CONVERGENCE.
+// A half-precision request's attempt (k_batch_half.h): reported where it
+// converged or may not fall back, else handed to the binary32 kernel
+// (prec[s] = FP32, reps[s].fallbacks = 1).
 template <int WAVES>
-__device__ __attribute__((noinline)) int b_half(const double *A, const double *B, double *X, int n, int np, int m,
-                                                void *Lp, void *Wp, double *d, double *R, double *Am, double mu,
-                                                int equil, int half, double tol, int max_iter,
-                                                half_path::SolveSmem &sm)
+SPD_DEV void b_half_system(const BatchArgs &a, int64_t s, half_path::SolveSmem &sm)
 {
-    n = uni(n);
-    np = uni(np);
-    m = uni(m);
-    float *L = (float *)Lp, *Winv = (float *)Wp;
+    const int n = a.n[s], m = a.nrhs[s], p = a.prec[s];
+    if (n <= 0 || m <= 0 || n > SPD_BATCH_NMAX || m > SPD_BATCH_MAXRHS || p < SPD_BF16 || p >= SPD_FP32)
+        return;
+    const unsigned long long t0 = wall_clock64();
     spd_report rep;
+    rep.prec_used = p;
     rep.iters_low = rep.iters_high = 0;
+    rep.fallbacks = 0;
     rep.eta = 0.0;
+    const double *A = a.A + a.a_off[s];
+    const double *B = a.B + a.b_off[s];
+    double *X = a.X + a.b_off[s];
+    const int np = ((n + BNB - 1) / BNB) * BNB;
+    const BatchWs w = batch_ws(a);
+    float *L = (float *)w.L, *Winv = (float *)w.Winv;
+    const double mu = (p == SPD_FP16) ? a.mu16 : 1.0;
+    half_path::b_convert<WAVES>(A, n, np, w.d, mu, a.equilibrate, L, w.Am, sm);
+    const int info = half_path::b_factor<WAVES>(L, np, Winv, p == SPD_FP16 ? HALF_F16 : HALF_BF16, sm);
+    rep.info = info;
     int r = SPD_ERR_NOT_SPD;
-    half_path::b_convert<WAVES>(A, n, np, d, mu, equil, L, Am, sm);
-    const int info = half_path::b_factor<WAVES>(L, np, Winv, half, sm);
     if (!info) {
-        b_rhs_max<WAVES>(B, d, n, m, sm);
-        half_path::b_solve<WAVES>(L, Winv, n, np, m, B, d, mu, X, 0, sm);
+        b_rhs_max<WAVES>(B, w.d, n, m, sm);
+        half_path::b_solve<WAVES>(L, Winv, n, np, m, B, w.d, mu, X, 0, sm);
         r = b_refine<float>(
-            tol, max_iter, m, rep, sm,
-            [&](int first) { half_path::b_residual<WAVES>(A, Am, n, np, m, X, B, d, R, first, sm); },
-            [&]() { half_path::b_solve<WAVES>(L, Winv, n, np, m, R, d, mu, X, 1, sm); });
+            a.tol, a.max_iter, m, rep, sm,
+            [&](int first, half_path::SolveSmem &h) {
+                half_path::b_residual<WAVES>(A, w.Am, n, np, m, X, B, w.d, w.R, first, h);
+            },
+            [&](half_path::SolveSmem &h) { half_path::b_solve<WAVES>(L, Winv, n, np, m, w.R, w.d, mu, X, 1, h); });
     }
-    if (threadIdx.x == 0) {
-        sm.rep.info = info;
-        sm.rep.iters_low = rep.iters_low;
-        sm.rep.iters_high = rep.iters_high;
-        sm.rep.eta = rep.eta;
-    }
+    rep.status = r;
     __syncthreads();
-    return r;
+    if (threadIdx.x == 0) {
+        if (r == SPD_OK || !a.fallback) {
+            a.reps[s] = rep;
+        } else {
+            a.reps[s].fallbacks = 1;
+            a.prec[s] = SPD_FP32;
+        }
+        if (a.ticks)
+            a.ticks[s] += (int64_t)(wall_clock64() - t0);
+    }
 }
 
 // One system through Algorithm 1 by one workgroup, at the precisions of the
-// kernel's factor type: HI = false takes BF16, FP16 and FP32 requests (and
-// the half -> binary32 fallback), HI = true the FP64 requests and every
-// system the low-precision kernel handed over (a binary32 breakdown or
-// non-convergence with fallback on: prec[s] = FP64, reps[s].fallbacks the
-// count so far).  Systems of the other kernel are skipped; the
-// low-precision kernel also reports invalid sizes.  ticks[s] (zeroed by the
-// order kernel) accumulates every kernel's time on the system.
+// kernel's factor type: HI = false takes FP32 requests and what the
+// half-precision kernel handed over, HI = true the FP64 requests and every
+// system the binary32 kernel handed over (a breakdown or non-convergence with
+// fallback on: prec[s] = the next precision, reps[s].fallbacks the count so
+// far).  Systems of the other kernels are skipped; the binary32 kernel also
+// reports empty systems and invalid sizes.  ticks[s] and reps[s].fallbacks
+// (zeroed by the order kernel) accumulate over the kernels.
 template <int WAVES, bool HI>
 SPD_DEV void b_system(const BatchArgs &a, int64_t s, SolveSmem &sm)
 {
@@ -1561,18 +1577,15 @@ SPD_DEV void b_system(const BatchArgs &a, int64_t s, SolveSmem &sm)
         p = SPD_FP32;
     const bool valid = n >= 0 && m >= 0 && n <= SPD_BATCH_NMAX && m <= SPD_BATCH_MAXRHS && p >= SPD_BF16 &&
                        p <= SPD_FP64;
-    if (HI ? (!valid || p != SPD_FP64) : (valid && p == SPD_FP64)) {
-        // the other kernel's system; the low-precision kernel starts its count
-        if (!HI && threadIdx.x == 0)
-            a.reps[s].fallbacks = 0;
-        return;
-    }
+    const bool half = valid && p < SPD_FP32 && n > 0 && m > 0;
+    if (HI ? (!valid || p != SPD_FP64) : (half || (valid && p == SPD_FP64)))
+        return;  // another kernel's system
     const unsigned long long t0 = wall_clock64();
     spd_report rep;
     rep.status = SPD_OK;
     rep.prec_used = p;
     rep.iters_low = rep.iters_high = 0;
-    rep.fallbacks = HI ? a.reps[s].fallbacks : 0;
+    rep.fallbacks = a.reps[s].fallbacks;
     rep.info = 0;
     rep.eta = 0.0;
     bool handover = false;
@@ -1584,50 +1597,26 @@ SPD_DEV void b_system(const BatchArgs &a, int64_t s, SolveSmem &sm)
         double *X = a.X + a.b_off[s];
         const int np = ((n + BNB - 1) / BNB) * BNB;
         const BatchWs w = batch_ws(a);
-        int status = SPD_OK;
-        for (;;) {
-            // a binary32 factor is equilibrated (for FP16 with mu), a binary64
-            // one that of A itself
-            int info, r = SPD_ERR_NOT_SPD;
-            rep.prec_used = p;
-            // factor; the first solve from B, then refinement
-            if (!HI && p != SPD_FP32) {
-                static_assert(sizeof(half_path::SolveSmem) <= sizeof(SolveSmem), "one workgroup's shared memory");
-                half_path::SolveSmem &hs = reinterpret_cast<half_path::SolveSmem &>(sm);
-                r = b_half<WAVES>(A, B, X, n, np, m, w.L, w.Winv, w.d, w.R, w.Am, p == SPD_FP16 ? a.mu16 : 1.0,
-                                  a.equilibrate, p == SPD_FP16 ? HALF_F16 : HALF_BF16, a.tol, a.max_iter, hs);
-                info = (int)hs.rep.info;
-                rep.iters_low = hs.rep.iters_low;
-                rep.iters_high = hs.rep.iters_high;
-                rep.eta = hs.rep.eta;
-                __syncthreads();
-            } else {
-                T *L = (T *)w.L, *Winv = (T *)w.Winv;
-                info = b_factor<T, WAVES>(A, n, np, w.d, 1.0, HI ? 0 : a.equilibrate, L, Winv, sm);
-                if (!info) {
-                    b_rhs_max<WAVES>(B, w.d, n, m, sm);
-                    b_solve<T, WAVES>(L, Winv, n, np, m, B, w.d, 1.0, X, 0, sm);
-                    r = b_refine<T>(
-                        a.tol, a.max_iter, m, rep, sm, [&](int first) { b_residual<WAVES>(A, n, m, X, B, w.d, w.R, first, sm); },
-                        [&]() { b_solve<T, WAVES>(L, Winv, n, np, m, w.R, w.d, 1.0, X, 1, sm); });
-                }
-            }
-            rep.info = info;
-            if (r == SPD_OK || !a.fallback || HI) {
-                status = r;
-                break;
-            }
-            // fallback: a half format retries in binary32 here; binary32 goes
-            // to the binary64 kernel
-            rep.fallbacks++;
-            if (p == SPD_FP32) {
-                handover = true;
-                status = r;
-                break;
-            }
-            p = SPD_FP32;
+        // a binary32 factor is equilibrated, a binary64 one that of A itself
+        T *L = (T *)w.L, *Winv = (T *)w.Winv;
+        rep.prec_used = p;
+        const int info = b_factor<T, WAVES>(A, n, np, w.d, 1.0, HI ? 0 : a.equilibrate, L, Winv, sm);
+        rep.info = info;
+        int r = SPD_ERR_NOT_SPD;
+        if (!info) {
+            // first solve from B, then refinement
+            b_rhs_max<WAVES>(B, w.d, n, m, sm);
+            b_solve<T, WAVES>(L, Winv, n, np, m, B, w.d, 1.0, X, 0, sm);
+            r = b_refine<T>(
+                a.tol, a.max_iter, m, rep, sm,
+                [&](int first, SolveSmem &h) { b_residual<WAVES>(A, n, m, X, B, w.d, w.R, first, h); },
+                [&](SolveSmem &h) { b_solve<T, WAVES>(L, Winv, n, np, m, w.R, w.d, 1.0, X, 1, h); });
         }
-        rep.status = status;
+        rep.status = r;
+        if (r != SPD_OK && a.fallback && !HI) {  // binary32 goes to the binary64 kernel
+            rep.fallbacks++;
+            handover = true;
+        }
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1664,6 +1653,8 @@ __global__ __launch_bounds__(256, 2) void k_batch_pick(BatchArgs a)
             const int p = b_pick(a.picker, sm);
             if (threadIdx.x == 0) {
                 a.prec[s] = p;
+                if (p < SPD_FP32)
+                    a.queue[3] = 1;
                 if (a.ticks)
                     a.ticks[s] += (int64_t)(wall_clock64() - t0);
             }
@@ -1689,6 +1680,27 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_batch(BatchArgs a)
     }
 }
 
+// The half-precision requests; nothing where there are none (queue[3], set by
+// the order kernel or the picker).
+template <int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 2) void k_batch_half(BatchArgs a)
+{
+    __shared__ half_path::SolveSmem sm;
+    __shared__ int s_q;
+    if (a.queue[3] == 0)
+        return;
+    for (;;) {
+        if (threadIdx.x == 0)
+            s_q = atomicAdd(a.queue + 4, 1);
+        __syncthreads();
+        const int64_t q = s_q;
+        if (q >= a.batch)
+            return;
+        b_half_system<WAVES>(a, a.order[q], sm);
+        __syncthreads();
+    }
+}
+
 // Features of every system (one workgroup each), for training the picker.
 __global__ __launch_bounds__(256, 2) void k_features(int64_t batch, const int32_t *__restrict__ n,
                                                   const int32_t *__restrict__ nrhs, const int64_t *__restrict__ a_off,
@@ -1709,15 +1721,24 @@ __global__ __launch_bounds__(256, 2) void k_features(int64_t batch, const int32_
 }
 
 // Order of work: systems sorted by decreasing n (counting sort, one
-// workgroup); also clears the work-queue counter.
+// workgroup); also clears the work-queue counters and the counts that add up
+// over the kernels, and notes whether there are half-precision requests.
 __global__ __launch_bounds__(1024) void k_batch_order(int64_t batch, const int32_t *__restrict__ n,
+                                                      const int32_t *__restrict__ prec, spd_report *reps,
                                                       int32_t *__restrict__ order, int *queue, int64_t *ticks)
 {
     constexpr int NBIN = SPD_BATCH_NMAX + 1;
-    __shared__ int hist[NBIN], start[NBIN];
+    __shared__ int hist[NBIN], start[NBIN], half;
     const int tid = threadIdx.x;
     for (int b = tid; b < NBIN; b += 1024) hist[b] = 0;
+    if (tid == 0)
+        half = 0;
     __syncthreads();
+    for (int64_t s = tid; s < batch; s += 1024) {
+        reps[s].fallbacks = 0;
+        if (prec[s] >= SPD_BF16 && prec[s] < SPD_FP32)
+            half = 1;  // (by several threads, the same value)
+    }
     for (int64_t s = tid; s < batch; s += 1024) {
         int v = n[s];
         v = (v < 0 || v > SPD_BATCH_NMAX) ? 0 : v;
@@ -1730,7 +1751,8 @@ __global__ __launch_bounds__(1024) void k_batch_order(int64_t batch, const int32
             start[b] = acc;
             acc += hist[b];
         }
-        queue[0] = queue[1] = queue[2] = 0;
+        queue[0] = queue[1] = queue[2] = queue[4] = 0;
+        queue[3] = half;
     }
     if (ticks)
         for (int64_t s = tid; s < batch; s += 1024) ticks[s] = 0;
@@ -1777,11 +1799,13 @@ hipError_t launch_batch(const BatchLaunch &l, hipStream_t st)
     a.ws_stride = batch_ws_stride();
     a.picker = l.picker;
     a.ticks = l.ticks;
-    hipLaunchKernelGGL(k_batch_order, dim3(1), dim3(1024), 0, st, l.batch, l.n, l.order, l.queue, l.ticks);
-    // picker (AUTO systems), then the low-precision systems, then binary64
-    // (requests and hand-overs); four wavefronts per workgroup
+    hipLaunchKernelGGL(k_batch_order, dim3(1), dim3(1024), 0, st, l.batch, l.n, l.prec, l.reps, l.order, l.queue,
+                       l.ticks);
+    // picker (AUTO systems), then half-precision requests, binary32 (requests
+    // and hand-overs), binary64 (the same); four wavefronts per workgroup
     if (l.picker)
         hipLaunchKernelGGL(k_batch_pick, dim3((unsigned)l.grid), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_batch_half<4>, dim3((unsigned)l.grid), dim3(256), 0, st, a);
     hipLaunchKernelGGL((k_batch<4, false>), dim3((unsigned)l.grid), dim3(256), 0, st, a);
     hipLaunchKernelGGL((k_batch<4, true>), dim3((unsigned)l.grid), dim3(256), 0, st, a);
     return hipGetLastError();

@@ -5,8 +5,8 @@
 // iteration limit -- the request's outcome, half precision or the fallback.
 // So this path keeps its order of operations: right-looking over a
 // column-major factor, the residual by whole rows from A and a mirror of its
-// lower triangle, the solves on the VALU.  (4096 systems at FP16: 10.8 ms; in
-// the order of the other paths 5 of 4096 requests ended otherwise than here.)
+// lower triangle, the solves on the VALU (in the order of the other paths 2 to
+// 12 of 4096 requests ended otherwise than here).
 #pragma once
 
 namespace half_path {
@@ -24,7 +24,6 @@ struct SolveSmem {
     double arow[SPD_BATCH_NMAX];  // row sums of |A|
     double part[4][SPD_BATCH_MAXRHS + 1][64];  // the residual's per-wave partial row sums (+ |A|)
     int info;
-    spd_report rep;  // an attempt's counts, eta and failing column
 };
 // ---------------------------------------------------------------------------
 // H = round(mu D A D) (lower), identity padding up to np; d (binary64); and
