@@ -796,7 +796,9 @@ struct spd_cg_s {
     size_t cap_At = 0;               // bytes allocated for At
     int m = 0;                       // right-hand sides the workspace is sized for
     double *R = nullptr, *P = nullptr, *Z = nullptr, *part = nullptr, *vpart = nullptr, *sc = nullptr;
-    double *norms = nullptr, *rscr = nullptr;
+    double *norms = nullptr;
+    double *rscr = nullptr;          // residual partials: no larger for more columns, so grown call by call
+    size_t cap_rscr = 0;
     double *Xs = nullptr;            // x at the start of the inner phase (its change is the correction)
     double *P2 = nullptr;            // second direction buffer of the fused banded iterations
     float *Pf = nullptr;             // binary32 directions of the dense products
@@ -816,6 +818,7 @@ void cg_free_ws(spd_cg_t H)
     if (H->norms_host) hipHostFree(H->norms_host);
     if (H->flags_host) hipHostFree(H->flags_host);
     H->R = H->P = H->Z = H->part = H->vpart = H->sc = H->norms = H->rscr = H->Xs = H->P2 = nullptr;
+    H->cap_rscr = 0;
     H->Pf = nullptr;
     H->Zp = nullptr;
     H->flags = nullptr;
@@ -824,6 +827,7 @@ void cg_free_ws(spd_cg_t H)
     H->m = 0;
 }
 
+// everything but the residual's partials, for up to m right-hand sides
 spd_status cg_ensure_ws(spd_cg_t H, int m, hipStream_t st)
 {
     if (H->m >= m) return SPD_OK;
@@ -835,14 +839,10 @@ spd_status cg_ensure_ws(spd_cg_t H, int m, hipStream_t st)
     HIP_TRY(hipMalloc(&H->P, nm));
     HIP_TRY(hipMalloc(&H->Z, nm));
     HIP_TRY(hipMalloc(&H->Xs, nm));
-    // product partials: sized for the most per column any m' <= m uses (the
-    // workspace is reused for fewer right-hand sides)
-    const int64_t mvp = std::max(spd::cg_mv_parts(n, ldt, H->k, m), spd::cg_mv_parts(n, ldt, H->k, 1));
-    HIP_TRY(hipMalloc(&H->part, (size_t)mvp * m * sizeof(double)));
+    HIP_TRY(hipMalloc(&H->part, (size_t)spd::cg_part_elems(n, ldt, H->k, m) * sizeof(double)));
     HIP_TRY(hipMalloc(&H->vpart, (size_t)spd::cg_vec_parts(n) * m * sizeof(double)));
     HIP_TRY(hipMalloc(&H->sc, (size_t)4 * m * sizeof(double)));
     HIP_TRY(hipMalloc(&H->norms, (size_t)(1 + 5 * m) * sizeof(double)));
-    HIP_TRY(hipMalloc(&H->rscr, (size_t)spd::resid_scratch(n, m) * sizeof(double)));
     if (H->k < 0) HIP_TRY(hipMalloc(&H->Pf, (size_t)spd::cg_pf_elems(ldt, m) * sizeof(float)));
     if (H->k >= 0 && spd::cg_band_fused(H->k)) HIP_TRY(hipMalloc(&H->P2, nm));
     if (H->k < 0 && spd::cg_zp_elems(n, ldt, m) > 0)
@@ -859,6 +859,7 @@ spd_status cg_refine(spd_cg_t H, const double *A, int64_t lda, const double *B, 
 {
     const int64_t n = H->n, ldt = H->ldt, k = H->k;
     SPD_TRY(cg_ensure_ws(H, m, st));
+    SPD_TRY(grow((void **)&H->rscr, &H->cap_rscr, (size_t)spd::resid_scratch(n, m) * sizeof(double), false, st));
     // Pf's padding (rows n..ldt-1, columns m.. of the last block) must read as zero
     if (H->Pf) spd::launch_zero((double *)H->Pf, spd::cg_pf_elems(ldt, m) / 2, st);
     const int64_t nmv = spd::cg_mv_parts(n, ldt, k, m), nv = spd::cg_vec_parts(n);

@@ -117,6 +117,7 @@ void launch_export(const T *L, int64_t ld, int64_t n, double *Lout, int64_t ldo,
 // norms[1 + k m + c] for k = 0..3: max|r|, max|x|, max|b|, max|d r| (atomic
 // max; zero them first);
 // with want_anorm, norms[0] = ||A||_inf.  P is scratch of resid_scratch(n, m) doubles.
+// (not monotone in m: one or two columns have a layout of their own)
 int64_t resid_scratch(int64_t n, int m);
 // eta (device, m) from the norms launch_residual wrote (with want_anorm)
 void launch_eta_from_norms(const double *norms, int m, double *eta, hipStream_t st);
@@ -180,7 +181,8 @@ void launch_cg_dense(const double *A, int64_t lda, int64_t n, float *At, int64_t
 void launch_cg_band(const double *A, int64_t lda, int64_t n, int64_t k, float *Bd, int64_t ldt, hipStream_t st);
 int cg_pf_width(int m);
 int64_t cg_pf_elems(int64_t ldt, int m);  // binary32 direction storage (elements)
-int64_t cg_mv_parts(int64_t n, int64_t ldt, int64_t k, int m);
+int64_t cg_mv_parts(int64_t n, int64_t ldt, int64_t k, int m);    // product partials per column, m columns
+int64_t cg_part_elems(int64_t n, int64_t ldt, int64_t k, int m);  // all of them, m or fewer columns
 int64_t cg_vec_parts(int64_t n);
 // the dense product of m columns reads A~'s lower triangle only
 bool cg_sym(int64_t ldt, int m);

@@ -692,6 +692,15 @@ int64_t cg_mv_parts(int64_t n, int64_t ldt, int64_t k, int m)
     return (m <= 4) ? ldt / 32 : (n + 255) / 256;
 }
 
+// (the products of 1, of 2 to 4 and of more columns have layouts of their own)
+int64_t cg_part_elems(int64_t n, int64_t ldt, int64_t k, int m)
+{
+    int64_t e = 0;
+    for (int q : {1, 2, 3, 4, m})
+        if (q <= m) e = std::max(e, cg_mv_parts(n, ldt, k, q) * q);
+    return e;
+}
+
 int64_t cg_zp_elems(int64_t n, int64_t ldt, int m)
 {
     return std::max((m > 4) ? (int64_t)CG_KS * m * n : 0, cg_sym(ldt, 1) ? ldt / 256 * ldt : 0);

@@ -248,3 +248,24 @@ def test_cg_dense_product_edges(spd, orc, n):
     X2, _ = spd.cg_refine(H, At, torch.from_numpy(Bt).cuda(), opts=o)
     assert np.array_equal(X2.cpu().numpy(), X)
     H.close()
+
+
+@pytest.mark.parametrize("n,first,then", [(2300, 3, 1), (2300, 4, 2), (4100, 3, 2), (4100, 6, 1), (5003, 32, 1)])
+@pytest.mark.parametrize("band", [-1, 5])
+def test_cg_handle_serves_fewer_right_hand_sides(spd, n, first, then, band):
+    """A handle whose workspace was made for more right-hand sides gives the
+    bits of a fresh one, at orders where the fewer need larger residual partials."""
+    import torch
+    _say(f"cg handle n={n} band={band} m={first} then {then}")
+    A = dev(spdgen.covariance(n, 2))
+    o = spd.cg_default_opts(max_outer=2, max_inner=4, inner_tol=0.0)
+    B = dev(spdgen.rhs(n, then, 17))
+    H = spd.cg_prepare(A, half_band=band)
+    spd.cg_refine(H, A, dev(spdgen.rhs(n, first, 18)), opts=o)
+    X, rep = spd.cg_refine(H, A, B, opts=o)
+    H.close()
+    H = spd.cg_prepare(A, half_band=band)
+    Y, ref = spd.cg_refine(H, A, B, opts=o)
+    torch.cuda.synchronize()
+    H.close()
+    assert rep.as_dict() == ref.as_dict() and torch.equal(X, Y)
