@@ -670,7 +670,7 @@ __global__ __launch_bounds__(256) void k_trsv_blk(const T *__restrict__ L, int64
 //   U(p, c): v_p[c] = y_p[c] - sum_{q < p} L_pq[rows c] z_q    (q in order)
 //   Z(p, c): z_p[c] = W_p[rows c] v_p                          (v_0 = y_0)
 // (transposed blocks for the backward solve).  A task waits only for tasks
-// handed out before it.  The sum over q stays in the MFMA accumulators of one
+// handed out before it.  The sum over q stays in the registers of one
 // workgroup, so there are no partial products in memory: with 32 columns
 // they would be as large as the blocks themselves.
 //
@@ -680,15 +680,23 @@ __global__ __launch_bounds__(256) void k_trsv_blk(const T *__restrict__ L, int64
 // values are 16 consecutive bytes, and so are its matrix values in the
 // backward solve.  Each vector value is needed by one wave only, so neither
 // operand goes through shared memory.  The matrix block is loaded before the
-// wait, the next one before the product.  The waves' sums are added in order
+// wait, the next one before the product.  The waves' sums are added in pairs
 // through shared memory.
 //
+// A wave's 128 products of a block make four sums of 32, then one, added to
+// those of the blocks before: the rounding error of a column does not exceed
+// that of BlockVec (binary32, random unit factor, in units of u: 2.5 at
+// n = 300 and 2.6 at 16384; BlockVec 2.6 and 4.2).  One sum over all blocks
+// gave 3.6 and 6.4; it took 1-2 % less time in binary32 and 5 % in binary64.
+//
 // Bound by the chain of 2 K tasks, each a poll, the loads of the vector and a
-// 1024-deep product.  In passes of 8 columns on the VALU (BlockVec) a solve
-// with 32 right-hand sides took 4 x (305 + 236) us at n = 10000, one with 5
-// 163 + 123 us at n = 6000; here 192 + 231 and 71 + 73 us.  One right-hand
-// side stays on BlockVec, whose 256 workgroups stream more (n = 16384: 231 +
-// 192 us against 268 + 279 here; n = 3000: 27 + 27 against 30 + 34).
+// 1024-deep product.  A solve, forward and backward, in passes of up to 8
+// columns on the VALU (BlockVec) and here: n = 10000 with 32 columns 2183 and
+// 457 us; n = 6000 with 3 and 8 columns 216 and 159, 306 and 167; n = 16384
+// 610 and 584, 919 and 614 (binary64 1025 and 1034, 1499 and 1068); n = 1300
+// 56 and 47, 82 and 50.  One or two columns stay on BlockVec, whose 256
+// workgroups stream more: n = 16384 450 and 510 us (with 3 columns here 581),
+// n = 3000 64 and 75 (83).
 #define TRSM_WAVES 8
 // raw buffer loads coherent at agent scope (the SC1 cache policy bit)
 #define SPD_BUFFER_AGENT 16
@@ -713,6 +721,7 @@ __global__ __launch_bounds__(64 * TRSM_WAVES) void k_trsv_mfma(const T *__restri
     constexpr bool F32 = sizeof(T) == 4;
     constexpr int MT = F32 ? 2 : 1, R = 16 * MT, MC = 16 * NT, NW = TRSM_WAVES, NBS = TRSV_NBS,
                   GM = NBS / (16 * NW);
+    static_assert(NW == 8 && GM == 8, "the order of the sums below");
     using acc_t = typename std::conditional<F32, floatx4, doublex4>::type;
     __shared__ T red[NW][MC][R + 1];
     __shared__ int s_task, s_ok[2];
@@ -803,6 +812,14 @@ __global__ __launch_bounds__(64 * TRSM_WAVES) void k_trsv_mfma(const T *__restri
                 }
             }
         }
+        // four sums, by step i, for the block, added in pairs
+        acc_t s[4][MT][NT];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int h = 0; h < MT; ++h)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) s[i][h][t] = acc_t{0, 0, 0, 0};
 #pragma unroll
         for (int g = 0; g < GM; ++g)
 #pragma unroll
@@ -812,10 +829,16 @@ __global__ __launch_bounds__(64 * TRSM_WAVES) void k_trsv_mfma(const T *__restri
 #pragma unroll
                     for (int h = 0; h < MT; ++h) {
                         if constexpr (F32)
-                            acc[h][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(z[g][t][i], a[g][i][h], acc[h][t], 0, 0, 0);
+                            s[i][h][t] =
+                                __builtin_amdgcn_mfma_f32_16x16x4f32(z[g][t][i], a[g][i][h], s[i][h][t], 0, 0, 0);
                         else
-                            acc[h][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(z[g][t][i], a[g][i][h], acc[h][t], 0, 0, 0);
+                            s[i][h][t] =
+                                __builtin_amdgcn_mfma_f64_16x16x4f64(z[g][t][i], a[g][i][h], s[i][h][t], 0, 0, 0);
                     }
+#pragma unroll
+        for (int h = 0; h < MT; ++h)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[h][t] += (s[0][h][t] + s[1][h][t]) + (s[2][h][t] + s[3][h][t]);
         __builtin_amdgcn_sched_barrier(0);
     };
     int slot = 0;  // s_ok alternates: a slot is rewritten only after the barrier that follows its reading
@@ -909,9 +932,8 @@ __global__ __launch_bounds__(64 * TRSM_WAVES) void k_trsv_mfma(const T *__restri
         __syncthreads();
         for (int e = tid; e < R * mc; e += 64 * NW) {
             const int row = e % R, cc = e / R;
-            T s = red[0][cc][row];
-#pragma unroll
-            for (int q = 1; q < NW; ++q) s += red[q][cc][row];
+            const T s = ((red[0][cc][row] + red[1][cc][row]) + (red[2][cc][row] + red[3][cc][row])) +
+                        ((red[4][cc][row] + red[5][cc][row]) + (red[6][cc][row] + red[7][cc][row]));
             const int64_t i = oi + c * R + row;
             if (ztask)
                 store_shared(&Zout[i + (int64_t)(c0 + cc) * ldy], s);
