@@ -5,9 +5,9 @@
 // sides: one pass over the lower triangle, every stored element serving its
 // row and its column (k_resid_sym).  More: the whole symmetric matrix on
 // binary64 MFMA, the part right of the diagonal read from the lower
-// triangle's columns (k_resid_mfma).  Both leave partial sums that a second kernel adds in a fixed order, so results are bitwise
-// reproducible run to run.  The same pass can accumulate sum_j |a_ij| for
-// ||A||_inf.
+// triangle's columns (k_resid_mfma).  Both leave partial sums that a second
+// kernel adds in a fixed order, so results are bitwise reproducible run to
+// run.  The same pass can accumulate sum_j |a_ij| for ||A||_inf.
 #include "common.h"
 #include "internal.h"
 #include <algorithm>
@@ -25,12 +25,19 @@
 // tile; pitch 66 doubles: 16-byte reads of 16 columns without bank
 // conflicts).  Operands are given as (X, A), so that register v of a lane is
 // right-hand side 4 v + u, row r: partials are stored along rows.
+// The products of two tiles (128 columns) make one sum, added to those before,
+// and the slices are added in pairs: the rounding error, in units of
+// u |a||x| sqrt(n), is 0.92, 1.6 and 2.0 at n = 1300, 6000 and 12000.  One sum
+// over a workgroup's whole slice, and the slices one after the other, gave
+// 1.5, 5.7 and 13.6 (and 1.5, 3.4 and 9.1 with twice the slices).  At 17 and
+// more columns the sums of the tiles before stay in shared memory, a thread's
+// own places: in registers 45 values would spill (n = 12000: 531 us a call).
 // Bound by reading the symmetric A once per chunk of 32 right-hand sides, and
 // by the binary64 MFMA rate at 17..32 columns.  Staging A's 64 x 64 tiles
 // through shared memory (two barriers per tile, X re-read for every 64 rows)
-// took 256 us at n = 10000 with 32 columns and 362 at n = 12000; this takes
-// 197 and 272 us (4.1 TB/s).  At n = 6000 with 5 columns one thread per row
-// and column pair on 64 x 64 tiles took 84 us, this 57.
+// took 256 us at n = 10000 with 32 columns and 362 at n = 12000, without the
+// reduction; with it this takes 221 and 296 us (3.9 TB/s).  With 5 columns at
+// n = 6000, and 8 at 16384, 69 and 382 us.
 typedef double double2u __attribute__((ext_vector_type(2), aligned(8)));  // 16-byte load, 8-byte aligned
 template <int NT>
 __global__ __launch_bounds__(256, 2) void k_resid_mfma(const double *__restrict__ A, int64_t lda, int64_t n,
@@ -45,11 +52,17 @@ __global__ __launch_bounds__(256, 2) void k_resid_mfma(const double *__restrict_
     const int s = blockIdx.y;
     const int64_t iw = (int64_t)blockIdx.x * 128 + 32 * w;  // the wave's first row
     const int njt = (int)((n + 63) / 64);
-    doublex4 acc[2][NT];
+    doublex4 acc[2][NT];  // of one or two tiles; tot of those before, a thread's own places where registers are short
+    __shared__ __align__(16) double2 tots[NT > 1 ? 4 * NT : 1][256];
+    doublex4 tot[2][NT];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) acc[h][t] = doublex4{0.0, 0.0, 0.0, 0.0};
+        for (int t = 0; t < NT; ++t) {
+            tot[h][t] = doublex4{0.0, 0.0, 0.0, 0.0};
+            if constexpr (NT > 1)
+                tots[2 * (NT * h + t)][tid] = tots[2 * (NT * h + t) + 1][tid] = double2{0.0, 0.0};
+        }
     double aabs[2] = {0.0, 0.0};
     // a[h][g][2 e + q]: row iw + 16 h + r, column 64 J + 16 g + 8 e + 2 u + q
     auto fetch = [&](double (&a)[2][4][4], int J) {
@@ -125,6 +138,23 @@ __global__ __launch_bounds__(256, 2) void k_resid_mfma(const double *__restrict_
 #pragma unroll
                     for (int q = 0; q < 4; ++q) aabs[h] += fabs(a[h][g][q]);
     };
+    auto fold = [&]() {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                if constexpr (NT > 1) {
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        double2 &p = tots[2 * (NT * h + t) + e][tid];
+                        const double2 v = p;
+                        p = double2{v.x + acc[h][t][2 * e], v.y + acc[h][t][2 * e + 1]};
+                    }
+                } else {
+                    tot[h][t] += acc[h][t];
+                }
+            }
+    };
     double a0[2][4][4], a1[2][4][4];
     if (s < njt) {
         fetch_x(s);
@@ -138,19 +168,26 @@ __global__ __launch_bounds__(256, 2) void k_resid_mfma(const double *__restrict_
             fetch(a1, J + S);
         }
         __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[h][t] = doublex4{0.0, 0.0, 0.0, 0.0};
         multiply(a0, 0);
         __builtin_amdgcn_sched_barrier(0);
         if (J + S < njt)
             stage_x(1);
         __syncthreads();
-        if (J + S >= njt)
+        if (J + S >= njt) {
+            fold();
             break;
+        }
         if (J + 2 * S < njt) {
             fetch_x(J + 2 * S);
             fetch(a0, J + 2 * S);
         }
         __builtin_amdgcn_sched_barrier(0);
         multiply(a1, 1);
+        fold();
         __builtin_amdgcn_sched_barrier(0);
         if (J + 2 * S < njt)
             stage_x(0);
@@ -159,12 +196,21 @@ __global__ __launch_bounds__(256, 2) void k_resid_mfma(const double *__restrict_
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int64_t gi = iw + 16 * h + r;
+        if constexpr (NT > 1)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; v += 2) {
+                    const double2 p = tots[2 * (NT * h + t) + v / 2][tid];
+                    tot[h][t][v] = p.x;
+                    tot[h][t][v + 1] = p.y;
+                }
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int c = c0 + 16 * t + 4 * v + u;
-                if (gi < n && c < m) P[((int64_t)s * m + c) * n + gi] = acc[h][t][v];
+                if (gi < n && c < m) P[((int64_t)s * m + c) * n + gi] = tot[h][t][v];
             }
         if (want_abs) {  // the four k-slots of a row, in a fixed order
             double v = aabs[h];
@@ -189,7 +235,9 @@ __global__ __launch_bounds__(256, 2) void k_resid_mfma(const double *__restrict_
 // matrices, whose chunks of 16 tiles in sequence left the chip idle, and the
 // column sums reduced 16 at a time (a lane keeps half of its sums at each
 // exchange: 17 exchanges instead of 96).  n = 300: 12.2 us before, 7.0 now;
-// n = 3000: 26.0 and 16.9 us.
+// n = 3000: 26.0 and 16.9 us.  (More column partials then: the reduction sums
+// them apart from the row partials, or they would cost accuracy: n = 2500
+// 1.05 u |a||x| sqrt(n), and 1.23 behind the rows'.)
 #define RSYM_CH 16
 template <int MC, bool WA>
 __global__ __launch_bounds__(256) void k_resid_sym(const double *__restrict__ A, int64_t lda, int64_t n,
@@ -318,18 +366,16 @@ __global__ __launch_bounds__(256) void k_resid_reduce(const double *__restrict__
     const int c = blockIdx.y;
     double vr = 0.0, vx = 0.0, vb = 0.0, vd = 0.0, va = 0.0;
     if (i < n) {
-        // the slices in order, eight loads in flight (one at a time they cost
-        // a memory round trip each: 10.6 us for the 21 slices of n = 1300)
+        // eight slices at a time, added in pairs (their loads in flight: one at
+        // a time they cost a memory round trip each, 10.6 us for the 21 slices
+        // of n = 1300)
         auto total = [&](const double *p, int64_t st) {
             double sum = 0.0;
             for (int s0 = 0; s0 < S; s0 += 8) {
                 double v[8];
 #pragma unroll
                 for (int k = 0; k < 8; ++k) v[k] = (s0 + k < S) ? p[(s0 + k) * st] : 0.0;
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    if (s0 + k < S)
-                        sum += v[k];
+                sum += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
             }
             return sum;
         };
@@ -362,8 +408,9 @@ __global__ __launch_bounds__(256) void k_resid_reduce(const double *__restrict__
 
 // R = B - (sum_J RP[I][J] + sum_q CP[I][q]) and the norms (as k_resid_reduce).
 // Workgroup (I, c): 64 rows of block I, four waves; wave p sums the row
-// partials J = p, p + 4, ... and the column partials q = p, p + 4, ... (loads
-// issued four at a time), and the four sums are added in the fixed order
+// partials J = p, p + 4, ... and the column partials q = p, p + 4, ... (four
+// at a time: their loads in flight, and added in pairs), each kind to a sum of
+// its own, and the four waves' sums are added in the fixed order
 // (s0 + s1) + (s2 + s3).
 template <int MC>
 __global__ __launch_bounds__(256) void k_resid_sym_reduce(const double *__restrict__ B, int64_t ldb,
@@ -380,17 +427,16 @@ __global__ __launch_bounds__(256) void k_resid_sym_reduce(const double *__restri
     const int nrb = (int)((n + 63) / 64);
     const bool wa = want_abs && c == 0;
     {
-        double y = 0.0, ya = 0.0;
         // v = p, p + 4, ... < cnt, consecutive ones st doubles apart
-        auto sum = [&](const double *rp, const double *ra, int64_t st, int cnt) {
+        auto sum = [&](const double *rp, const double *ra, int64_t st, int cnt, double &y, double &ya) {
             int v = p;
             for (; v + 12 < cnt; v += 16) {
                 const double v0 = rp[v * st], v1 = rp[(v + 4) * st], v2 = rp[(v + 8) * st], v3 = rp[(v + 12) * st];
                 if (wa) {
                     const double a0 = ra[v * st], a1 = ra[(v + 4) * st], a2 = ra[(v + 8) * st], a3 = ra[(v + 12) * st];
-                    ya = (((ya + a0) + a1) + a2) + a3;
+                    ya += (a0 + a1) + (a2 + a3);
                 }
-                y = (((y + v0) + v1) + v2) + v3;
+                y += (v0 + v1) + (v2 + v3);
             }
             for (; v < cnt; v += 4) {
                 y += rp[v * st];
@@ -399,8 +445,11 @@ __global__ __launch_bounds__(256) void k_resid_sym_reduce(const double *__restri
             }
         };
         const double *rp = RP + (int64_t)I * nrb * NC * 64 + il, *cp = CP + (int64_t)I * Q * NC * 64 + il;
-        sum(rp + c * 64, rp + MC * 64, (int64_t)NC * 64, I + 1);
-        sum(cp + c * 64, cp + MC * 64, (int64_t)NC * 64, (nrb - I + ch - 1) / ch);
+        double y = 0.0, ya = 0.0, yc = 0.0, yca = 0.0;
+        sum(rp + c * 64, rp + MC * 64, (int64_t)NC * 64, I + 1, y, ya);
+        sum(cp + c * 64, cp + MC * 64, (int64_t)NC * 64, (nrb - I + ch - 1) / ch, yc, yca);
+        y += yc;
+        ya += yca;
         part[0][p][il] = y;
         part[1][p][il] = ya;
     }

@@ -47,3 +47,34 @@ def _edge(spd, orc, n, m, pad):
     assert np.all(np.abs(R - Ro) <= bound)
     want = np.abs(R).max(axis=1) / (np.abs(A).sum(axis=1).max() * np.abs(X).max(axis=1) + np.abs(Bt).max(axis=1))
     assert np.allclose(eta, want, rtol=1e-12, atol=0)
+
+
+# rms rounding error in units of u |a||x| sqrt(n) (rms values) on the inputs
+# below of the kernels before the single pass took fewer tiles per workgroup
+# and the many-column one to registers: one column, three or more
+FORMER = {300: (0.612, 0.700), 700: (0.788, 1.086), 1300: (0.901, 1.536), 2500: (1.065, 2.084), 4000: (1.254, 2.156),
+          6000: (1.372, 3.385)}
+
+
+@pytest.mark.parametrize("n", sorted(FORMER))
+@pytest.mark.parametrize("m", [1, 3, 8, 32])
+def test_residual_rounding(spd, n, m):
+    """The rounding error of A X against the exact one in whole numbers, no
+    larger than it has been (10 % for the sampling)."""
+    import torch
+    g = torch.Generator(device="cuda")
+    sq = count = 0
+    for seed in range(max(1, 6000 // n)):
+        g.manual_seed(1000 * n + seed)
+        A = torch.randint(-2 ** 24, 2 ** 24, (n, n), device="cuda", generator=g)
+        A = torch.tril(A) + torch.tril(A, -1).t()
+        X = torch.randint(-2 ** 26, 2 ** 26, (m, n), device="cuda", generator=g)  # sums below 2^63
+        R = spd.residual(A.double(), X.double(), torch.zeros(m, n, dtype=torch.float64, device="cuda"))[0]
+        for c in range(min(m, 3)):
+            exact = -(A * X[c]).sum(1)
+            hi = exact.double()
+            sq += float((((R[c] - hi) - (exact - hi.long()).double()) ** 2).sum())
+            count += n
+    err = (sq / count) ** 0.5 / (2.0 ** 50 / 3 * n ** 0.5 * U64)
+    print(f"residual rounding n={n} m={m}: {err:.3f}", flush=True)
+    assert err <= 1.1 * FORMER[n][0 if m == 1 else 1], err
