@@ -284,7 +284,15 @@ SPD_DEV T *b_tile(T *L, int I, int J)
 // system.  32 column steps with row j read back from shared memory, and a
 // 32-deep substitution, took 16 us (binary32) and 20 us (binary64) a block;
 // 16 columns in registers at a time, unrolled (29 KB of code, which took
-// longer to fetch than to run), 11 and 16; this takes 8.6 and 11.4.
+// longer to fetch than to run), 11 and 16; this took 8.6 and 11.4 with the
+// products straight off A's values.
+// The products are summed by themselves and come off A's values once, before a
+// panel's columns (and those of the panels before come off the diagonal tile
+// once, in b_factor): off the values one by one, each rounds at their size,
+// and the first solve's error for n = 33..64 and 65..128 was 4.8 and 5.7 u
+// (binary64), 4.5 and 5.5 (binary32); this way 3.6 and 3.9, 3.7 and 4.1.
+// 4096 mixed systems take 3.98 ms and 3.64 (binary64: A's values in the
+// registers of another slot leave more to the loops), 4.72 and 4.76 (binary32).
 template <typename T>
 SPD_DEV int b_diag_body(T *Ws, T *Lr, T *buf)
 {
@@ -301,15 +309,17 @@ SPD_DEV int b_diag_body(T *Ws, T *Lr, T *buf)
     using acc_t = typename std::conditional<sizeof(T) == 4, floatx4, doublex4>::type;
     // row of accumulator register q
     auto arow = [&](int q) { return sizeof(T) == 4 ? 4 * u + q : 4 * q + u; };
-    // columns 16 c .. 16 c + 15: of A's rows (ta: block rows 0 and 1 of column
-    // 0, block row 1 of column 1) and of the identity's (ti: block row 0 of
-    // columns 0 and 1, block row 1 of column 1)
-    acc_t ta[3], ti[3];
+    // columns 16 c .. 16 c + 15: of A's rows (va: block rows 0 and 1 of column
+    // 0, block row 1 of column 1; ta: the panels' products to come off them)
+    // and of the identity's (ti: block row 0 of columns 0 and 1, block row 1 of
+    // column 1; zero where products come off)
+    const acc_t zero = {0, 0, 0, 0};
+    acc_t va[3], ta[3] = {zero, zero, zero}, ti[3];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        ta[0][q] = Lr[r16 * S + arow(q)];
-        ta[1][q] = Lr[(H + r16) * S + arow(q)];
-        ta[2][q] = Lr[(H + r16) * S + H + arow(q)];
+        va[0][q] = Lr[r16 * S + arow(q)];
+        va[1][q] = Lr[(H + r16) * S + arow(q)];
+        va[2][q] = Lr[(H + r16) * S + H + arow(q)];
         ti[0][q] = ti[2][q] = (r16 == arow(q)) ? (T)1 : (T)0;
         ti[1][q] = (T)0;
     }
@@ -327,11 +337,11 @@ SPD_DEV int b_diag_body(T *Ws, T *Lr, T *buf)
     for (int p = 0; p < BNB / 4; ++p) {
         const int c0 = 4 * p, pc = p & 3;
         if (p < 4) {
-            put(ta[0], pc, 0);
-            put(ta[1], pc, H);
+            put(va[0] - ta[0], pc, 0);
+            put(va[1] - ta[1], pc, H);
             put(ti[0], pc, 2 * H);
         } else {
-            put(ta[2], pc, H);
+            put(va[2] - ta[2], pc, H);
             put(ti[1], pc, 2 * H);
             put(ti[2], pc, 3 * H);
         }
@@ -363,13 +373,13 @@ SPD_DEV int b_diag_body(T *Ws, T *Lr, T *buf)
 #pragma unroll
         for (int t = 0; t < 4; ++t) o[t] = buf[(H * t + r16) * P + u];
         if (p < 4) {
-            ta[0] = mma(-o[0], o[0], ta[0]);
-            ta[1] = mma(-o[0], o[1], ta[1]);
+            ta[0] = mma(o[0], o[0], ta[0]);
+            ta[1] = mma(o[0], o[1], ta[1]);
             ti[0] = mma(-o[0], o[2], ti[0]);
         } else {
             ti[2] = mma(-o[1], o[3], ti[2]);
         }
-        ta[2] = mma(-o[1], o[1], ta[2]);
+        ta[2] = mma(o[1], o[1], ta[2]);
         ti[1] = mma(-o[1], o[2], ti[1]);
         __builtin_amdgcn_wave_barrier();
     }
@@ -552,10 +562,12 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
         const int I0 = kb + wave;
         A32 acc[SLOTS];
         if (wave == 0) {
-            init(acc[0], kb, kb);
+            init(acc[1], kb, kb);
+            acc[0].zero();
             products_diag(acc[0], kb);
 #pragma unroll
-            for (int j = 0; j < 16; ++j) Lr[A32::col(j, lane) * BDIAG_S + A32::row(j, lane)] = acc[0].get(j);
+            for (int j = 0; j < 16; ++j)
+                Lr[A32::col(j, lane) * BDIAG_S + A32::row(j, lane)] = acc[1].get(j) + acc[0].get(j);
             __builtin_amdgcn_wave_barrier();
             const int bad = b_diag(Ws, Lr, Lr + BNB * BDIAG_S);
             if (lane == 0)

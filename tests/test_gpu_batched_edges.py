@@ -55,3 +55,29 @@ def test_half_requests_by_themselves_and_falling_back(spd, prec):
     for s in (1, 3):
         lo, hi = pb.b_off[s], pb.b_off[s] + shapes[s][0] * shapes[s][2]
         assert p1[s] == p3[s] == spd.PREC["fp32"] and np.array_equal(X1[lo:hi], X3[lo:hi])
+
+
+# geometric mean over 384 systems of the first solve's error in units of u,
+# on the inputs below, of the kernels with a left-looking diagonal block
+FORMER = {("fp32", 64): 3.827, ("fp32", 128): 4.936, ("fp64", 64): 3.895, ("fp64", 128): 5.158}
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("top", [64, 128])
+def test_first_solve_rounding(spd, prec, top):
+    """The error of one solve without corrections, a few panels deep, no
+    larger than it has been (5 %: sampling, 0.7 % rms)."""
+    rng = np.random.Generator(np.random.PCG64(top))
+    pb = spdgen.packed_batch_grouped([(int(n), 10.0, 2) for n in rng.integers(top // 2, top + 1, 384)], seed=top)
+    pb.A, pb.B = pb.A.cpu().numpy(), pb.B.cpu().numpy()
+    _, X, reps, _ = _run(spd, pb, prec, spd.default_opts(max_iter=0, fallback=0))
+    err = []
+    for s in range(384):
+        n, a, b = int(pb.n[s]), int(pb.a_off[s]), int(pb.b_off[s])
+        A, B = pb.A[a:a + n * n].reshape(n, n), pb.B[b:b + 2 * n].reshape(2, n).T
+        x = np.linalg.solve(A, B)
+        x = x + np.linalg.solve(A, (B - A.astype(np.longdouble) @ x).astype(np.float64))
+        err.append(np.linalg.norm(X[b:b + 2 * n].reshape(2, n).T - x) / np.linalg.norm(x))
+    err = float(np.exp(np.mean(np.log(err)))) / (2.0 ** -24 if prec == "fp32" else 2.0 ** -53)
+    _say(f"batched rounding {prec} n<={top}: {err:.3f}")
+    assert err <= 1.05 * FORMER[prec, top], err
