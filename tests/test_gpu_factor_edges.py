@@ -54,3 +54,32 @@ def test_zero_pivot(spd, prec, j0):
     F, info, st = spd.factor(dev(A), prec)
     F.close()
     assert st == spd.ERR_NOT_SPD and info == j0, (info, st)
+
+
+@pytest.mark.parametrize("k", [100, -500, 480, 500, 505, 510, 520])
+def test_power_of_four_scales_through(spd, k):
+    """Roots and quotients of the binary64 diagonal block keep their bits over
+    the whole range: A 4^-k has the factor L 2^-k, exactly, for 2 x 2 blocks of
+    few-bit numbers (subnormal ones, too, for k = 510 and 520)."""
+    n = 192
+    rng = np.random.Generator(np.random.PCG64(5))
+    A = np.zeros((n, n))
+    for i in range(0, n, 2):
+        p, q, r = rng.integers(2 ** 17, 2 ** 19), rng.integers(1, 2 ** 16), rng.integers(2 ** 18, 2 ** 19)
+        A[i, i], A[i + 1, i], A[i, i + 1], A[i + 1, i + 1] = p, q, q, r
+    A *= 2.0 ** -18
+    _say(f"factor scaled by 4^-{k}")
+
+    def factor(M):
+        F, info, st = spd.factor(dev(M), "fp64")
+        L = host(spd.export(F)[0])
+        F.close()
+        assert info == 0 and st == 0
+        return L
+
+    L, S = factor(A), factor(A * 2.0 ** (-2 * k))
+    want = L * 2.0 ** -k
+    if k < 505:  # beyond, what comes off the second pivot is itself rounded as a subnormal
+        assert np.array_equal(S, want), np.argwhere(S != want)[:5]
+    i = np.arange(0, n, 2)
+    assert np.array_equal(S[i, i], want[i, i]) and np.array_equal(S[i + 1, i], want[i + 1, i])
