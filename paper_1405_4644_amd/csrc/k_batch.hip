@@ -19,6 +19,7 @@
 
 #include "common.h"
 #include "internal.h"
+#include "sym_rows.h"
 
 #define BNB 32  // panel and tile width
 #define BDIAG_S 36  // row stride of a diagonal block in shared memory
@@ -866,41 +867,44 @@ SPD_DEV void b_sym(const double *A, int n, int m, const double *x, double *y, do
     for (int idx = tid; idx < m * BPITCH; idx += NT) y[idx] = 0.0;
     if constexpr (WA)
         for (int i = tid; i < n; i += NT) ya[i] = 0.0;
-    // a[h][t]: row 32 I + 8 (t / 2) + 2 u + t % 2, column 32 J + 16 h + j16.
-    // 16 bytes at a time; a pair of rows that would pass the last one comes
-    // from the last two, a column past the last one from that one (trim drops
-    // or moves what does not belong)
+    // a[h][t]: row 32 I + 8 (t / 2) + 2 u + t % 2, column 32 J + 16 h + j16,
+    // 16 bytes at a time (sym_rows.h: what is not in the matrix's lower
+    // triangle is loaded from there all the same, and dropped by trim)
     auto load = [&](double (&a)[2][8], int I, int J) {
-        unsigned cj[2];
+        int cj[2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) cj[h] = (unsigned)(min(J * BNB + 16 * h + j16, n - 1) * n);
+        for (int h = 0; h < 2; ++h) cj[h] = min(J * BNB + 16 * h + j16, n - 1);
+        if (J == nb - 1) {  // the end of the diagonal
 #pragma unroll
-        for (int t = 0; t < 8; t += 2) {
-            const unsigned i = (unsigned)max(min(I * BNB + 4 * t + 2 * u, n - 2), 0);
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    a[h][t] = gA[(unsigned)(cj[h] * n + sym_row(I * BNB + 8 * (t >> 1) + 2 * u + (t & 1), cj[h], n))];
+            return;
+        }
+#pragma unroll
+        for (int t = 0; t < 8; t += 2)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                if (n > 1) {
-                    const double2u v = *(const __attribute__((address_space(1))) double2u *)(gA + (cj[h] + i));
-                    a[h][t] = v.x;
-                    a[h][t + 1] = v.y;
-                } else {
-                    a[h][t] = a[h][t + 1] = gA[0];
-                }
+                const int i = sym_first(I * BNB + 4 * t + 2 * u, cj[h], n, I == J);
+                const double2u v = *(const __attribute__((address_space(1))) double2u *)(gA + (unsigned)(cj[h] * n + i));
+                a[h][t] = v.x;
+                a[h][t + 1] = v.y;
             }
-        }
     };
     // a block at the end of the matrix or on the diagonal: rows past the last
     // one and what is above the diagonal to zero, the diagonal halved (it is
     // in the rows' sums and in the columns')
     auto trim = [&](double (&a)[2][8], int I, int J) {
+        const bool end = J == nb - 1;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int t = 0; t < 8; t += 2) {
                 const int i = I * BNB + 4 * t + 2 * u, j = J * BNB + 16 * h + j16;
-                const double x = (i + 1 < n) ? a[h][t] : a[h][t + 1], y = a[h][t + 1];
-                a[h][t] = (i < n && i >= j) ? (i == j ? 0.5 * x : x) : 0.0;
-                a[h][t + 1] = (i + 1 < n && i + 1 >= j) ? (i + 1 == j ? 0.5 * y : y) : 0.0;
+                const double v0 = a[h][t], v1 = a[h][t + 1];
+                a[h][t] = sym_even(v0, v1, i, j, n, end);
+                a[h][t + 1] = sym_odd(v0, v1, i, j, n, I == J, end);
             }
     };
     double a[2][8], an[2][8];
