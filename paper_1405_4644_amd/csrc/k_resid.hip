@@ -277,7 +277,15 @@ __global__ __launch_bounds__(256) void k_resid_sym(const double *__restrict__ A,
             an[jj] = (gi < n && gj < n) ? A[gi + gj * lda] : 0.0;
         }
     };
-    load_tile(I0);
+    if (I0 == J) {  // the tile on the diagonal, always a chunk's first: its lower triangle
+#pragma unroll
+        for (int jj = 0; jj < CW; ++jj) {
+            const int64_t gi = j0 + lane, gj = j0 + CW * w + jj;
+            an[jj] = (gi < n && gj <= gi) ? A[gi + gj * lda] : 0.0;
+        }
+    } else {
+        load_tile(I0);
+    }
     for (int I = I0; I < I1; ++I) {
         const int64_t gi = (int64_t)I * 64 + lane;
         double a[CW];
@@ -286,12 +294,6 @@ __global__ __launch_bounds__(256) void k_resid_sym(const double *__restrict__ A,
         if (I + 1 < I1)
             load_tile(I + 1);
         const int dj = lane - CW * w;  // on the diagonal tile: row minus the wave's first column
-        if (I == J) {
-#pragma unroll
-            for (int jj = 0; jj < CW; ++jj)
-                if (dj < jj)
-                    a[jj] = 0.0;
-        }
         double xi[MC];
 #pragma unroll
         for (int c = 0; c < MC; ++c) xi[c] = (gi < n && c < m) ? X[gi + (int64_t)c * ldx] : 0.0;
