@@ -528,6 +528,11 @@ __device__ __attribute__((noinline)) void b_solve(const T *L, const T *Winv, int
 // order, so the result does not depend on timing.  Splitting the columns
 // rather than the rows keeps the waves level for every n (rows per wave
 // left one wave a second full pass whenever n was just above 256).
+// Bound by latency with 512 systems in flight.  4096 systems that all
+// converge take 10.2 (FP16) and 13.2 ms (BF16); 11.0 and 14.4 with a choice
+// between A and the mirror at every element (most batches lie on one side of
+// the diagonal), bounds looked at for every column, and the maxima one kind
+// after the other.
 template <int WAVES>
 __device__ __attribute__((noinline)) void b_residual(const double *A, const double *Am, int n, int np, int m,
                                                      const double *X, const double *B, const double *d, double *R,
@@ -535,18 +540,24 @@ __device__ __attribute__((noinline)) void b_residual(const double *A, const doub
 {
     constexpr int NT = WAVES * 64, NM = SPD_BATCH_NMAX;
     static_assert(WAVES == 4, "partial sums are laid out for four waves");
-    const auto gA = gmem(A), gAm = gmem(Am), gX = gmem(X), gB = gmem(B);
+    n = uni(n);
+    np = uni(np);
+    m = uni(m);
+    const auto gA = gmem(uni(A)), gAm = gmem(uni(Am)), gX = gmem(X), gB = gmem(B);
     const auto gR = gmem(R);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int MR = SPD_BATCH_MAXRHS;
     double *xs = sm.ys;  // xs[c * NMAX + j]
     double *abs_rows = sm.arow;
-    for (int idx = tid; idx < m * n; idx += NT) {
-        const int c = idx / n, j = idx % n;
-        xs[c * NM + j] = gX[j + (int64_t)c * n];
+    // (past the last element it is repeated, up to a whole batch: those
+    // products are with zeros)
+    constexpr int CH = 16;
+    const int nx = (n + CH - 1) / CH * CH;
+    for (int idx = tid; idx < m * nx; idx += NT) {
+        const int c = idx / nx, j = idx % nx;
+        xs[c * NM + j] = gX[min(j, n - 1) + c * n];
     }
     __syncthreads();
-    constexpr int CH = 16;
     const int nch = (n + CH - 1) / CH, cpw = (nch + WAVES - 1) / WAVES;
     const int jlo = wave * cpw * CH, jhi = min(n, (wave + 1) * cpw * CH);
     for (int i0 = 0; i0 < n; i0 += 64) {
@@ -555,12 +566,26 @@ __device__ __attribute__((noinline)) void b_residual(const double *A, const doub
 #pragma unroll
         for (int c = 0; c < MR; ++c) acc[c] = 0.0;
         double a[CH], an[CH];
+        // (rows past the last one repeat it; their sums are dropped)
+        const unsigned ic = (unsigned)min(i, n - 1);
         auto load = [&](double *dst, int j0) {
+            auto from = [&](auto p, int ld) {
 #pragma unroll
-            for (int u = 0; u < CH; ++u) {
-                const int j = j0 + u;
-                dst[u] = (i < n && j < jhi) ? ((j <= i) ? gA[i + (int64_t)j * n] : gAm[i + (int64_t)j * np]) : 0.0;
-            }
+                for (int u = 0; u < CH; ++u) dst[u] = p[ic + (unsigned)(min(j0 + u, n - 1) * ld)];
+            };
+            if (j0 + CH - 1 <= i0)  // every j <= i
+                from(gA, n);
+            else if (j0 > i0 + 63)  // every j > i
+                from(gAm, np);
+            else
+#pragma unroll
+                for (int u = 0; u < CH; ++u) {
+                    const unsigned j = (unsigned)min(j0 + u, n - 1);
+                    dst[u] = (j <= ic) ? gA[ic + j * (unsigned)n] : gAm[ic + j * (unsigned)np];
+                }
+            if (j0 + CH > jhi)
+#pragma unroll
+                for (int u = 0; u < CH; ++u) dst[u] = (j0 + u < jhi) ? dst[u] : 0.0;
         };
         if (jlo < jhi)
             load(a, jlo);
@@ -569,7 +594,7 @@ __device__ __attribute__((noinline)) void b_residual(const double *A, const doub
                 load(an, j0 + CH);
 #pragma unroll
             for (int u = 0; u < CH; ++u) {
-                const int j = min(j0 + u, n - 1);
+                const int j = j0 + u;
 #pragma unroll
                 for (int c = 0; c < MR; ++c)
                     if (c < m)
@@ -599,40 +624,36 @@ __device__ __attribute__((noinline)) void b_residual(const double *A, const doub
         }
         __syncthreads();
     }
-    // maxima (NaN propagates), per column, one kind at a time (kind 0..3:
-    // |r|, |x|, |b|, |d r|), then ||A||_inf
-#pragma unroll 1
-    for (int kind = 0; kind < 4; ++kind) {
-        double v[MR];
+    // maxima (NaN propagates): a wave takes whole columns, four rows a lane at a time
+    for (int c = wave; c < m; c += WAVES) {
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int q0 = lane; q0 < n; q0 += 4 * 64) {
+            double rv[4], bv[4], dv[4];
 #pragma unroll
-        for (int c = 0; c < MR; ++c) v[c] = 0.0;
-        for (int i = tid; i < n; i += NT) {
+            for (int k = 0; k < 4; ++k) {
+                const int q = min(q0 + 64 * k, n - 1);
+                rv[k] = gR[q + c * n];
+                bv[k] = gB[q + c * n];
+                dv[k] = gmem(d)[q];
+            }
 #pragma unroll
-            for (int c = 0; c < MR; ++c)
-                if (c < m) {
-                    const double x = (kind == 0) ? gR[i + (int64_t)c * n]
-                                     : (kind == 1) ? xs[c * NM + i]
-                                     : (kind == 2) ? gB[i + (int64_t)c * n]
-                                                   : gmem(d)[i] * gR[i + (int64_t)c * n];
-                    v[c] = b_nanmax(v[c], fabs(x));
+            for (int k = 0; k < 4; ++k) {
+                const int q = q0 + 64 * k;
+                if (q < n) {
+                    v[0] = b_nanmax(v[0], fabs(rv[k]));
+                    v[1] = b_nanmax(v[1], fabs(xs[c * NM + q]));
+                    v[2] = b_nanmax(v[2], fabs(bv[k]));
+                    v[3] = b_nanmax(v[3], fabs(dv[k] * rv[k]));
                 }
+            }
         }
 #pragma unroll
-        for (int c = 0; c < MR; ++c) {
-            if (c >= m)
-                break;
+        for (int k = 0; k < 4; ++k) {
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v[c] = b_nanmax(v[c], __shfl_xor(v[c], off));
+            for (int off = 32; off > 0; off >>= 1) v[k] = b_nanmax(v[k], __shfl_xor(v[k], off));
             if (lane == 0)
-                sm.red[wave][c] = v[c];
+                sm.norms[1 + k * m + c] = v[k];
         }
-        __syncthreads();
-        if (tid < m) {
-            double x = 0.0;
-            for (int w = 0; w < WAVES; ++w) x = b_nanmax(x, sm.red[w][tid]);
-            sm.norms[1 + kind * m + tid] = x;
-        }
-        __syncthreads();
     }
     if (want_anorm) {
         double x = 0.0;
@@ -647,8 +668,8 @@ __device__ __attribute__((noinline)) void b_residual(const double *A, const doub
             for (int w = 0; w < WAVES; ++w) y = b_nanmax(y, sm.red[w][0]);
             sm.norms[0] = y;
         }
-        __syncthreads();
     }
+    __syncthreads();
 }
 
 }  // namespace half_path
