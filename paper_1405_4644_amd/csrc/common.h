@@ -77,68 +77,26 @@ template <> struct Acc32<double> {
     SPD_DEV void set(int j, double x) { v[j / 8][(j / 4) % 2][j % 4] = x; }
 };
 
-// One k-step fragment of a 32-row operand block whose rows are contiguous in
-// memory (element (r, k) at p[r + k*ks]).  binary32: one value per lane
-// (rows l%32, k-step 2); binary64: two values per lane (rows l%16 and
-// 16 + l%16, k-step 4).
-template <typename T> struct Frag;
-template <> struct Frag<float> {
+// One k-step (of 2) of a 32-row operand block whose rows are contiguous in
+// memory (element (r, k) at p[r + k*ks]): a value per lane, row l%32.
+struct Frag {
     static constexpr int K = 2;
     float v;
     SPD_DEV void load(const float *p, int ks, int lane) { v = p[(lane & 31) + (lane >> 5) * ks]; }
     SPD_DEV void negate() { v = -v; }
 };
-template <> struct Frag<double> {
-    static constexpr int K = 4;
-    double v[2];
-    SPD_DEV void load(const double *p, int ks, int lane)
-    {
-        const int r = lane & 15, kk = lane >> 4;
-        v[0] = p[r + kk * ks];
-        v[1] = p[16 + r + kk * ks];
-    }
-    SPD_DEV void negate() { v[0] = -v[0]; v[1] = -v[1]; }
-};
-SPD_DEV void mma(Acc32<float> &acc, const Frag<float> &a, const Frag<float> &b) { acc.mma(a.v, b.v); }
-
-SPD_DEV void mma(Acc32<double> &acc, const Frag<double> &a, const Frag<double> &b) { acc.mma(a.v, b.v); }
+SPD_DEV void mma(Acc32<float> &acc, const Frag &a, const Frag &b) { acc.mma(a.v, b.v); }
 
 // acc += A(32 x kc) * B(32 x kc)^T with A(r,k) = pa[r + k*aks], B(r,k) = pb[r + k*bks];
-// kc a multiple of Frag<T>::K.
-template <typename T>
-SPD_DEV void mma_tile(Acc32<T> &acc, const T *pa, int aks, const T *pb, int bks, int kc, int lane)
+// kc a multiple of Frag::K.
+SPD_DEV void mma_tile(Acc32<float> &acc, const float *pa, int aks, const float *pb, int bks, int kc, int lane)
 {
 #pragma unroll 4
-    for (int k = 0; k < kc; k += Frag<T>::K) {
-        Frag<T> a, b;
+    for (int k = 0; k < kc; k += Frag::K) {
+        Frag a, b;
         a.load(pa + (size_t)k * aks, aks, lane);
         b.load(pb + (size_t)k * bks, bks, lane);
         mma(acc, a, b);
-    }
-}
-
-// Cooperative copy of a ROWS x cols column-major block (leading dimension ld)
-// into LDS as dst[c * dld + r].  Each thread issues UNROLL global loads
-// before storing any of them, so load latency overlaps instead of
-// serialising on every element.  NT = threads taking part (tid < NT).
-template <typename T, int ROWS, int NT, int UNROLL>
-SPD_DEV void copy_g2s(T *dst, int dld, const T *__restrict__ src, int64_t ld, int cols, int tid)
-{
-    const int total = ROWS * cols;
-    for (int base = 0; base < total; base += NT * UNROLL) {
-        T v[UNROLL];
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            const int idx = base + u * NT + tid;
-            if (idx < total)
-                v[u] = src[(idx % ROWS) + (int64_t)(idx / ROWS) * ld];
-        }
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            const int idx = base + u * NT + tid;
-            if (idx < total)
-                dst[(idx / ROWS) * dld + (idx % ROWS)] = v[u];
-        }
     }
 }
 

@@ -125,16 +125,9 @@ struct PickSmem {
     float logit[PICK_NCLS];
 };
 
-template <typename T>
-SPD_DEV T round_half(T v, int half)
+SPD_DEV float round_half(float v, int half)
 {
-    if constexpr (sizeof(T) == 4) {
-        if (half == HALF_F16)
-            return (float)(_Float16)v;
-        if (half == HALF_BF16)
-            return (float)(__bf16)v;
-    }
-    return v;
+    return half == HALF_F16 ? (float)(_Float16)v : (float)(__bf16)v;
 }
 
 // value of v in lane src (src uniform); binary64 as two 32-bit halves
@@ -164,7 +157,6 @@ template <> struct BTile<float> {
     using V = floatx4;
     float v[16];  // lane (r = l % 32, h = l / 32): column 8 (j / 4) + 4 h + j % 4 in v[j]
     static SPD_DEV int pos(int r, int c) { return ((c >> 2) * 32 + r) * 4 + (c & 3); }
-    static SPD_DEV void coords(int e, int &r, int &c) { r = (e >> 2) & 31; c = 4 * (e >> 7) + (e & 3); }
     SPD_DEV void load(const float *t, int lane)
     {
 #pragma unroll
@@ -199,12 +191,6 @@ template <> struct BTile<double> {
     typedef double V __attribute__((ext_vector_type(2)));
     double v[2][2][4];  // lane (r = l % 16, u = l / 16): row 16 b + r, column 16 a + 4 q + u in v[b][a][q]
     static SPD_DEV int pos(int r, int c) { return ((4 * (c >> 4) + (c & 3)) * 32 + r) * 4 + ((c >> 2) & 3); }
-    static SPD_DEV void coords(int e, int &r, int &c)
-    {
-        const int g = e >> 7;
-        r = (e >> 2) & 31;
-        c = 16 * (g >> 2) + 4 * (e & 3) + (g & 3);
-    }
     // columns 16 a .. 16 a + 15
     static SPD_DEV void load_half(double (&x)[2][4], const double *t, int a, int lane)
     {
@@ -677,7 +663,7 @@ template <typename T, int WAVES>
 __device__ __attribute__((noinline)) void b_solve(const T *L, const T *Winv, int n, int np, int m, const double *R, const double *d, double mu,
                      double *X, int accumulate, SolveSmem &sm)
 {
-    constexpr int NT = WAVES * 64, YS = BVec<T>::YS;
+    constexpr int YS = BVec<T>::YS;
     using acc_t = typename BVec<T>::acc;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, u = lane >> 4;

@@ -3,7 +3,7 @@
 // its product with the search directions, and the binary64 vector steps.
 //
 // Storage.  Dense A~: binary32, ldt x ldt (ldt = n rounded up to 256, zero
-// outside n x n), both triangles, in the MFMA fragment order of frag_off so
+// outside n x n), both triangles, in MFMA fragment order (below) so
 // that each product streams it with fully coalesced loads.  Band A~:
 // Bd[(d + k) ldt + i] = A~(i, i + d) for d = -k..k (zero where i + d falls
 // outside 0..n-1, and in rows n..ldt-1).  Search directions: P (binary64,
@@ -37,13 +37,6 @@ __device__ inline double wave_sum(double v)
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
-__device__ inline float wave_sumf(float v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 // fixed-order sum of one value per thread over a 256-thread block
 __device__ inline double block_sum256(double v, double *red)
 {
@@ -55,18 +48,12 @@ __device__ inline double block_sum256(double v, double *red)
     return ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-// Offset of A~(j, i) in the dense fragment order: column block I = i / 32,
+// A~(j, i) in the dense fragment order (k_cg_dense): column block I = i / 32,
 // row block J = j / 16 (512 values, contiguous, blocks of one column block
 // consecutive along J); inside a block, value e of the float4 number s of
 // lane l, with l = 32 h + i % 32 and j % 16 = 8 h + 4 s + e.  A wave's float4
 // load of one (s) half of a block is then 1 KB contiguous, and lane l holds
 // exactly the MFMA operand values of row i % 32 at k-slot h.
-__device__ inline int64_t frag_off(int64_t j, int64_t i, int64_t nJ)
-{
-    const int64_t jj = j & 15;
-    const int h = (int)(jj >> 3), s = (int)((jj >> 2) & 1), e = (int)(jj & 3);
-    return ((i >> 5) * nJ + (j >> 4)) * 512 + s * 256 + (h * 32 + (int)(i & 31)) * 4 + e;
-}
 
 // Offset of the binary32 direction value (j, c): right-hand sides in blocks
 // of W columns (W = m for m <= 4, else 32), each block ldt x W stored with
