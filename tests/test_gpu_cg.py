@@ -269,3 +269,69 @@ def test_cg_handle_serves_fewer_right_hand_sides(spd, n, first, then, band):
     torch.cuda.synchronize()
     H.close()
     assert rep.as_dict() == ref.as_dict() and torch.equal(X, Y)
+
+
+def _even_matrix(n, band, seed):
+    """Off-diagonal entries of one size, +-(1/2 .. 3/2), over the whole matrix
+    or band, and a diagonal that makes it positive definite."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    A = np.where(rng.random((n, n)) < 0.5, -1.0, 1.0) * (0.5 + rng.random((n, n)))
+    i = np.arange(n)
+    if band >= 0:
+        A[np.abs(i[:, None] - i[None, :]) > band] = 0.0
+    A = np.tril(A, -1)
+    A = A + A.T
+    w = n if band < 0 else 2 * band + 1
+    A[i, i] = 3.2 * math.sqrt(w)
+    return A, w
+
+
+def _cg_steps(A, b, k):
+    A, x, r = A.astype(np.float32).astype(np.float64), np.zeros_like(b), b.copy()
+    p, rho = r.copy(), (r * r).sum(axis=0)
+    for _ in range(k):
+        z = A @ p.astype(np.float32).astype(np.float64)
+        al = rho / (p * z).sum(axis=0)
+        x, r = x + al * p, r - al * z
+        rn = (r * r).sum(axis=0)
+        p, rho = r + rn / rho * p, rn
+    return x
+
+
+@pytest.mark.parametrize("n,band,m", [(2816, -1, 1), (2817, -1, 1), (3072, -1, 1), (3073, -1, 1), (3330, -1, 1),
+                                      (3073, -1, 3), (3073, -1, 6), (2100, 5, 1), (2100, 128, 5), (2100, 129, 5),
+                                      (2100, 128, 1), (2100, 129, 1), (2100, 1887, 3), (2100, 1888, 3)])
+def test_cg_products_miss_nothing(spd, n, band, m):
+    """Three steps on a matrix without decay against the same in binary64 on
+    the binary32 matrix.  A product of rows of w entries is off by about
+    sqrt(w) u |A||p| at most, and twice as much for each step that follows:
+    6 sqrt(w) u max(|A||b|) / max|A b| of max|x|.  A 256-wide tile, an outermost
+    diagonal or a row of a block's halo left out (planted here, in the
+    reference) exceeds that more than twentyfold."""
+    k = 3
+    _say(f"cg products n={n} band={band} m={m}")
+    A, w = _even_matrix(n, band, n + band)
+    b = np.random.Generator(np.random.PCG64(9)).standard_normal((n, m))
+    x = _cg_steps(A, b, k)
+    bar = 6 * math.sqrt(w) * U32 * (np.abs(A) @ np.abs(b)).max() / np.abs(A @ b).max()
+    lost = A.copy()
+    if band < 0:
+        last = (n - 1) // 256
+        lost[256 * last:, :256] = 0.0
+        lost[:256, 256 * last:] = 0.0
+    else:
+        lost[256:512, 256 - band if band <= 256 else 0] = 0.0
+    edge = A.copy()
+    if band >= 0:
+        i = np.arange(n)
+        edge[np.abs(i[:, None] - i[None, :]) == band] = 0.0
+    else:
+        edge[768:1024, 256:512] = 0.0
+        edge[256:512, 768:1024] = 0.0
+    for planted in (lost, edge):
+        assert np.abs(_cg_steps(planted, b, k) - x).max() / np.abs(x).max() > 20 * bar
+    X, rep = _gpu_cg(spd, A, np.ascontiguousarray(b.T), band, max_outer=1, max_inner=k, inner_tol=0.0)
+    assert rep.iters_low == k
+    err = np.abs(X.T - x).max(axis=0) / np.abs(x).max(axis=0)
+    _say(f"  {err.max() / bar:.4f} of the bar {bar:.2e}")
+    assert err.max() <= bar, (err.max(), bar)
