@@ -394,7 +394,7 @@ SPD_DEV int b_diag(float *Ws, float *Lr, float *buf) { return b_diag_body<float>
 // and 31 GB in binary64, at 4.3 TB/s, a factorisation of 394 and 600 us (mean
 // over the systems).  With the residual's mirror of A gone as well (b_sym),
 // 20 and 17 GB, 194 and 330 us.
-template <typename T, int WAVES>
+template <typename T, int WAVES, int KERN>
 __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np, double *d, double mu, int equil,
                                                   T *L, T *Winv, SolveSmem &sm)
 {
@@ -659,7 +659,7 @@ struct BOp {
     }
 };
 
-template <typename T, int WAVES>
+template <typename T, int WAVES, int KERN>
 __device__ __attribute__((noinline)) void b_solve(const T *L, const T *Winv, int n, int np, int m, const double *R, const double *d, double mu,
                      double *X, int accumulate, SolveSmem &sm)
 {
@@ -1031,7 +1031,7 @@ SPD_DEV void b_sym(const double *A, int n, int m, const double *x, double *y, do
 // R = B - A X (binary64) and the norms: norms[1 + k m + c], k = 0..3:
 // max|r|, max|x|, max|b|, max|d r|; with want_anorm also norms[0] =
 // ||A||_inf.
-template <int WAVES>
+template <int WAVES, int KERN>
 __device__ __attribute__((noinline)) void b_residual(const double *A, int n, int m, const double *X, const double *B,
                                                      const double *d, double *R, int want_anorm, SolveSmem &sm)
 {
@@ -1511,15 +1511,93 @@ SPD_DEV void b_rhs_max(const double *B, const double *d, int n, int m, Smem &sm)
     __syncthreads();
 }
 
+// One system through Algorithm 1 by one workgroup, at the precisions of the
+// kernel's factor type: HI = false takes FP32 requests (and, from the
+// half-precision kernel, those that fall back), HI = true the FP64 requests
+// and every system handed over (a breakdown or non-convergence in binary32
+// with fallback on: prec[s] = the next precision, reps[s].fallbacks the count
+// so far).  Systems of the other kernels are skipped; the binary32 kernel also
+// reports empty systems and invalid sizes.  ticks[s] and reps[s].fallbacks
+// (zeroed by the order kernel) accumulate over the kernels.  KERN: the
+// functions that are not inlined once more for the half-precision kernel (1);
+// shared with it they are slower in the other (4096 binary32 systems: 4.76 ms
+// apart, 4.87 shared).
+template <int WAVES, bool HI, int KERN>
+SPD_DEV void b_system(const BatchArgs &a, int64_t s, SolveSmem &sm)
+{
+    using T = typename std::conditional<HI, double, float>::type;
+    const int n = a.n[s], m = a.nrhs[s];
+    int p = a.prec[s];
+    if (p == SPD_AUTO)
+        p = SPD_FP32;
+    const bool valid = n >= 0 && m >= 0 && n <= SPD_BATCH_NMAX && m <= SPD_BATCH_MAXRHS && p >= SPD_BF16 &&
+                       p <= SPD_FP64;
+    const bool half = valid && p < SPD_FP32 && n > 0 && m > 0;
+    if (HI ? (!valid || p != SPD_FP64) : (half || (valid && p == SPD_FP64)))
+        return;  // another kernel's system
+    if (!HI && KERN == 0 && valid && a.reps[s].fallbacks)
+        return;  // a half-precision request that has been through binary32
+    const unsigned long long t0 = wall_clock64();
+    spd_report rep;
+    rep.status = SPD_OK;
+    rep.prec_used = p;
+    rep.iters_low = rep.iters_high = 0;
+    rep.fallbacks = a.reps[s].fallbacks;
+    rep.info = 0;
+    rep.eta = 0.0;
+    bool handover = false;
+    if (!valid) {
+        rep.status = SPD_ERR_INVALID_ARG;
+    } else if (n > 0 && m > 0) {
+        const double *A = a.A + a.a_off[s];
+        const double *B = a.B + a.b_off[s];
+        double *X = a.X + a.b_off[s];
+        const int np = ((n + BNB - 1) / BNB) * BNB;
+        const BatchWs w = batch_ws(a);
+        // a binary32 factor is equilibrated, a binary64 one that of A itself
+        T *L = (T *)w.L, *Winv = (T *)w.Winv;
+        rep.prec_used = p;
+        const int info = b_factor<T, WAVES, KERN>(A, n, np, w.d, 1.0, HI ? 0 : a.equilibrate, L, Winv, sm);
+        rep.info = info;
+        int r = SPD_ERR_NOT_SPD;
+        if (!info) {
+            // first solve from B, then refinement
+            b_rhs_max<WAVES>(B, w.d, n, m, sm);
+            b_solve<T, WAVES, KERN>(L, Winv, n, np, m, B, w.d, 1.0, X, 0, sm);
+            r = b_refine<T>(
+                a.tol, a.max_iter, m, rep, sm,
+                [&](int first, SolveSmem &h) { b_residual<WAVES, KERN>(A, n, m, X, B, w.d, w.R, first, h); },
+                [&](SolveSmem &h) { b_solve<T, WAVES, KERN>(L, Winv, n, np, m, w.R, w.d, 1.0, X, 1, h); });
+        }
+        rep.status = r;
+        if (r != SPD_OK && a.fallback && !HI) {  // binary32 goes to the binary64 kernel
+            rep.fallbacks++;
+            handover = true;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (handover) {
+            a.reps[s].fallbacks = rep.fallbacks;
+            a.prec[s] = SPD_FP64;
+        } else {
+            a.reps[s] = rep;
+            a.prec[s] = rep.prec_used;
+        }
+        if (a.ticks)
+            a.ticks[s] += (int64_t)(wall_clock64() - t0);
+    }
+}
+
 // A half-precision request's attempt (k_batch_half.h): reported where it
-// converged or may not fall back, else handed to the binary32 kernel
-// (prec[s] = FP32, reps[s].fallbacks = 1).
+// converged or may not fall back, else it is a binary32 request from here on
+// (prec[s] = FP32, reps[s].fallbacks = 1).  Returns whether it is.
 template <int WAVES>
-SPD_DEV void b_half_system(const BatchArgs &a, int64_t s, half_path::SolveSmem &sm)
+SPD_DEV bool b_half_system(const BatchArgs &a, int64_t s, half_path::SolveSmem &sm)
 {
     const int n = a.n[s], m = a.nrhs[s], p = a.prec[s];
     if (n <= 0 || m <= 0 || n > SPD_BATCH_NMAX || m > SPD_BATCH_MAXRHS || p < SPD_BF16 || p >= SPD_FP32)
-        return;
+        return false;
     const unsigned long long t0 = wall_clock64();
     spd_report rep;
     rep.prec_used = p;
@@ -1548,9 +1626,10 @@ SPD_DEV void b_half_system(const BatchArgs &a, int64_t s, half_path::SolveSmem &
             [&](half_path::SolveSmem &h) { half_path::b_solve<WAVES>(L, Winv, n, np, m, w.R, w.d, mu, X, 1, h); });
     }
     rep.status = r;
+    const bool back = r != SPD_OK && a.fallback;
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (r == SPD_OK || !a.fallback) {
+        if (!back) {
             a.reps[s] = rep;
         } else {
             a.reps[s].fallbacks = 1;
@@ -1559,79 +1638,8 @@ SPD_DEV void b_half_system(const BatchArgs &a, int64_t s, half_path::SolveSmem &
         if (a.ticks)
             a.ticks[s] += (int64_t)(wall_clock64() - t0);
     }
-}
-
-// One system through Algorithm 1 by one workgroup, at the precisions of the
-// kernel's factor type: HI = false takes FP32 requests and what the
-// half-precision kernel handed over, HI = true the FP64 requests and every
-// system the binary32 kernel handed over (a breakdown or non-convergence with
-// fallback on: prec[s] = the next precision, reps[s].fallbacks the count so
-// far).  Systems of the other kernels are skipped; the binary32 kernel also
-// reports empty systems and invalid sizes.  ticks[s] and reps[s].fallbacks
-// (zeroed by the order kernel) accumulate over the kernels.
-template <int WAVES, bool HI>
-SPD_DEV void b_system(const BatchArgs &a, int64_t s, SolveSmem &sm)
-{
-    using T = typename std::conditional<HI, double, float>::type;
-    const int n = a.n[s], m = a.nrhs[s];
-    int p = a.prec[s];
-    if (p == SPD_AUTO)
-        p = SPD_FP32;
-    const bool valid = n >= 0 && m >= 0 && n <= SPD_BATCH_NMAX && m <= SPD_BATCH_MAXRHS && p >= SPD_BF16 &&
-                       p <= SPD_FP64;
-    const bool half = valid && p < SPD_FP32 && n > 0 && m > 0;
-    if (HI ? (!valid || p != SPD_FP64) : (half || (valid && p == SPD_FP64)))
-        return;  // another kernel's system
-    const unsigned long long t0 = wall_clock64();
-    spd_report rep;
-    rep.status = SPD_OK;
-    rep.prec_used = p;
-    rep.iters_low = rep.iters_high = 0;
-    rep.fallbacks = a.reps[s].fallbacks;
-    rep.info = 0;
-    rep.eta = 0.0;
-    bool handover = false;
-    if (!valid) {
-        rep.status = SPD_ERR_INVALID_ARG;
-    } else if (n > 0 && m > 0) {
-        const double *A = a.A + a.a_off[s];
-        const double *B = a.B + a.b_off[s];
-        double *X = a.X + a.b_off[s];
-        const int np = ((n + BNB - 1) / BNB) * BNB;
-        const BatchWs w = batch_ws(a);
-        // a binary32 factor is equilibrated, a binary64 one that of A itself
-        T *L = (T *)w.L, *Winv = (T *)w.Winv;
-        rep.prec_used = p;
-        const int info = b_factor<T, WAVES>(A, n, np, w.d, 1.0, HI ? 0 : a.equilibrate, L, Winv, sm);
-        rep.info = info;
-        int r = SPD_ERR_NOT_SPD;
-        if (!info) {
-            // first solve from B, then refinement
-            b_rhs_max<WAVES>(B, w.d, n, m, sm);
-            b_solve<T, WAVES>(L, Winv, n, np, m, B, w.d, 1.0, X, 0, sm);
-            r = b_refine<T>(
-                a.tol, a.max_iter, m, rep, sm,
-                [&](int first, SolveSmem &h) { b_residual<WAVES>(A, n, m, X, B, w.d, w.R, first, h); },
-                [&](SolveSmem &h) { b_solve<T, WAVES>(L, Winv, n, np, m, w.R, w.d, 1.0, X, 1, h); });
-        }
-        rep.status = r;
-        if (r != SPD_OK && a.fallback && !HI) {  // binary32 goes to the binary64 kernel
-            rep.fallbacks++;
-            handover = true;
-        }
-    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        if (handover) {
-            a.reps[s].fallbacks = rep.fallbacks;
-            a.prec[s] = SPD_FP64;
-        } else {
-            a.reps[s] = rep;
-            a.prec[s] = rep.prec_used;
-        }
-        if (a.ticks)
-            a.ticks[s] += (int64_t)(wall_clock64() - t0);
-    }
+    return back;
 }
 
 // The precision picker for SPD_AUTO systems: features and perceptron by one
@@ -1677,17 +1685,24 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_batch(BatchArgs a)
         const int64_t q = s_q;
         if (q >= a.batch)
             return;
-        b_system<WAVES, HI>(a, a.order[q], sm);
+        b_system<WAVES, HI, 0>(a, a.order[q], sm);
         __syncthreads();
     }
 }
 
 // The half-precision requests; nothing where there are none (queue[3], set by
-// the order kernel or the picker).
+// the order kernel or the picker).  One that falls back goes on in binary32 at
+// once: left to the binary32 kernel, it would wait for the slowest attempt of
+// the batch (8 FP16 requests of which one falls back: 2.90 ms, and 2.22 so; 600
+// of which 267 do: 6.86 and 6.56).  The binary32 kernel, which runs after this
+// one, tells it by its count of fallbacks.
 template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64, 2) void k_batch_half(BatchArgs a)
 {
-    __shared__ half_path::SolveSmem sm;
+    __shared__ union {
+        half_path::SolveSmem half;
+        SolveSmem low;
+    } sm;
     __shared__ int s_q;
     if (a.queue[3] == 0)
         return;
@@ -1698,7 +1713,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_batch_half(BatchArgs a)
         const int64_t q = s_q;
         if (q >= a.batch)
             return;
-        b_half_system<WAVES>(a, a.order[q], sm);
+        if (b_half_system<WAVES>(a, a.order[q], sm.half))
+            b_system<WAVES, false, 1>(a, a.order[q], sm.low);
         __syncthreads();
     }
 }
@@ -1803,8 +1819,9 @@ hipError_t launch_batch(const BatchLaunch &l, hipStream_t st)
     a.ticks = l.ticks;
     hipLaunchKernelGGL(k_batch_order, dim3(1), dim3(1024), 0, st, l.batch, l.n, l.prec, l.reps, l.order, l.queue,
                        l.ticks);
-    // picker (AUTO systems), then half-precision requests, binary32 (requests
-    // and hand-overs), binary64 (the same); four wavefronts per workgroup
+    // picker (AUTO systems), then half-precision requests (with their fallback
+    // to binary32), binary32 ones, binary64 (requests and hand-overs); four
+    // wavefronts per workgroup
     if (l.picker)
         hipLaunchKernelGGL(k_batch_pick, dim3((unsigned)l.grid), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_batch_half<4>, dim3((unsigned)l.grid), dim3(256), 0, st, a);

@@ -81,3 +81,27 @@ def test_first_solve_rounding(spd, prec, top):
     err = float(np.exp(np.mean(np.log(err)))) / (2.0 ** -24 if prec == "fp32" else 2.0 ** -53)
     _say(f"batched rounding {prec} n<={top}: {err:.3f}")
     assert err <= 1.05 * FORMER[prec, top], err
+
+
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+def test_half_requests_through_both_fallbacks(spd, prec):
+    """A half request that fails in binary32 too (cond 1e10) ends as a binary64
+    request does, beside others that fall back once, not at all, or start in
+    binary32; every system is solved and counted once."""
+    conds = [1e1, 1e10, 1e5, 1e10, 1e1, 1e5, 1e10]
+    shapes = [(n, c, m) for n, c, m in zip((70, 90, 150, 257, 300, 410, 512), conds, (1, 2, 8, 3, 4, 1, 2))]
+    _say("batched both fallbacks", prec)
+    pb = spdgen.packed_batch(shapes, config=3, first_index=6100)
+    asked = [prec] * 5 + ["fp32", "fp32"]
+    _, X, r, p = _run(spd, pb, asked)
+    _, X32, r32, p32 = _run(spd, pb, "fp32")
+    _, X64, _, _ = _run(spd, pb, "fp64")
+    assert np.all(r["status"] == 0), r
+    assert list(p) == [spd.PREC[q] for q in (prec, "fp64", "fp32", "fp64", prec, "fp32", "fp64")], p
+    assert list(r["fallbacks"]) == [0, 2, 1, 2, 0, 0, 1], r
+    for s, (n, _, m) in enumerate(shapes):
+        b = slice(int(pb.b_off[s]), int(pb.b_off[s]) + n * m)
+        if p[s] == spd.PREC["fp64"]:
+            assert np.array_equal(X[b], X64[b]), s
+        elif p[s] == spd.PREC["fp32"]:
+            assert np.array_equal(X[b], X32[b]), s
