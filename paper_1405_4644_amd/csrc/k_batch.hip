@@ -273,13 +273,15 @@ SPD_DEV T *b_tile(T *L, int I, int J)
 // 16 columns in registers at a time, unrolled (29 KB of code, which took
 // longer to fetch than to run), 11 and 16; this took 8.6 and 11.4 with the
 // products straight off A's values.
-// The products are summed by themselves and come off A's values once, before a
-// panel's columns (and those of the panels before come off the diagonal tile
-// once, in b_factor): off the values one by one, each rounds at their size,
-// and the first solve's error for n = 33..64 and 65..128 was 4.8 and 5.7 u
-// (binary64), 4.5 and 5.5 (binary32); this way 3.6 and 3.9, 3.7 and 4.1.
-// 4096 mixed systems take 3.98 ms and 3.64 (binary64: A's values in the
-// registers of another slot leave more to the loops), 4.72 and 4.76 (binary32).
+// A panel's products are summed by themselves and come off what is left of A's
+// values once (and in b_factor eight columns' off the diagonal tile):
+// products taken off the values one by one each round at the values' size, and
+// one sum over all of them rounds at the size of A where little is left of it.
+// First solve, binary64, error / u for n = 33..64 and 65..128 at cond 10: 4.8
+// and 5.7 one by one, 3.5 and 3.9 with one sum, 3.7 and 4.1 this way; error /
+// (u cond) at cond 1e6: 0.133 and 0.095, 0.140 and 0.107, 0.131 and 0.092.
+// 4096 mixed systems take 3.87 ms (binary64) and 4.64 (binary32), one by one
+// 3.97 and 4.71.
 template <typename T>
 SPD_DEV int b_diag_body(T *Ws, T *Lr, T *buf)
 {
@@ -296,17 +298,16 @@ SPD_DEV int b_diag_body(T *Ws, T *Lr, T *buf)
     using acc_t = typename std::conditional<sizeof(T) == 4, floatx4, doublex4>::type;
     // row of accumulator register q
     auto arow = [&](int q) { return sizeof(T) == 4 ? 4 * u + q : 4 * q + u; };
-    // columns 16 c .. 16 c + 15: of A's rows (va: block rows 0 and 1 of column
-    // 0, block row 1 of column 1; ta: the panels' products to come off them)
-    // and of the identity's (ti: block row 0 of columns 0 and 1, block row 1 of
-    // column 1; zero where products come off)
+    // columns 16 c .. 16 c + 15: of A's rows (ta: block rows 0 and 1 of column
+    // 0, block row 1 of column 1) and of the identity's (ti: block row 0 of
+    // columns 0 and 1, block row 1 of column 1; zero where products come off)
     const acc_t zero = {0, 0, 0, 0};
-    acc_t va[3], ta[3] = {zero, zero, zero}, ti[3];
+    acc_t ta[3], ti[3];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        va[0][q] = Lr[r16 * S + arow(q)];
-        va[1][q] = Lr[(H + r16) * S + arow(q)];
-        va[2][q] = Lr[(H + r16) * S + H + arow(q)];
+        ta[0][q] = Lr[r16 * S + arow(q)];
+        ta[1][q] = Lr[(H + r16) * S + arow(q)];
+        ta[2][q] = Lr[(H + r16) * S + H + arow(q)];
         ti[0][q] = ti[2][q] = (r16 == arow(q)) ? (T)1 : (T)0;
         ti[1][q] = (T)0;
     }
@@ -324,11 +325,11 @@ SPD_DEV int b_diag_body(T *Ws, T *Lr, T *buf)
     for (int p = 0; p < BNB / 4; ++p) {
         const int c0 = 4 * p, pc = p & 3;
         if (p < 4) {
-            put(va[0] - ta[0], pc, 0);
-            put(va[1] - ta[1], pc, H);
+            put(ta[0], pc, 0);
+            put(ta[1], pc, H);
             put(ti[0], pc, 2 * H);
         } else {
-            put(va[2] - ta[2], pc, H);
+            put(ta[2], pc, H);
             put(ti[1], pc, 2 * H);
             put(ti[2], pc, 3 * H);
         }
@@ -360,13 +361,13 @@ SPD_DEV int b_diag_body(T *Ws, T *Lr, T *buf)
 #pragma unroll
         for (int t = 0; t < 4; ++t) o[t] = buf[(H * t + r16) * P + u];
         if (p < 4) {
-            ta[0] = mma(o[0], o[0], ta[0]);
-            ta[1] = mma(o[0], o[1], ta[1]);
+            ta[0] -= mma(o[0], o[0], zero);
+            ta[1] -= mma(o[0], o[1], zero);
             ti[0] = mma(-o[0], o[2], ti[0]);
         } else {
             ti[2] = mma(-o[1], o[3], ti[2]);
         }
-        ta[2] = mma(o[1], o[1], ta[2]);
+        ta[2] -= mma(o[1], o[1], zero);
         ti[1] = mma(-o[1], o[2], ti[1]);
         __builtin_amdgcn_wave_barrier();
     }
@@ -499,8 +500,9 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
             }
         }
     };
-    // the same for the diagonal tile, both operands the same tile
-    auto products_diag = [&](A32 &acc, int kb) {
+    // the same for the diagonal tile, both operands the same tile, the products
+    // of 8 columns summed by themselves in t
+    auto products_diag = [&](A32 &acc, A32 &t, int kb) {
         if (kb == 0)
             return;
         BTile<T> f, nx;
@@ -508,18 +510,23 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
         for (int q = 0; q < kb; ++q) {
             nx.load(b_tile(L, kb, min(q + 1, kb - 1)), lane);
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (sizeof(T) == 4) {
-                BTile<T>::submul(acc, f, f);
-            } else {
 #pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    double x[2][4];
+            for (int c = 0; c < BNB; c += 8) {
+                t.zero();
+                if constexpr (sizeof(T) == 4) {
 #pragma unroll
-                    for (int b = 0; b < 2; ++b)
+                    for (int j = c / 2; j < (c + 8) / 2; ++j) t.mma(-f.v[j], f.v[j]);
+                } else {
 #pragma unroll
-                        for (int p = 0; p < 4; ++p) x[b][p] = f.v[b][a][p];
-                    BTile<T>::submul_half(acc, x, x);
+                    for (int p = c / 4; p < (c + 8) / 4; ++p) {
+                        const double fx[2] = {-f.v[0][p >> 2][p & 3], -f.v[1][p >> 2][p & 3]},
+                                     fy[2] = {f.v[0][p >> 2][p & 3], f.v[1][p >> 2][p & 3]};
+                        t.mma(fx, fy);
+                    }
                 }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < 16; ++j) acc.set(j, acc.get(j) + t.get(j));
             }
             f = nx;
         }
@@ -549,12 +556,10 @@ __device__ __attribute__((noinline)) int b_factor(const double *A, int n, int np
         const int I0 = kb + wave;
         A32 acc[SLOTS];
         if (wave == 0) {
-            init(acc[1], kb, kb);
-            acc[0].zero();
-            products_diag(acc[0], kb);
+            init(acc[1], kb, kb);  // (in other slots' registers: in acc[0] the loops spill)
+            products_diag(acc[1], acc[2], kb);
 #pragma unroll
-            for (int j = 0; j < 16; ++j)
-                Lr[A32::col(j, lane) * BDIAG_S + A32::row(j, lane)] = acc[1].get(j) + acc[0].get(j);
+            for (int j = 0; j < 16; ++j) Lr[A32::col(j, lane) * BDIAG_S + A32::row(j, lane)] = acc[1].get(j);
             __builtin_amdgcn_wave_barrier();
             const int bad = b_diag(Ws, Lr, Lr + BNB * BDIAG_S);
             if (lane == 0)

@@ -105,3 +105,31 @@ def test_half_requests_through_both_fallbacks(spd, prec):
             assert np.array_equal(X[b], X64[b]), s
         elif p[s] == spd.PREC["fp32"]:
             assert np.array_equal(X[b], X32[b]), s
+
+
+# the same in units of u cond
+FORMER_ILL = {("fp32", 64): 0.1410, ("fp32", 128): 0.1219, ("fp64", 64): 0.1299, ("fp64", 128): 0.0921}
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("top", [64, 128])
+def test_first_solve_rounding_ill_conditioned(spd, prec, top):
+    """As test_first_solve_rounding where elimination leaves little of A's
+    values: cond 1e6, and 1e4 for binary32, whose factor still resolves that."""
+    cond = 1e4 if prec == "fp32" else 1e6
+    rng = np.random.Generator(np.random.PCG64(top + 1))
+    pb = spdgen.packed_batch_grouped([(int(n), cond, 2) for n in rng.integers(top // 2, top + 1, 384)], seed=top + 1)
+    pb.A, pb.B = pb.A.cpu().numpy(), pb.B.cpu().numpy()
+    _, X, reps, _ = _run(spd, pb, prec, spd.default_opts(max_iter=0, fallback=0))
+    err = []
+    for s in range(384):
+        n, a, b = int(pb.n[s]), int(pb.a_off[s]), int(pb.b_off[s])
+        A, B = pb.A[a:a + n * n].reshape(n, n), pb.B[b:b + 2 * n].reshape(2, n).T
+        x = np.linalg.solve(A, B)
+        for _ in range(2):
+            x = x + np.linalg.solve(A, (B - A.astype(np.longdouble) @ x).astype(np.float64))
+        d = (X[b:b + 2 * n].reshape(2, n).T - x).astype(np.float64)
+        err.append(np.linalg.norm(d) / np.linalg.norm(x.astype(np.float64)))
+    err = float(np.exp(np.mean(np.log(err)))) / cond / (2.0 ** -24 if prec == "fp32" else 2.0 ** -53)
+    _say(f"batched rounding, ill-conditioned {prec} n<={top}: {err:.4f}")
+    assert err <= 1.05 * FORMER_ILL[prec, top], err
